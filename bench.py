@@ -115,7 +115,7 @@ def inference_bench(w, dev, batches=(1, 8), iters=50):
             per[name] = per.get(name, 0.0) + ms
         lrsa.timing_enable(False)
         attn_us = (per.get("k_decode_attn", 0.0) + per.get("k_decode_combine", 0.0)) * 1e3 / iters
-        comp_us = per.get("k_cache_compress", 0.0) * 1e3 / iters
+        comp_us = sum(v for k, v in per.items() if not k.startswith("k_decode")) * 1e3 / iters
         attn_bytes = 2 * B * w.Hkv * length * w.d * esz
         comp_bytes = 2 * B * w.Hkv * (2 * w.L + (w.K + w.L)) * w.d * esz * 1   # two chunks read, survivors + tail moved
         out[f"B{B}"] = {"decode_attn_us": attn_us, "decode_attn_GBps": attn_bytes / attn_us / 1e3,

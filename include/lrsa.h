@@ -79,7 +79,7 @@ typedef struct {
 /* Which call a workspace size is asked for. */
 typedef enum {
     LRSA_WS_SCORE = 0, LRSA_WS_SELECT = 1, LRSA_WS_ATTN_FWD = 2, LRSA_WS_ATTN_BWD = 3,
-    LRSA_WS_DECODE_ATTN = 4 /* lrsa_decode_attn; lrsa_cache_compress needs none */
+    LRSA_WS_DECODE_ATTN = 4 /* lrsa_decode_attn; lrsa_cache_compress needs none, lrsa_cache_compress_ws has a function of its own */
 } lrsa_ws_kind;
 
 /* Ns of the partition above; pure host arithmetic.  Returns a negative lrsa_status on bad params. */
@@ -219,6 +219,13 @@ int lrsa_attn_bwd_finish(const lrsa_params *p, const float *dK_acc, const float 
  * Nothing is launched when the tail is shorter than 2*lag. */
 int lrsa_cache_compress(const lrsa_params *p, void *Kc, void *Vc, int32_t *pos, int32_t len, int32_t done,
                         int32_t *len_out, int32_t *done_out, void *stream);
+
+/* lrsa_cache_compress with a device workspace: the same rows end up in the same places, but all steps of the call
+ * run at once and over many workgroups (without a workspace: one workgroup per (batch, KV head), step after step).
+ *   ws : lrsa_cache_compress_ws_bytes(p, len, done) bytes, 256-byte aligned; may be NULL when that is 0 */
+size_t lrsa_cache_compress_ws_bytes(const lrsa_params *p, int32_t len, int32_t done);
+int lrsa_cache_compress_ws(const lrsa_params *p, void *Kc, void *Vc, int32_t *pos, int32_t len, int32_t done,
+                           int32_t *len_out, int32_t *done_out, void *ws, size_t ws_bytes, void *stream);
 
 /* Single-query attention over the cache (Eq. 3, every cache row visible): for each query head,
  * O = softmax(scale q.Kc^T) Vc over rows [0, len).  Query head hq reads KV head hq / G.

@@ -21,7 +21,7 @@ WS_SCORE, WS_SELECT, WS_ATTN_FWD, WS_ATTN_BWD, WS_DECODE_ATTN = 0, 1, 2, 3, 4
 
 EXPORTS = ("lrsa_abi_version", "lrsa_last_error", "lrsa_num_scored_chunks", "lrsa_score_route", "lrsa_score_poll_limit", "lrsa_workspace_bytes",
            "lrsa_score", "lrsa_select", "lrsa_score_select", "lrsa_check_idx", "lrsa_attn_fwd", "lrsa_attn_bwd",
-           "lrsa_cache_compress", "lrsa_decode_attn", "lrsa_decode_attn_static",
+           "lrsa_cache_compress", "lrsa_cache_compress_ws", "lrsa_cache_compress_ws_bytes", "lrsa_decode_attn", "lrsa_decode_attn_static",
            "lrsa_fill_workspace_bytes", "lrsa_attn_fwd_fill", "lrsa_attn_bwd_fill", "lrsa_attn_bwd_finish",
            "lrsa_timing_enable", "lrsa_timing_count", "lrsa_timing_read")
 
@@ -68,6 +68,9 @@ def lib() -> ctypes.CDLL:
         L.lrsa_score_select.argtypes = [vp, vp, vp, vp, vp, vp, sz, vp]
         L.lrsa_check_idx.argtypes = [vp, vp, vp, vp]
         L.lrsa_cache_compress.argtypes = [vp, vp, vp, vp, ctypes.c_int32, ctypes.c_int32, vp, vp, vp]
+        L.lrsa_cache_compress_ws_bytes.restype = ctypes.c_size_t
+        L.lrsa_cache_compress_ws_bytes.argtypes = [vp, ctypes.c_int32, ctypes.c_int32]
+        L.lrsa_cache_compress_ws.argtypes = [vp, vp, vp, vp, ctypes.c_int32, ctypes.c_int32, vp, vp, vp, sz, vp]
         L.lrsa_decode_attn.argtypes = [vp, vp, vp, vp, ctypes.c_int32, vp, vp, vp, sz, vp]
         L.lrsa_decode_attn_static.argtypes = [vp, vp, vp, vp, ctypes.c_int32, vp, vp, vp]
         i32 = ctypes.c_int32
@@ -245,8 +248,10 @@ def lrsa_cache_compress(p: LrsaParams, Kc: torch.Tensor, Vc: torch.Tensor, pos: 
     """Inference-time cache: compress (in place) while the uncompressed tail holds 2*lag rows.
     Kc, Vc: [B, Hkv, cap, d] with cap = p.seq; pos: int32 [B, Hkv, cap] or None.  Returns (length, done)."""
     new_len, new_done = ctypes.c_int32(0), ctypes.c_int32(0)
-    _check(lib().lrsa_cache_compress(ctypes.byref(p), _ptr(Kc), _ptr(Vc), _ptr(pos), int(length), int(done),
-                                     ctypes.byref(new_len), ctypes.byref(new_done), _stream()))
+    need = lib().lrsa_cache_compress_ws_bytes(ctypes.byref(p), int(length), int(done))
+    ws = torch.empty(need, dtype=torch.uint8, device=Kc.device) if need else None
+    _check(lib().lrsa_cache_compress_ws(ctypes.byref(p), _ptr(Kc), _ptr(Vc), _ptr(pos), int(length), int(done),
+                                        ctypes.byref(new_len), ctypes.byref(new_done), _ptr(ws), need, _stream()))
     return new_len.value, new_done.value
 
 

@@ -174,24 +174,61 @@ int lrsa_score_select(const lrsa_params* p, const void* K, const void* V, float*
     return hip_result(lrsa::launch_score_select(D, K, V, score, idx, ws, (hipStream_t)stream), "lrsa_score_select");
 }
 
-int lrsa_cache_compress(const lrsa_params* p, void* Kc, void* Vc, int32_t* pos, int32_t len, int32_t done,
-                        int32_t* len_out, int32_t* done_out, void* stream) {
+// Arguments of a compression call: derived dimensions, steps to take and the new counts (host arithmetic)
+static int compress_plan(const lrsa_params* p, int32_t len, int32_t done, lrsa::Dims* D, int* steps) {
+    const int rc = make_dims(p, D);
+    if (rc != LRSA_OK) return rc;
+    if (!lrsa::cache_compress_supported(*D))
+        return fail(LRSA_ERR_UNSUPPORTED, "lrsa_cache_compress needs local_prev == 1 and lag <= 4096");
+    if (len < 0 || len > D->n || done < 0) return fail(LRSA_ERR_INVALID_ARG, "lrsa_cache_compress: len %d outside [0, cap=%d] or done < 0", len, D->n);
+    const int64_t tail = (int64_t)len - D->S - (int64_t)D->K * done;
+    if (done > 0 && tail < D->L) return fail(LRSA_ERR_INVALID_ARG, "lrsa_cache_compress: len %d is too short for %d compressed chunks", len, done);
+    *steps = tail >= 2 * (int64_t)D->L ? (int)(tail / D->L) - 1 : 0;
+    return LRSA_OK;
+}
+
+static size_t compress_ws_need(const lrsa::Dims& D, int32_t len, int32_t done, int steps) {
+    // nothing moves; beyond the launch grid or 32-bit row pieces: step by step
+    if (steps == 0 || D.K == D.L || steps > 65535 || int64_t(len) * 32 > INT32_MAX) return 0;
+    return lrsa::cache_compress_ws_bytes(D, len, done, steps);
+}
+
+static int cache_compress(const lrsa_params* p, void* Kc, void* Vc, int32_t* pos, int32_t len, int32_t done, int32_t* len_out,
+                          int32_t* done_out, void* ws, size_t ws_bytes, bool with_ws, void* stream) {
     lrsa::Dims D;
-    int rc = make_dims(p, &D);
+    int rc = make_dims(p, &D), steps = 0;
     if (rc != LRSA_OK) return rc;
     if (!len_out || !done_out) return fail(LRSA_ERR_INVALID_ARG, "lrsa_cache_compress: len_out and done_out must not be NULL");
-    if (!lrsa::cache_compress_supported(D))
-        return fail(LRSA_ERR_UNSUPPORTED, "lrsa_cache_compress needs local_prev == 1 and lag <= 4096");
-    if (len < 0 || len > D.n || done < 0) return fail(LRSA_ERR_INVALID_ARG, "lrsa_cache_compress: len %d outside [0, cap=%d] or done < 0", len, D.n);
-    const int64_t tail = (int64_t)len - D.S - (int64_t)D.K * done;
-    if (done > 0 && tail < D.L) return fail(LRSA_ERR_INVALID_ARG, "lrsa_cache_compress: len %d is too short for %d compressed chunks", len, done);
-    int steps = tail >= 2 * (int64_t)D.L ? (int)(tail / D.L) - 1 : 0;
+    if ((rc = compress_plan(p, len, done, &D, &steps)) != LRSA_OK) return rc;
     *len_out = len - steps * (D.L - D.K);
     *done_out = done + steps;
     if (steps == 0) return LRSA_OK;
     if (!Kc || !Vc) return fail(LRSA_ERR_INVALID_ARG, "lrsa_cache_compress: Kc and Vc must not be NULL");
     if (misaligned16(Kc) || misaligned16(Vc)) return fail(LRSA_ERR_INVALID_ARG, "lrsa_cache_compress: Kc and Vc must be 16-byte aligned");
+    const size_t need = with_ws ? compress_ws_need(D, len, done, steps) : 0;
+    if (need > 0) {
+        if (!ws || ws_bytes < need || reinterpret_cast<uintptr_t>(ws) % 256 != 0)
+            return fail(LRSA_ERR_INVALID_ARG, "lrsa_cache_compress_ws: a 256-byte aligned workspace of %zu bytes is needed", need);
+        return hip_result(lrsa::launch_cache_compress_ws(D, Kc, Vc, pos, len, done, steps, ws, (hipStream_t)stream), "lrsa_cache_compress_ws");
+    }
+    if (D.K == D.L) return LRSA_OK;                               // every row survives where it is
     return hip_result(lrsa::launch_cache_compress(D, Kc, Vc, pos, len, done, steps, (hipStream_t)stream), "lrsa_cache_compress");
+}
+
+int lrsa_cache_compress(const lrsa_params* p, void* Kc, void* Vc, int32_t* pos, int32_t len, int32_t done,
+                        int32_t* len_out, int32_t* done_out, void* stream) {
+    return cache_compress(p, Kc, Vc, pos, len, done, len_out, done_out, nullptr, 0, false, stream);
+}
+
+size_t lrsa_cache_compress_ws_bytes(const lrsa_params* p, int32_t len, int32_t done) {
+    lrsa::Dims D;
+    int steps = 0;
+    return compress_plan(p, len, done, &D, &steps) == LRSA_OK ? compress_ws_need(D, len, done, steps) : 0;
+}
+
+int lrsa_cache_compress_ws(const lrsa_params* p, void* Kc, void* Vc, int32_t* pos, int32_t len, int32_t done, int32_t* len_out,
+                           int32_t* done_out, void* ws, size_t ws_bytes, void* stream) {
+    return cache_compress(p, Kc, Vc, pos, len, done, len_out, done_out, ws, ws_bytes, true, stream);
 }
 
 int lrsa_decode_attn(const lrsa_params* p, const void* q, const void* Kc, const void* Vc, int32_t len, void* O,

@@ -52,6 +52,13 @@ hipError_t launch_check_idx(const Dims&, const int32_t* idx, int32_t* bad_rows, 
 size_t decode_ws_bytes(const Dims&);
 bool cache_compress_supported(const Dims&);
 hipError_t launch_cache_compress(const Dims&, void* Kc, void* Vc, int32_t* pos, int len, int done, int steps, hipStream_t st);
+// the same with a workspace: all steps at once over many workgroups
+size_t cache_compress_ws_bytes(const Dims&, int len, int done, int steps);
+hipError_t launch_cache_compress_ws(const Dims&, void* Kc, void* Vc, int32_t* pos, int len, int done, int steps, void* ws,
+                                    hipStream_t st);
+size_t cache_sigma_ws_floats(const Dims&);
+hipError_t launch_cache_sigma(const Dims&, const void* K, const void* V, float* mm, float* sigma, hipStream_t st);
+hipError_t launch_cache_select(const Dims&, const float* sigma, int32_t* idx, hipStream_t st);
 hipError_t launch_decode_attn(const Dims&, const void* q, const void* Kc, const void* Vc, int len, void* O, float* lse,
                               void* ws, hipStream_t st);
 // lrsa_decode_attn_static: bytes of the library-owned scratch array and what a call needs of it

@@ -36,9 +36,10 @@ size_t score_ws_bytes(const Dims& D) {
     return align256(mm_floats(D) * 4) + align256(sigma_floats(D) * 4);
 }
 
+// rows_wg: rows of a slice (the grid holds ceil(L / rows_wg) slices)
 template <typename T>
 __global__ __launch_bounds__(SCORE_THREADS) void k_minmax(Dims D, const T* __restrict__ Kp, const T* __restrict__ Vp,
-                                                           float* __restrict__ mm) {
+                                                           float* __restrict__ mm, int rows_wg) {
     constexpr int VEC = Elem<T>::VEC;
     const int lpr = D.d / VEC;               // lanes per row
     const int rpp = SCORE_THREADS / lpr;     // rows per pass
@@ -46,7 +47,6 @@ __global__ __launch_bounds__(SCORE_THREADS) void k_minmax(Dims D, const T* __res
     const int z = blockIdx.z & 1, bh = blockIdx.z >> 1;
     const int b = bh / D.Hkv, h = bh % D.Hkv;
     const T* Z = (z ? Vp : Kp) + b * D.ks[0] + h * D.ks[1];
-    const int rows_wg = score_rows_per_wg(D.L);
     const int r0 = split * rows_wg;
     const int r1 = min(r0 + rows_wg, D.L);
     const int64_t base = int64_t(D.S) + int64_t(p + 1) * D.L;   // first row of the reference chunk
@@ -88,7 +88,8 @@ __global__ __launch_bounds__(SCORE_THREADS) void k_minmax(Dims D, const T* __res
 
 template <typename T>
 __global__ __launch_bounds__(SCORE_THREADS) void k_sigma(Dims D, const T* __restrict__ Kp, const T* __restrict__ Vp,
-                                                          const float* __restrict__ mm, float* __restrict__ sigma) {
+                                                          const float* __restrict__ mm, float* __restrict__ sigma,
+                                                          int rows_wg) {
     constexpr int VEC = Elem<T>::VEC;
     const int lpr = D.d / VEC;
     const int rpp = SCORE_THREADS / lpr;
@@ -96,7 +97,6 @@ __global__ __launch_bounds__(SCORE_THREADS) void k_sigma(Dims D, const T* __rest
     const int z = blockIdx.z & 1, bh = blockIdx.z >> 1;
     const int b = bh / D.Hkv, h = bh % D.Hkv;
     const T* Z = (z ? Vp : Kp) + b * D.ks[0] + h * D.ks[1];
-    const int rows_wg = score_rows_per_wg(D.L);
     const int nsplit = gridDim.x;
     const int r0 = split * rows_wg;
     const int r1 = min(r0 + rows_wg, D.L);
@@ -260,6 +260,30 @@ int score_route(const Dims& D) {
     return int64_t(D.Ns) * D.B * D.Hkv * 2 <= 256 && D.L >= 1024 ? 2 : 1;
 }
 
+// Std of every row of every scored chunk (Eq. 4-7 before the softmax) into sigma, by slices of rows_wg rows
+template <typename T>
+static void run_sigma(const Dims& D, const void* K, const void* V, float* mm, float* sigma, int rows_wg, hipStream_t st) {
+    const dim3 grid((D.L + rows_wg - 1) / rows_wg, D.Ns, D.B * D.Hkv * 2);
+    LRSA_TIMED_LAUNCH("k_minmaxT", st, k_minmax<T>, grid, dim3(SCORE_THREADS), 0, st, D, (const T*)K, (const T*)V, mm, rows_wg);
+    LRSA_TIMED_LAUNCH("k_sigmaT", st, k_sigma<T>, grid, dim3(SCORE_THREADS), 0, st, D, (const T*)K, (const T*)V, mm, sigma, rows_wg);
+}
+
+// The same for the chunks of an inference-time cache (D.S = first row of the oldest chunk, D.Ns chunks): slices of 64
+// rows while they are needed to give every CU one, of 128 beyond that.
+static int cache_rows_per_wg(const Dims& D) {
+    const int64_t units = int64_t(D.B) * D.Hkv * 2 * D.Ns;
+    return units * ((D.L + 127) / 128) >= 256 ? 128 : 64;
+}
+size_t cache_sigma_ws_floats(const Dims& D) {
+    const int rows = cache_rows_per_wg(D);
+    return size_t(D.B) * D.Hkv * 2 * D.Ns * ((D.L + rows - 1) / rows) * 2 * D.d;
+}
+hipError_t launch_cache_sigma(const Dims& D, const void* K, const void* V, float* mm, float* sigma, hipStream_t st) {
+    if (D.dtype == 1) run_sigma<bf16_t>(D, K, V, mm, sigma, cache_rows_per_wg(D), st);
+    else run_sigma<float>(D, K, V, mm, sigma, cache_rows_per_wg(D), st);
+    return hipGetLastError();
+}
+
 // idx != nullptr: scores AND the selection (taken by the last kernel of the route, except on route 4)
 template <typename T>
 static hipError_t run_score(const Dims& D, const void* K, const void* V, float* score, int32_t* idx, void* ws,
@@ -277,9 +301,7 @@ static hipError_t run_score(const Dims& D, const void* K, const void* V, float* 
     }
     float* mm = reinterpret_cast<float*>(ws);
     float* sigma = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + align256(mm_floats(D) * 4));
-    const dim3 grid(score_splits(D.L), D.Ns, D.B * D.Hkv * 2);
-    LRSA_TIMED_LAUNCH("k_minmaxT", st, k_minmax<T>, grid, dim3(SCORE_THREADS), 0, st, D, (const T*)K, (const T*)V, mm);
-    LRSA_TIMED_LAUNCH("k_sigmaT", st, k_sigma<T>, grid, dim3(SCORE_THREADS), 0, st, D, (const T*)K, (const T*)V, mm, sigma);
+    run_sigma<T>(D, K, V, mm, sigma, score_rows_per_wg(D.L), st);
     if (route == 2) return launch_softmax_select(D, sigma, score, idx, st);
     LRSA_TIMED_LAUNCH("k_softmax", st, k_softmax, dim3(D.Ns, D.B * D.Hkv), dim3(SCORE_THREADS), 0, st, D, sigma, score);
     hipError_t e = hipGetLastError();

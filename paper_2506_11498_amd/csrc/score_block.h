@@ -69,6 +69,64 @@ __device__ __forceinline__ void softmax_sum_block(float* sig0, const float* sig1
     }
 }
 
+// The same from standard deviations in global memory: a thread keeps its rows r = tid, tid + NT, ... in registers from
+// the load to the score.  Scores go to out[r] (global) and key[r] (LDS), where these are not null.  The same values in
+// the same order as softmax_sum_block<NT>.
+template <int NT>
+__device__ __forceinline__ void softmax_sum_regs(const float* __restrict__ sk, const float* __restrict__ sv, float* sm,
+                                                 int L, float* __restrict__ out, float* key) {
+    constexpr int NW = NT / 64, MAXJ = FUSED_MAX_L / NT;   // rows of a thread: at most MAXJ
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // a row past the chunk counts as -inf (its exponential is 0)
+    float vk[MAXJ], vv[MAXJ];
+#pragma unroll
+    for (int j = 0; j < MAXJ; ++j) {
+        const int r = tid + j * NT;
+        const bool in = j * NT < L && r < L;
+        vk[j] = in ? sk[r] : -INFINITY;
+        vv[j] = in ? sv[r] : -INFINITY;
+    }
+    // the K and the V value reduced over the block together (one pair of barriers for both)
+    auto block_red2 = [&](float& a, float& b, bool is_max) {
+        a = is_max ? wave_max(a) : wave_sum(a);
+        b = is_max ? wave_max(b) : wave_sum(b);
+        __syncthreads();
+        if (lane == 0) { sm[wave] = a; sm[NW + wave] = b; }
+        __syncthreads();
+        float ra = sm[0], rb = sm[NW];
+        for (int i = 1; i < NW; ++i) {
+            ra = is_max ? fmaxf(ra, sm[i]) : ra + sm[i];
+            rb = is_max ? fmaxf(rb, sm[NW + i]) : rb + sm[NW + i];
+        }
+        a = ra;
+        b = rb;
+    };
+    float mk = -INFINITY, mv = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < MAXJ; ++j) { mk = fmaxf(mk, vk[j]); mv = fmaxf(mv, vv[j]); }
+    block_red2(mk, mv, true);
+    float zk = 0.0f, zv = 0.0f;
+#pragma unroll
+    for (int j = 0; j < MAXJ; ++j) {
+        if (j * NT < L) {
+            vk[j] = expf(vk[j] - mk);
+            vv[j] = expf(vv[j] - mv);
+            zk += vk[j];
+            zv += vv[j];
+        }
+    }
+    block_red2(zk, zv, false);
+#pragma unroll
+    for (int j = 0; j < MAXJ; ++j) {
+        const int r = tid + j * NT;
+        if (j * NT < L && r < L) {
+            const float sc = vk[j] / zk + vv[j] / zv;      // Eq. 7-8
+            if (out) out[r] = sc;
+            if (key) key[r] = sc;
+        }
+    }
+}
+
 template <typename T>
 __device__ __forceinline__ void score_chunk_block(int L, int d, int ddof, const T* __restrict__ Kcur,
                                                   const T* __restrict__ Kref, const T* __restrict__ Vcur,
