@@ -123,14 +123,19 @@ template <> struct Elem<float> {
         float4 v = *reinterpret_cast<const float4*>(p);
         out[0] = v.x; out[1] = v.y; out[2] = v.z; out[3] = v.w;
     }
+    __device__ static __forceinline__ void unpack(const uint4& v, float (&out)[4]) {   // the 16 bytes of a load
+        out[0] = __uint_as_float(v.x); out[1] = __uint_as_float(v.y); out[2] = __uint_as_float(v.z); out[3] = __uint_as_float(v.w);
+    }
     __device__ static __forceinline__ float get(const float* p) { return *p; }
     __device__ static __forceinline__ void put(float* p, float v) { *p = v; }
 };
 template <> struct Elem<bf16_t> {
     static constexpr int VEC = 8;
     __device__ static __forceinline__ void load(const bf16_t* p, float (&out)[8]) {
-        uint4 v = *reinterpret_cast<const uint4*>(p);
-        uint32_t w[4] = {v.x, v.y, v.z, v.w};
+        unpack(*reinterpret_cast<const uint4*>(p), out);
+    }
+    __device__ static __forceinline__ void unpack(const uint4& v, float (&out)[8]) {
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             out[2 * i] = __uint_as_float(w[i] << 16);
@@ -141,14 +146,56 @@ template <> struct Elem<bf16_t> {
     __device__ static __forceinline__ void put(bf16_t* p, float v) { *p = f32_to_bf16(v); }
 };
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+// ---- reductions and scans over the lanes of a wave -----------------------------------------------------------------
+// All in the vector pipe: half-wave and row exchanges by permlane swaps, rotations inside a row of 16 lanes by
+// data-parallel primitives.  (A shuffle through LDS costs its latency at every one of the six levels: the block-wide
+// chains of softmax and selection take 7.4 us at 240 chunks of 1024 rows, 8.6 us with shuffles.)
+typedef unsigned int lanes_u32x2 __attribute__((ext_vector_type(2)));
+// {own, other} in some order: the values of lane l and of lane l ^ 32 (l ^ 16)
+__device__ __forceinline__ lanes_u32x2 pair32(uint32_t v) { return __builtin_amdgcn_permlane32_swap(v, v, false, false); }
+__device__ __forceinline__ lanes_u32x2 pair16(uint32_t v) { return __builtin_amdgcn_permlane16_swap(v, v, false, false); }
+template <int N>
+__device__ __forceinline__ uint32_t row_ror(uint32_t v) {   // rotation by N inside the row of 16
+    return uint32_t(__builtin_amdgcn_update_dpp(0, int(v), 0x120 | N, 0xf, 0xf, false));
 }
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+// op over all 64 lanes, every lane gets the result; the pairs are those of a butterfly 32, 16, 8, 4, 2, 1
+template <class Op>
+__device__ __forceinline__ float row16_all(float v, Op op) {
+    v = op(v, __uint_as_float(row_ror<8>(__float_as_uint(v))));
+    v = op(v, __uint_as_float(row_ror<4>(__float_as_uint(v))));
+    v = op(v, __uint_as_float(row_ror<2>(__float_as_uint(v))));
+    return op(v, __uint_as_float(row_ror<1>(__float_as_uint(v))));
+}
+template <class Op>
+__device__ __forceinline__ float wave_all(float v, Op op) {
+    const lanes_u32x2 a = pair32(__float_as_uint(v));
+    v = op(__uint_as_float(a.x), __uint_as_float(a.y));
+    const lanes_u32x2 c = pair16(__float_as_uint(v));
+    v = op(__uint_as_float(c.x), __uint_as_float(c.y));
+    return row16_all(v, op);
+}
+__device__ __forceinline__ float wave_sum(float v) { return wave_all(v, [](float a, float b) { return a + b; }); }
+__device__ __forceinline__ float wave_max(float v) { return wave_all(v, [](float a, float b) { return fmaxf(a, b); }); }
+// sum over the 16 lanes of a row, every lane gets the total
+__device__ __forceinline__ float row16_sum(float v) { return row16_all(v, [](float a, float b) { return a + b; }); }
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
+    lanes_u32x2 a = pair32(v);
+    v = a.x < a.y ? a.x : a.y;
+    a = pair16(v);
+    v = a.x < a.y ? a.x : a.y;
+    uint32_t o = row_ror<8>(v); v = o < v ? o : v;
+    o = row_ror<4>(v); v = o < v ? o : v;
+    o = row_ror<2>(v); v = o < v ? o : v;
+    o = row_ror<1>(v); return o < v ? o : v;
+}
+// inclusive prefix sum over the 64 lanes (lanes before the first contribute zero)
+__device__ __forceinline__ int wave_iscan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);   // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);   // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);   // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
     return v;
 }
 #endif

@@ -124,8 +124,8 @@ hipError_t launch_cache_compress(const Dims& D, void* Kc, void* Vc, int32_t* pos
 //   one step               k_cache_select_move: softmax, selection and the move in place
 //   several steps          k_softmax_select, then k_cache_gather (rows to the workspace) and k_cache_place (and back)
 // k_cache_compress is bound by one CU's loads per head, two in flight per thread, and repeats the move of the whole tail
-// for every step.  Measured against it (bf16, d 128): one step at 8 heads, lag 1024: 50 us -> 25 us (4 + 7 + 14); a
-// 32K-token prompt of 2 heads, 30 steps: 9600 us -> 45 us (8 + 13 + 9 + 7 + 8).
+// for every step.  Measured against it (bf16, d 128): one step at 8 heads, lag 1024: 50 us -> 22 us (4 + 6 + 12); a
+// 32K-token prompt of 2 heads, 30 steps: 9600 us -> 43 us (8 + 12 + 7 + 8 + 8).
 // The scores are those of k_cache_compress bit for bit, so the same rows survive.
 //
 // Row dst of the new cache comes from row src(dst) >= dst of the old one.

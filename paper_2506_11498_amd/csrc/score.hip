@@ -104,6 +104,17 @@ __global__ __launch_bounds__(SCORE_THREADS) void k_sigma(Dims D, const T* __rest
     const int lane = threadIdx.x % lpr, rg = threadIdx.x / lpr;
     const int64_t unit = (int64_t(bh) * 2 + z) * D.Ns + p;
 
+    // Four rows per thread and iteration, so that four loads are in flight; a row past the slice repeats this thread's
+    // first row and is not stored.  The first four are asked for before anything else: they do not depend on the
+    // min / max, whose combination they would otherwise wait behind.
+    uint4 raw[4];
+    auto fetch = [&](int r) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            raw[j] = *reinterpret_cast<const uint4*>(Z + (base + (r + j * rpp < r1 ? r + j * rpp : r)) * D.ks[2] + lane * VEC);
+    };
+    if (r0 + rg < r1) fetch(r0 + rg);
+
     // combine the partial min / max of the reference chunk: thread t reduces entry t of the 2 * d floats of a
     // partial (coalesced, the loads of different partials independent of each other), then every thread picks
     // up its own channels from LDS
@@ -130,18 +141,23 @@ __global__ __launch_bounds__(SCORE_THREADS) void k_sigma(Dims D, const T* __rest
         inv[i] = 1.0f / den[i];
     }
     const float inv_d = 1.0f / float(D.d), inv_dof = 1.0f / float(D.d - D.ddof);
-    // Four rows per thread and iteration, so that four loads are in flight; a row past the slice repeats the
-    // slice's last row of this thread and is not stored.  The lanes of one row run the same iterations, so
-    // the shuffles stay among active lanes.  The quotient of Eq. 6 is the reciprocal product with one fused
-    // residual correction, which reproduces the IEEE quotient.
+    // The lanes of one row run the same iterations, so the exchanges stay among active lanes.  The quotient of Eq. 6 is
+    // the reciprocal product with one fused residual correction, which reproduces the IEEE quotient.
+    auto row_sums = [&](float (&x)[4]) {
+        if (lpr == 16) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[j] = row16_sum(x[j]);
+            return;
+        }
+        for (int o = lpr >> 1; o > 0; o >>= 1)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[j] += __shfl_xor(x[j], o, 64);
+    };
     for (int r = r0 + rg; r < r1; r += 4 * rpp) {
         float v[4][VEC], s[4], q[4];
-        int rr[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            rr[j] = r + j * rpp < r1 ? r + j * rpp : r;
-            Elem<T>::load(Z + (base + rr[j]) * D.ks[2] + lane * VEC, v[j]);
-        }
+        for (int j = 0; j < 4; ++j) Elem<T>::unpack(raw[j], v[j]);
+        if (r + 4 * rpp < r1) fetch(r + 4 * rpp);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             float acc = 0.0f;
@@ -155,9 +171,7 @@ __global__ __launch_bounds__(SCORE_THREADS) void k_sigma(Dims D, const T* __rest
             }
             s[j] = acc;
         }
-        for (int o = lpr >> 1; o > 0; o >>= 1)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) s[j] += __shfl_xor(s[j], o, 64);
+        row_sums(s);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const float mean = s[j] * inv_d;
@@ -166,13 +180,11 @@ __global__ __launch_bounds__(SCORE_THREADS) void k_sigma(Dims D, const T* __rest
             for (int i = 0; i < VEC; ++i) { const float dv = v[j][i] - mean; acc += dv * dv; }
             q[j] = acc;
         }
-        for (int o = lpr >> 1; o > 0; o >>= 1)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) q[j] += __shfl_xor(q[j], o, 64);
+        row_sums(q);
         if (lane == 0) {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                if (j == 0 || r + j * rpp < r1) sigma[unit * D.L + rr[j]] = sqrtf(q[j] * inv_dof);
+                if (j == 0 || r + j * rpp < r1) sigma[unit * D.L + r + j * rpp] = sqrtf(q[j] * inv_dof);
         }
     }
 }

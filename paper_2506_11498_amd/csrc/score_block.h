@@ -22,16 +22,6 @@ struct ScoreLds {
 // between rows; L <= FUSED_MAX_L rows each.  On return sh.sig[0][r] holds the score of row r (also written
 // to out[r] when out is not null); all threads have passed a barrier after the last LDS write they depend on
 // only for their own r = tid, tid + 1024, ... -- callers that read other rows synchronise first.
-// sum over the 16 lanes that share a row, every lane gets the total: four rotations inside the row of 16
-// (data-parallel primitive, no LDS round trip)
-__device__ __forceinline__ float row16_sum(float v) {
-    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x128, 0xf, 0xf, false));   // row_ror:8
-    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x124, 0xf, 0xf, false));   // row_ror:4
-    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x122, 0xf, 0xf, false));   // row_ror:2
-    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x121, 0xf, 0xf, false));   // row_ror:1
-    return v;
-}
-
 // Eq. 7-8 given the standard deviations: max-subtracted softmax of sig0 over the L tokens, the same for sig1,
 // their sum written to sig0[r] (and to out[r] when out is not null).  sig0, sig1: LDS, L floats each, complete
 // and visible to the NT threads of the block on entry; sm: 2 * NT/64 floats of LDS.  Each thread touches only rows

@@ -72,10 +72,6 @@ struct MinMax8 {   // running min / max of 8 channels (one 16-byte piece of a ro
         mn[0] = pk_min(mn[0], v.x); mn[1] = pk_min(mn[1], v.y); mn[2] = pk_min(mn[2], v.z); mn[3] = pk_min(mn[3], v.w);
         mx[0] = pk_max(mx[0], v.x); mx[1] = pk_max(mx[1], v.y); mx[2] = pk_max(mx[2], v.z); mx[3] = pk_max(mx[3], v.w);
     }
-    __device__ __forceinline__ void merge(const uint32_t (&omn)[4], const uint32_t (&omx)[4]) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { mn[i] = pk_min(mn[i], omn[i]); mx[i] = pk_max(mx[i], omx[i]); }
-    }
 };
 
 __device__ __forceinline__ float bf16lo(uint32_t w) { return __uint_as_float(w << 16); }
@@ -212,11 +208,12 @@ __global__ __launch_bounds__(NT) void k_score_resident(Dims D, const bf16_t* __r
 
     auto reduce_to_lds = [&](MinMax8& m) {       // the four rows of a wave (lanes 16, 32 apart), then one record per wave
 #pragma unroll
-        for (int off = 16; off < 64; off <<= 1) {
-            uint32_t omn[4], omx[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) { omn[k] = __shfl_xor(m.mn[k], off, 64); omx[k] = __shfl_xor(m.mx[k], off, 64); }
-            m.merge(omn, omx);
+        for (int k = 0; k < 4; ++k) {
+            lanes_u32x2 p = pair16(m.mn[k]), q = pair16(m.mx[k]);
+            p = pair32(pk_min(p.x, p.y));
+            q = pair32(pk_max(q.x, q.y));
+            m.mn[k] = pk_min(p.x, p.y);
+            m.mx[k] = pk_max(q.x, q.y);
         }
         if (lane < 16) {
 #pragma unroll

@@ -29,12 +29,7 @@ struct SelectLds {
 template <int NT>
 __device__ __forceinline__ int block_exscan(int v, int* sm /*[NT/64]*/, int* total) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    int inc = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        int t = __shfl_up(inc, o, 64);
-        if (lane >= o) inc += t;
-    }
+    const int inc = wave_iscan(v);
     __syncthreads();
     if (lane == 63) sm[w] = inc;
     __syncthreads();
@@ -63,12 +58,8 @@ __device__ __forceinline__ void select_topk_block(const uint32_t* key, int L, in
         lo = k < lo ? k : lo;
         hi = k > hi ? k : hi;
     }
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t a = uint32_t(__shfl_xor(int(lo), o, 64)), b = uint32_t(__shfl_xor(int(hi), o, 64));
-        lo = a < lo ? a : lo;
-        hi = b > hi ? b : hi;
-    }
+    lo = wave_min_u32(lo);
+    hi = ~wave_min_u32(~hi);
     if (lane == 0) { sh.hist[wave] = int(lo); sh.hist[NW + wave] = int(hi); }
     __syncthreads();
 #pragma unroll
@@ -98,13 +89,7 @@ __device__ __forceinline__ void select_topk_block(const uint32_t* key, int L, in
             int c[4], tot = 0;
 #pragma unroll
             for (int i = 0; i < 4; ++i) { c[i] = sh.hist[255 - 4 * lane - i]; tot += c[i]; }
-            int inc = tot;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int t = __shfl_up(inc, o, 64);
-                if (lane >= o) inc += t;
-            }
-            int above = inc - tot;
+            int above = wave_iscan(tot) - tot;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 if (above < need && need <= above + c[i]) {
