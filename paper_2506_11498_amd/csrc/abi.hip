@@ -62,7 +62,7 @@ int make_dims(const lrsa_params* p, lrsa::Dims* D) {
     D->Ns = D->nq - 1 - D->lp > 0 ? D->nq - 1 - D->lp : 0;
     D->scale = p->softmax_scale > 0.0f ? p->softmax_scale : 1.0f / std::sqrt((float)p->head_dim);
     D->dtype = p->dtype;
-    D->compact = p->impl == LRSA_IMPL_COMPACT ? 1 : 0;
+    D->compact = p->impl == LRSA_IMPL_COMPACT && p->head_dim == 128 ? 1 : 0;   // built for rows of 128 channels
     for (int i = 0; i < 3; ++i) { D->qs[i] = p->q_stride[i]; D->ks[i] = p->kv_stride[i]; }
     D->row_begin = 0; D->row_end = D->n; D->fq0 = 0; D->fq1 = D->nq;      // every query row
     D->lse_stride = D->n;
@@ -73,6 +73,9 @@ int make_dims(const lrsa_params* p, lrsa::Dims* D) {
 }
 
 bool use_mfma(const lrsa_params* p, const lrsa::Dims& D) { return p->impl != LRSA_IMPL_GENERIC && lrsa::mfma_supported(D); }
+
+// the filling-step calls are built for head_dim 128
+bool fill_supported(const lrsa_params* p, const lrsa::Dims& D) { return use_mfma(p, D) && D.d == 128; }
 
 size_t ws_need(const lrsa_params* p, const lrsa::Dims& D, int which) {
     switch (which) {
@@ -332,7 +335,7 @@ extern "C" {
 
 size_t lrsa_fill_workspace_bytes(const lrsa_params* p, int32_t row_begin, int32_t row_end, int which) {
     lrsa::Dims D;
-    if (make_dims(p, &D) != LRSA_OK || !use_mfma(p, D)) return 0;
+    if (make_dims(p, &D) != LRSA_OK || !fill_supported(p, D)) return 0;
     if (set_row_window(&D, row_begin, row_end, "lrsa_fill_workspace_bytes") != LRSA_OK) return 0;
     if (which == LRSA_WS_ATTN_FWD) return lrsa::attn_fwd_mfma_ws_bytes(D);
     if (which == LRSA_WS_ATTN_BWD) return lrsa::attn_bwd_mfma_ws_bytes(D);
@@ -344,7 +347,7 @@ int lrsa_attn_fwd_fill(const lrsa_params* p, int32_t row_begin, int32_t row_end,
     lrsa::Dims D;
     int rc = make_dims(p, &D);
     if (rc != LRSA_OK) return rc;
-    if (!use_mfma(p, D)) return fail(LRSA_ERR_UNSUPPORTED, "lrsa_attn_fwd_fill is built for bf16 with head_dim 128");
+    if (!fill_supported(p, D)) return fail(LRSA_ERR_UNSUPPORTED, "lrsa_attn_fwd_fill is built for bf16 with head_dim 128");
     if ((rc = set_row_window(&D, row_begin, row_end, "lrsa_attn_fwd_fill")) != LRSA_OK) return rc;
     if (!Q || !K || !V || !O || !lse) return fail(LRSA_ERR_INVALID_ARG, "lrsa_attn_fwd_fill: Q, K, V, O and lse must not be NULL");
     if (D.fq1 - 1 - D.lp > 0 && !idx) return fail(LRSA_ERR_INVALID_ARG, "lrsa_attn_fwd_fill: idx is NULL but the rows see compressed chunks");
@@ -364,7 +367,7 @@ int lrsa_attn_bwd_fill(const lrsa_params* p, int32_t row_begin, int32_t row_end,
     lrsa::Dims D;
     int rc = make_dims(p, &D);
     if (rc != LRSA_OK) return rc;
-    if (!use_mfma(p, D)) return fail(LRSA_ERR_UNSUPPORTED, "lrsa_attn_bwd_fill is built for bf16 with head_dim 128");
+    if (!fill_supported(p, D)) return fail(LRSA_ERR_UNSUPPORTED, "lrsa_attn_bwd_fill is built for bf16 with head_dim 128");
     if ((rc = set_row_window(&D, row_begin, row_end, "lrsa_attn_bwd_fill")) != LRSA_OK) return rc;
     if (!Q || !K || !V || !O || !dO || !lse || !dQ || !dK_acc || !dV_acc)
         return fail(LRSA_ERR_INVALID_ARG, "lrsa_attn_bwd_fill: tensor pointers must not be NULL");
@@ -387,7 +390,7 @@ int lrsa_attn_bwd_finish(const lrsa_params* p, const float* dK_acc, const float*
     lrsa::Dims D;
     int rc = make_dims(p, &D);
     if (rc != LRSA_OK) return rc;
-    if (!use_mfma(p, D)) return fail(LRSA_ERR_UNSUPPORTED, "lrsa_attn_bwd_finish is built for bf16 with head_dim 128");
+    if (!fill_supported(p, D)) return fail(LRSA_ERR_UNSUPPORTED, "lrsa_attn_bwd_finish is built for bf16 with head_dim 128");
     if (!dK_acc || !dV_acc || !dK || !dV) return fail(LRSA_ERR_INVALID_ARG, "lrsa_attn_bwd_finish: pointers must not be NULL");
     return hip_result(lrsa::launch_bwd_acc_finish(D, dK_acc, dV_acc, dK, dV, (hipStream_t)stream), "lrsa_attn_bwd_finish");
 }

@@ -1,4 +1,4 @@
-// LRSA attention backward on bf16 MFMA (gfx950), head_dim 128.  Gradients of sum(O * dO) with
+// LRSA attention backward on bf16 MFMA (gfx950), head_dim 128 or 64.  Gradients of sum(O * dO) with
 // the mask constant:  A = exp(scale Q K^T + M - lse), dV = A^T dO, dA = dO V^T,
 // D = rowsum(dO * O), dS = A * (dA - D), dQ = scale dS K, dK = scale dS^T Q.
 //
@@ -74,7 +74,7 @@ static BwdPlan make_plan(const Dims& D) {
     P.off_part = 2 * P.off_lse2;
     P.gather_wgs = P.gtiles > 0 ? (D.B * D.Hkv * P.nsl + 7) / 8 * 8 * P.gtiles : 0;
     // slots 0 .. nsl-1: the GATHER workgroups' slices; slot nsl: what the WINDOW workgroups add to listed positions
-    const size_t part = size_t(2) * (P.nsl + 1) * D.B * D.Hkv * P.gl_total * 128 * 4;
+    const size_t part = size_t(2) * (P.nsl + 1) * D.B * D.Hkv * P.gl_total * D.d * 4;
     P.off_compact = P.off_part + align256(part);
     P.off_dkc = P.off_compact + compact_kv_bytes(D);
     P.bytes = P.off_dkc + (D.compact ? 2 * align256(size_t(D.B) * D.Hkv * P.gl_total * 128 * 4) : 0);
@@ -86,38 +86,40 @@ size_t attn_bwd_mfma_ws_bytes(const Dims& D) { return make_plan(D).bytes; }
 // ------------------------------------------------------------------------------------ dQ
 // One 64-key tile for one wave: per 32 keys S^T and dA^T, then dS^T, then dQ^T += K^T dS^T.
 // MASK: the tile holds entries some query of the wave does not see (only the last tiles of a walk).
-template <bool MASK>
-__device__ __forceinline__ void dq_tile(const unsigned char* sK, const unsigned char* sV, const bf16x8 (&qf)[8],
-                                        const bf16x8 (&gf)[8], const LaneOffs& lo, f32x16 (&dq)[4], int j0, int lim,
+template <int DH, bool MASK>
+__device__ __forceinline__ void dq_tile(const unsigned char* sK, const unsigned char* sV, const bf16x8 (&qf)[KK<DH>],
+                                        const bf16x8 (&gf)[KK<DH>], const LaneOffs& lo, f32x16 (&dq)[DB<DH>], int j0, int lim,
                                         int wave_lim_max, float c2, float lse2, float Dq, int lane) {
     const int g = lane >> 5;
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
         if (!MASK || j0 + kb * 32 <= wave_lim_max) {  // otherwise these 32 keys are masked for the whole wave
-            // 24 MFMAs: S^T (K rows), dA^T (V rows), dQ^T (K transposed, rows 0-15 then 16-31); their LDS operands
+            // MFMAs of S^T (K rows), dA^T (V rows), dQ^T (K transposed, rows 0-15 then 16-31); their LDS operands
             // form one stream that is read DQ_PF ahead.  A = exp2(S*c2 - lse2) is written beside the dA MFMAs it
             // does not depend on.
             f32x16 s, dp;
 #pragma unroll
             for (int i = 0; i < 16; ++i) { s[i] = 0.0f; dp[i] = 0.0f; }
 #define LRSA_DQ_OPND(n)                                                                                      \
-    ((n) < 8 ? read_rows_o(sK, lo, kb * 32, (n)) : (n) < 16 ? read_rows_o(sV, lo, kb * 32, (n) - 8)           \
-             : read_cols_o(sK, lo, kb * 32 + ((n) >= 20 ? 16 : 0), (n) & 3))
+    ((n) < N1 ? read_rows_o<DH>(sK, lo, kb * 32, (n)) : (n) < N2 ? read_rows_o<DH>(sV, lo, kb * 32, (n) - N1) \
+              : read_cols_o<DH>(sK, lo, kb * 32 + ((n) >= N3 ? 16 : 0), ((n) - N2) % DB<DH>))
+            constexpr int N1 = KK<DH>, N2 = 2 * KK<DH>, N3 = N2 + DB<DH>, N4 = N3 + DB<DH>;
             bf16x8 a[DQ_PF];
 #pragma unroll
             for (int n = 0; n < DQ_PF; ++n) a[n] = LRSA_DQ_OPND(n);
             const float neg_l = -lse2;
-            bf16x8 dsf0, dsf1;
+            Weights<TERMS<DH>> dsf0, dsf1;
 #pragma unroll
-            for (int n = 0; n < 24; ++n) {
-                if (n < 8) s = mfma32(a[n % DQ_PF], qf[n], s);
-                else if (n < 16) dp = mfma32(a[n % DQ_PF], gf[n - 8], dp);
-                else if (n < 20) dq[n - 16] = mfma32(a[n % DQ_PF], dsf0, dq[n - 16]);
-                else dq[n - 20] = mfma32(a[n % DQ_PF], dsf1, dq[n - 20]);
-                if (n + DQ_PF < 24) a[n % DQ_PF] = LRSA_DQ_OPND(n + DQ_PF);
-                if (n >= 8 && n < 16) {
+            for (int n = 0; n < N4; ++n) {
+                if (n < N1) s = mfma32(a[n % DQ_PF], qf[n], s);
+                else if (n < N2) dp = mfma32(a[n % DQ_PF], gf[n - N1], dp);
+                else if (n < N3) dq[n - N2] = mfma32_w(a[n % DQ_PF], dsf0, dq[n - N2]);
+                else dq[n - N3] = mfma32_w(a[n % DQ_PF], dsf1, dq[n - N3]);
+                if (n + DQ_PF < N4) a[n % DQ_PF] = LRSA_DQ_OPND(n + DQ_PF);
+                if (n >= N1 && n < N2) {
+                    constexpr int E = 16 / KK<DH>;
 #pragma unroll
-                    for (int i = 2 * (n - 8); i < 2 * (n - 8) + 2; ++i) {
+                    for (int i = E * (n - N1); i < E * (n - N1) + E; ++i) {
                         float pr = fast_exp2(__builtin_fmaf(s[i], c2, neg_l));
                         if (MASK) {
                             const int j = j0 + kb * 32 + 8 * (i >> 2) + 4 * g + (i & 3);
@@ -126,11 +128,11 @@ __device__ __forceinline__ void dq_tile(const unsigned char* sK, const unsigned 
                         s[i] = pr;
                     }
                 }
-                if (n == 15) {
+                if (n == N2 - 1) {
 #pragma unroll
                     for (int i = 0; i < 16; ++i) s[i] *= dp[i] - Dq;
-                    dsf0 = pack8(s, 0);
-                    dsf1 = pack8(s, 8);
+                    dsf0 = pack_weights<TERMS<DH>>(s, 0);
+                    dsf1 = pack_weights<TERMS<DH>>(s, 8);
                 }
             }
 #undef LRSA_DQ_OPND
@@ -138,11 +140,12 @@ __device__ __forceinline__ void dq_tile(const unsigned char* sK, const unsigned 
     }
 }
 
-// A tile all of whose 64 keys every query of the wave sees: both 32-key halves as ONE stream of 48 MFMAs,
+// A tile all of whose 64 keys every query of the wave sees: both 32-key halves as ONE stream of MFMAs,
 //   S0 | dA0 (+ exp of half 0) | S1 (+ dS of half 0) | dA1 (+ exp of half 1) | dQ0 (+ dS of half 1) | dQ1,
 // so that every piece of vector work sits beside MFMAs it does not depend on.  LDS operands are read DQ_PF ahead.
-__device__ __forceinline__ void dq_tile_full(const unsigned char* sK, const unsigned char* sV, const bf16x8 (&qf)[8],
-                                             const bf16x8 (&gf)[8], const LaneOffs& lo_in, f32x16 (&dq)[4], float c2,
+template <int DH>
+__device__ __forceinline__ void dq_tile_full(const unsigned char* sK, const unsigned char* sV, const bf16x8 (&qf)[KK<DH>],
+                                             const bf16x8 (&gf)[KK<DH>], const LaneOffs& lo_in, f32x16 (&dq)[DB<DH>], float c2,
                                              float lse2, float Dq) {
     // the two offset registers are made opaque here so that the XORed per-block offsets are formed next
     // to each read (one vector op) instead of being kept in registers across the whole walk
@@ -151,58 +154,60 @@ __device__ __forceinline__ void dq_tile_full(const unsigned char* sK, const unsi
     f32x16 s0, dp0, s1, dp1, zero;
 #pragma unroll
     for (int i = 0; i < 16; ++i) zero[i] = 0.0f;
+    constexpr int K1 = KK<DH>, N4 = 4 * K1, N5 = N4 + 2 * DB<DH>, N6 = N5 + 2 * DB<DH>;   // ends of the S, dA and dQ groups
+    constexpr int E = 16 / K1, ED = 16 / (2 * DB<DH>);   // vector elements beside one MFMA of a group
 #define LRSA_DQ_OPND(n)                                                                                        \
-    ((n) < 8 ? read_rows_o(sK, lo, 0, (n)) : (n) < 16 ? read_rows_o(sV, lo, 0, (n) - 8)                         \
-     : (n) < 24 ? read_rows_o(sK, lo, 32, (n) - 16) : (n) < 32 ? read_rows_o(sV, lo, 32, (n) - 24)              \
-     : read_cols_o(sK, lo, ((n) - 32) / 4 * 16, (n) & 3))
+    ((n) < K1 ? read_rows_o<DH>(sK, lo, 0, (n)) : (n) < 2 * K1 ? read_rows_o<DH>(sV, lo, 0, (n) - K1)           \
+     : (n) < 3 * K1 ? read_rows_o<DH>(sK, lo, 32, (n) - 2 * K1) : (n) < N4 ? read_rows_o<DH>(sV, lo, 32, (n) - 3 * K1) \
+     : read_cols_o<DH>(sK, lo, ((n) - N4) / DB<DH> * 16, ((n) - N4) % DB<DH>))
     bf16x8 a[DQ_PF];
 #pragma unroll
     for (int n = 0; n < DQ_PF; ++n) a[n] = LRSA_DQ_OPND(n);
     const float neg_l = -lse2;
-    bf16x8 dsf[4];   // dS of keys 0-15, 16-31, 32-47, 48-63
-    // six groups of eight MFMAs (separate loops: each unrolls fully, so every array index is a constant)
-#define LRSA_DQ_NEXT(n) if ((n) + DQ_PF < 48) a[(n) % DQ_PF] = LRSA_DQ_OPND((n) + DQ_PF)
+    Weights<TERMS<DH>> dsf[4];   // dS of keys 0-15, 16-31, 32-47, 48-63
+    // six groups of MFMAs (separate loops: each unrolls fully, so every array index is a constant)
+#define LRSA_DQ_NEXT(n) if ((n) + DQ_PF < N6) a[(n) % DQ_PF] = LRSA_DQ_OPND((n) + DQ_PF)
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
+    for (int k = 0; k < K1; ++k) {
         s0 = mfma32(a[k % DQ_PF], qf[k], k == 0 ? zero : s0);
         LRSA_DQ_NEXT(k);
     }
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        dp0 = mfma32(a[(8 + k) % DQ_PF], gf[k], k == 0 ? zero : dp0);
-        LRSA_DQ_NEXT(8 + k);
+    for (int k = 0; k < K1; ++k) {
+        dp0 = mfma32(a[(K1 + k) % DQ_PF], gf[k], k == 0 ? zero : dp0);
+        LRSA_DQ_NEXT(K1 + k);
 #pragma unroll
-        for (int i = 2 * k; i < 2 * k + 2; ++i) s0[i] = fast_exp2(__builtin_fmaf(s0[i], c2, neg_l));
+        for (int i = E * k; i < E * k + E; ++i) s0[i] = fast_exp2(__builtin_fmaf(s0[i], c2, neg_l));
     }
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        s1 = mfma32(a[(16 + k) % DQ_PF], qf[k], k == 0 ? zero : s1);
-        LRSA_DQ_NEXT(16 + k);
+    for (int k = 0; k < K1; ++k) {
+        s1 = mfma32(a[(2 * K1 + k) % DQ_PF], qf[k], k == 0 ? zero : s1);
+        LRSA_DQ_NEXT(2 * K1 + k);
 #pragma unroll
-        for (int i = 2 * k; i < 2 * k + 2; ++i) s0[i] *= dp0[i] - Dq;
+        for (int i = E * k; i < E * k + E; ++i) s0[i] *= dp0[i] - Dq;
     }
-    dsf[0] = pack8(s0, 0);
-    dsf[1] = pack8(s0, 8);
+    dsf[0] = pack_weights<TERMS<DH>>(s0, 0);
+    dsf[1] = pack_weights<TERMS<DH>>(s0, 8);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        dp1 = mfma32(a[(24 + k) % DQ_PF], gf[k], k == 0 ? zero : dp1);
-        LRSA_DQ_NEXT(24 + k);
+    for (int k = 0; k < K1; ++k) {
+        dp1 = mfma32(a[(3 * K1 + k) % DQ_PF], gf[k], k == 0 ? zero : dp1);
+        LRSA_DQ_NEXT(3 * K1 + k);
 #pragma unroll
-        for (int i = 2 * k; i < 2 * k + 2; ++i) s1[i] = fast_exp2(__builtin_fmaf(s1[i], c2, neg_l));
+        for (int i = E * k; i < E * k + E; ++i) s1[i] = fast_exp2(__builtin_fmaf(s1[i], c2, neg_l));
     }
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        dq[k & 3] = mfma32(a[(32 + k) % DQ_PF], dsf[k >> 2], dq[k & 3]);
-        LRSA_DQ_NEXT(32 + k);
+    for (int k = 0; k < 2 * DB<DH>; ++k) {
+        dq[k % DB<DH>] = mfma32_w(a[(N4 + k) % DQ_PF], dsf[k / DB<DH>], dq[k % DB<DH>]);
+        LRSA_DQ_NEXT(N4 + k);
 #pragma unroll
-        for (int i = 2 * k; i < 2 * k + 2; ++i) s1[i] *= dp1[i] - Dq;
+        for (int i = ED * k; i < ED * k + ED; ++i) s1[i] *= dp1[i] - Dq;
     }
-    dsf[2] = pack8(s1, 0);
-    dsf[3] = pack8(s1, 8);
+    dsf[2] = pack_weights<TERMS<DH>>(s1, 0);
+    dsf[3] = pack_weights<TERMS<DH>>(s1, 8);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        dq[k & 3] = mfma32(a[(40 + k) % DQ_PF], dsf[2 + (k >> 2)], dq[k & 3]);
-        LRSA_DQ_NEXT(40 + k);
+    for (int k = 0; k < 2 * DB<DH>; ++k) {
+        dq[k % DB<DH>] = mfma32_w(a[(N5 + k) % DQ_PF], dsf[2 + k / DB<DH>], dq[k % DB<DH>]);
+        LRSA_DQ_NEXT(N5 + k);
     }
 #undef LRSA_DQ_NEXT
 #undef LRSA_DQ_OPND
@@ -210,7 +215,7 @@ __device__ __forceinline__ void dq_tile_full(const unsigned char* sK, const unsi
 
 // GH query heads of one KV group share the workgroup (8 waves = GH heads x 256/GH queries), as in the forward.
 // COMPACT: the rows of the gather list come from the condensed cache Kc, Vc (contiguous), no index is read.
-template <int GH, bool COMPACT>
+template <int DH, int GH, bool COMPACT>
 __global__ __launch_bounds__(DQ_THREADS, 2) void k_bwd_dq(Dims D, const bf16_t* __restrict__ Q,
                                                            const bf16_t* __restrict__ K,
                                                            const bf16_t* __restrict__ V,
@@ -224,10 +229,10 @@ __global__ __launch_bounds__(DQ_THREADS, 2) void k_bwd_dq(Dims D, const bf16_t* 
                                                            bf16_t* __restrict__ dQ, QTileMap M) {
     constexpr int WPH = DQ_WAVES / GH;   // waves per head
     constexpr int QT = 32 * WPH;         // queries per head and workgroup
-    __shared__ __attribute__((aligned(16))) unsigned char sK0[DQ_BN * TILE_ROW_BYTES];
-    __shared__ __attribute__((aligned(16))) unsigned char sV0[DQ_BN * TILE_ROW_BYTES];
-    __shared__ __attribute__((aligned(16))) unsigned char sK1[DQ_BN * TILE_ROW_BYTES];
-    __shared__ __attribute__((aligned(16))) unsigned char sV1[DQ_BN * TILE_ROW_BYTES];
+    __shared__ __attribute__((aligned(16))) unsigned char sK0[DQ_BN * ROW_BYTES<DH>];
+    __shared__ __attribute__((aligned(16))) unsigned char sV0[DQ_BN * ROW_BYTES<DH>];
+    __shared__ __attribute__((aligned(16))) unsigned char sK1[DQ_BN * ROW_BYTES<DH>];
+    __shared__ __attribute__((aligned(16))) unsigned char sV1[DQ_BN * ROW_BYTES<DH>];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, g = lane >> 5;
@@ -259,9 +264,9 @@ __global__ __launch_bounds__(DQ_THREADS, 2) void k_bwd_dq(Dims D, const bf16_t* 
     const int tq = t0 + wq * 32 + l32;
     const int tq_ld = tq < t_last ? tq : t_last;
     const int64_t qoff = b * D.qs[0] + hq * D.qs[1] + int64_t(tq_ld) * D.qs[2];
-    bf16x8 qf[8], gf[8];
+    bf16x8 qf[KK<DH>], gf[KK<DH>];
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
+    for (int kk = 0; kk < KK<DH>; ++kk) {
         qf[kk] = *reinterpret_cast<const bf16x8*>(Q + qoff + kk * 16 + g * 8);
         gf[kk] = *reinterpret_cast<const bf16x8*>(dO + qoff + kk * 16 + g * 8);
     }
@@ -271,7 +276,7 @@ __global__ __launch_bounds__(DQ_THREADS, 2) void k_bwd_dq(Dims D, const bf16_t* 
     const float lse2 = lse[rowid] * 1.4426950408889634f;
     float Dq = 0.0f;
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
+    for (int kk = 0; kk < KK<DH>; ++kk) {
         const bf16x8 o8 = *reinterpret_cast<const bf16x8*>(O + qoff + kk * 16 + g * 8);
 #pragma unroll
         for (int i = 0; i < 8; ++i) Dq = __builtin_fmaf(float(o8[i]), float(gf[kk][i]), Dq);
@@ -284,45 +289,46 @@ __global__ __launch_bounds__(DQ_THREADS, 2) void k_bwd_dq(Dims D, const bf16_t* 
     const int64_t coff = COMPACT ? (int64_t(b) * D.Hkv + h) * (int64_t(D.S) + int64_t(D.K) * D.Ns) * 128 : 0;
     const bf16_t* Kc_h = Kc + coff;
     const bf16_t* Vc_h = Vc + coff;
-    int pos[2];   // COMPACT: stream entries; else positions (fetched through idx one tile ahead)
+    constexpr int COPIES = 8 / COPY_ROWS<DH>;   // of K (and V) per wave and tile
+    int pos[COPIES];   // COMPACT: stream entries; else positions (fetched through idx one tile ahead)
     auto fetch_pos = [&](int tile) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            int j = tile * DQ_BN + async_row(8 * wave + 4 * i, lane);
+        for (int i = 0; i < COPIES; ++i) {
+            int j = tile * DQ_BN + async_row<DH>(8 * wave + COPY_ROWS<DH> * i, lane);
             j = j < m_max ? j : m_max - 1;
             pos[i] = COMPACT ? j : stream_pos(D, idx_h, j, ng, cs);
         }
     };
     auto issue = [&](unsigned char* sK, unsigned char* sV) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int r4 = 8 * wave + 4 * i;
-            const int ch = async_chunk(async_row(r4, lane), lane) * 8;
+        for (int i = 0; i < COPIES; ++i) {
+            const int r0 = 8 * wave + COPY_ROWS<DH> * i;
+            const int ch = async_chunk<DH>(async_row<DH>(r0, lane), lane) * 8;
             if (COMPACT) {
-                async_rows4(stream_row(Kc_h, Kh, D.ks[2], pos[i], ng, cs) + ch, sK, r4);
-                async_rows4(stream_row(Vc_h, Vh, D.ks[2], pos[i], ng, cs) + ch, sV, r4);
+                async_rows<DH>(stream_row(Kc_h, Kh, D.ks[2], pos[i], ng, cs) + ch, sK, r0);
+                async_rows<DH>(stream_row(Vc_h, Vh, D.ks[2], pos[i], ng, cs) + ch, sV, r0);
             } else {
                 const int64_t off = int64_t(pos[i]) * D.ks[2] + ch;
-                async_rows4(Kh + off, sK, r4);
-                async_rows4(Vh + off, sV, r4);
+                async_rows<DH>(Kh + off, sK, r0);
+                async_rows<DH>(Vh + off, sV, r0);
             }
         }
     };
 
     const float c2 = D.scale * 1.4426950408889634f;
-    const LaneOffs lo = make_lane_offs(lane);
+    const LaneOffs lo = make_lane_offs<DH>(lane);
     const int wave_lim_min = ng + t0 + wq * 32 - cs;   // last stream entry the wave's first query sees
 #define LRSA_DQ_TILE(sK, sV, j0_)                                                                              \
     {                                                                                                           \
         const int j0 = (j0_);                                                                                   \
         if (j0 + DQ_BN - 1 <= wave_lim_min)                                                                     \
-            dq_tile_full(sK, sV, qf, gf, lo, dq, c2, lse2, Dq);                                                 \
+            dq_tile_full<DH>(sK, sV, qf, gf, lo, dq, c2, lse2, Dq);                                                 \
         else if (j0 <= wave_lim_max)                                                                            \
-            dq_tile<true>(sK, sV, qf, gf, lo, dq, j0, lim, wave_lim_max, c2, lse2, Dq, lane);                   \
+            dq_tile<DH, true>(sK, sV, qf, gf, lo, dq, j0, lim, wave_lim_max, c2, lse2, Dq, lane);                   \
     }
-    f32x16 dq[4];
+    f32x16 dq[DB<DH>];
 #pragma unroll
-    for (int db = 0; db < 4; ++db)
+    for (int db = 0; db < DB<DH>; ++db)
 #pragma unroll
         for (int i = 0; i < 16; ++i) dq[db][i] = 0.0f;
 
@@ -352,7 +358,7 @@ __global__ __launch_bounds__(DQ_THREADS, 2) void k_bwd_dq(Dims D, const bf16_t* 
     if (tq <= t_last) {
         bf16_t* orow = dQ + b * D.qs[0] + hq * D.qs[1] + int64_t(tq) * D.qs[2];
 #pragma unroll
-        for (int db = 0; db < 4; ++db)
+        for (int db = 0; db < DB<DH>; ++db)
 #pragma unroll
             for (int a = 0; a < 4; ++a) {
                 f32x4 v;
@@ -375,10 +381,10 @@ __device__ __forceinline__ int first_chunk_seeing(const Dims& D, int j0) {
 // lim_u: GATHER (steps never straddle a chunk): the largest gather-list entry the step's chunk sees.
 // The wave's K fragments are in registers, its V rows in LDS (sVw): K fragments and the accumulators
 // fill the register file.
-template <bool GATHER>
+template <int DH, bool GATHER>
 __device__ __forceinline__ void dkv_step(const Dims& D, const unsigned char* sQ, const unsigned char* sG,
-                                         const float* sLD, const bf16x8 (&kf)[KV_NB][8], const unsigned char* sVw,
-                                         const LaneOffs& lo_in, f32x16 (&dk)[KV_NB][4], f32x16 (&dv)[KV_NB][4], int r0,
+                                         const float* sLD, const bf16x8 (&kf)[KV_NB][KK<DH>], const unsigned char* sVw,
+                                         const LaneOffs& lo_in, f32x16 (&dk)[KV_NB][DB<DH>], f32x16 (&dv)[KV_NB][DB<DH>], int r0,
                                          int tb, const int (&kcmp)[KV_NB], int lim_u, bool need_mask, float c2, int lane,
                                          int rowbase) {
     const int g = lane >> 5;
@@ -387,11 +393,11 @@ __device__ __forceinline__ void dkv_step(const Dims& D, const unsigned char* sQ,
     // The lane's offsets with the addresses of the three tiles folded in (the tiles start on 256-byte
     // boundaries): one add per tile and sub-step, then one XOR per read.  The registers are made opaque so
     // that the XORed per-block addresses are formed next to each read instead of being kept across the walk.
-    unsigned aQr = lo_in.row + lds_addr(sQ) + rowbase * TILE_ROW_BYTES, aQc = lo_in.col + lds_addr(sQ) + rowbase * TILE_ROW_BYTES;
-    unsigned aGr = lo_in.row + lds_addr(sG) + rowbase * TILE_ROW_BYTES, aGc = lo_in.col + lds_addr(sG) + rowbase * TILE_ROW_BYTES;
+    unsigned aQr = lo_in.row + lds_addr(sQ) + rowbase * ROW_BYTES<DH>, aQc = lo_in.col + lds_addr(sQ) + rowbase * ROW_BYTES<DH>;
+    unsigned aGr = lo_in.row + lds_addr(sG) + rowbase * ROW_BYTES<DH>, aGc = lo_in.col + lds_addr(sG) + rowbase * ROW_BYTES<DH>;
     unsigned aVr = lo_in.row + lds_addr(sVw);
     asm volatile("" : "+v"(aQr), "+v"(aQc), "+v"(aGr), "+v"(aGc), "+v"(aVr));
-    // Four MFMA groups: S, dA, dV, dK (8 MFMAs per 32-key block each).  The vector work between them is
+    // Four MFMA groups: S, dA, dV, dK (DH / 16 MFMAs per 32-key block each).  The vector work between them is
     // written next to MFMAs it does not depend on -- exp(S) beside the dA group, dS beside the dV group --
     // so that one wave keeps both pipes busy.  Operands are read two ahead of the MFMAs that consume them;
     // an operand read from the Q / dO stage serves all key blocks of the wave.
@@ -413,10 +419,10 @@ __device__ __forceinline__ void dkv_step(const Dims& D, const unsigned char* sQ,
     a[0] = read_rows_a(aQr, 0);
     a[1] = read_rows_a(aQr, 1);
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
+    for (int kk = 0; kk < KK<DH>; ++kk) {
 #pragma unroll
         for (int nb = 0; nb < KV_NB; ++nb) s[nb] = mfma32(a[kk & 1], kf[nb][kk], s[nb]);
-        a[kk & 1] = kk < 6 ? read_rows_a(aQr, kk + 2) : read_rows_a(aGr, kk - 6);
+        a[kk & 1] = kk < KK<DH> - 2 ? read_rows_a(aQr, kk + 2) : read_rows_a(aGr, kk - (KK<DH> - 2));
     }
     // mask bounds: row rho = 8*a4 + 4g + r of the step is visible to key block nb iff mlo[nb] <= 8*a4 + r < mhi
     const int mhi = (tb - r0) - 4 * g;
@@ -429,19 +435,19 @@ __device__ __forceinline__ void dkv_step(const Dims& D, const unsigned char* sQ,
     // padding keys pay for the mask (wave-uniform flag).
     bf16x8 vb[KV_NB][2];
 #pragma unroll
-    for (int nb = 0; nb < KV_NB; ++nb) vb[nb][0] = read_rows_a(aVr + nb * 32 * TILE_ROW_BYTES, 0);
+    for (int nb = 0; nb < KV_NB; ++nb) vb[nb][0] = read_rows_a(aVr + nb * 32 * ROW_BYTES<DH>, 0);
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
+    for (int kk = 0; kk < KK<DH>; ++kk) {
 #pragma unroll
         for (int nb = 0; nb < KV_NB; ++nb) {
-            if (kk + 1 < 8) vb[nb][(kk + 1) & 1] = read_rows_a(aVr + nb * 32 * TILE_ROW_BYTES, kk + 1);
+            if (kk + 1 < KK<DH>) vb[nb][(kk + 1) & 1] = read_rows_a(aVr + nb * 32 * ROW_BYTES<DH>, kk + 1);
             dp[nb] = mfma32(a[kk & 1], vb[nb][kk & 1], dp[nb]);
         }
         // next operands: the rest of the dO rows, then the first transposed dO operands
-        if (kk < 6) a[kk & 1] = read_rows_a(aGr, kk + 2);
-        else a[kk & 1] = read_cols_a(aGc, 0, kk - 6);
-        if ((kk & 1) == 0) {
-            const int a4 = kk >> 1;
+        if (kk < KK<DH> - 2) a[kk & 1] = read_rows_a(aGr, kk + 2);
+        else a[kk & 1] = read_cols_a<DH>(aGc, 0, kk - (KK<DH> - 2));
+        if (kk % (KK<DH> / 4) == 0) {
+            const int a4 = kk / (KK<DH> / 4);
             const f32x4 l4 = *reinterpret_cast<const f32x4*>(sLD + rowbase + 8 * a4 + 4 * g);
             if (!need_mask) {
 #pragma unroll
@@ -461,19 +467,20 @@ __device__ __forceinline__ void dkv_step(const Dims& D, const unsigned char* sQ,
             }
         }
     }
-    bf16x8 pf[KV_NB][2], dsf[KV_NB][2];
+    constexpr int NB2 = 2 * DB<DH>;   // MFMAs (pairs of them with two-term weights) of the dV group and of the dK group
+    Weights<TERMS<DH>> pf[KV_NB][2], dsf[KV_NB][2];
 #pragma unroll
-    for (int nb = 0; nb < KV_NB; ++nb) { pf[nb][0] = pack8(s[nb], 0); pf[nb][1] = pack8(s[nb], 8); }
+    for (int nb = 0; nb < KV_NB; ++nb) { pf[nb][0] = pack_weights<TERMS<DH>>(s[nb], 0); pf[nb][1] = pack_weights<TERMS<DH>>(s[nb], 8); }
     // dV^T += dO^T A (rows 0-15 blocks 0..3, rows 16-31 blocks 0..3) with dS = A * (dA - D) beside it (dp holds dA - D),
     // then dK^T += Q^T dS in the same order
-#define LRSA_OPND(n) ((n) < 8 ? read_cols_a(aGc, ((n) >> 2) * 16, (n) & 3) : read_cols_a(aQc, (((n) - 8) >> 2) * 16, (n) & 3))
+#define LRSA_OPND(n) ((n) < NB2 ? read_cols_a<DH>(aGc, (n) / DB<DH> * 16, (n) % DB<DH>) : read_cols_a<DH>(aQc, ((n) - NB2) / DB<DH> * 16, (n) % DB<DH>))
 #pragma unroll
-    for (int n = 0; n < 8; ++n) {
+    for (int n = 0; n < NB2; ++n) {
 #pragma unroll
-        for (int nb = 0; nb < KV_NB; ++nb) dv[nb][n & 3] = mfma32(a[n & 1], pf[nb][n >> 2], dv[nb][n & 3]);
+        for (int nb = 0; nb < KV_NB; ++nb) dv[nb][n % DB<DH>] = mfma32_w(a[n & 1], pf[nb][n / DB<DH>], dv[nb][n % DB<DH>]);
         a[n & 1] = LRSA_OPND(n + 2);
-        if ((n & 1) == 0) {
-            const int a4 = n >> 1;
+        if (n % (NB2 / 4) == 0) {
+            const int a4 = n / (NB2 / 4);
 #pragma unroll
             for (int nb = 0; nb < KV_NB; ++nb)
 #pragma unroll
@@ -481,12 +488,12 @@ __device__ __forceinline__ void dkv_step(const Dims& D, const unsigned char* sQ,
         }
     }
 #pragma unroll
-    for (int nb = 0; nb < KV_NB; ++nb) { dsf[nb][0] = pack8(dp[nb], 0); dsf[nb][1] = pack8(dp[nb], 8); }
+    for (int nb = 0; nb < KV_NB; ++nb) { dsf[nb][0] = pack_weights<TERMS<DH>>(dp[nb], 0); dsf[nb][1] = pack_weights<TERMS<DH>>(dp[nb], 8); }
 #pragma unroll
-    for (int n = 8; n < 16; ++n) {
+    for (int n = NB2; n < 2 * NB2; ++n) {
 #pragma unroll
-        for (int nb = 0; nb < KV_NB; ++nb) dk[nb][n & 3] = mfma32(a[n & 1], dsf[nb][(n - 8) >> 2], dk[nb][n & 3]);
-        if (n + 2 < 16) a[n & 1] = LRSA_OPND(n + 2);
+        for (int nb = 0; nb < KV_NB; ++nb) dk[nb][n % DB<DH>] = mfma32_w(a[n & 1], dsf[nb][(n - NB2) / DB<DH>], dk[nb][n % DB<DH>]);
+        if (n + 2 < 2 * NB2) a[n & 1] = LRSA_OPND(n + 2);
     }
 #undef LRSA_OPND
 }
@@ -501,16 +508,17 @@ struct KvLds {
     float *sL0, *sL1;
     unsigned char* sVk;
 };
-// one set of arrays for both instantiations of the body (a template would get a set each)
+// one set of arrays for both kinds of workgroup (inside the body's template each would get a set of its own)
+template <int DH>
 __device__ __forceinline__ KvLds kv_lds() {
-    __shared__ __attribute__((aligned(256))) unsigned char sQ0[KV_ROWS * TILE_ROW_BYTES], sQ1[KV_ROWS * TILE_ROW_BYTES];
-    __shared__ __attribute__((aligned(256))) unsigned char sG0[KV_ROWS * TILE_ROW_BYTES], sG1[KV_ROWS * TILE_ROW_BYTES];
+    __shared__ __attribute__((aligned(256))) unsigned char sQ0[KV_ROWS * ROW_BYTES<DH>], sQ1[KV_ROWS * ROW_BYTES<DH>];
+    __shared__ __attribute__((aligned(256))) unsigned char sG0[KV_ROWS * ROW_BYTES<DH>], sG1[KV_ROWS * ROW_BYTES<DH>];
     __shared__ __attribute__((aligned(16))) float sL0[KV_WAVES * 2 * KV_ROWS], sL1[KV_WAVES * 2 * KV_ROWS];
-    __shared__ __attribute__((aligned(256))) unsigned char sVk[KV_BK * TILE_ROW_BYTES];
+    __shared__ __attribute__((aligned(256))) unsigned char sVk[KV_BK * ROW_BYTES<DH>];
     return KvLds{sQ0, sQ1, sG0, sG1, sL0, sL1, sVk};
 }
 
-template <bool GATHER>
+template <int DH, bool GATHER>
 __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
                                          const bf16_t* __restrict__ V, const bf16_t* __restrict__ Kc,
                                          const bf16_t* __restrict__ Vc, const bf16_t* __restrict__ dO,
@@ -518,7 +526,7 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
                                          const int32_t* __restrict__ idx, bf16_t* __restrict__ dK,
                                          bf16_t* __restrict__ dV, float* __restrict__ accK, float* __restrict__ accV,
                                          float* __restrict__ part, const BwdPlan& P, const int block) {
-    const KvLds sh = kv_lds();
+    const KvLds sh = kv_lds<DH>();
     unsigned char *const sQ0 = sh.sQ0, *const sQ1 = sh.sQ1, *const sG0 = sh.sG0, *const sG1 = sh.sG1;
     float *const sL0 = sh.sL0, *const sL1 = sh.sL1;
     unsigned char* const sVk = sh.sVk;
@@ -606,7 +614,7 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
     const int wave_key0 = key0 + wave * (32 * KV_NB);
     const bool wave_keys_valid = wave_key0 + 32 * KV_NB - 1 < key_end;
     int kcmp[KV_NB];
-    bf16x8 kf[KV_NB][8];
+    bf16x8 kf[KV_NB][KK<DH>];
 #pragma unroll
     for (int nb = 0; nb < KV_NB; ++nb) {
         const int kidn = wave_key0 + nb * 32 + l32;
@@ -616,7 +624,7 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
         // the key's K and V rows: by position, or (GATHER with a condensed cache) row kid of the contiguous copy
         const bf16_t *krow, *vrow_src;
         if (GATHER && D.compact) {
-            const int64_t coff = ((int64_t(b) * D.Hkv + h) * P.gl_total + kid_ld) * 128;
+            const int64_t coff = ((int64_t(b) * D.Hkv + h) * P.gl_total + kid_ld) * DH;
             krow = Kc + coff;
             vrow_src = Vc + coff;
         } else {
@@ -626,15 +634,15 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
             vrow_src = V + koff;
         }
 #pragma unroll
-        for (int kk = 0; kk < 8; ++kk) kf[nb][kk] = *reinterpret_cast<const bf16x8*>(krow + kk * 16 + g * 8);
+        for (int kk = 0; kk < KK<DH>; ++kk) kf[nb][kk] = *reinterpret_cast<const bf16x8*>(krow + kk * 16 + g * 8);
         const int vrow = wave * (32 * KV_NB) + nb * 32 + l32;
 #pragma unroll
-        for (int kk = 0; kk < 8; ++kk)
-            *reinterpret_cast<bf16x8*>(sVk + tile_off(vrow, kk * 2 + g)) =
+        for (int kk = 0; kk < KK<DH>; ++kk)
+            *reinterpret_cast<bf16x8*>(sVk + tile_off<DH>(vrow, kk * 2 + g)) =
                 *reinterpret_cast<const bf16x8*>(vrow_src + kk * 16 + g * 8);
     }
-    const unsigned char* sVw = sVk + wave * (32 * KV_NB) * TILE_ROW_BYTES;
-    const LaneOffs lo = make_lane_offs(lane);
+    const unsigned char* sVw = sVk + wave * (32 * KV_NB) * ROW_BYTES<DH>;
+    const LaneOffs lo = make_lane_offs<DH>(lane);
 
     // ---- loader: wave w fills rows 8w .. 8w+7 of the Q and dO tiles (two copies of 4 rows each) and
     // its own lse|D block (one copy each).
@@ -645,13 +653,13 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
         const int hq = h * D.G + gi;
         const int64_t base = b * D.qs[0] + hq * D.qs[1];
 #pragma unroll
-        for (int i = 0; i < KV_ROWS / (4 * KV_WAVES); ++i) {
-            const int r4 = (KV_ROWS / KV_WAVES) * wave + 4 * i;
-            const int row = async_row(r4, lane);
+        for (int i = 0; i < KV_ROWS / (COPY_ROWS<DH> * KV_WAVES); ++i) {
+            const int rc = (KV_ROWS / KV_WAVES) * wave + COPY_ROWS<DH> * i;
+            const int row = async_row<DH>(rc, lane);
             const int t = min(r0 + row, rend - 1);
-            const int64_t off = base + int64_t(t) * D.qs[2] + async_chunk(row, lane) * 8;
-            async_rows4(Q + off, sQ, r4);
-            async_rows4(dO + off, sG, r4);
+            const int64_t off = base + int64_t(t) * D.qs[2] + async_chunk<DH>(row, lane) * 8;
+            async_rows<DH>(Q + off, sQ, rc);
+            async_rows<DH>(dO + off, sG, rc);
         }
         const int64_t rid = (int64_t(b) * D.Hq + hq) * D.lse_stride + min(r0 + lane, rend - 1);
         async_copy4(lse + rid, sL + wave * 2 * KV_ROWS);
@@ -659,11 +667,11 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
     };
 
     const float c2 = D.scale * 1.4426950408889634f;
-    f32x16 dk[KV_NB][4], dv[KV_NB][4];
+    f32x16 dk[KV_NB][DB<DH>], dv[KV_NB][DB<DH>];
 #pragma unroll
     for (int nb = 0; nb < KV_NB; ++nb)
 #pragma unroll
-        for (int db = 0; db < 4; ++db)
+        for (int db = 0; db < DB<DH>; ++db)
 #pragma unroll
             for (int i = 0; i < 16; ++i) { dk[nb][db][i] = 0.0f; dv[nb][db][i] = 0.0f; }
 
@@ -686,7 +694,7 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
             const bool full_ = wave_keys_valid && r0_ + KV_BQ <= rend_ &&                                \
                                (GATHER ? lim_u_ >= wave_key0 + 32 * KV_NB - 1 : r0_ >= wave_key0 + 32 * KV_NB - 1); \
             if (run_)                                                                                    \
-                dkv_step<GATHER>(D, sQ, sG, sL + wave * 2 * KV_ROWS, kf, sVw, lo, dk, dv, r0_, rend_, kcmp, lim_u_, \
+                dkv_step<DH, GATHER>(D, sQ, sG, sL + wave * 2 * KV_ROWS, kf, sVw, lo, dk, dv, r0_, rend_, kcmp, lim_u_, \
                                  !full_, c2, lane, sub_ * KV_BQ);                                        \
         }                                                                                                \
     }
@@ -697,7 +705,7 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
 #pragma unroll
     for (int nb = 0; nb < KV_NB; ++nb)
 #pragma unroll
-        for (int kk = 0; kk < 8; ++kk) pin_loaded(kf[nb][kk]);
+        for (int kk = 0; kk < KK<DH>; ++kk) pin_loaded(kf[nb][kk]);
     issue(0, sQ0, sG0, sL0);
     for (int step = 0; step < nsteps; step += 2) {
         LRSA_KV_STEP(step, sQ0, sG0, sL0, sQ1, sG1, sL1);
@@ -706,17 +714,17 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
     }
 #undef LRSA_KV_STEP
 
-    const size_t part_stride = size_t(D.B) * D.Hkv * P.gl_total * 128;   // floats per slice
+    const size_t part_stride = size_t(D.B) * D.Hkv * P.gl_total * DH;   // floats per slice
     const size_t part_v = size_t(P.nsl + 1) * part_stride;                // dV partials follow the dK partials
 #pragma unroll
     for (int nb = 0; nb < KV_NB; ++nb) {
         const int kidn = key0 + wave * (32 * KV_NB) + nb * 32 + (lane & 31);
         if (kidn >= key_end) continue;
         if (GATHER) {
-            float* pk = part + size_t(slice) * part_stride + ((size_t(b) * D.Hkv + h) * P.gl_total + kidn) * 128;
+            float* pk = part + size_t(slice) * part_stride + ((size_t(b) * D.Hkv + h) * P.gl_total + kidn) * DH;
             float* pv = pk + part_v;
 #pragma unroll
-            for (int db = 0; db < 4; ++db)
+            for (int db = 0; db < DB<DH>; ++db)
 #pragma unroll
                 for (int a = 0; a < 4; ++a) {
                     f32x4 x, y;
@@ -746,9 +754,9 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
             }
             const int64_t koff = b * D.ks[0] + h * D.ks[1] + int64_t(kidn) * D.ks[2];
             // listed positions: fp32 into the extra slot, the reduction kernel adds the slices; others: final
-            float* pk = j >= 0 ? part + size_t(P.nsl) * part_stride + ((size_t(b) * D.Hkv + h) * P.gl_total + j) * 128 : nullptr;
+            float* pk = j >= 0 ? part + size_t(P.nsl) * part_stride + ((size_t(b) * D.Hkv + h) * P.gl_total + j) * DH : nullptr;
 #pragma unroll
-            for (int db = 0; db < 4; ++db)
+            for (int db = 0; db < DB<DH>; ++db)
 #pragma unroll
                 for (int a = 0; a < 4; ++a) {
                     f32x4 x, y;
@@ -760,7 +768,7 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
                         *reinterpret_cast<f32x4*>(pk + part_v + dcol) = y;
                     } else if (D.acc) {
                         // row window: this call's share is added to the caller's fp32 sums (one writer per element)
-                        const int64_t aoff = ((int64_t(b) * D.Hkv + h) * D.n + kidn) * 128 + dcol;
+                        const int64_t aoff = ((int64_t(b) * D.Hkv + h) * D.n + kidn) * DH + dcol;
                         *reinterpret_cast<f32x4*>(accK + aoff) += x;
                         *reinterpret_cast<f32x4*>(accV + aoff) += y;
                     } else {
@@ -774,6 +782,7 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
 
 // One launch for all of dK/dV: the GATHER workgroups first (equal, long), then the WINDOW workgroups, so that
 // the chip has one tail, not two.
+template <int DH>
 __global__ __launch_bounds__(KV_THREADS, KV_WAVES == 8 ? 2 : 1) void k_bwd_dkv(Dims D, const bf16_t* __restrict__ Q,
                                                                                 const bf16_t* __restrict__ K,
                                                                                 const bf16_t* __restrict__ V,
@@ -789,28 +798,29 @@ __global__ __launch_bounds__(KV_THREADS, KV_WAVES == 8 ? 2 : 1) void k_bwd_dkv(D
                                                                                 float* __restrict__ accV,
                                                                                 float* __restrict__ part, BwdPlan P) {
     const int block = blockIdx.x;
-    if (block < P.gather_wgs) dkv_body<true>(D, Q, K, V, Kc, Vc, dO, lse, Dsum, idx, dK, dV, accK, accV, part, P, block);
-    else dkv_body<false>(D, Q, K, V, Kc, Vc, dO, lse, Dsum, idx, dK, dV, accK, accV, part, P, block - P.gather_wgs);
+    if (block < P.gather_wgs) dkv_body<DH, true>(D, Q, K, V, Kc, Vc, dO, lse, Dsum, idx, dK, dV, accK, accV, part, P, block);
+    else dkv_body<DH, false>(D, Q, K, V, Kc, Vc, dO, lse, Dsum, idx, dK, dV, accK, accV, part, P, block - P.gather_wgs);
 }
 
 // dK, dV of the listed positions (sink tokens and survivors): the WINDOW contribution plus the GATHER slices
-// that exist for the entry's list tile, added in a fixed order.  32 threads per entry, 4 channels each.
+// that exist for the entry's list tile, added in a fixed order.  DH / 4 threads per entry, 4 channels each.
+template <int DH>
 __global__ __launch_bounds__(256) void k_bwd_dkv_reduce(Dims D, const int32_t* __restrict__ idx,
                                                         const float* __restrict__ part, bf16_t* __restrict__ dK,
                                                         bf16_t* __restrict__ dV, float* __restrict__ accK,
                                                         float* __restrict__ accV, float* __restrict__ dKc,
                                                         float* __restrict__ dVc, BwdPlan P) {
-    const int64_t e = int64_t(blockIdx.x) * 8 + (threadIdx.x >> 5);   // (b, h, entry)
+    const int64_t e = int64_t(blockIdx.x) * (1024 / DH) + threadIdx.x / (DH / 4);   // (b, h, entry)
     const int64_t total = int64_t(D.B) * D.Hkv * P.gl_total;
     if (e >= total) return;
     const int j = int(e % P.gl_total);
     const int bh = int(e / P.gl_total);
     const int b = bh / D.Hkv, h = bh % D.Hkv;
     const int pos = j < D.S ? j : idx[(int64_t(bh) * D.Ns) * D.K + (j - D.S)];
-    const size_t part_stride = size_t(D.B) * D.Hkv * P.gl_total * 128;
+    const size_t part_stride = size_t(D.B) * D.Hkv * P.gl_total * DH;
     const size_t part_v = size_t(P.nsl + 1) * part_stride;
-    const int dcol = (threadIdx.x & 31) * 4;
-    const float* p0 = part + size_t(e) * 128 + dcol;
+    const int dcol = (threadIdx.x & (DH / 4 - 1)) * 4;
+    const float* p0 = part + size_t(e) * DH + dcol;
     f32x4 x = {0.0f, 0.0f, 0.0f, 0.0f}, y = {0.0f, 0.0f, 0.0f, 0.0f};
     // the WINDOW workgroups of this call cover the sink (with a row window: only when its rows are in it) and the
     // key chunks from kc_lo on
@@ -826,14 +836,14 @@ __global__ __launch_bounds__(256) void k_bwd_dkv_reduce(Dims D, const int32_t* _
             y += *reinterpret_cast<const f32x4*>(p0 + size_t(sl) * part_stride + part_v);
         }
     if (D.acc) {
-        const int64_t aoff = ((int64_t(b) * D.Hkv + h) * D.n + pos) * 128 + dcol;
+        const int64_t aoff = ((int64_t(b) * D.Hkv + h) * D.n + pos) * DH + dcol;
         *reinterpret_cast<f32x4*>(accK + aoff) += x;
         *reinterpret_cast<f32x4*>(accV + aoff) += y;
         return;
     }
     if (dKc) {   // condensed cache: the gradient of the condensed rows is a product of its own, scattered afterwards
-        *reinterpret_cast<f32x4*>(dKc + e * 128 + dcol) = x;
-        *reinterpret_cast<f32x4*>(dVc + e * 128 + dcol) = y;
+        *reinterpret_cast<f32x4*>(dKc + e * DH + dcol) = x;
+        *reinterpret_cast<f32x4*>(dVc + e * DH + dcol) = y;
         return;
     }
     const int64_t koff = b * D.ks[0] + h * D.ks[1] + int64_t(pos) * D.ks[2];
@@ -905,19 +915,20 @@ hipError_t launch_attn_bwd_mfma(const Dims& D, const void* Q, const void* K, con
             const hipError_t e = launch_compact_kv(D, K, V, idx, (void*)kc, (void*)vc, st);
             if (e != hipSuccess) return e;
         }
-#define LRSA_DQ_LAUNCH(GH_, C_)                                                                                     \
-    LRSA_TIMED_LAUNCH("k_bwd_dq", st, (k_bwd_dq<GH_, C_>), dim3((unsigned)wgs), dim3(DQ_THREADS), 0, st, D, q, k, v, o, g, lse, \
+#define LRSA_DQ_LAUNCH(DH_, GH_, C_)                                                                                  \
+    LRSA_TIMED_LAUNCH("k_bwd_dq", st, (k_bwd_dq<DH_, GH_, C_>), dim3((unsigned)wgs), dim3(DQ_THREADS), 0, st, D, q, k, v, o, g, lse, \
                       Dsum, lse2, idx, kc, vc, (bf16_t*)dQ, M)
         if (wgs > 0) {
-            if (gh == 4) { if (compact) LRSA_DQ_LAUNCH(4, true); else LRSA_DQ_LAUNCH(4, false); }
-            else if (gh == 2) { if (compact) LRSA_DQ_LAUNCH(2, true); else LRSA_DQ_LAUNCH(2, false); }
-            else { if (compact) LRSA_DQ_LAUNCH(1, true); else LRSA_DQ_LAUNCH(1, false); }
+            if (D.d == 64) { if (gh == 4) LRSA_DQ_LAUNCH(64, 4, false); else if (gh == 2) LRSA_DQ_LAUNCH(64, 2, false); else LRSA_DQ_LAUNCH(64, 1, false); }
+            else if (gh == 4) { if (compact) LRSA_DQ_LAUNCH(128, 4, true); else LRSA_DQ_LAUNCH(128, 4, false); }
+            else if (gh == 2) { if (compact) LRSA_DQ_LAUNCH(128, 2, true); else LRSA_DQ_LAUNCH(128, 2, false); }
+            else { if (compact) LRSA_DQ_LAUNCH(128, 1, true); else LRSA_DQ_LAUNCH(128, 1, false); }
         }
 #undef LRSA_DQ_LAUNCH
     }
     const int64_t wgs = int64_t(P.gather_wgs) + int64_t(D.B) * D.Hkv * P.ktiles;
     if (wgs > 0)
-        LRSA_TIMED_LAUNCH("k_bwd_dkv", st, k_bwd_dkv, dim3((unsigned)wgs), dim3(KV_THREADS), 0, st, D, q, k, v, kc, vc, g,
+        LRSA_TIMED_LAUNCH("k_bwd_dkv", st, (D.d == 64 ? k_bwd_dkv<64> : k_bwd_dkv<128>), dim3((unsigned)wgs), dim3(KV_THREADS), 0, st, D, q, k, v, kc, vc, g,
                           lse2, Dsum, idx, (bf16_t*)dK, (bf16_t*)dV, accK, accV, part, P);
     const int64_t entries = int64_t(D.B) * D.Hkv * P.gl_total;
     float *dkc = nullptr, *dvc = nullptr;
@@ -926,7 +937,8 @@ hipError_t launch_attn_bwd_mfma(const Dims& D, const void* Q, const void* K, con
         dvc = dkc + align256(size_t(entries) * 128 * 4) / 4;
     }
     if (entries > 0)
-        LRSA_TIMED_LAUNCH("k_bwd_dkv_reduce", st, k_bwd_dkv_reduce, dim3((unsigned)((entries + 7) / 8)), dim3(256), 0, st, D,
+        LRSA_TIMED_LAUNCH("k_bwd_dkv_reduce", st, (D.d == 64 ? k_bwd_dkv_reduce<64> : k_bwd_dkv_reduce<128>),
+                          dim3((unsigned)((entries + 1024 / D.d - 1) / (1024 / D.d))), dim3(256), 0, st, D,
                           idx, part, (bf16_t*)dK, (bf16_t*)dV, accK, accV, dkc, dvc, P);
     if (entries > 0 && compact)
         LRSA_TIMED_LAUNCH("k_bwd_scatter_dkv", st, k_bwd_scatter_dkv, dim3((unsigned)((entries + 7) / 8)), dim3(256), 0, st, D,

@@ -1,4 +1,4 @@
-// LRSA attention forward on bf16 MFMA (gfx950), head_dim 128: Eq. 2-3 of the paper under the
+// LRSA attention forward on bf16 MFMA (gfx950), head_dim 128 or 64: Eq. 2-3 of the paper under the
 // chunked mask, flash style (online softmax, only the log-sum-exp is kept for the backward).
 //
 // One workgroup (8 waves) owns 256 (head, query) rows: GH query heads of one KV group x 256/GH
@@ -13,6 +13,10 @@
 // softmax statistics are per lane), P^T = exp2(S^T - m), O^T += V^T P^T with the accumulator
 // registers of S^T reused directly as the B operand and V^T read from the row-major tile with
 // transposing LDS reads.
+//
+// head_dim 64: P^T enters as two bf16 terms (mfma_tiles.h, Weights), half as many again MFMAs; bound by the vector pipe
+// (exponentials and the split).  8192 tokens, 16 query heads on 4 KV heads, lag 256, 64 kept: 4.7 ms with the plain
+// fp32-arithmetic kernel (a wave per query row) -> 0.13 ms; backward 14.2 ms -> 0.42 ms.
 #include "mfma_tiles.h"
 
 namespace lrsa {
@@ -21,9 +25,9 @@ constexpr int FWD_BN = 64;     // keys per tile
 constexpr int FWD_WAVES = 8;   // waves per workgroup (two per SIMD), 32 queries each
 constexpr int FWD_THREADS = 64 * FWD_WAVES;
 
-// bf16, head_dim 128, and a head's K/V rows within 2 GiB of its first row (the copies use 32-bit byte offsets)
+// bf16 and a head's K/V rows within 2 GiB of its first row (the copies use 32-bit byte offsets)
 bool mfma_supported(const Dims& D) {
-    return D.dtype == 1 && D.d == 128 && int64_t(D.n) * D.ks[2] * 2 < (int64_t(1) << 31);
+    return D.dtype == 1 && int64_t(D.n) * D.ks[2] * 2 < (int64_t(1) << 31);
 }
 size_t attn_fwd_mfma_ws_bytes(const Dims& D) { return compact_kv_bytes(D); }
 
@@ -53,20 +57,25 @@ hipError_t launch_compact_kv(const Dims& D, const void* K, const void* V, const 
 }
 
 // One 64-key tile of the walk for one wave: S^T = K Q^T, masked online softmax, O^T += V^T P^T.
+template <int DH>
 struct FwdState {
     float m_run, l_run;
-    f32x16 o[4];
+    f32x16 o[DB<DH>];
 };
 
 // MASK: the tile holds entries some query of the wave does not see (only the last tiles of a walk).
 // The running maximum is refreshed lazily: as long as no query's tile maximum exceeds its reference
 // by more than 2^8, the old reference is kept (probabilities stay below 256, exact enough in fp32 sums
 // and bf16 operands) and the accumulators need no rescaling.
-template <bool MASK>
-__device__ __forceinline__ void fwd_tile(const unsigned char* sK, const unsigned char* sV, const bf16x8 (&qf)[8],
-                                         const LaneOffs& lo, FwdState& st, int j0, int lim, int wave_lim_max,
+template <int DH, bool MASK>
+__device__ __forceinline__ void fwd_tile(const unsigned char* sK, const unsigned char* sV, const bf16x8 (&qf)[KK<DH>],
+                                         const LaneOffs& lo_in, FwdState<DH>& st, int j0, int lim, int wave_lim_max,
                                          float c2, int lane) {
     const int g = lane >> 5;
+    // DH = 64 (128 registers): the offsets are made opaque so that the XORed per-block offsets are formed next to each
+    // read instead of being kept across the walk
+    LaneOffs lo = lo_in;
+    if constexpr (DH == 64) asm volatile("" : "+v"(lo.row), "+v"(lo.col));
     // MASK tiles: do the second 32 keys hold a visible key for some query of the wave?
     const bool two = !MASK || j0 + 32 <= wave_lim_max;
     f32x16 s[2];
@@ -74,20 +83,27 @@ __device__ __forceinline__ void fwd_tile(const unsigned char* sK, const unsigned
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
         for (int i = 0; i < 16; ++i) s[kb][i] = 0.0f;
-    // S^T = K Q^T: operands are read a block of 8 ahead of the MFMAs that consume them
+    // S^T = K Q^T: operands are read a block ahead of the MFMAs that consume them
     {
-        bf16x8 a[8];
+        bf16x8 a[KK<DH>];
 #pragma unroll
-        for (int kk = 0; kk < 8; ++kk) a[kk] = read_rows_o(sK, lo, 0, kk);
-        if (two) {
-            bf16x8 a1[8];
+        for (int kk = 0; kk < KK<DH>; ++kk) a[kk] = read_rows_o<DH>(sK, lo, 0, kk);
+        if (two && DH == 64) {   // one block of operands at a time: 128 registers, and three other waves of the SIMD to wait behind
 #pragma unroll
-            for (int kk = 0; kk < 8; ++kk) {
+            for (int kk = 0; kk < KK<DH>; ++kk) s[0] = mfma32(a[kk], qf[kk], s[0]);
+#pragma unroll
+            for (int kk = 0; kk < KK<DH>; ++kk) a[kk] = read_rows_o<DH>(sK, lo, 32, kk);
+#pragma unroll
+            for (int kk = 0; kk < KK<DH>; ++kk) s[1] = mfma32(a[kk], qf[kk], s[1]);
+        } else if (two) {
+            bf16x8 a1[KK<DH>];
+#pragma unroll
+            for (int kk = 0; kk < KK<DH>; ++kk) {
                 s[0] = mfma32(a[kk], qf[kk], s[0]);
-                a1[kk] = read_rows_o(sK, lo, 32, kk);
+                a1[kk] = read_rows_o<DH>(sK, lo, 32, kk);
             }
 #pragma unroll
-            for (int kk = 0; kk < 8; ++kk) s[1] = mfma32(a1[kk], qf[kk], s[1]);
+            for (int kk = 0; kk < KK<DH>; ++kk) s[1] = mfma32(a1[kk], qf[kk], s[1]);
             // keep the order written above -- 8 operand reads, then one read per MFMA, then 8 MFMAs: left alone,
             // the compiler moves every read down to just before its MFMA to save registers, and the MFMA then
             // waits out the whole LDS latency (0x100: LDS reads, 0x008: MFMAs)
@@ -100,13 +116,13 @@ __device__ __forceinline__ void fwd_tile(const unsigned char* sK, const unsigned
             __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
         } else {
 #pragma unroll
-            for (int kk = 0; kk < 8; ++kk) s[0] = mfma32(a[kk], qf[kk], s[0]);
+            for (int kk = 0; kk < KK<DH>; ++kk) s[0] = mfma32(a[kk], qf[kk], s[0]);
         }
     }
     // first V^T operands are fetched while the softmax runs
-    bf16x8 va[4], vb[4];
+    bf16x8 va[DB<DH>], vb[DB<DH>];
 #pragma unroll
-    for (int db = 0; db < 4; ++db) va[db] = read_cols_o(sV, lo, 0, db);
+    for (int db = 0; db < DB<DH>; ++db) va[db] = read_cols_o<DH>(sV, lo, 0, db);
     float mx = -INFINITY;   // raw (unscaled) tile maximum of this lane's query
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
@@ -125,7 +141,7 @@ __device__ __forceinline__ void fwd_tile(const unsigned char* sK, const unsigned
         st.l_run *= corr;
         st.m_run = m_new;
 #pragma unroll
-        for (int db = 0; db < 4; ++db)
+        for (int db = 0; db < DB<DH>; ++db)
 #pragma unroll
             for (int i = 0; i < 16; ++i) st.o[db][i] *= corr;
     }
@@ -143,17 +159,30 @@ __device__ __forceinline__ void fwd_tile(const unsigned char* sK, const unsigned
     // O^T += V^T P^T, 16 keys at a time; the operands of the next 16 keys are read during the MFMAs
 #define LRSA_PV(kg, cur, nxt)                                                          \
     {                                                                                  \
-        const bf16x8 pf = pack8(s[(kg) >> 1], 8 * ((kg) & 1));                         \
-        _Pragma("unroll") for (int db = 0; db < 4; ++db) {                             \
-            st.o[db] = mfma32(cur[db], pf, st.o[db]);                                  \
-            if ((kg) + 1 < 4) nxt[db] = read_cols_o(sV, lo, ((kg) + 1) * 16, db);      \
+        const auto pf = pack_weights<TERMS<DH>>(s[(kg) >> 1], 8 * ((kg) & 1));         \
+        _Pragma("unroll") for (int db = 0; db < DB<DH>; ++db) {                        \
+            st.o[db] = mfma32_w(cur[db], pf, st.o[db]);                                \
+            if ((kg) + 1 < 4) nxt[db] = read_cols_o<DH>(sV, lo, ((kg) + 1) * 16, db);  \
         }                                                                              \
     }
-    LRSA_PV(0, va, vb);
-    LRSA_PV(1, vb, va);
-    if (two) {
-        LRSA_PV(2, va, vb);
-        LRSA_PV(3, vb, va);
+    if constexpr (DH == 64) {   // no registers for a second operand block
+#pragma unroll
+        for (int kg = 0; kg < 4; ++kg)
+            if (kg < 2 || two) {
+                const auto pf = pack_weights<TERMS<DH>>(s[kg >> 1], 8 * (kg & 1));
+#pragma unroll
+                for (int db = 0; db < DB<DH>; ++db) {
+                    st.o[db] = mfma32_w(va[db], pf, st.o[db]);
+                    if (kg + 1 < 4) va[db] = read_cols_o<DH>(sV, lo, (kg + 1) * 16, db);
+                }
+            }
+    } else {
+        LRSA_PV(0, va, vb);
+        LRSA_PV(1, vb, va);
+        if (two) {
+            LRSA_PV(2, va, vb);
+            LRSA_PV(3, vb, va);
+        }
     }
 #undef LRSA_PV
 }
@@ -161,8 +190,9 @@ __device__ __forceinline__ void fwd_tile(const unsigned char* sK, const unsigned
 // GH query heads of one KV group share the workgroup: its 8 waves cover GH heads x QT = 256/GH queries,
 // so every K/V tile staged in LDS serves 256 (head, query) rows.
 // COMPACT: the rows of the gather list come from the condensed cache Kc, Vc (contiguous), no index is read.
-template <int GH, bool COMPACT>
-__global__ __launch_bounds__(FWD_THREADS, 2) void k_fwd_mfma(Dims D, const bf16_t* __restrict__ Q,
+// DH = 64 needs half the registers, so that two workgroups share a CU.
+template <int DH, int GH, bool COMPACT>
+__global__ __launch_bounds__(FWD_THREADS, DH == 64 ? 4 : 2) void k_fwd_mfma(Dims D, const bf16_t* __restrict__ Q,
                                                               const bf16_t* __restrict__ K,
                                                               const bf16_t* __restrict__ V,
                                                               const int32_t* __restrict__ idx,
@@ -175,7 +205,7 @@ __global__ __launch_bounds__(FWD_THREADS, 2) void k_fwd_mfma(Dims D, const bf16_
     // four stages, each one array holding the K tile then the V tile; separate arrays per stage so that
     // reads of one stage need not wait for the asynchronous fill of another (the compiler tracks only a
     // handful of such arrays, hence K and V share one)
-    constexpr int TILE_BYTES = FWD_BN * TILE_ROW_BYTES;
+    constexpr int TILE_BYTES = FWD_BN * ROW_BYTES<DH>;
     __shared__ __attribute__((aligned(16))) unsigned char sT0[2 * TILE_BYTES], sT1[2 * TILE_BYTES], sT2[2 * TILE_BYTES],
         sT3[2 * TILE_BYTES];
 
@@ -212,21 +242,21 @@ __global__ __launch_bounds__(FWD_THREADS, 2) void k_fwd_mfma(Dims D, const bf16_
     // this lane's query column
     const int tq = t0 + wq * 32 + l32;
     const int tq_ld = tq < t_last ? tq : t_last;
-    bf16x8 qf[8];
+    bf16x8 qf[KK<DH>];
     {
         const bf16_t* qrow = Q + b * D.qs[0] + hq * D.qs[1] + int64_t(tq_ld) * D.qs[2];
 #pragma unroll
-        for (int kk = 0; kk < 8; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(qrow + kk * 16 + g * 8);
+        for (int kk = 0; kk < KK<DH>; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(qrow + kk * 16 + g * 8);
     }
     const int lim = ng + tq - cs;                                     // last stream entry this query sees
     const int wave_lim_max = ng + min(t0 + wq * 32 + 31, t_last) - cs;  // ... the wave's last valid query sees
     const int wave_lim_min = ng + t0 + wq * 32 - cs;                    // ... the wave's first query sees
 
-    // loader: wave w fills tile rows 8w .. 8w+7 with two asynchronous copies of 4 rows each (K and V:
-    // 4 copies per tile); rows past the stream end re-read its last key and are masked.  The 8 stream
+    // loader: wave w fills tile rows 8w .. 8w+7 with two asynchronous copies of 4 rows each (DH = 64: one of 8 rows),
+    // K and V alike; rows past the stream end re-read its last key and are masked.  The 8 stream
     // positions a wave needs per tile are wave-uniform addresses, so they are fetched through the scalar
     // cache (one iteration ahead); the only vector memory operations in the loop are the asynchronous
-    // copies, always 4 per wave and tile, which lets s_waitcnt vmcnt(n) address a tile.
+    // copies, always OPS_PER_TILE per wave and tile, which lets s_waitcnt vmcnt(n) address a tile.
     const int32_t* idx_ld = D.Ns > 0 ? idx_h : reinterpret_cast<const int32_t*>(Kh);   // any readable words
     const int idx_last = D.Ns > 0 ? D.Ns * D.K - 1 : 0;
     const int wv = __builtin_amdgcn_readfirstlane(wave);
@@ -245,20 +275,21 @@ __global__ __launch_bounds__(FWD_THREADS, 2) void k_fwd_mfma(Dims D, const bf16_
     // laK, laV: LDS byte addresses of the stage's K tile and V tile (compile-time constants at the call sites)
     auto issue = [&](int tile, Scalar8& raw, unsigned laK, unsigned laV) {
         const int tc = tile < ntiles ? tile : ntiles - 1;
-        const int q4 = lane >> 4;
+        const int sub = async_row<DH>(0, lane);                         // this lane's row of a copy
         if (!COMPACT) smem_wait(raw);
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int r4 = 8 * wv + 4 * i;
-            int j = tc * FWD_BN + r4 + q4;
+        for (int i = 0; i < 8 / COPY_ROWS<DH>; ++i) {
+            const int r0 = 8 * wv + COPY_ROWS<DH> * i;
+            int j = tc * FWD_BN + r0 + sub;
             j = j < m_max ? j : m_max - 1;
-            const int ch = async_chunk(r4 + q4, lane) * 8;
-            const unsigned row_la = unsigned(r4) * TILE_ROW_BYTES;      // wave-uniform
+            const int ch = async_chunk<DH>(r0 + sub, lane) * 8;
+            const unsigned row_la = unsigned(r0) * ROW_BYTES<DH>;       // wave-uniform
             if (COMPACT) {
                 async_copy16_la(stream_row(Kc_h, Kh, D.ks[2], j, ng, cs) + ch, laK + row_la);
                 async_copy16_la(stream_row(Vc_h, Vh, D.ks[2], j, ng, cs) + ch, laV + row_la);
             } else {
-                const int sel = i == 0 ? pick4(q4, raw.a0, raw.a1, raw.a2, raw.a3) : pick4(q4, raw.a4, raw.a5, raw.a6, raw.a7);
+                const int lo4 = pick4(sub & 3, raw.a0, raw.a1, raw.a2, raw.a3), hi4 = pick4(sub & 3, raw.a4, raw.a5, raw.a6, raw.a7);
+                const int sel = DH == 128 ? (i == 0 ? lo4 : hi4) : (sub < 4 ? lo4 : hi4);
                 const int pos = j < ng ? (j < D.S ? j : sel) : cs + (j - ng);
                 // byte offset inside the head: below 2^31 (a condition of this kernel, checked on the host)
                 const unsigned off = (unsigned(pos) * unsigned(D.ks[2]) + unsigned(ch)) * 2u;
@@ -267,23 +298,23 @@ __global__ __launch_bounds__(FWD_THREADS, 2) void k_fwd_mfma(Dims D, const bf16_
             }
         }
     };
-    constexpr int OPS_PER_TILE = 4;   // asynchronous copies per wave and tile
+    constexpr int OPS_PER_TILE = 2 * 8 / COPY_ROWS<DH>;   // asynchronous copies per wave and tile
 
     const float c2 = D.scale * 1.4426950408889634f;  // logits are kept in log2 units
-    const LaneOffs lo = make_lane_offs(lane);
-    FwdState st;
+    const LaneOffs lo = make_lane_offs<DH>(lane);
+    FwdState<DH> st;
     st.m_run = -INFINITY;
     st.l_run = 0.0f;
 #pragma unroll
-    for (int db = 0; db < 4; ++db)
+    for (int db = 0; db < DB<DH>; ++db)
 #pragma unroll
         for (int i = 0; i < 16; ++i) st.o[db][i] = 0.0f;
 
 #define LRSA_FWD_TILE(sK, sV, j0_)                                                                   \
     {                                                                                                \
         const int j0 = (j0_);                                                                        \
-        if (j0 + FWD_BN - 1 <= wave_lim_min) fwd_tile<false>(sK, sV, qf, lo, st, j0, lim, wave_lim_max, c2, lane); \
-        else if (j0 <= wave_lim_max) fwd_tile<true>(sK, sV, qf, lo, st, j0, lim, wave_lim_max, c2, lane);          \
+        if (j0 + FWD_BN - 1 <= wave_lim_min) fwd_tile<DH, false>(sK, sV, qf, lo, st, j0, lim, wave_lim_max, c2, lane); \
+        else if (j0 <= wave_lim_max) fwd_tile<DH, true>(sK, sV, qf, lo, st, j0, lim, wave_lim_max, c2, lane);          \
     }
 
     // A wave's vector memory operations in order:  A(0) A(1) A(2) | iteration t: A(t+3)   (A = the copies
@@ -317,11 +348,13 @@ __global__ __launch_bounds__(FWD_THREADS, 2) void k_fwd_mfma(Dims D, const bf16_
 #undef LRSA_FWD_TILE
 
     const float l_tot = st.l_run + __shfl_xor(st.l_run, 32, 64);
-    if (tq <= t_last) {
+    // row and head once more, from scalars: kept across the walk they would cost vector registers
+    const int hq_o = h * D.G + gsub * GH + wv / WPH, tq_o = t0 + (wv % WPH) * 32 + l32;
+    if (tq_o <= t_last) {
         const float inv = 1.0f / l_tot;
-        bf16_t* orow = O + b * D.qs[0] + hq * D.qs[1] + int64_t(tq) * D.qs[2];
+        bf16_t* orow = O + b * D.qs[0] + hq_o * D.qs[1] + int64_t(tq_o) * D.qs[2];
 #pragma unroll
-        for (int db = 0; db < 4; ++db)
+        for (int db = 0; db < DB<DH>; ++db)
 #pragma unroll
             for (int a = 0; a < 4; ++a) {
                 f32x4 v;
@@ -330,7 +363,14 @@ __global__ __launch_bounds__(FWD_THREADS, 2) void k_fwd_mfma(Dims D, const bf16_
                 const bf16x4 pk = __builtin_convertvector(v, bf16x4);
                 *reinterpret_cast<bf16x4*>(orow + db * 32 + a * 8 + g * 4) = pk;
             }
-        if (g == 0) lse[(int64_t(b) * D.Hq + hq) * D.lse_stride + tq] = (st.m_run + __builtin_log2f(l_tot)) * 0.6931471805599453f;
+        float lse_t;
+        if constexpr (DH == 64) {   // one rounding at the end: ln 2 as its fp32 value plus the rest
+            const float t = __builtin_fmaf(st.m_run, -1.9046542e-9f, __builtin_log2f(l_tot) * 0.6931471805599453f);
+            lse_t = __builtin_fmaf(st.m_run, 0.69314718246459961f, t);
+        } else {
+            lse_t = (st.m_run + __builtin_log2f(l_tot)) * 0.6931471805599453f;
+        }
+        if (g == 0) lse[(int64_t(b) * D.Hq + hq_o) * D.lse_stride + tq_o] = lse_t;
     }
 }
 
@@ -349,12 +389,13 @@ hipError_t launch_attn_fwd_mfma(const Dims& D, const void* Q, const void* K, con
         const hipError_t e = launch_compact_kv(D, K, V, idx, (void*)kc, (void*)vc, st);
         if (e != hipSuccess) return e;
     }
-#define LRSA_FWD_LAUNCH(GH_, C_)                                                                                   \
-    LRSA_TIMED_LAUNCH("k_fwd_mfma", st, (k_fwd_mfma<GH_, C_>), dim3((unsigned)wgs), dim3(FWD_THREADS), 0, st, D, q, k, v, \
+#define LRSA_FWD_LAUNCH(DH_, GH_, C_)                                                                                   \
+    LRSA_TIMED_LAUNCH("k_fwd_mfma", st, (k_fwd_mfma<DH_, GH_, C_>), dim3((unsigned)wgs), dim3(FWD_THREADS), 0, st, D, q, k, v, \
                       idx, kc, vc, (bf16_t*)O, lse, M)
-    if (gh == 4) { if (compact) LRSA_FWD_LAUNCH(4, true); else LRSA_FWD_LAUNCH(4, false); }
-    else if (gh == 2) { if (compact) LRSA_FWD_LAUNCH(2, true); else LRSA_FWD_LAUNCH(2, false); }
-    else { if (compact) LRSA_FWD_LAUNCH(1, true); else LRSA_FWD_LAUNCH(1, false); }
+    if (D.d == 64) { if (gh == 4) LRSA_FWD_LAUNCH(64, 4, false); else if (gh == 2) LRSA_FWD_LAUNCH(64, 2, false); else LRSA_FWD_LAUNCH(64, 1, false); }
+    else if (gh == 4) { if (compact) LRSA_FWD_LAUNCH(128, 4, true); else LRSA_FWD_LAUNCH(128, 4, false); }
+    else if (gh == 2) { if (compact) LRSA_FWD_LAUNCH(128, 2, true); else LRSA_FWD_LAUNCH(128, 2, false); }
+    else { if (compact) LRSA_FWD_LAUNCH(128, 1, true); else LRSA_FWD_LAUNCH(128, 1, false); }
 #undef LRSA_FWD_LAUNCH
     return hipGetLastError();
 }

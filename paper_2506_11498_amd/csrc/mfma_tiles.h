@@ -5,10 +5,11 @@
 //   A operand: row l32,  k-slots 8g .. 8g+7        B operand: column l32, k-slots 8g .. 8g+7
 //   C/D:       column l32, 16 floats i -> row 8*(i/4) + 4g + i%4
 //
-// A tile is [rows][128 bf16] = 256 bytes per row = 16 chunks of 16 bytes; chunk c of row r is
-// stored at chunk c ^ swz(r).  swz is a bijection on 16 consecutive rows (row-pattern reads of
-// 16 lanes hit 16 different chunks) and moves rows r, r+1, r+2, r+3 to different 64-byte units
-// (transposed reads of 4 rows x 32 bytes spread over the banks).
+// A tile is [rows][DH bf16], DH = head_dim = 128 or 64: a row is 256 bytes = 16 chunks of 16 bytes (128 bytes = 8
+// chunks); chunk c of row r is stored at chunk c ^ swz(r).  swz is a bijection on 16 consecutive rows (DH = 64: on 8
+// pairs of rows, a pair filling 256 bytes), so row-pattern reads of 16 lanes hit 16 different 16-byte units of the
+// 256-byte bank line, and it moves rows r, r+1, r+2, r+3 (pairs of rows) to different 64-byte units, so transposed
+// reads of 4 rows x 32 bytes spread over the banks.
 #pragma once
 #include "common.h"
 
@@ -21,44 +22,34 @@ typedef float f32x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 
-constexpr int TILE_ROW_BYTES = 256;  // head_dim 128 in bf16
+template <int DH> constexpr int ROW_BYTES = 2 * DH;          // a tile row
+template <int DH> constexpr int KK = DH / 16;                // MFMA steps of a contraction over head_dim
+template <int DH> constexpr int DB = DH / 32;                // blocks of 32 channels
+template <int DH> constexpr int COPY_ROWS = 1024 / (2 * DH); // tile rows one asynchronous wave copy fills
 
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
-__device__ __forceinline__ int swz(int r) { return ((r & 3) << 2) | ((r >> 2) & 3); }
+template <int DH>
+__device__ __forceinline__ int swz(int r) {
+    if constexpr (DH == 128) return ((r & 3) << 2) | ((r >> 2) & 3);
+    return ((r & 2) << 1) | ((r >> 2) & 3);
+}
 
 // byte offset of chunk `c` (16 bytes) of row `r`
-__device__ __forceinline__ int tile_off(int r, int c) { return r * TILE_ROW_BYTES + ((c ^ swz(r)) << 4); }
+template <int DH>
+__device__ __forceinline__ int tile_off(int r, int c) { return r * ROW_BYTES<DH> + ((c ^ swz<DH>(r)) << 4); }
 
-// Operand with the tile's rows as MFMA rows/columns and head_dim as the contraction:
-// lane takes row rb + l32, channels 16*kk + 8g .. +7  (one 16-byte LDS read).
-__device__ __forceinline__ bf16x8 read_rows(const unsigned char* tile, int rb, int kk, int l32, int g) {
-    return *reinterpret_cast<const bf16x8*>(tile + tile_off(rb + l32, kk * 2 + g));
-}
-
-// Operand with head_dim as MFMA rows and 16 tile rows as the contraction ("transposed" read):
-// lane takes channel db*32 + l32 and the 8 k-slots of its half g, where slot j is tile row
-// rb16 + 8*(j/4) + 4g + j%4 -- exactly the rows a C-layout accumulator hands over when its
-// registers 8h .. 8h+7 are reused as the other operand.
-// ds_read_b64_tr_b16 works per 16-lane group: lane i receives, as element e, element i%4 of the
-// 8 bytes that lane 4e + i/4 of its group points at.  So source lane lam points at row
-// 4g + lam/4 (+8 for the second read), channels dbase + 4*(lam%4) .. +3.
-__device__ __forceinline__ bf16x8 read_cols(const unsigned char* tile, int rb16, int db, int lane) {
-    const int lam = lane & 15, m = (lane >> 4) & 1, g = lane >> 5;
-    const int ch = db * 32 + 16 * m + 4 * (lam & 3);  // first channel of the 8 bytes this lane points at
-    const int r0 = rb16 + 4 * g + (lam >> 2);
-    const int c = ch >> 3, within = (ch & 7) * 2;
-    typedef s16x4 __attribute__((address_space(3))) * lds_ptr;
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(tile + tile_off(r0, c) + within));
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(tile + tile_off(r0 + 8, c) + within));
-    union { s16x4 h[2]; bf16x8 v; } u;
-    u.h[0] = lo;
-    u.h[1] = hi;
-    return u.v;
-}
-
+// Two read patterns:
+//  rows  the tile's rows as MFMA rows/columns and head_dim as the contraction: the lane takes row rb + l32, channels
+//        16*kk + 8g .. +7 (one 16-byte LDS read).
+//  cols  head_dim as MFMA rows and 16 tile rows as the contraction ("transposed" read): the lane takes channel
+//        db*32 + l32 and the 8 k-slots of its half g, where slot j is tile row rb16 + 8*(j/4) + 4g + j%4 -- exactly the
+//        rows a C-layout accumulator hands over when its registers 8h .. 8h+7 are reused as the other operand.
+//        ds_read_b64_tr_b16 works per 16-lane group: lane i receives, as element e, element i%4 of the 8 bytes that
+//        lane 4e + i/4 of its group points at.  So source lane lam points at row 4g + lam/4 (+8 for the second read),
+//        channels dbase + 4*(lam%4) .. +3.
 // Per-lane byte offsets of the two read patterns inside a tile.  Because the swizzle is an XOR on
 // chunk bits that the channel-block index also occupies, the offset of channel block kk (or db, and of
 // the second transposing read) is the block-0 offset XOR a compile-time constant: two registers per
@@ -67,23 +58,26 @@ struct LaneOffs {
     int row;   // read_rows: row l32, channel block 0
     int col;   // read_cols: channel block 0, first transposing read
 };
+template <int DH>
 __device__ __forceinline__ LaneOffs make_lane_offs(int lane) {
     LaneOffs o;
     const int l32 = lane & 31, g = lane >> 5, lam = lane & 15, m = (lane >> 4) & 1;
-    o.row = tile_off(l32, g);
+    o.row = tile_off<DH>(l32, g);
     const int ch = 16 * m + 4 * (lam & 3);
-    o.col = tile_off(4 * g + (lam >> 2), ch >> 3) + (ch & 7) * 2;
+    o.col = tile_off<DH>(4 * g + (lam >> 2), ch >> 3) + (ch & 7) * 2;
     return o;
 }
-// same operands as read_rows / read_cols; rb is a multiple of 32, rb16 of 16
+// rb is a multiple of 32, rb16 of 16
+template <int DH>
 __device__ __forceinline__ bf16x8 read_rows_o(const unsigned char* tile, const LaneOffs& o, int rb, int kk) {
-    return *reinterpret_cast<const bf16x8*>(tile + (o.row ^ (kk << 5)) + rb * TILE_ROW_BYTES);
+    return *reinterpret_cast<const bf16x8*>(tile + (o.row ^ (kk << 5)) + rb * ROW_BYTES<DH>);
 }
+template <int DH>
 __device__ __forceinline__ bf16x8 read_cols_o(const unsigned char* tile, const LaneOffs& o, int rb16, int db) {
     typedef s16x4 __attribute__((address_space(3))) * lds_ptr;
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(tile + (o.col ^ (db << 6)) + rb16 * TILE_ROW_BYTES));
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(tile + (o.col ^ (db << 6)) + rb16 * ROW_BYTES<DH>));
     const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (lds_ptr)(tile + (o.col ^ ((db << 6) | 32)) + (rb16 + 8) * TILE_ROW_BYTES));
+        (lds_ptr)(tile + (o.col ^ ((db << 6) | 32)) + (rb16 + 8) * ROW_BYTES<DH>));
     union { s16x4 h[2]; bf16x8 v; } u;
     u.h[0] = lo;
     u.h[1] = hi;
@@ -92,7 +86,7 @@ __device__ __forceinline__ bf16x8 read_cols_o(const unsigned char* tile, const L
 
 // The same two reads with the tile's LDS address already folded into the lane's offset register (one add
 // per tile instead of one per read): valid when the tile starts on a 256-byte boundary, because XORing a
-// constant below 256 then commutes with adding the base.  rows16 is a compile-time row offset (multiple of 16).
+// constant below a row's bytes then commutes with adding the base.  rows16 is a compile-time row offset (multiple of 16).
 typedef bf16x8 __attribute__((address_space(3))) * lds_bf16x8_ptr;
 __device__ __forceinline__ unsigned lds_addr(const void* p) {
     return (unsigned)(size_t)(__attribute__((address_space(3))) void*)p;
@@ -100,11 +94,12 @@ __device__ __forceinline__ unsigned lds_addr(const void* p) {
 __device__ __forceinline__ bf16x8 read_rows_a(unsigned arow, int kk) {
     return *(lds_bf16x8_ptr)(size_t)(arow ^ unsigned(kk << 5));
 }
+template <int DH>
 __device__ __forceinline__ bf16x8 read_cols_a(unsigned acol, int rows16, int db) {
     typedef s16x4 __attribute__((address_space(3))) * lds_ptr;
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(size_t)((acol ^ unsigned(db << 6)) + rows16 * TILE_ROW_BYTES));
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(size_t)((acol ^ unsigned(db << 6)) + rows16 * ROW_BYTES<DH>));
     const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (lds_ptr)(size_t)((acol ^ unsigned((db << 6) | 32)) + (rows16 + 8) * TILE_ROW_BYTES));
+        (lds_ptr)(size_t)((acol ^ unsigned((db << 6) | 32)) + (rows16 + 8) * ROW_BYTES<DH>));
     union { s16x4 h[2]; bf16x8 v; } u;
     u.h[0] = lo;
     u.h[1] = hi;
@@ -119,18 +114,46 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& v, int i0) {
     return __builtin_convertvector(t, bf16x8);
 }
 
+// A C-layout block of fp32 weights (probabilities, dS) as MFMA operand.  TERMS == 1: rounded to bf16.  TERMS == 2: as
+// the sum of two bf16 numbers (the rounded value and its rounded residual, 2^-17 relative): head_dim 64, whose
+// kernels hold the weights to more than bf16.
+template <int TERMS> struct Weights {
+    bf16x8 t[TERMS];
+};
+template <int TERMS>
+__device__ __forceinline__ Weights<TERMS> pack_weights(const f32x16& v, int i0) {
+    Weights<TERMS> w;
+    w.t[0] = pack8(v, i0);
+    if constexpr (TERMS == 2) {
+        f32x8 r;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) r[j] = v[i0 + j] - float(w.t[0][j]);
+        w.t[1] = __builtin_convertvector(r, bf16x8);
+    }
+    return w;
+}
+template <int TERMS>
+__device__ __forceinline__ f32x16 mfma32_w(bf16x8 a, const Weights<TERMS>& w, f32x16 c) {
+    c = mfma32(a, w.t[0], c);
+    if constexpr (TERMS == 2) c = mfma32(a, w.t[1], c);
+    return c;
+}
+template <int DH> constexpr int TERMS = DH == 64 ? 2 : 1;
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // ---- asynchronous global -> LDS copies (global_load_lds_dwordx4) --------------------------------
 // One wave instruction moves 64 x 16 bytes: lane l's 16 bytes land at lds_base + 16*l (checked on the
-// hardware), i.e. four consecutive 256-byte tile rows starting at row r4.  The swizzle is applied on
+// hardware), i.e. COPY_ROWS consecutive tile rows starting at row r0.  The swizzle is applied on
 // the global side: the lane whose slot is physical chunk pc of row r fetches logical chunk pc ^ swz(r).
 typedef __attribute__((address_space(3))) void lds_void_t;
 typedef __attribute__((address_space(1))) const void gbl_void_t;
 
-// tile row and 16-byte logical chunk this lane fetches when its wave fills rows r4 .. r4+3
-__device__ __forceinline__ int async_row(int r4, int lane) { return r4 + (lane >> 4); }
-__device__ __forceinline__ int async_chunk(int row, int lane) { return (lane & 15) ^ swz(row); }
+// tile row and 16-byte logical chunk this lane fetches when its wave fills COPY_ROWS rows from r0 on
+template <int DH>
+__device__ __forceinline__ int async_row(int r0, int lane) { return r0 + lane / (DH / 8); }
+template <int DH>
+__device__ __forceinline__ int async_chunk(int row, int lane) { return (lane & (DH / 8 - 1)) ^ swz<DH>(row); }
 
 // The copies are issued through inline assembly, so the compiler does not know that LDS is written
 // behind its back: it would otherwise make LDS reads of OTHER ring stages wait for all copies in flight
@@ -177,9 +200,10 @@ __device__ __forceinline__ void async_copy16_la(const void* src, unsigned lds_by
         : "v"(src), "s"(lds_byte_addr)
         : "memory");
 }
-// src: this lane's 16 bytes in global memory; tile: LDS tile base; r4: first of the 4 rows (wave-uniform)
-__device__ __forceinline__ void async_rows4(const void* src, unsigned char* tile, int r4) {
-    async_copy16(src, tile + r4 * TILE_ROW_BYTES);
+// src: this lane's 16 bytes in global memory; tile: LDS tile base; r0: first of the COPY_ROWS rows (wave-uniform)
+template <int DH>
+__device__ __forceinline__ void async_rows(const void* src, unsigned char* tile, int r0) {
+    async_copy16(src, tile + r0 * ROW_BYTES<DH>);
 }
 
 // s_waitcnt vmcnt(0) in the form the compiler understands: every vector memory load it has issued so far

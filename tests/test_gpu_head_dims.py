@@ -1,0 +1,77 @@
+"""The tiled attention kernels of head_dim 64 (bf16) at the edges of their tiles, against the fp64 oracle.
+
+These kernels hold the fp32 probabilities and dS as two bf16 terms (2^-17 relative), where the plain fp32-arithmetic
+kernels (IMPL_GENERIC) hold them in fp32.  Against the rounding of the bf16 results (2^-9) that is nothing, so the bar is
+the plain kernels' own error: at most 5 % above it (two independent roundings of some thousand values differ by less)
+plus 2^-16 of the result's norm.
+"""
+import numpy as np
+import pytest
+import torch
+
+import paper_2506_11498_amd as lrsa
+from paper_2506_11498_amd import inputs
+from oracle import lrsa_ref as ref
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+# tiles: 64 keys and 256 (head, query) rows in the query-outer kernels, 256 keys and 64 query rows in the key-outer one
+BF16_D64 = [
+    dict(n=1, L=8, S=0, K=2, Hq=1, Hkv=1),                          # one row
+    dict(n=40, L=32, S=64, K=8, Hq=2, Hkv=1),                       # sink only
+    dict(n=5 + 7 * 100 + 33, L=100, S=5, K=37, Hq=6, Hkv=2, B=2),   # group of 3: one head per workgroup
+    dict(n=16 + 5 * 64 + 63, L=64, S=16, K=16, Hq=64, Hkv=8),       # group of 8, heads spread over the XCDs
+    dict(n=33 + 4 * 257 + 1, L=257, S=33, K=64, Hq=2, Hkv=1),       # a chunk one row past a key tile, a tail of one row
+    dict(n=7 + 6 * 130 + 129, L=130, S=7, K=130, Hq=4, Hkv=1),      # every token survives
+    dict(n=4 + 9 * 64, L=64, S=4, K=1, Hq=3, Hkv=3, B=2),           # one survivor per chunk
+]
+
+
+def run(w, xd, idx, impl, **kw):
+    p = lrsa.params_for(xd["Q"], xd["K"], sink=w.S, lag=w.L, topk=w.K, impl=impl, **kw)
+    lrsa.timing_enable(True)
+    O, lse = lrsa.lrsa_attn_fwd(p, xd["Q"], xd["K"], xd["V"], idx)
+    dQ, dK, dV = lrsa.lrsa_attn_bwd(p, xd["Q"], xd["K"], xd["V"], O, xd["dO"], lse, idx)
+    torch.cuda.synchronize()
+    names = {n for n, _ in lrsa.timing_records()}
+    lrsa.timing_enable(False)
+    return dict(O=O, lse=lse, dQ=dQ, dK=dK, dV=dV), names
+
+
+def reference(w, x, local_prev):
+    xf = {k: v.float().numpy() for k, v in x.items()}
+    idx = None
+    if ref.partition(w.n, w.S, w.L, local_prev)["Ns"]:
+        idx = ref.select(ref.score(xf["K"], xf["V"], w.S, w.L, local_prev=local_prev), w.S, w.L, w.K)
+    O, lse = ref.attn_fwd_dense(xf["Q"], xf["K"], xf["V"], idx, w.S, w.L, local_prev=local_prev)
+    g = ref.attn_bwd_dense(xf["Q"], xf["K"], xf["V"], xf["dO"], idx, w.S, w.L, local_prev=local_prev)
+    return idx, dict(O=O, lse=lse, dQ=g[0], dK=g[1], dV=g[2])
+
+
+def err(x, r):
+    x = x.detach().double().cpu().numpy()
+    return np.linalg.norm(x - r) / max(np.linalg.norm(r), 1e-30) if np.abs(r).max() > 0 else np.abs(x).max()
+
+
+def rows_strided(t):
+    """The same values as [B, n, H, d] memory seen as [B, H, n, d]."""
+    return t.permute(0, 2, 1, 3).contiguous().permute(0, 2, 1, 3)
+
+
+@pytest.mark.parametrize("layout", ["bhnd", "bnhd"])
+@pytest.mark.parametrize("local_prev", [1, 2])
+@pytest.mark.parametrize("cfg", BF16_D64, ids=[f"n{c['n']}_L{c['L']}_K{c['K']}_G{c['Hq'] // c['Hkv']}" for c in BF16_D64])
+def test_bf16_head_dim_64(cfg, local_prev, layout):
+    w = inputs.small_workload(d=64, dtype="bf16", **cfg)
+    x = inputs.make_inputs(w)
+    idx, want = reference(w, x, local_prev)
+    idx_dev = None if idx is None else torch.from_numpy(idx).to(DEV)
+    xd = {k: v.to(DEV) if layout == "bhnd" else rows_strided(v.to(DEV)) for k, v in x.items()}
+    got, names = run(w, xd, idx_dev, lrsa.IMPL_AUTO, local_prev=local_prev)
+    assert {"k_fwd_mfma", "k_bwd_dq", "k_bwd_dkv"} <= names
+    plain, names = run(w, xd, idx_dev, lrsa.IMPL_GENERIC, local_prev=local_prev)
+    assert not any("mfma" in n for n in names)
+    for k in want:
+        bar = 1.05 * err(plain[k], want[k]) + 2.0 ** -16
+        assert err(got[k], want[k]) <= bar, f"{k}: {err(got[k], want[k]):.3e} (bar {bar:.3e})"
