@@ -74,6 +74,7 @@ int make_dims(const lrsa_params* p, lrsa::Dims* D) {
 
 bool use_mfma(const lrsa_params* p, const lrsa::Dims& D) { return p->impl != LRSA_IMPL_GENERIC && lrsa::mfma_supported(D); }
 
+bool use_f32_tiles(const lrsa_params* p, const lrsa::Dims& D) { return p->impl != LRSA_IMPL_GENERIC && lrsa::f32_tiles_supported(D); }
 // the filling-step calls are built for head_dim 128
 bool fill_supported(const lrsa_params* p, const lrsa::Dims& D) { return use_mfma(p, D) && D.d == 128; }
 
@@ -82,7 +83,7 @@ size_t ws_need(const lrsa_params* p, const lrsa::Dims& D, int which) {
         case LRSA_WS_SCORE: return lrsa::score_ws_bytes(D);
         case LRSA_WS_SELECT: return lrsa::select_ws_bytes(D);
         case LRSA_WS_ATTN_FWD: return use_mfma(p, D) ? lrsa::attn_fwd_mfma_ws_bytes(D) : lrsa::attn_fwd_generic_ws_bytes(D);
-        case LRSA_WS_ATTN_BWD: return use_mfma(p, D) ? lrsa::attn_bwd_mfma_ws_bytes(D) : lrsa::attn_bwd_generic_ws_bytes(D);
+        case LRSA_WS_ATTN_BWD: return use_mfma(p, D) ? lrsa::attn_bwd_mfma_ws_bytes(D) : use_f32_tiles(p, D) ? lrsa::attn_bwd_f32_ws_bytes(D) : lrsa::attn_bwd_generic_ws_bytes(D);
         case LRSA_WS_DECODE_ATTN: return lrsa::decode_ws_bytes(D);
         default: return 0;
     }
@@ -276,6 +277,7 @@ int lrsa_attn_fwd(const lrsa_params* p, const void* Q, const void* K, const void
         return fail(LRSA_ERR_INVALID_ARG, "lrsa_attn_fwd: tensors must be 16-byte aligned");
     if ((rc = check_ws(p, D, LRSA_WS_ATTN_FWD, ws, ws_bytes)) != LRSA_OK) return rc;
     const hipError_t e = use_mfma(p, D) ? lrsa::launch_attn_fwd_mfma(D, Q, K, V, idx, O, lse, ws, (hipStream_t)stream)
+                                        : use_f32_tiles(p, D) ? lrsa::launch_attn_fwd_f32(D, Q, K, V, idx, O, lse, (hipStream_t)stream)
                                         : lrsa::launch_attn_fwd_generic(D, Q, K, V, idx, O, lse, ws, (hipStream_t)stream);
     return hip_result(e, "lrsa_attn_fwd");
 }
@@ -295,6 +297,7 @@ int lrsa_attn_bwd(const lrsa_params* p, const void* Q, const void* K, const void
     if ((rc = check_ws(p, D, LRSA_WS_ATTN_BWD, ws, ws_bytes)) != LRSA_OK) return rc;
     const hipError_t e =
         use_mfma(p, D) ? lrsa::launch_attn_bwd_mfma(D, Q, K, V, O, dO, lse, idx, dQ, dK, dV, nullptr, nullptr, ws, (hipStream_t)stream)
+                       : use_f32_tiles(p, D) ? lrsa::launch_attn_bwd_f32(D, Q, K, V, O, dO, lse, idx, dQ, dK, dV, ws, (hipStream_t)stream)
                        : lrsa::launch_attn_bwd_generic(D, Q, K, V, O, dO, lse, idx, dQ, dK, dV, ws, (hipStream_t)stream);
     return hip_result(e, "lrsa_attn_bwd");
 }

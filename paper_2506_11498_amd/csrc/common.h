@@ -76,6 +76,13 @@ hipError_t launch_attn_bwd_generic(const Dims&, const void* Q, const void* K, co
                                    const void* dO, const float* lse, const int32_t* idx, void* dQ, void* dK,
                                    void* dV, void* ws, hipStream_t st);
 
+// fp32 data on the fp32 matrix instruction
+bool f32_tiles_supported(const Dims&);
+size_t attn_bwd_f32_ws_bytes(const Dims&);
+hipError_t launch_attn_fwd_f32(const Dims&, const void* Q, const void* K, const void* V, const int32_t* idx, void* O, float* lse, hipStream_t st);
+hipError_t launch_attn_bwd_f32(const Dims&, const void* Q, const void* K, const void* V, const void* O, const void* dO, const float* lse,
+                               const int32_t* idx, void* dQ, void* dK, void* dV, void* ws, hipStream_t st);
+
 bool mfma_supported(const Dims&);
 size_t attn_fwd_mfma_ws_bytes(const Dims&);
 hipError_t launch_attn_fwd_mfma(const Dims&, const void* Q, const void* K, const void* V, const int32_t* idx,

@@ -1,9 +1,12 @@
-"""The tiled attention kernels of head_dim 64 (bf16) at the edges of their tiles, against the fp64 oracle.
+"""The tiled attention kernels of head_dim 64 (bf16) and of fp32 data at the edges of their tiles, against the fp64 oracle.
 
-These kernels hold the fp32 probabilities and dS as two bf16 terms (2^-17 relative), where the plain fp32-arithmetic
+bf16, head_dim 64: these kernels hold the fp32 probabilities and dS as two bf16 terms (2^-17 relative), where the plain fp32-arithmetic
 kernels (IMPL_GENERIC) hold them in fp32.  Against the rounding of the bf16 results (2^-9) that is nothing, so the bar is
 the plain kernels' own error: at most 5 % above it (two independent roundings of some thousand values differ by less)
 plus 2^-16 of the result's norm.
+
+fp32: both kinds of kernel sum in fp32, in different orders; the tiled ones may be off by a quarter more than the plain
+ones, plus one ulp (2^-23) of the result's norm where the plain error is that small.
 """
 import numpy as np
 import pytest
@@ -51,7 +54,11 @@ def reference(w, x, local_prev):
 
 def err(x, r):
     x = x.detach().double().cpu().numpy()
-    return np.linalg.norm(x - r) / max(np.linalg.norm(r), 1e-30) if np.abs(r).max() > 0 else np.abs(x).max()
+    if np.abs(r).max() < 1e-12:
+        # one key: dA = D, so dQ and dK vanish but for the rounding of two sums of d products of O(1) inputs, which is
+        # at most d * 2^-23 of them: counted in that unit
+        return np.abs(x).max() / (x.shape[-1] * 2.0 ** -23) * 2.0 ** -23
+    return np.linalg.norm(x - r) / np.linalg.norm(r)
 
 
 def rows_strided(t):
@@ -74,4 +81,37 @@ def test_bf16_head_dim_64(cfg, local_prev, layout):
     assert not any("mfma" in n for n in names)
     for k in want:
         bar = 1.05 * err(plain[k], want[k]) + 2.0 ** -16
+        assert err(got[k], want[k]) <= bar, f"{k}: {err(got[k], want[k]):.3e} (bar {bar:.3e})"
+
+
+# tiles: 16 keys, 16 query rows; 16 waves (head_dim 64) or 8 (128) take the tiles in turn; up to 8 workgroups share the rows
+# of a key tile, one where there are more than 512 key tiles
+F32 = [
+    dict(n=1, L=8, S=0, K=2, Hq=1, Hkv=1),
+    dict(n=40, L=32, S=64, K=8, Hq=2, Hkv=1),                       # sink only
+    dict(n=6 + 2 * 32, L=32, S=6, K=8, Hq=2, Hkv=1),                # nothing compressed
+    dict(n=5 + 7 * 50 + 33, L=50, S=5, K=17, Hq=6, Hkv=2, B=2),     # 33 rows of a chunk do not survive: 2 tiles and a row
+    dict(n=17 + 5 * 65 + 1, L=65, S=17, K=16, Hq=4, Hkv=1),         # tail of one row, sink one past a tile
+    dict(n=3 + 6 * 33 + 32, L=33, S=3, K=33, Hq=2, Hkv=2),          # every token survives
+    dict(n=4 + 9 * 48, L=48, S=4, K=1, Hq=3, Hkv=3, B=2),           # one survivor per chunk
+    dict(n=64 + 3 * 300 + 77, L=300, S=64, K=75, Hq=16, Hkv=8, B=1),   # one slice, several workgroups per CU
+]
+
+
+@pytest.mark.parametrize("layout", ["bhnd", "bnhd"])
+@pytest.mark.parametrize("local_prev", [1, 2])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("cfg", F32, ids=[f"n{c['n']}_L{c['L']}_K{c['K']}_G{c['Hq'] // c['Hkv']}" for c in F32])
+def test_f32(cfg, d, local_prev, layout):
+    w = inputs.small_workload(d=d, dtype="f32", **cfg)
+    x = inputs.make_inputs(w)
+    idx, want = reference(w, x, local_prev)
+    idx_dev = None if idx is None else torch.from_numpy(idx).to(DEV)
+    xd = {k: v.to(DEV) if layout == "bhnd" else rows_strided(v.to(DEV)) for k, v in x.items()}
+    got, names = run(w, xd, idx_dev, lrsa.IMPL_AUTO, local_prev=local_prev)
+    assert names - {"k_bwd_dkv_f32_sum"} == {"k_fwd_f32", "k_bwd_dq_f32", "k_bwd_dkv_f32"}
+    plain, names = run(w, xd, idx_dev, lrsa.IMPL_GENERIC, local_prev=local_prev)
+    assert not any("f32" in n for n in names)
+    for k in want:
+        bar = 1.25 * err(plain[k], want[k]) + 2.0 ** -23
         assert err(got[k], want[k]) <= bar, f"{k}: {err(got[k], want[k]):.3e} (bar {bar:.3e})"
