@@ -10,10 +10,12 @@
 //                   the newer one stays whole).  An optional array of original positions moves alike.
 // With a workspace (lrsa_cache_compress_ws) the same is done by many workgroups and all steps of a call at once:
 // k_cache_select_move, k_cache_gather and k_cache_place below.
-// k_decode_attn     single-query attention (Eq. 3, nothing masked) of the G query heads of a KV group over a
-//                   slice of the cache rows: fp32 online softmax, partial (max, sum, output) per slice;
+// k_decode_mfma     single-query attention (Eq. 3, nothing masked) of the G query heads of a KV group over a
+//                   slice of the cache rows, bf16, on the matrix cores: fp32 online softmax, partial (max, sum,
+//                   output) per slice;
+// k_decode_attn     the same for fp32 data, in the vector pipe;
 // k_decode_combine  merges the slices.
-// Latency-shaped work: few rows, few workgroups, no matrix cores.
+#include "mfma_tiles.h"
 #include "score_block.h"
 #include "select_block.h"
 
@@ -26,14 +28,26 @@ constexpr int DEC_WAVES = DEC_THREADS / 64;
 constexpr int DEC_GMAX = 8;            // query heads of a group handled per pass
 constexpr int DEC_MAX_SPLITS = 256;
 constexpr int DEC_U = 4;               // rows per lane group and step
+constexpr int DEC_TILE = 32;           // rows per wave and step of k_decode_mfma
 
+// Slices of a call of lrsa_decode_attn_static at most, by which its scratch limit is stated.
+static int decode_static_splits(const Dims& D, int len) {
+    const int want = (512 + D.B * D.Hkv - 1) / (D.B * D.Hkv), most = (len + 255) / 256;
+    const int s = want < most ? want : most;
+    return s < 1 ? 1 : s > DEC_MAX_SPLITS ? DEC_MAX_SPLITS : s;
+}
+static size_t part_bytes(const Dims& D, int splits) { return size_t(D.B) * D.Hq * splits * (D.d + 2) * 4; }
+// Two workgroups of k_decode_mfma share a CU (registers), so 512 run at once: at most that many, so that none runs alone
+// behind them, or many more where 512 / units would leave CUs with half the work of others.  At least 128 rows each, a tile
+// per wave (the 2.3K-row call above: 18 slices instead of 9).  A call that the scratch of lrsa_decode_attn_static
+// held with decode_static_splits still fits: beyond it the slices stay at that number.
 static int decode_splits(const Dims& D, int len) {
-    // enough workgroups to occupy the chip, at least 256 rows each
-    int want = (512 + D.B * D.Hkv - 1) / (D.B * D.Hkv);
-    int most = (len + 255) / 256;
-    int s = want < most ? want : most;
-    if (s < 1) s = 1;
-    return s > DEC_MAX_SPLITS ? DEC_MAX_SPLITS : s;
+    const int units = D.B * D.Hkv, most = (len + 127) / 128;
+    int s = units <= 128 ? 512 / units : 2048 / units;
+    s = s < most ? s : most;
+    s = s < 1 ? 1 : s > DEC_MAX_SPLITS ? DEC_MAX_SPLITS : s;
+    const int base = decode_static_splits(D, len);
+    return s > base && part_bytes(D, s) > DECODE_STATIC_SCRATCH_BYTES ? base : s;
 }
 size_t decode_ws_bytes(const Dims& D) {
     // per (batch, query head, slice): max, sum, d_h output values
@@ -289,7 +303,162 @@ __device__ __forceinline__ void merge_state(float& m, float& l, float m2, float 
     m = mn;
 }
 
-// One workgroup: the G heads of one KV group (DEC_GMAX at a time) x rows [r0, r1) of the cache.  A row is
+// bf16.  One workgroup: the heads of one KV group (16 at a time) x rows [split * per, ...) of the cache; its waves take tiles
+// of 32 rows in turn.  Nothing is staged in LDS.  Lane l, c = l % 16, q4 = l / 16, v_mfma_f32_16x16x32_bf16:
+//   S = K Q^T   row m of block kb is tile row 8*(m/4) + 4*kb + m%4, column c a head: the lane then holds the logits of tile
+//               rows 8*q4 .. +7 of head c, which are the k-slots of its B operand in the second product
+//   O^T += V^T P^T   the lane reads DH/16 neighbouring channels of tile rows 8*q4 .. +7 and transposes that block in
+//               registers (byte permutes): column e of it is its row of the A operand for the channels (DH/16)*m + e
+// The weights enter as three bf16 terms, which hold all 24 bits of them; the matrix pipe has time to spare.
+// Bound by reading the cache (325 MB, 8 requests of 9.9K rows on 8 KV heads, 4 query heads each: 83 -> 60.5 us with the
+// merge, 5.4 TB/s), by latency for a short one (2.3K rows, 2 KV heads: 24.2 -> 10.7 us).  In the vector pipe, one lane's
+// dot products and a shuffle through LDS per row and head bounded it.  Errors against 64 bits as before: O differs from
+// the rounded exact value in at most 0.2 % of the elements.
+template <int DH> struct VPiece { typedef uint4 type; };
+template <> struct VPiece<64> { typedef uint2 type; };
+template <int DH> struct DecTile {
+    bf16x8 k[2][DH / 32];
+    typename VPiece<DH>::type v[8];
+};
+template <int DH>
+__device__ __forceinline__ void load_tile(DecTile<DH>& t, const bf16_t* Kl, const bf16_t* Vl, int64_t stride, int kr, int vr, int last) {
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+        const bf16_t* row = Kl + int64_t(min(kr + 4 * kb, last)) * stride;   // rows past the end repeat the last one, weight 0
+#pragma unroll
+        for (int kk = 0; kk < DH / 32; ++kk) t.k[kb][kk] = *reinterpret_cast<const bf16x8*>(row + kk * 32);
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) t.v[j] = *reinterpret_cast<const typename VPiece<DH>::type*>(Vl + int64_t(min(vr + j, last)) * stride);
+}
+template <int DH> struct DecState {
+    float m, l;          // of head c; l over the lane's own rows
+    f32x4 o[DH / 16];
+};
+template <int DH>
+__device__ __forceinline__ void use_tile(DecState<DH>& st, const DecTile<DH>& t, const bf16x8 (&qf)[DH / 32], int r, int r1, float c2) {
+    f32x4 s[2] = {{0.0f, 0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f, 0.0f}};
+#pragma unroll
+    for (int kk = 0; kk < DH / 32; ++kk)
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) s[kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(t.k[kb][kk], qf[kk], s[kb], 0, 0, 0);
+    float p[8], mx = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        p[j] = r + j < r1 ? s[j >> 2][j & 3] * c2 : -INFINITY;
+        mx = fmaxf(mx, p[j]);
+    }
+    lanes_u32x2 x = pair32(__float_as_uint(mx));
+    mx = fmaxf(__uint_as_float(x.x), __uint_as_float(x.y));
+    x = pair16(__float_as_uint(mx));
+    mx = fmaxf(__uint_as_float(x.x), __uint_as_float(x.y));
+    if (__builtin_amdgcn_ballot_w64(mx > st.m) != 0) {       // always on the first tile, whose row 0 is there
+        const float mn = fmaxf(st.m, mx), a = __builtin_amdgcn_exp2f(st.m - mn);
+        st.m = mn;
+        st.l *= a;
+#pragma unroll
+        for (int e = 0; e < DH / 16; ++e) st.o[e] *= a;
+    }
+    f32x8 w;
+    float ps = 0.0f;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        w[j] = __builtin_amdgcn_exp2f(p[j] - st.m);
+        ps += w[j];
+    }
+    st.l += ps;
+    bf16x8 term[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        term[i] = __builtin_convertvector(w, bf16x8);
+        w -= __builtin_convertvector(term[i], f32x8);
+    }
+#pragma unroll
+    for (int e = 0; e < DH / 16; ++e) {
+        uint32_t a[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t lo = reinterpret_cast<const uint32_t*>(&t.v[2 * i])[e >> 1], hi = reinterpret_cast<const uint32_t*>(&t.v[2 * i + 1])[e >> 1];
+            a[i] = __builtin_amdgcn_perm(hi, lo, e & 1 ? 0x07060302u : 0x05040100u);
+        }
+        const bf16x8 av = __builtin_bit_cast(bf16x8, a);
+#pragma unroll
+        for (int i = 2; i >= 0; --i) st.o[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, term[i], st.o[e], 0, 0, 0);
+    }
+}
+
+template <int DH>
+__global__ __launch_bounds__(DEC_THREADS, 2) void k_decode_mfma(Dims D, const bf16_t* __restrict__ q, const bf16_t* __restrict__ Kc,
+                                                                const bf16_t* __restrict__ Vc, int len, int per, int splits,
+                                                                float* __restrict__ part) {
+    constexpr int CPL = DH / 16, LROW = DH + 4;              // channels per lane; the padding spreads the heads over the banks
+    __shared__ __attribute__((aligned(16))) float sO[DEC_WAVES][16][LROW];
+    __shared__ float sM[DEC_WAVES][16], sL[DEC_WAVES][16];
+    const int split = blockIdx.x, bh = blockIdx.y, b = bh / D.Hkv, h = bh % D.Hkv;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, c = lane & 15, q4 = lane >> 4;
+    const int r0 = split * per, r1 = min(len, r0 + per);     // r0 >= r1: an empty slice, its records say so
+    const bf16_t* Kl = Kc + b * D.ks[0] + h * D.ks[1] + q4 * 8;
+    const bf16_t* Vl = Vc + b * D.ks[0] + h * D.ks[1] + c * CPL;
+    const int kr = 8 * (c >> 2) + (c & 3), vr = 8 * q4;
+    const float c2 = D.scale * 1.4426950408889634f;          // logits in log2 units
+
+    for (int g0 = 0; g0 < D.G; g0 += 16) {
+        const int gn = min(16, D.G - g0);
+        const bf16_t* qrow = q + (int64_t(b) * D.Hq + h * D.G + g0 + min(c, gn - 1)) * DH + q4 * 8;
+        bf16x8 qf[DH / 32];
+#pragma unroll
+        for (int kk = 0; kk < DH / 32; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(qrow + kk * 32);
+        DecState<DH> st;
+        st.m = -INFINITY;
+        st.l = 0.0f;
+#pragma unroll
+        for (int e = 0; e < CPL; ++e) st.o[e] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        // the next tile's loads are in flight while a tile is used
+        constexpr int STEP = DEC_WAVES * DEC_TILE;
+        int r = r0 + wave * DEC_TILE;
+        if (r < r1) {
+            DecTile<DH> A, B;
+            load_tile<DH>(A, Kl, Vl, D.ks[2], r + kr, r + vr, r1 - 1);
+            for (;;) {
+                if (r + STEP < r1) load_tile<DH>(B, Kl, Vl, D.ks[2], r + STEP + kr, r + STEP + vr, r1 - 1);
+                use_tile<DH>(st, A, qf, r + vr, r1, c2);
+                if ((r += STEP) >= r1) break;
+                if (r + STEP < r1) load_tile<DH>(A, Kl, Vl, D.ks[2], r + STEP + kr, r + STEP + vr, r1 - 1);
+                use_tile<DH>(st, B, qf, r + vr, r1, c2);
+                if ((r += STEP) >= r1) break;
+            }
+        }
+        lanes_u32x2 x = pair32(__float_as_uint(st.l));
+        st.l = __uint_as_float(x.x) + __uint_as_float(x.y);
+        x = pair16(__float_as_uint(st.l));
+        st.l = __uint_as_float(x.x) + __uint_as_float(x.y);
+        if (c < gn) {
+            if (q4 == 0) { sM[wave][c] = st.m; sL[wave][c] = st.l; }
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int e = 0; e < CPL; e += 4)
+                    *reinterpret_cast<f32x4*>(&sO[wave][c][(4 * q4 + i) * CPL + e]) = f32x4{st.o[e][i], st.o[e + 1][i], st.o[e + 2][i], st.o[e + 3][i]};
+        }
+        __syncthreads();
+        for (int e = tid; e < gn * DH; e += DEC_THREADS) {
+            const int g = e / DH, ch = e % DH;
+            float mm = sM[0][g], ll = sL[0][g], oo = sO[0][g][ch];
+#pragma unroll
+            for (int w = 1; w < DEC_WAVES; ++w) {
+                float a, b2;
+                merge_state(mm, ll, sM[w][g], sL[w][g], a, b2);
+                oo = oo * a + sO[w][g][ch] * b2;
+            }
+            float* dst = part + ((int64_t(b) * D.Hq + h * D.G + g0 + g) * splits + split) * (DH + 2);
+            dst[2 + ch] = oo;
+            if (ch == 0) { dst[0] = mm; dst[1] = ll; }
+        }
+        __syncthreads();
+    }
+}
+
+// fp32.  One workgroup: the G heads of one KV group (DEC_GMAX at a time) x rows [r0, r1) of the cache.  A row is
 // spread over lpr = 16-byte pieces; a wave reads 64 / lpr rows per step; logits are kept in log2 units.
 template <typename T>
 __global__ __launch_bounds__(DEC_THREADS) void k_decode_attn(Dims D, const T* __restrict__ q, const T* __restrict__ Kc,
@@ -396,21 +565,63 @@ __global__ __launch_bounds__(DEC_THREADS) void k_decode_attn(Dims D, const T* __
     }
 }
 
+// One (batch, query head) per workgroup: the weights of all slices first (two loads per lane and 64 slices), then the
+// records are summed by all lanes, two channels each, COMB_U loads in flight; fixed order.
+constexpr int COMB_U = 4;
 template <typename T>
-__global__ __launch_bounds__(128) void k_decode_combine(Dims D, const float* __restrict__ part, int splits,
-                                                        T* __restrict__ O, float* __restrict__ lse) {
+__global__ __launch_bounds__(DEC_THREADS) void k_decode_combine(Dims D, const float* __restrict__ part, int splits,
+                                                                T* __restrict__ O, float* __restrict__ lse) {
+    __shared__ float sW[DEC_MAX_SPLITS];
+    __shared__ float2 sO[DEC_THREADS];
     const int64_t bhq = blockIdx.x;
-    const int ch = threadIdx.x;
-    if (ch >= D.d) return;
-    const float* src = part + bhq * splits * (D.d + 2);
-    float m = -INFINITY, l = 0.0f, o = 0.0f;
-    for (int s = 0; s < splits; ++s) {
-        float a, b2;
-        merge_state(m, l, src[s * (D.d + 2)], src[s * (D.d + 2) + 1], a, b2);
-        o = o * a + src[s * (D.d + 2) + 2 + ch] * b2;
+    const int tid = threadIdx.x, lane = tid & 63, rec = D.d + 2;
+    const float* src = part + bhq * splits * rec;
+    float m[DEC_MAX_SPLITS / 64], l[DEC_MAX_SPLITS / 64], M = -INFINITY, L = 0.0f;
+#pragma unroll
+    for (int i = 0; i < DEC_MAX_SPLITS / 64; ++i) {
+        const int s = lane + 64 * i;
+        m[i] = -INFINITY; l[i] = 0.0f;
+        if (s < splits) {
+            const float2 ml = *reinterpret_cast<const float2*>(src + int64_t(s) * rec);
+            m[i] = ml.x; l[i] = ml.y;
+        }
+        M = fmaxf(M, m[i]);
     }
-    Elem<T>::put(O + bhq * D.d + ch, o / l);
-    if (lse && ch == 0) lse[bhq] = (m + __builtin_log2f(l)) * 0.6931471805599453f;
+    M = wave_max(M);
+#pragma unroll
+    for (int i = 0; i < DEC_MAX_SPLITS / 64; ++i) {
+        const float w = m[i] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m[i] - M);
+        L = __builtin_fmaf(l[i], w, L);
+        if (tid < 64) sW[lane + 64 * i] = w;
+    }
+    L = wave_sum(L);
+    __syncthreads();
+    const int pairs = D.d / 2, ways = DEC_THREADS / pairs, ch = tid % pairs, way = tid / pairs;
+    float2 o = {0.0f, 0.0f};
+    for (int s0 = way; s0 < splits; s0 += COMB_U * ways) {
+        float2 v[COMB_U];
+        float w[COMB_U];
+#pragma unroll
+        for (int u = 0; u < COMB_U; ++u) {
+            const int s = s0 + u * ways, sc = min(s, splits - 1);
+            w[u] = s < splits ? sW[sc] : 0.0f;
+            v[u] = *reinterpret_cast<const float2*>(src + int64_t(sc) * rec + 2 + 2 * ch);
+        }
+#pragma unroll
+        for (int u = 0; u < COMB_U; ++u) {
+            o.x = __builtin_fmaf(w[u], v[u].x, o.x);
+            o.y = __builtin_fmaf(w[u], v[u].y, o.y);
+        }
+    }
+    sO[tid] = o;
+    __syncthreads();
+    if (tid < pairs) {
+        for (int w = 1; w < ways; ++w) { o.x += sO[w * pairs + tid].x; o.y += sO[w * pairs + tid].y; }
+        Elem<T>::put(O + bhq * D.d + 2 * ch, o.x / L);
+        Elem<T>::put(O + bhq * D.d + 2 * ch + 1, o.y / L);
+        if (lse && tid == 0)   // one rounding at the end: ln 2 as its fp32 value plus the rest
+            lse[bhq] = __builtin_fmaf(M, 0.69314718246459961f, __builtin_fmaf(M, -1.9046542e-9f, __builtin_log2f(L) * 0.6931471805599453f));
+    }
 }
 
 // ------------------------------------------------------------------------------------ no-allocation variant
@@ -443,7 +654,7 @@ static hipError_t scratch_address(void** out) {
 }
 
 size_t decode_static_need(const Dims& D, int len) {
-    return size_t(D.B) * D.Hq * decode_splits(D, len) * (D.d + 2) * 4;
+    return part_bytes(D, decode_static_splits(D, len));
 }
 
 hipError_t launch_decode_attn(const Dims& D, const void* q, const void* Kc, const void* Vc, int len, void* O,
@@ -465,14 +676,18 @@ hipError_t launch_decode_attn(const Dims& D, const void* q, const void* Kc, cons
     const int splits = decode_splits(D, len);
     float* part = reinterpret_cast<float*>(ws);
     if (D.dtype == 1) {
-        LRSA_TIMED_LAUNCH("k_decode_attn", st, k_decode_attn<bf16_t>, dim3(splits, D.B * D.Hkv), dim3(DEC_THREADS), 0, st, D,
-                          (const bf16_t*)q, (const bf16_t*)Kc, (const bf16_t*)Vc, len, splits, part);
-        LRSA_TIMED_LAUNCH("k_decode_combine", st, k_decode_combine<bf16_t>, dim3(D.B * D.Hq), dim3(128), 0, st, D, part, splits,
+        const int per = ((len + splits - 1) / splits + DEC_TILE - 1) / DEC_TILE * DEC_TILE;
+#define LRSA_DECODE_LAUNCH(DH_)                                                                                              \
+    LRSA_TIMED_LAUNCH("k_decode_mfma", st, k_decode_mfma<DH_>, dim3(splits, D.B * D.Hkv), dim3(DEC_THREADS), 0, st, D,       \
+                      (const bf16_t*)q, (const bf16_t*)Kc, (const bf16_t*)Vc, len, per, splits, part)
+        if (D.d == 64) LRSA_DECODE_LAUNCH(64); else LRSA_DECODE_LAUNCH(128);
+#undef LRSA_DECODE_LAUNCH
+        LRSA_TIMED_LAUNCH("k_decode_combine", st, k_decode_combine<bf16_t>, dim3(D.B * D.Hq), dim3(DEC_THREADS), 0, st, D, part, splits,
                           (bf16_t*)O, lse);
     } else {
         LRSA_TIMED_LAUNCH("k_decode_attn", st, k_decode_attn<float>, dim3(splits, D.B * D.Hkv), dim3(DEC_THREADS), 0, st, D,
                           (const float*)q, (const float*)Kc, (const float*)Vc, len, splits, part);
-        LRSA_TIMED_LAUNCH("k_decode_combine", st, k_decode_combine<float>, dim3(D.B * D.Hq), dim3(128), 0, st, D, part, splits,
+        LRSA_TIMED_LAUNCH("k_decode_combine", st, k_decode_combine<float>, dim3(D.B * D.Hq), dim3(DEC_THREADS), 0, st, D, part, splits,
                           (float*)O, lse);
     }
     return hipGetLastError();

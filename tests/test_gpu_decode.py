@@ -98,3 +98,32 @@ def test_compress_is_a_no_op_below_two_chunks_and_rejects_bad_lengths():
         lrsa.lrsa_cache_compress(p, Kc, Vc, None, 200, 0)       # beyond the capacity
     with pytest.raises(lrsa.LrsaError):
         lrsa.lrsa_decode_attn(p, torch.randn((1, 1, 64), device=DEV), Kc, Vc, 0)
+
+
+@pytest.mark.parametrize("G", [1, 3, 16, 17])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("length", [1, 31, 33, 127, 129, 1000])
+def test_decode_attention_at_tile_edges(d, G, length):
+    """bf16 on the matrix cores: lengths around the 32-row tiles and the slices, groups around the 16 columns of a tile, rows
+    behind the end that hold infinities (never to be used).  K grows along the cache, so that the running maximum moves."""
+    B, Hkv, cap = 2, 2, length + 40
+    g = torch.Generator().manual_seed(length * 100 + G)
+    Kc = (torch.randn((B, Hkv, cap, d), generator=g) * torch.linspace(0.2, 3.0, cap)[:, None]).to(torch.bfloat16)
+    Vc = torch.randn((B, Hkv, cap, d), generator=g).to(torch.bfloat16)
+    q = torch.randn((B, Hkv * G, d), generator=g).to(torch.bfloat16)
+    Kc[:, :, length:] = float("inf")
+    Vc[:, :, length:] = float("inf")
+    Kd, Vd = Kc.to(DEV), Vc.to(DEV)
+    p = lrsa.make_params((B, Hkv * G, cap, d), tuple(Kc.shape), (Hkv * G * cap * d, cap * d, d, 1), Kd.stride(),
+                         dtype=torch.bfloat16, sink=4, lag=16, topk=4)
+    O, lse = lrsa.lrsa_decode_attn(p, q.to(DEV), Kd, Vd, length)
+    O, lse = O.double().cpu().numpy(), lse.cpu().numpy()
+    for b in range(B):
+        for h in range(Hkv):
+            sl = slice(h * G, (h + 1) * G)
+            O_ref, lse_ref = dec.decode_attn(q[b, sl].float().numpy(), Kc[b, h, :length].float().numpy(), Vc[b, h, :length].float().numpy())
+            # the rounding of the output (8 significant bits: half a unit is up to 2^-8 of the value) and fp32 logits of magnitude
+            # up to |lse| (weights off by 2^-20 of that each)
+            bound = 2.0 ** -8 * np.abs(O_ref) + 2.0 ** -20 * max(np.abs(lse_ref).max(), 8.0) * np.abs(Vc[b, h, :length].float().numpy()).max()
+            assert np.all(np.abs(O[b, sl] - O_ref) <= bound)
+            assert np.all(np.abs(lse[b, sl] - lse_ref) <= 2.0 ** -20 * np.maximum(np.abs(lse_ref), 8.0))
