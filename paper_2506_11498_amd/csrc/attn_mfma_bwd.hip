@@ -40,10 +40,38 @@ struct BwdPlan {
     int fq0, fq1;               // query chunks whose rows take part (all of them unless a row window is set)
     int gl_total, gtiles;       // gather list length per KV head as the last query chunk sees it, its tiles
     int qch, nsl;               // query chunks per slice, slices per gather tile (<= KV_MAX_SLICES)
-    int gather_wgs;             // workgroups of the GATHER part of the dK/dV launch (a multiple of 8)
-    size_t off_lse2, off_part, off_compact, off_dkc, bytes;   // workspace: D, lse in log2 units, the fp32 partials,
-                                                              // condensed K/V, condensed dK/dV (fp32)
+    int hsl, wsl;               // parts that the group's heads are split into: GATHER slices, WINDOW tiles
+    int wlo, whi;               // positions [wlo, whi) of the WINDOW tiles
+    int gather_wgs, window_wgs; // workgroups of the two parts of the dK/dV launch (multiples of 8)
+    int window_first;           // the WINDOW part comes first (its workgroups are the longer ones)
+    size_t off_lse2, off_part, off_wpart, off_compact, off_dkc, bytes;   // workspace: D, lse in log2 units, the fp32 partials of
+                                                              // the two parts, condensed K/V, condensed dK/dV (fp32)
 };
+
+// first query chunk that sees entry j0 of the gather list
+__host__ __device__ __forceinline__ int first_chunk_seeing(const Dims& D, int j0) {
+    return j0 < D.S ? 0 : (j0 - D.S) / D.K + D.lp + 1;
+}
+
+// Parts that the heads of a group are split into, for launches in which a workgroup is long beside what every CU has to do:
+// half of the longest workgroup is idle time at the end of the launch, and every part writes fp32 partials that the
+// reduction reads again.  The number of parts with the smallest sum of the two, if it saves a tenth.  `rows`: (head, query)
+// rows of a workgroup with one part, `bytes`: partials of one part, `bytes_one`: partials where there is only one part.
+// Rates as measured: 16 (head_dim 64: 30) rows per us and CU; 4.4 TB/s for a write and a read.
+// The filling steps live from it: their windows of a few chunks leave about as many workgroups as CUs, of which the WINDOW
+// ones (whole chunks, all heads) were twice as long as the others and came last.  32K tokens, 12 heads on 2, lag 1024, four
+// chunks per step: dK/dV launches of 7.0 ms in all, the whole training step 12.1 -> 9.5 ms; 11.5K tokens, 8 on 2, lag 479:
+// 1.94 -> 1.16 ms.  Training steps of 2.6K tokens in one call 206 -> 163 us; from about 8K tokens on as before (one part).
+static int head_parts(const Dims& D, double rows, double bytes, double bytes_one) {
+    const double rate = D.d == 64 ? 30.0 : 16.0;   // query rows per us and CU
+    int best = 1;
+    double t_best = 0.5 * rows / rate + bytes_one / 2.2e6;
+    for (int k = 2; k <= D.G; ++k) {
+        const double t = 0.5 * rows * ((D.G + k - 1) / k) / D.G / rate + k * bytes / 2.2e6;
+        if (t < 0.9 * t_best) { best = k; t_best = t; }
+    }
+    return best;
+}
 
 static BwdPlan make_plan(const Dims& D) {
     BwdPlan P;
@@ -72,10 +100,30 @@ static BwdPlan make_plan(const Dims& D) {
     P.nsl = nqf > 0 ? (nqf + P.qch - 1) / P.qch : 0;
     P.off_lse2 = align256(size_t(D.B) * D.Hq * D.lse_stride * 4);
     P.off_part = 2 * P.off_lse2;
-    P.gather_wgs = P.gtiles > 0 ? (D.B * D.Hkv * P.nsl + 7) / 8 * 8 * P.gtiles : 0;
-    // slots 0 .. nsl-1: the GATHER workgroups' slices; slot nsl: what the WINDOW workgroups add to listed positions
-    const size_t part = size_t(2) * (P.nsl + 1) * D.B * D.Hkv * P.gl_total * D.d * 4;
-    P.off_compact = P.off_part + align256(part);
+    P.wlo = P.sink_tiles_k > 0 ? 0 : D.S + P.kc_lo * D.L;
+    P.whi = D.row_end;
+    P.hsl = P.wsl = 1;
+    const int units = D.B * D.Hkv;
+    const double w_rows = double(D.lp + 1) * D.L * D.G, g_rows = P.nsl > 0 ? double(P.qch) * D.L * D.G : 0.0;   // of a workgroup
+    if (D.G > 1) {
+        double visible = 0.0;   // query chunks that see a list tile, over all tiles
+        for (int t = 0; t < P.gtiles; ++t) {
+            const int qf = first_chunk_seeing(D, t * KV_BK);
+            visible += qf < P.fq1 ? P.fq1 - (qf > P.fq0 ? qf : P.fq0) : 0;
+        }
+        const double per_cu = units * (visible * D.L * D.G + 0.75 * w_rows * P.ktiles) / 256.0;
+        const double row = 2.0 * units * D.d * 4;   // bytes of a row of dK and dV partials of all heads
+        // a workgroup shorter than a quarter of a CU's work is no tail worth partials
+        if (per_cu < 4.0 * w_rows) P.wsl = head_parts(D, w_rows, row * (P.whi - P.wlo), 0.0);
+        if (per_cu < 4.0 * g_rows) P.hsl = head_parts(D, g_rows, 0.5 * row * P.nsl * P.gl_total, 0.5 * row * P.nsl * P.gl_total);
+    }
+    P.window_first = w_rows * ((D.G + P.wsl - 1) / P.wsl) > g_rows * ((D.G + P.hsl - 1) / P.hsl);
+    P.gather_wgs = P.gtiles > 0 ? (units * P.nsl * P.hsl + 7) / 8 * 8 * P.gtiles : 0;
+    P.window_wgs = (units * P.ktiles * P.wsl + 7) / 8 * 8;
+    // slots 0 .. nsl*hsl-1: the GATHER workgroups' slices; the last slot: what the WINDOW workgroups add to listed positions
+    const size_t part = size_t(2) * (P.nsl * P.hsl + 1) * D.B * D.Hkv * P.gl_total * D.d * 4;
+    P.off_wpart = P.off_part + align256(part);
+    P.off_compact = P.off_wpart + (P.wsl > 1 ? align256(size_t(2) * P.wsl * units * (P.whi - P.wlo) * D.d * 4) : 0);
     P.off_dkc = P.off_compact + compact_kv_bytes(D);
     P.bytes = P.off_dkc + (D.compact ? 2 * align256(size_t(D.B) * D.Hkv * P.gl_total * 128 * 4) : 0);
     return P;
@@ -370,11 +418,6 @@ __global__ __launch_bounds__(DQ_THREADS, 2) void k_bwd_dq(Dims D, const bf16_t* 
 }
 
 // ------------------------------------------------------------------------------------ dK, dV
-// first query chunk that sees entry j0 of the gather list
-__device__ __forceinline__ int first_chunk_seeing(const Dims& D, int j0) {
-    return j0 < D.S ? 0 : (j0 - D.S) / D.K + D.lp + 1;
-}
-
 // One sub-step (32 query rows: rows rowbase .. rowbase+31 of the stage tiles) of the key-outer walk for
 // one wave.  sLD holds this wave's copy of the stage rows' lse in log2 units (floats 0..KV_ROWS-1) and -D
 // (the next KV_ROWS floats; D = rowsum(dO * O), negated by the query-outer kernel that wrote it).  r0 = first row of the sub-step; rows >= tb are padding.
@@ -518,6 +561,22 @@ __device__ __forceinline__ KvLds kv_lds() {
     return KvLds{sQ0, sQ1, sG0, sG1, sL0, sL1, sVk};
 }
 
+// gather-list entry of a position, if it is a sink token or a survivor that some query of this call sees there; else -1
+__device__ __forceinline__ int listed_entry(const Dims& D, const BwdPlan& P, const int32_t* idx_h, int pos) {
+    if (P.gtiles == 0) return -1;
+    if (pos < D.S) return pos;
+    const int c = (pos - D.S) / D.L;
+    if (D.S + (c + 1) * D.K > P.gl_total) return -1;   // chunk c is not compressed for any of them
+    const int32_t* rowp = idx_h + int64_t(c) * D.K;
+    int lo = 0, hi = D.K - 1;
+    while (lo <= hi) {
+        const int mid = (lo + hi) >> 1, v = rowp[mid];
+        if (v == pos) return D.S + c * D.K + mid;
+        if (v < pos) lo = mid + 1; else hi = mid - 1;
+    }
+    return -1;
+}
+
 template <int DH, bool GATHER>
 __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
                                          const bf16_t* __restrict__ V, const bf16_t* __restrict__ Kc,
@@ -525,7 +584,8 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
                                          const float* __restrict__ lse, const float* __restrict__ Dsum,
                                          const int32_t* __restrict__ idx, bf16_t* __restrict__ dK,
                                          bf16_t* __restrict__ dV, float* __restrict__ accK, float* __restrict__ accV,
-                                         float* __restrict__ part, const BwdPlan& P, const int block) {
+                                         float* __restrict__ part, float* __restrict__ wpart, const BwdPlan& P,
+                                         const int block) {
     const KvLds sh = kv_lds<DH>();
     unsigned char *const sQ0 = sh.sQ0, *const sQ1 = sh.sQ1, *const sG0 = sh.sG0, *const sG1 = sh.sG1;
     float *const sL0 = sh.sL0, *const sL1 = sh.sL1;
@@ -541,26 +601,35 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
     int key0, key_end;   // key ids of this workgroup: positions (WINDOW) or gather-list entries (GATHER)
     int ta, tb;          // query rows [ta, tb) of every head of the group
     int qa = 0;          // GATHER: first query chunk of the slice
-    int slice = 0;
+    int slot = 0;        // GATHER: slot of the partials; WINDOW: part of the heads
+    int h0, h1;          // heads [h0, h1) of the group
     int unit;
     {
         const int xcd = block & 7, seq = block >> 3;
         if (GATHER) {
             const int grp = xcd + 8 * (seq / P.gtiles);
             const int units = D.B * D.Hkv;
-            if (grp >= units * P.nsl) return;
+            if (grp >= units * P.nsl * P.hsl) return;
             unit = grp % units;
-            slice = P.nsl - 1 - grp / units;          // latest slices (most list tiles) first
+            slot = P.nsl * P.hsl - 1 - grp / units;   // latest slices (most list tiles) first
             key0 = (seq % P.gtiles) * KV_BK;
+            h0 = slot % P.hsl * D.G / P.hsl;
+            h1 = (slot % P.hsl + 1) * D.G / P.hsl;
         } else {
-            unit = block / P.ktiles;
-            key0 = P.ktiles - 1 - block % P.ktiles;   // tile index for now
+            const int w = block % (P.ktiles * P.wsl);
+            unit = block / (P.ktiles * P.wsl);
+            if (unit >= D.B * D.Hkv) return;
+            key0 = P.ktiles - 1 - w / P.wsl;          // tile index for now
+            slot = w % P.wsl;
+            h0 = slot * D.G / P.wsl;
+            h1 = (slot + 1) * D.G / P.wsl;
         }
     }
     const int h = unit % D.Hkv, b = unit / D.Hkv;
     const int32_t* idx_h = idx + (int64_t(b) * D.Hkv + h) * D.Ns * D.K;
     if (GATHER) {
         // slice = query chunks [slice*qch, (slice+1)*qch), of which the tile sees those from qf on
+        const int slice = slot / P.hsl;
         key_end = P.gl_total;
         const int qf = first_chunk_seeing(D, key0);
         qa = max(P.fq0 + slice * P.qch, qf);
@@ -592,7 +661,7 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
     // of a chunk may be partial), so that one step never sees two different gather-list prefixes.
     const int spc = (D.L + KV_ROWS - 1) / KV_ROWS;                               // GATHER: steps per chunk
     const int sph = GATHER ? ((tb - ta + D.L - 1) / D.L) * spc : (tb - ta + KV_ROWS - 1) / KV_ROWS;   // steps per head
-    const int nsteps = sph * D.G;
+    const int nsteps = sph * (h1 - h0);
     // first row, row end and chunk-visible limit of a step
     auto step_rows = [&](int sidx, int& r0, int& rend, int& lim_u) {
         const int w = sidx % sph;
@@ -650,7 +719,7 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
         const int gi = step / sph;
         int r0, rend, lim_unused;
         step_rows(step, r0, rend, lim_unused);
-        const int hq = h * D.G + gi;
+        const int hq = h * D.G + h0 + gi;
         const int64_t base = b * D.qs[0] + hq * D.qs[1];
 #pragma unroll
         for (int i = 0; i < KV_ROWS / (COPY_ROWS<DH> * KV_WAVES); ++i) {
@@ -715,14 +784,17 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
 #undef LRSA_KV_STEP
 
     const size_t part_stride = size_t(D.B) * D.Hkv * P.gl_total * DH;   // floats per slice
-    const size_t part_v = size_t(P.nsl + 1) * part_stride;                // dV partials follow the dK partials
+    const size_t part_v = size_t(P.nsl * P.hsl + 1) * part_stride;        // dV partials follow the dK partials
 #pragma unroll
     for (int nb = 0; nb < KV_NB; ++nb) {
         const int kidn = key0 + wave * (32 * KV_NB) + nb * 32 + (lane & 31);
         if (kidn >= key_end) continue;
-        if (GATHER) {
-            float* pk = part + size_t(slice) * part_stride + ((size_t(b) * D.Hkv + h) * P.gl_total + kidn) * DH;
-            float* pv = pk + part_v;
+        if (GATHER || P.wsl > 1) {
+            // WINDOW with the heads in parts: [dK, dV][part][batch, KV head][position][DH], all added by the reduction kernel
+            const size_t wrow = size_t(D.B) * D.Hkv * (P.whi - P.wlo) * DH;
+            float* pk = GATHER ? part + size_t(slot) * part_stride + ((size_t(b) * D.Hkv + h) * P.gl_total + kidn) * DH
+                               : wpart + size_t(slot) * wrow + ((size_t(b) * D.Hkv + h) * (P.whi - P.wlo) + (kidn - P.wlo)) * DH;
+            float* pv = pk + (GATHER ? part_v : size_t(P.wsl) * wrow);
 #pragma unroll
             for (int db = 0; db < DB<DH>; ++db)
 #pragma unroll
@@ -734,27 +806,10 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
                     *reinterpret_cast<f32x4*>(pv + db * 32 + a * 8 + g * 4) = y;
                 }
         } else {
-            // gather-list entry of this position, if it is a sink token or a survivor
-            int j = -1;
-            if (P.gtiles > 0) {
-                if (kidn < D.S) j = kidn;
-                else {
-                    const int c = (kidn - D.S) / D.L;
-                    if (D.S + (c + 1) * D.K <= P.gl_total) {   // chunk c is compressed for some query of this call
-                        const int32_t* rowp = idx_h + int64_t(c) * D.K;
-                        int lo_ = 0, hi_ = D.K - 1;
-                        while (lo_ <= hi_) {
-                            const int mid = (lo_ + hi_) >> 1;
-                            const int v = rowp[mid];
-                            if (v == kidn) { j = D.S + c * D.K + mid; break; }
-                            if (v < kidn) lo_ = mid + 1; else hi_ = mid - 1;
-                        }
-                    }
-                }
-            }
+            const int j = listed_entry(D, P, idx_h, kidn);
             const int64_t koff = b * D.ks[0] + h * D.ks[1] + int64_t(kidn) * D.ks[2];
             // listed positions: fp32 into the extra slot, the reduction kernel adds the slices; others: final
-            float* pk = j >= 0 ? part + size_t(P.nsl) * part_stride + ((size_t(b) * D.Hkv + h) * P.gl_total + j) * DH : nullptr;
+            float* pk = j >= 0 ? part + size_t(P.nsl * P.hsl) * part_stride + ((size_t(b) * D.Hkv + h) * P.gl_total + j) * DH : nullptr;
 #pragma unroll
             for (int db = 0; db < DB<DH>; ++db)
 #pragma unroll
@@ -780,8 +835,7 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
     }
 }
 
-// One launch for all of dK/dV: the GATHER workgroups first (equal, long), then the WINDOW workgroups, so that
-// the chip has one tail, not two.
+// One launch for all of dK/dV, so that the chip has one tail, not two: the part with the longer workgroups first.
 template <int DH>
 __global__ __launch_bounds__(KV_THREADS, KV_WAVES == 8 ? 2 : 1) void k_bwd_dkv(Dims D, const bf16_t* __restrict__ Q,
                                                                                 const bf16_t* __restrict__ K,
@@ -796,52 +850,79 @@ __global__ __launch_bounds__(KV_THREADS, KV_WAVES == 8 ? 2 : 1) void k_bwd_dkv(D
                                                                                 bf16_t* __restrict__ dV,
                                                                                 float* __restrict__ accK,
                                                                                 float* __restrict__ accV,
-                                                                                float* __restrict__ part, BwdPlan P) {
-    const int block = blockIdx.x;
-    if (block < P.gather_wgs) dkv_body<DH, true>(D, Q, K, V, Kc, Vc, dO, lse, Dsum, idx, dK, dV, accK, accV, part, P, block);
-    else dkv_body<DH, false>(D, Q, K, V, Kc, Vc, dO, lse, Dsum, idx, dK, dV, accK, accV, part, P, block - P.gather_wgs);
+                                                                                float* __restrict__ part,
+                                                                                float* __restrict__ wpart, BwdPlan P) {
+    const int first = P.window_first ? P.window_wgs : P.gather_wgs;
+    const bool in_first = int(blockIdx.x) < first;
+    const int block = in_first ? blockIdx.x : blockIdx.x - first;
+    if (in_first != bool(P.window_first)) dkv_body<DH, true>(D, Q, K, V, Kc, Vc, dO, lse, Dsum, idx, dK, dV, accK, accV, part, wpart, P, block);
+    else dkv_body<DH, false>(D, Q, K, V, Kc, Vc, dO, lse, Dsum, idx, dK, dV, accK, accV, part, wpart, P, block);
 }
 
 // dK, dV of the listed positions (sink tokens and survivors): the WINDOW contribution plus the GATHER slices
 // that exist for the entry's list tile, added in a fixed order.  DH / 4 threads per entry, 4 channels each.
+// With the heads of the WINDOW tiles in parts, entries whose position is in the window are left to a second range of rows,
+// the positions [wlo, whi), listed or not.
 template <int DH>
 __global__ __launch_bounds__(256) void k_bwd_dkv_reduce(Dims D, const int32_t* __restrict__ idx,
-                                                        const float* __restrict__ part, bf16_t* __restrict__ dK,
+                                                        const float* __restrict__ part, const float* __restrict__ wpart,
+                                                        bf16_t* __restrict__ dK,
                                                         bf16_t* __restrict__ dV, float* __restrict__ accK,
                                                         float* __restrict__ accV, float* __restrict__ dKc,
                                                         float* __restrict__ dVc, BwdPlan P) {
-    const int64_t e = int64_t(blockIdx.x) * (1024 / DH) + threadIdx.x / (DH / 4);   // (b, h, entry)
+    int64_t e = int64_t(blockIdx.x) * (1024 / DH) + threadIdx.x / (DH / 4);   // (b, h, entry), then (b, h, position)
     const int64_t total = int64_t(D.B) * D.Hkv * P.gl_total;
-    if (e >= total) return;
-    const int j = int(e % P.gl_total);
-    const int bh = int(e / P.gl_total);
-    const int b = bh / D.Hkv, h = bh % D.Hkv;
-    const int pos = j < D.S ? j : idx[(int64_t(bh) * D.Ns) * D.K + (j - D.S)];
-    const size_t part_stride = size_t(D.B) * D.Hkv * P.gl_total * DH;
-    const size_t part_v = size_t(P.nsl + 1) * part_stride;
+    const int wn = P.whi - P.wlo;
     const int dcol = (threadIdx.x & (DH / 4 - 1)) * 4;
-    const float* p0 = part + size_t(e) * DH + dcol;
+    int j, bh, pos;
     f32x4 x = {0.0f, 0.0f, 0.0f, 0.0f}, y = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (e < total) {
+        j = int(e % P.gl_total);
+        bh = int(e / P.gl_total);
+        pos = j < D.S ? j : idx[(int64_t(bh) * D.Ns) * D.K + (j - D.S)];
+    } else {
+        const int64_t w = e - total;
+        if (P.wsl == 1 || w >= int64_t(D.B) * D.Hkv * wn) return;
+        bh = int(w / wn);
+        pos = P.wlo + int(w % wn);
+        j = listed_entry(D, P, idx + (int64_t(bh) * D.Ns) * D.K, pos);
+        const size_t wrow = size_t(D.B) * D.Hkv * wn * DH;
+        const float* p0 = wpart + size_t(w) * DH + dcol;
+        for (int sl = 0; sl < P.wsl; ++sl) {
+            x += *reinterpret_cast<const f32x4*>(p0 + size_t(sl) * wrow);
+            y += *reinterpret_cast<const f32x4*>(p0 + size_t(P.wsl + sl) * wrow);
+        }
+        e = int64_t(bh) * P.gl_total + j;
+    }
+    const int b = bh / D.Hkv, h = bh % D.Hkv;
     // the WINDOW workgroups of this call cover the sink (with a row window: only when its rows are in it) and the
     // key chunks from kc_lo on
+    const bool entry = int64_t(blockIdx.x) * (1024 / DH) + threadIdx.x / (DH / 4) < total;
     const bool in_window = pos < D.S ? P.sink_tiles_k > 0 : (pos - D.S) / D.L >= P.kc_lo;
-    if (in_window) {
-        x = *reinterpret_cast<const f32x4*>(p0 + size_t(P.nsl) * part_stride);
-        y = *reinterpret_cast<const f32x4*>(p0 + size_t(P.nsl) * part_stride + part_v);
-    }
-    const int qf0 = first_chunk_seeing(D, (j / KV_BK) * KV_BK);
-    if (qf0 < P.fq1)
-        for (int sl = qf0 > P.fq0 ? (qf0 - P.fq0) / P.qch : 0; sl < P.nsl; ++sl) {
-            x += *reinterpret_cast<const f32x4*>(p0 + size_t(sl) * part_stride);
-            y += *reinterpret_cast<const f32x4*>(p0 + size_t(sl) * part_stride + part_v);
+    if (entry && in_window && P.wsl > 1) return;
+    if (j >= 0) {
+        const size_t part_stride = size_t(D.B) * D.Hkv * P.gl_total * DH;
+        const int slots = P.nsl * P.hsl;
+        const size_t part_v = size_t(slots + 1) * part_stride;
+        const float* p0 = part + size_t(e) * DH + dcol;
+        if (in_window && P.wsl == 1) {
+            x = *reinterpret_cast<const f32x4*>(p0 + size_t(slots) * part_stride);
+            y = *reinterpret_cast<const f32x4*>(p0 + size_t(slots) * part_stride + part_v);
         }
+        const int qf0 = first_chunk_seeing(D, (j / KV_BK) * KV_BK);
+        if (qf0 < P.fq1)
+            for (int sl = qf0 > P.fq0 ? (qf0 - P.fq0) / P.qch * P.hsl : 0; sl < slots; ++sl) {
+                x += *reinterpret_cast<const f32x4*>(p0 + size_t(sl) * part_stride);
+                y += *reinterpret_cast<const f32x4*>(p0 + size_t(sl) * part_stride + part_v);
+            }
+    }
     if (D.acc) {
         const int64_t aoff = ((int64_t(b) * D.Hkv + h) * D.n + pos) * DH + dcol;
         *reinterpret_cast<f32x4*>(accK + aoff) += x;
         *reinterpret_cast<f32x4*>(accV + aoff) += y;
         return;
     }
-    if (dKc) {   // condensed cache: the gradient of the condensed rows is a product of its own, scattered afterwards
+    if (dKc && j >= 0) {   // condensed cache: the gradient of the condensed rows is a product of its own, scattered afterwards
         *reinterpret_cast<f32x4*>(dKc + e * DH + dcol) = x;
         *reinterpret_cast<f32x4*>(dVc + e * DH + dcol) = y;
         return;
@@ -926,20 +1007,22 @@ hipError_t launch_attn_bwd_mfma(const Dims& D, const void* Q, const void* K, con
         }
 #undef LRSA_DQ_LAUNCH
     }
-    const int64_t wgs = int64_t(P.gather_wgs) + int64_t(D.B) * D.Hkv * P.ktiles;
+    float* wpart = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + P.off_wpart);
+    const int64_t wgs = int64_t(P.gather_wgs) + P.window_wgs;
     if (wgs > 0)
         LRSA_TIMED_LAUNCH("k_bwd_dkv", st, (D.d == 64 ? k_bwd_dkv<64> : k_bwd_dkv<128>), dim3((unsigned)wgs), dim3(KV_THREADS), 0, st, D, q, k, v, kc, vc, g,
-                          lse2, Dsum, idx, (bf16_t*)dK, (bf16_t*)dV, accK, accV, part, P);
+                          lse2, Dsum, idx, (bf16_t*)dK, (bf16_t*)dV, accK, accV, part, wpart, P);
     const int64_t entries = int64_t(D.B) * D.Hkv * P.gl_total;
     float *dkc = nullptr, *dvc = nullptr;
     if (compact) {
         dkc = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + P.off_dkc);
         dvc = dkc + align256(size_t(entries) * 128 * 4) / 4;
     }
-    if (entries > 0)
+    const int64_t rows = entries + (P.wsl > 1 ? int64_t(D.B) * D.Hkv * (P.whi - P.wlo) : 0);   // of the reduction
+    if (rows > 0)
         LRSA_TIMED_LAUNCH("k_bwd_dkv_reduce", st, (D.d == 64 ? k_bwd_dkv_reduce<64> : k_bwd_dkv_reduce<128>),
-                          dim3((unsigned)((entries + 1024 / D.d - 1) / (1024 / D.d))), dim3(256), 0, st, D,
-                          idx, part, (bf16_t*)dK, (bf16_t*)dV, accK, accV, dkc, dvc, P);
+                          dim3((unsigned)((rows + 1024 / D.d - 1) / (1024 / D.d))), dim3(256), 0, st, D,
+                          idx, part, wpart, (bf16_t*)dK, (bf16_t*)dV, accK, accV, dkc, dvc, P);
     if (entries > 0 && compact)
         LRSA_TIMED_LAUNCH("k_bwd_scatter_dkv", st, k_bwd_scatter_dkv, dim3((unsigned)((entries + 7) / 8)), dim3(256), 0, st, D,
                           idx, dkc, dvc, (bf16_t*)dK, (bf16_t*)dV, P.gl_total);

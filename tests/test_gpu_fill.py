@@ -21,6 +21,8 @@ SHAPES = [
     dict(name="gqa", n=16 + 6 * 64 + 40, L=64, S=16, K=16, d=128, Hq=8, Hkv=2, B=2),
     dict(name="odd_sizes_no_tail_chunk", n=5 + 7 * 100, L=100, S=5, K=37, d=128, Hq=2, Hkv=1, B=1),
     dict(name="no_sink_long_chunks", n=0 + 5 * 320 + 100, L=320, S=0, K=80, d=128, Hq=4, Hkv=1, B=1),
+    dict(name="heads_in_uneven_parts", n=16 + 9 * 128 + 50, L=128, S=16, K=32, d=128, Hq=10, Hkv=2, B=1),
+    dict(name="group_of_six", n=7 + 12 * 96 + 20, L=96, S=7, K=24, d=128, Hq=6, Hkv=1, B=1),
     dict(name="many_chunks", n=64 + 20 * 128 + 9, L=128, S=64, K=32, d=128, Hq=8, Hkv=1, B=1),
 ]
 
