@@ -55,20 +55,22 @@ __host__ __device__ __forceinline__ int first_chunk_seeing(const Dims& D, int j0
 
 // Parts that the heads of a group are split into, for launches in which a workgroup is long beside what every CU has to do:
 // half of the longest workgroup is idle time at the end of the launch, and every part writes fp32 partials that the
-// reduction reads again.  The number of parts with the smallest sum of the two, if it saves a tenth.  `rows`: (head, query)
+// reduction reads again.  The number of parts with the smallest sum of the two, if it saves a fifth.  `rows`: (head, query)
 // rows of a workgroup with one part, `bytes`: partials of one part, `bytes_one`: partials where there is only one part.
-// Rates as measured: 16 (head_dim 64: 30) rows per us and CU; 4.4 TB/s for a write and a read.
+// Rates as measured: 16 (head_dim 64: 30) rows per us and CU; 1 TB/s for partials (each CU stores 32 bytes of a row at a time).
 // The filling steps live from it: their windows of a few chunks leave about as many workgroups as CUs, of which the WINDOW
 // ones (whole chunks, all heads) were twice as long as the others and came last.  32K tokens, 12 heads on 2, lag 1024, four
 // chunks per step: dK/dV launches of 7.0 ms in all, the whole training step 12.1 -> 9.5 ms; 11.5K tokens, 8 on 2, lag 479:
-// 1.94 -> 1.16 ms.  Training steps of 2.6K tokens in one call 206 -> 163 us; from about 8K tokens on as before (one part).
+// 1.94 -> 1.16 ms.  Training steps of 2.6K tokens in one call 206 -> 155 us (with the finer slices
+// of make_plan); long sequences keep one part.  With partials at 4.4 TB/s and a tenth instead of a fifth it splits too often:
+// 3.5K tokens, 16 heads on 4, 4 requests 505 -> 535 us, now as before.
 static int head_parts(const Dims& D, double rows, double bytes, double bytes_one) {
     const double rate = D.d == 64 ? 30.0 : 16.0;   // query rows per us and CU
     int best = 1;
-    double t_best = 0.5 * rows / rate + bytes_one / 2.2e6;
+    double t_best = 0.5 * rows / rate + bytes_one / 1.0e6;
     for (int k = 2; k <= D.G; ++k) {
-        const double t = 0.5 * rows * ((D.G + k - 1) / k) / D.G / rate + k * bytes / 2.2e6;
-        if (t < 0.9 * t_best) { best = k; t_best = t; }
+        const double t = 0.5 * rows * ((D.G + k - 1) / k) / D.G / rate + k * bytes / 1.0e6;
+        if (t < 0.8 * t_best) { best = k; t_best = t; }
     }
     return best;
 }
@@ -95,6 +97,12 @@ static BwdPlan make_plan(const Dims& D) {
     // half of the (tile, slice) grid sees any query -- fill the chip twice
     while (qch > min_qch && qch > 1 && (qch / 2) * int64_t(D.L) * D.G >= 1024 &&
            int64_t(D.B) * D.Hkv * P.gtiles * ((nqf + qch - 1) / qch) / 2 < 512)
+        qch /= 2;
+    // fewer than a quarter as many as CUs: down to 256 rows.  (2.6K tokens, 4 heads on 2, 2 requests, 24 workgroups: 164 ->
+    // 157 us; 2.2K tokens in filling steps, 4 heads on 1: 710 -> 633 us.  From 84 workgroups on it costs more than it gives:
+    // 5.5K tokens, 4 heads on 2, 4 requests 264 -> 272 us, 4K tokens, 8 heads on 8, 2 requests, 128 of them, 271 -> 295 us.)
+    while (qch > min_qch && qch > 1 && (qch / 2) * int64_t(D.L) * D.G >= 256 &&
+           int64_t(D.B) * D.Hkv * P.gtiles * ((nqf + qch - 1) / qch) / 2 < 64)
         qch /= 2;
     P.qch = int(qch);
     P.nsl = nqf > 0 ? (nqf + P.qch - 1) / P.qch : 0;
