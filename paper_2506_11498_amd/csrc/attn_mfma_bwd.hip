@@ -5,7 +5,7 @@
 // Deterministic, no atomics.  Three launches on one stream:
 //   k_bwd_dq          query-outer: a workgroup owns 256 (head, query) rows of one KV group and walks their
 //                     key stream exactly like the forward (gather list, then the local window), recomputing A;
-//                     it also leaves D[b,hq,t] = dO[t] . O[t] and lse in log2 units in the workspace
+//                     it also leaves D[b,hq,t] = dO[t] . O[t] and lse in the units of the logits (mfma_tiles.h) in the workspace
 //   k_bwd_dkv         key-outer, two kinds of workgroups in one launch.  GATHER: 256 consecutive entries of one
 //                     KV head's gather list (sink ++ survivors) x one slice of query chunks -> fp32 partial
 //                     dK, dV rows in the workspace.  WINDOW: 256 consecutive positions x the queries that see
@@ -44,7 +44,7 @@ struct BwdPlan {
     int wlo, whi;               // positions [wlo, whi) of the WINDOW tiles
     int gather_wgs, window_wgs; // workgroups of the two parts of the dK/dV launch (multiples of 8)
     int window_first;           // the WINDOW part comes first (its workgroups are the longer ones)
-    size_t off_lse2, off_part, off_wpart, off_compact, off_dkc, bytes;   // workspace: D, lse in log2 units, the fp32 partials of
+    size_t off_lse2, off_part, off_wpart, off_compact, off_dkc, bytes;   // workspace: D, lse in the logits' units, the fp32 partials of
                                                               // the two parts, condensed K/V, condensed dK/dV (fp32)
 };
 
@@ -57,7 +57,7 @@ __host__ __device__ __forceinline__ int first_chunk_seeing(const Dims& D, int j0
 // half of the longest workgroup is idle time at the end of the launch, and every part writes fp32 partials that the
 // reduction reads again.  The number of parts with the smallest sum of the two, if it saves a fifth.  `rows`: (head, query)
 // rows of a workgroup with one part, `bytes`: partials of one part, `bytes_one`: partials where there is only one part.
-// Rates as measured: 16 (head_dim 64: 30) rows per us and CU; 1 TB/s for partials (each CU stores 32 bytes of a row at a time).
+// Rates as measured: 16 (head_dim 64: 24) rows per us and CU; 1 TB/s for partials (each CU stores 32 bytes of a row at a time).
 // The filling steps live from it: their windows of a few chunks leave about as many workgroups as CUs, of which the WINDOW
 // ones (whole chunks, all heads) were twice as long as the others and came last.  32K tokens, 12 heads on 2, lag 1024, four
 // chunks per step: dK/dV launches of 7.0 ms in all, the whole training step 12.1 -> 9.5 ms; 11.5K tokens, 8 on 2, lag 479:
@@ -65,7 +65,7 @@ __host__ __device__ __forceinline__ int first_chunk_seeing(const Dims& D, int j0
 // of make_plan); long sequences keep one part.  With partials at 4.4 TB/s and a tenth instead of a fifth it splits too often:
 // 3.5K tokens, 16 heads on 4, 4 requests 505 -> 535 us, now as before.
 static int head_parts(const Dims& D, double rows, double bytes, double bytes_one) {
-    const double rate = D.d == 64 ? 30.0 : 16.0;   // query rows per us and CU
+    const double rate = D.d == 64 ? 24.0 : 16.0;   // query rows per us and CU
     int best = 1;
     double t_best = 0.5 * rows / rate + bytes_one / 1.0e6;
     for (int k = 2; k <= D.G; ++k) {
@@ -151,7 +151,7 @@ __device__ __forceinline__ void dq_tile(const unsigned char* sK, const unsigned 
     for (int kb = 0; kb < 2; ++kb) {
         if (!MASK || j0 + kb * 32 <= wave_lim_max) {  // otherwise these 32 keys are masked for the whole wave
             // MFMAs of S^T (K rows), dA^T (V rows), dQ^T (K transposed, rows 0-15 then 16-31); their LDS operands
-            // form one stream that is read DQ_PF ahead.  A = exp2(S*c2 - lse2) is written beside the dA MFMAs it
+            // form one stream that is read DQ_PF ahead.  A = exp(scale S - lse) is written beside the dA MFMAs it
             // does not depend on.
             f32x16 s, dp;
 #pragma unroll
@@ -163,7 +163,6 @@ __device__ __forceinline__ void dq_tile(const unsigned char* sK, const unsigned 
             bf16x8 a[DQ_PF];
 #pragma unroll
             for (int n = 0; n < DQ_PF; ++n) a[n] = LRSA_DQ_OPND(n);
-            const float neg_l = -lse2;
             Weights<TERMS<DH>> dsf0, dsf1;
 #pragma unroll
             for (int n = 0; n < N4; ++n) {
@@ -176,7 +175,7 @@ __device__ __forceinline__ void dq_tile(const unsigned char* sK, const unsigned 
                     constexpr int E = 16 / KK<DH>;
 #pragma unroll
                     for (int i = E * (n - N1); i < E * (n - N1) + E; ++i) {
-                        float pr = fast_exp2(__builtin_fmaf(s[i], c2, neg_l));
+                        float pr = weight<DH>(s[i], c2, lse2);
                         if (MASK) {
                             const int j = j0 + kb * 32 + 8 * (i >> 2) + 4 * g + (i & 3);
                             pr = j <= lim ? pr : 0.0f;
@@ -219,7 +218,6 @@ __device__ __forceinline__ void dq_tile_full(const unsigned char* sK, const unsi
     bf16x8 a[DQ_PF];
 #pragma unroll
     for (int n = 0; n < DQ_PF; ++n) a[n] = LRSA_DQ_OPND(n);
-    const float neg_l = -lse2;
     Weights<TERMS<DH>> dsf[4];   // dS of keys 0-15, 16-31, 32-47, 48-63
     // six groups of MFMAs (separate loops: each unrolls fully, so every array index is a constant)
 #define LRSA_DQ_NEXT(n) if ((n) + DQ_PF < N6) a[(n) % DQ_PF] = LRSA_DQ_OPND((n) + DQ_PF)
@@ -233,7 +231,7 @@ __device__ __forceinline__ void dq_tile_full(const unsigned char* sK, const unsi
         dp0 = mfma32(a[(K1 + k) % DQ_PF], gf[k], k == 0 ? zero : dp0);
         LRSA_DQ_NEXT(K1 + k);
 #pragma unroll
-        for (int i = E * k; i < E * k + E; ++i) s0[i] = fast_exp2(__builtin_fmaf(s0[i], c2, neg_l));
+        for (int i = E * k; i < E * k + E; ++i) s0[i] = weight<DH>(s0[i], c2, lse2);
     }
 #pragma unroll
     for (int k = 0; k < K1; ++k) {
@@ -249,7 +247,7 @@ __device__ __forceinline__ void dq_tile_full(const unsigned char* sK, const unsi
         dp1 = mfma32(a[(3 * K1 + k) % DQ_PF], gf[k], k == 0 ? zero : dp1);
         LRSA_DQ_NEXT(3 * K1 + k);
 #pragma unroll
-        for (int i = E * k; i < E * k + E; ++i) s1[i] = fast_exp2(__builtin_fmaf(s1[i], c2, neg_l));
+        for (int i = E * k; i < E * k + E; ++i) s1[i] = weight<DH>(s1[i], c2, lse2);
     }
 #pragma unroll
     for (int k = 0; k < 2 * DB<DH>; ++k) {
@@ -326,10 +324,10 @@ __global__ __launch_bounds__(DQ_THREADS, 2) void k_bwd_dq(Dims D, const bf16_t* 
         qf[kk] = *reinterpret_cast<const bf16x8*>(Q + qoff + kk * 16 + g * 8);
         gf[kk] = *reinterpret_cast<const bf16x8*>(dO + qoff + kk * 16 + g * 8);
     }
-    // D = rowsum(dO * O) of this lane's row and its lse in log2 units: used here and, through the workspace,
+    // D = rowsum(dO * O) of this lane's row and its lse in the logits' units: used here and, through the workspace,
     // by the key-outer kernel that runs after this one (every (head, query) row belongs to exactly one wave)
     const int64_t rowid = (int64_t(b) * D.Hq + hq) * D.lse_stride + tq_ld;
-    const float lse2 = lse[rowid] * 1.4426950408889634f;
+    const float lse2 = lse[rowid] * LOGIT_UNIT<DH>;
     float Dq = 0.0f;
 #pragma unroll
     for (int kk = 0; kk < KK<DH>; ++kk) {
@@ -371,7 +369,7 @@ __global__ __launch_bounds__(DQ_THREADS, 2) void k_bwd_dq(Dims D, const bf16_t* 
         }
     };
 
-    const float c2 = D.scale * 1.4426950408889634f;
+    const float c2 = D.scale * LOGIT_UNIT<DH>;
     const LaneOffs lo = make_lane_offs<DH>(lane);
     const int wave_lim_min = ng + t0 + wq * 32 - cs;   // last stream entry the wave's first query sees
 #define LRSA_DQ_TILE(sK, sV, j0_)                                                                              \
@@ -427,7 +425,7 @@ __global__ __launch_bounds__(DQ_THREADS, 2) void k_bwd_dq(Dims D, const bf16_t* 
 
 // ------------------------------------------------------------------------------------ dK, dV
 // One sub-step (32 query rows: rows rowbase .. rowbase+31 of the stage tiles) of the key-outer walk for
-// one wave.  sLD holds this wave's copy of the stage rows' lse in log2 units (floats 0..KV_ROWS-1) and -D
+// one wave.  sLD holds this wave's copy of the stage rows' lse in the logits' units (floats 0..KV_ROWS-1) and -D
 // (the next KV_ROWS floats; D = rowsum(dO * O), negated by the query-outer kernel that wrote it).  r0 = first row of the sub-step; rows >= tb are padding.
 // lim_u: GATHER (steps never straddle a chunk): the largest gather-list entry the step's chunk sees.
 // The wave's K fragments are in registers, its V rows in LDS (sVw): K fragments and the accumulators
@@ -481,8 +479,8 @@ __device__ __forceinline__ void dkv_step(const Dims& D, const unsigned char* sQ,
 #pragma unroll
     for (int nb = 0; nb < KV_NB; ++nb)
         mlo[nb] = GATHER ? (kcmp[nb] <= lim_u ? -64 : 64) : (kcmp[nb] == 0x7fffffff ? 64 : kcmp[nb] - r0 - 4 * g);
-    // A = exp2(S*c2 - lse2), four values per key block and pair of MFMA rounds; sLD holds lse already in
-    // log2 units.  Only steps that touch the diagonal, a partly visible gather prefix, padding rows or
+    // A = exp(scale S - lse), four values per key block and pair of MFMA rounds; sLD holds lse already in
+    // the logits' units.  Only steps that touch the diagonal, a partly visible gather prefix, padding rows or
     // padding keys pay for the mask (wave-uniform flag).
     bf16x8 vb[KV_NB][2];
 #pragma unroll
@@ -505,20 +503,20 @@ __device__ __forceinline__ void dkv_step(const Dims& D, const unsigned char* sQ,
                 for (int nb = 0; nb < KV_NB; ++nb)
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
-                        s[nb][a4 * 4 + r] = fast_exp2(__builtin_fmaf(s[nb][a4 * 4 + r], c2, -l4[r]));
+                        s[nb][a4 * 4 + r] = weight<DH>(s[nb][a4 * 4 + r], c2, l4[r]);
             } else {
 #pragma unroll
                 for (int nb = 0; nb < KV_NB; ++nb)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        const float pr = fast_exp2(__builtin_fmaf(s[nb][a4 * 4 + r], c2, -l4[r]));
+                        const float pr = weight<DH>(s[nb][a4 * 4 + r], c2, l4[r]);
                         const int c = 8 * a4 + r;
                         s[nb][a4 * 4 + r] = (c >= mlo[nb] && c < mhi) ? pr : 0.0f;
                     }
             }
         }
     }
-    constexpr int NB2 = 2 * DB<DH>;   // MFMAs (pairs of them with two-term weights) of the dV group and of the dK group
+    constexpr int NB2 = 2 * DB<DH>;   // MFMAs (one per term of the weights) of the dV group and of the dK group
     Weights<TERMS<DH>> pf[KV_NB][2], dsf[KV_NB][2];
 #pragma unroll
     for (int nb = 0; nb < KV_NB; ++nb) { pf[nb][0] = pack_weights<TERMS<DH>>(s[nb], 0); pf[nb][1] = pack_weights<TERMS<DH>>(s[nb], 8); }
@@ -743,7 +741,7 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
         async_copy4(Dsum + rid, sL + wave * 2 * KV_ROWS + KV_ROWS);
     };
 
-    const float c2 = D.scale * 1.4426950408889634f;
+    const float c2 = D.scale * LOGIT_UNIT<DH>;
     f32x16 dk[KV_NB][DB<DH>], dv[KV_NB][DB<DH>];
 #pragma unroll
     for (int nb = 0; nb < KV_NB; ++nb)
@@ -984,7 +982,7 @@ hipError_t launch_attn_bwd_mfma(const Dims& D, const void* Q, const void* K, con
                                 const void* dO, const float* lse, const int32_t* idx, void* dQ, void* dK,
                                 void* dV, float* accK, float* accV, void* ws, hipStream_t st) {
     const BwdPlan P = make_plan(D);
-    // D and lse in log2 units hold the rows of the window only; like the caller's tensors they are addressed by
+    // D and lse in the logits' units hold the rows of the window only; like the caller's tensors they are addressed by
     // absolute row, hence the shifted bases
     float* Dsum = reinterpret_cast<float*>(ws) - D.row_begin;
     float* lse2 = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + P.off_lse2) - D.row_begin;

@@ -14,9 +14,11 @@
 // registers of S^T reused directly as the B operand and V^T read from the row-major tile with
 // transposing LDS reads.
 //
-// head_dim 64: P^T enters as two bf16 terms (mfma_tiles.h, Weights), half as many again MFMAs; bound by the vector pipe
-// (exponentials and the split).  8192 tokens, 16 query heads on 4 KV heads, lag 256, 64 kept: 4.7 ms with the plain
-// fp32-arithmetic kernel (a wave per query row) -> 0.13 ms; backward 14.2 ms -> 0.42 ms.
+// head_dim 64: P^T enters as three bf16 terms (mfma_tiles.h, Weights), which is all of an fp32 weight, twice as many MFMAs
+// in all; bound by the vector pipe (exponentials and the split).  8192 tokens, 16 query heads on 4 KV heads, lag 256, 64
+// kept: 4.7 ms with the plain fp32-arithmetic kernel (a wave per query row) -> 0.16 ms; backward 14.2 ms -> 0.50 ms.  With two
+// terms and logits in log2 units 0.125 and 0.40 ms, but 1.6 per mille of the elements of O are then off the correct rounding
+// of the exact value, of dV 2.2 (1K to 4K rows, five kinds of values); now 0.22 and 0.41, the plain kernels 0.21 and 0.40.
 #include "mfma_tiles.h"
 
 namespace lrsa {
@@ -65,7 +67,7 @@ struct FwdState {
 
 // MASK: the tile holds entries some query of the wave does not see (only the last tiles of a walk).
 // The running maximum is refreshed lazily: as long as no query's tile maximum exceeds its reference
-// by more than 2^8, the old reference is kept (probabilities stay below 256, exact enough in fp32 sums
+// by more than 2^8 (e^5), the old reference is kept (probabilities stay below 256, exact enough in fp32 sums
 // and bf16 operands) and the accumulators need no rescaling.
 template <int DH, bool MASK>
 __device__ __forceinline__ void fwd_tile(const unsigned char* sK, const unsigned char* sV, const bf16x8 (&qf)[KK<DH>],
@@ -134,10 +136,15 @@ __device__ __forceinline__ void fwd_tile(const unsigned char* sK, const unsigned
             }
             mx = fmaxf(mx, s[kb][i]);
         }
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * c2;
-    if (__builtin_amdgcn_ballot_w64(mx > st.m_run + 8.0f) != 0) {   // wave-uniform; always taken on the first tile
+    if constexpr (DH == 64) {   // a swap needs no address registers
+        const lanes_u32x2 x = pair32(__float_as_uint(mx));
+        mx = fmaxf(__uint_as_float(x.x), __uint_as_float(x.y)) * c2;
+    } else {
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * c2;
+    }
+    if (__builtin_amdgcn_ballot_w64(mx > st.m_run + (DH == 64 ? 5.0f : 8.0f)) != 0) {   // wave-uniform; always taken on the first tile
         const float m_new = fmaxf(st.m_run, mx);   // finite: the first tile holds a visible key for every query
-        const float corr = fast_exp2(st.m_run - m_new);
+        const float corr = exp_units<DH>(st.m_run - m_new);
         st.l_run *= corr;
         st.m_run = m_new;
 #pragma unroll
@@ -145,13 +152,12 @@ __device__ __forceinline__ void fwd_tile(const unsigned char* sK, const unsigned
 #pragma unroll
             for (int i = 0; i < 16; ++i) st.o[db][i] *= corr;
     }
-    const float neg_m = -st.m_run;
     float psum = 0.0f;
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            const float pv = fast_exp2(__builtin_fmaf(s[kb][i], c2, neg_m));
+            const float pv = weight<DH>(s[kb][i], c2, st.m_run);
             s[kb][i] = pv;
             psum += pv;
         }
@@ -169,11 +175,19 @@ __device__ __forceinline__ void fwd_tile(const unsigned char* sK, const unsigned
 #pragma unroll
         for (int kg = 0; kg < 4; ++kg)
             if (kg < 2 || two) {
-                const auto pf = pack_weights<TERMS<DH>>(s[kg >> 1], 8 * (kg & 1));
+                // a term at a time, what is left of the weights in their own registers
+                f32x16& w = s[kg >> 1];
 #pragma unroll
-                for (int db = 0; db < DB<DH>; ++db) {
-                    st.o[db] = mfma32_w(va[db], pf, st.o[db]);
-                    if (kg + 1 < 4) va[db] = read_cols_o<DH>(sV, lo, (kg + 1) * 16, db);
+                for (int t = 0; t < TERMS<DH>; ++t) {
+                    const bf16x8 pf = pack8(w, 8 * (kg & 1));
+#pragma unroll
+                    for (int db = 0; db < DB<DH>; ++db) {
+                        st.o[db] = mfma32(va[db], pf, st.o[db]);
+                        if (t + 1 == TERMS<DH> && kg + 1 < 4) va[db] = read_cols_o<DH>(sV, lo, (kg + 1) * 16, db);
+                    }
+                    if (t + 1 < TERMS<DH>)
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) w[8 * (kg & 1) + j] -= float(pf[j]);
                 }
             }
     } else {
@@ -300,7 +314,7 @@ __global__ __launch_bounds__(FWD_THREADS, DH == 64 ? 4 : 2) void k_fwd_mfma(Dims
     };
     constexpr int OPS_PER_TILE = 2 * 8 / COPY_ROWS<DH>;   // asynchronous copies per wave and tile
 
-    const float c2 = D.scale * 1.4426950408889634f;  // logits are kept in log2 units
+    const float c2 = D.scale * LOGIT_UNIT<DH>;
     const LaneOffs lo = make_lane_offs<DH>(lane);
     FwdState<DH> st;
     st.m_run = -INFINITY;
@@ -363,13 +377,9 @@ __global__ __launch_bounds__(FWD_THREADS, DH == 64 ? 4 : 2) void k_fwd_mfma(Dims
                 const bf16x4 pk = __builtin_convertvector(v, bf16x4);
                 *reinterpret_cast<bf16x4*>(orow + db * 32 + a * 8 + g * 4) = pk;
             }
-        float lse_t;
-        if constexpr (DH == 64) {   // one rounding at the end: ln 2 as its fp32 value plus the rest
-            const float t = __builtin_fmaf(st.m_run, -1.9046542e-9f, __builtin_log2f(l_tot) * 0.6931471805599453f);
-            lse_t = __builtin_fmaf(st.m_run, 0.69314718246459961f, t);
-        } else {
-            lse_t = (st.m_run + __builtin_log2f(l_tot)) * 0.6931471805599453f;
-        }
+        // m in natural units: one rounding at the end
+        const float lse_t = DH == 64 ? __builtin_fmaf(__builtin_log2f(l_tot), 0.6931471805599453f, st.m_run)
+                                     : (st.m_run + __builtin_log2f(l_tot)) * 0.6931471805599453f;
         if (g == 0) lse[(int64_t(b) * D.Hq + hq_o) * D.lse_stride + tq_o] = lse_t;
     }
 }

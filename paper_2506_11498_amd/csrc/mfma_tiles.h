@@ -114,33 +114,47 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& v, int i0) {
     return __builtin_convertvector(t, bf16x8);
 }
 
-// A C-layout block of fp32 weights (probabilities, dS) as MFMA operand.  TERMS == 1: rounded to bf16.  TERMS == 2: as
-// the sum of two bf16 numbers (the rounded value and its rounded residual, 2^-17 relative): head_dim 64, whose
-// kernels hold the weights to more than bf16.
+// A C-layout block of fp32 weights (probabilities, dS) as MFMA operand.  TERMS == 1: rounded to bf16.  TERMS == 3: as
+// the sum of three bf16 numbers (the rounded value, its rounded residual and the residual of that), which hold all 24
+// bits: head_dim 64, where the weights are fp32 also in the plain kernels.
 template <int TERMS> struct Weights {
     bf16x8 t[TERMS];
 };
 template <int TERMS>
 __device__ __forceinline__ Weights<TERMS> pack_weights(const f32x16& v, int i0) {
     Weights<TERMS> w;
-    w.t[0] = pack8(v, i0);
-    if constexpr (TERMS == 2) {
-        f32x8 r;
+    f32x8 r;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) r[j] = v[i0 + j] - float(w.t[0][j]);
-        w.t[1] = __builtin_convertvector(r, bf16x8);
+    for (int j = 0; j < 8; ++j) r[j] = v[i0 + j];
+#pragma unroll
+    for (int t = 0; t < TERMS; ++t) {
+        w.t[t] = __builtin_convertvector(r, bf16x8);
+        if (t + 1 < TERMS)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) r[j] -= float(w.t[t][j]);
     }
     return w;
 }
 template <int TERMS>
 __device__ __forceinline__ f32x16 mfma32_w(bf16x8 a, const Weights<TERMS>& w, f32x16 c) {
-    c = mfma32(a, w.t[0], c);
-    if constexpr (TERMS == 2) c = mfma32(a, w.t[1], c);
+#pragma unroll
+    for (int t = TERMS - 1; t >= 0; --t) c = mfma32(a, w.t[t], c);   // the small terms first
     return c;
 }
-template <int DH> constexpr int TERMS = DH == 64 ? 2 : 1;
+template <int DH> constexpr int TERMS = DH == 64 ? 3 : 1;
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// Units of the logits inside the kernels: log2 units, so that a weight is one fma and one exponential; head_dim 64: natural
+// units and a multiplication more, because scale * log2(e) and lse * log2(e) are rounded numbers, whose errors grow with the
+// logit (scale = 1/8 is exact) and would show beside weights of 24 bits.
+constexpr float LOG2E = 1.4426950408889634f;
+template <int DH> constexpr float LOGIT_UNIT = DH == 64 ? 1.0f : LOG2E;   // factor of a natural logit
+template <int DH>
+__device__ __forceinline__ float exp_units(float x) { return fast_exp2(DH == 64 ? x * LOG2E : x); }
+// exp(scale * s - ref); c = scale in the kernel's units
+template <int DH>
+__device__ __forceinline__ float weight(float s, float c, float ref) { return exp_units<DH>(__builtin_fmaf(s, c, -ref)); }
 
 // ---- asynchronous global -> LDS copies (global_load_lds_dwordx4) --------------------------------
 // One wave instruction moves 64 x 16 bytes: lane l's 16 bytes land at lds_base + 16*l (checked on the

@@ -1,9 +1,9 @@
 """The tiled attention kernels of head_dim 64 (bf16) and of fp32 data at the edges of their tiles, against the fp64 oracle.
 
-bf16, head_dim 64: these kernels hold the fp32 probabilities and dS as two bf16 terms (2^-17 relative), where the plain fp32-arithmetic
-kernels (IMPL_GENERIC) hold them in fp32.  Against the rounding of the bf16 results (2^-9) that is nothing, so the bar is
-the plain kernels' own error: at most 5 % above it (two independent roundings of some thousand values differ by less)
-plus 2^-16 of the result's norm.
+bf16, head_dim 64: these kernels hold the fp32 probabilities and dS as three bf16 terms, which is all 24 bits of them, as the
+plain fp32-arithmetic kernels (IMPL_GENERIC) do.  The bar is the plain kernels' own error: at most 5 % above it (two independent
+roundings of some thousand values differ by less) plus 2^-16 of the result's norm.  That error is the rounding of the bf16 results
+(2^-9); test_bf16_head_dim_64_keeps_fp32_weights looks below it.
 
 fp32: both kinds of kernel sum in fp32, in different orders; the tiled ones may be off by a quarter more than the plain
 ones, plus one ulp (2^-23) of the result's norm where the plain error is that small.
@@ -82,6 +82,25 @@ def test_bf16_head_dim_64(cfg, local_prev, layout):
     for k in want:
         bar = 1.05 * err(plain[k], want[k]) + 2.0 ** -16
         assert err(got[k], want[k]) <= bar, f"{k}: {err(got[k], want[k]):.3e} (bar {bar:.3e})"
+
+
+@pytest.mark.parametrize("structure", ["none", "channel_scale"])
+def test_bf16_head_dim_64_keeps_fp32_weights(structure):
+    """O and dV are sums of weights times bf16 numbers, rounded once to bf16: with fp32 weights an element misses the correctly
+    rounded exact value only where that lies within some 2^-24 of a rounding boundary.  Their number grows with the error of the
+    weights (two bf16 terms, 2^-17: about eight times as many as the plain fp32-arithmetic kernels miss).  Bar: twice the plain kernels'
+    number, and 10 for the spread of the small counts."""
+    w = inputs.small_workload(d=64, dtype="bf16", n=16 + 10 * 128 + 100, L=128, S=16, K=32, Hq=8, Hkv=2, structure=structure)
+    x = inputs.make_inputs(w)
+    idx, want = reference(w, x, 1)
+    idx_dev = torch.from_numpy(idx).to(DEV)
+    xd = {k: v.to(DEV) for k, v in x.items()}
+    got, _ = run(w, xd, idx_dev, lrsa.IMPL_AUTO)
+    plain, _ = run(w, xd, idx_dev, lrsa.IMPL_GENERIC)
+    for k in ("O", "dV"):
+        ideal = torch.from_numpy(want[k]).to(torch.bfloat16)
+        missed = [int((o[k].cpu() != ideal).sum()) for o in (got, plain)]
+        assert missed[0] <= 2 * missed[1] + 10, f"{k}: {missed[0]} elements off the correct rounding, the plain kernels {missed[1]}"
 
 
 # tiles: 16 keys, 16 query rows; 16 waves (head_dim 64) or 8 (128) take the tiles in turn; up to 8 workgroups share the rows
