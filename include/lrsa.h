@@ -94,6 +94,11 @@ int lrsa_num_scored_chunks(const lrsa_params *p);
  * 4096 tokens.  Returns a negative lrsa_status on bad params. */
 int lrsa_score_route(const lrsa_params *p);
 
+/* Which kernels lrsa_attn_fwd / lrsa_attn_bwd use for these params (`impl`, type, head_dim, and the limits of a launch);
+ * pure host arithmetic, for tests and for reading profiles.  0: plain fp32-arithmetic kernels, 1: fp32 matrix
+ * kernels, 2: bf16 MFMA kernels.  Returns a negative lrsa_status on bad params. */
+int lrsa_attn_route(const lrsa_params *p);
+
 /* On route 3 a scoring workgroup takes the min / max of its reference chunk (Eq. 4-5) from hint words that
  * the workgroups of that chunk publish; `polls` is how many times it looks for them before it computes
  * these min / max from the rows themselves (a second read of the chunk).  Default 256 (about a

@@ -72,11 +72,11 @@ int make_dims(const lrsa_params* p, lrsa::Dims* D) {
     return LRSA_OK;
 }
 
-bool use_mfma(const lrsa_params* p, const lrsa::Dims& D) { return p->impl != LRSA_IMPL_GENERIC && lrsa::mfma_supported(D); }
+bool use_mfma(const lrsa_params* p, const lrsa::Dims& D) { return p->impl != LRSA_IMPL_GENERIC && lrsa::mfma_supported(D) && lrsa::mfma_grids_fit(D); }
 
 bool use_f32_tiles(const lrsa_params* p, const lrsa::Dims& D) { return p->impl != LRSA_IMPL_GENERIC && lrsa::f32_tiles_supported(D); }
-// the filling-step calls are built for head_dim 128
-bool fill_supported(const lrsa_params* p, const lrsa::Dims& D) { return use_mfma(p, D) && D.d == 128; }
+// the filling-step calls are built for head_dim 128; their grids are those of a window of rows
+bool fill_supported(const lrsa_params* p, const lrsa::Dims& D) { return p->impl != LRSA_IMPL_GENERIC && lrsa::mfma_supported(D) && D.d == 128; }
 
 size_t ws_need(const lrsa_params* p, const lrsa::Dims& D, int which) {
     switch (which) {
@@ -123,6 +123,12 @@ int lrsa_score_route(const lrsa_params* p) {
     lrsa::Dims D;
     const int rc = make_dims(p, &D);
     return rc != LRSA_OK ? rc : lrsa::score_route(D);
+}
+
+int lrsa_attn_route(const lrsa_params* p) {
+    lrsa::Dims D;
+    const int rc = make_dims(p, &D);
+    return rc != LRSA_OK ? rc : use_mfma(p, D) ? 2 : use_f32_tiles(p, D) ? 1 : 0;
 }
 
 int lrsa_score_poll_limit(int polls) { return lrsa::score_poll_limit(polls); }
@@ -322,6 +328,7 @@ int set_row_window(lrsa::Dims* D, int32_t row_begin, int32_t row_end, const char
     D->fq0 = row_begin <= S ? 0 : (row_begin - S) / L;
     D->fq1 = row_end == n ? D->nq : (row_end - S) / L;
     D->lse_stride = row_end - row_begin;
+    if (!lrsa::mfma_grids_fit(*D)) return fail(LRSA_ERR_UNSUPPORTED, "%s: the rows need a launch of more than 2^32 work-items; take fewer chunks per step", who);
     D->compact = 0;     // the condensed copy would be rebuilt at every step: the window calls gather by index
     return LRSA_OK;
 }

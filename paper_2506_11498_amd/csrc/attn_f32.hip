@@ -419,9 +419,12 @@ __global__ __launch_bounds__(256) void k_bwd_dkv_f32_sum(Dims D, const float* __
 }
 
 // ------------------------------------------------------------------------------------ launchers
-// grid of one dimension: query tiles (key tiles) x heads
+// grid of one dimension: query tiles (key tiles) x heads.  A tile holds up to 16 rows and ends with its chunk, so short chunks reach
+// the limit first: lag 2, 131072 tokens, 64 query heads of 64 channels are 2^22 workgroups of 1024 threads.
 bool f32_tiles_supported(const Dims& D) {
-    return D.dtype == 0 && int64_t(make_qtiles(D).count) * D.B * D.Hq < INT32_MAX && int64_t(make_ktiles(D).count) * D.B * D.Hkv < INT32_MAX;   // (one slice)
+    const int q_threads = 64 * (D.d == 64 ? F32_WAVES<64> : F32_WAVES<128>);
+    return D.dtype == 0 && grid_fits(int64_t(make_qtiles(D).count) * D.B * D.Hq, q_threads) &&
+           grid_fits(int64_t(make_ktiles(D).count) * D.B * D.Hkv * f32_slices(D), 64 * F32_KV_WAVES);
 }
 
 template <int DH>

@@ -1,7 +1,7 @@
 // Plain fp32-arithmetic LRSA attention kernels (Eq. 2-3 of the paper under the chunked mask),
 // forward and backward, for any supported dtype / head_dim.  The matrix-core kernels (attn_mfma_*.hip for bf16,
 // attn_f32.hip for fp32) can be cross-checked against them on the GPU; beyond those kernels' limits (a bf16 head's rows
-// spread over 2 GiB, a grid of more than 2^31 workgroups) they are the fallback.
+// spread over 2 GiB, a grid of 2^32 work-items) they are the fallback.
 //
 // One wave works on one query row (forward, dQ) or one key column (dK, dV); its 64 lanes take
 // visible keys (or visible queries) round-robin, each keeping a private online-softmax state or

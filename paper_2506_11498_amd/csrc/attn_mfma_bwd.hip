@@ -75,6 +75,9 @@ static int head_parts(const Dims& D, double rows, double bytes, double bytes_one
     return best;
 }
 
+static int64_t gather_workgroups(const Dims& D, const BwdPlan& P) { return (int64_t(D.B) * D.Hkv * P.nsl * P.hsl + 7) / 8 * 8 * P.gtiles; }
+static int64_t window_workgroups(const Dims& D, const BwdPlan& P) { return (int64_t(D.B) * D.Hkv * P.ktiles * P.wsl + 7) / 8 * 8; }
+
 static BwdPlan make_plan(const Dims& D) {
     BwdPlan P;
     const int sink_rows = D.S < D.n ? D.S : D.n;
@@ -126,8 +129,8 @@ static BwdPlan make_plan(const Dims& D) {
         if (per_cu < 4.0 * g_rows) P.hsl = head_parts(D, g_rows, 0.5 * row * P.nsl * P.gl_total, 0.5 * row * P.nsl * P.gl_total);
     }
     P.window_first = w_rows * ((D.G + P.wsl - 1) / P.wsl) > g_rows * ((D.G + P.hsl - 1) / P.hsl);
-    P.gather_wgs = P.gtiles > 0 ? (units * P.nsl * P.hsl + 7) / 8 * 8 * P.gtiles : 0;
-    P.window_wgs = (units * P.ktiles * P.wsl + 7) / 8 * 8;
+    P.gather_wgs = int(gather_workgroups(D, P));
+    P.window_wgs = int(window_workgroups(D, P));
     // slots 0 .. nsl*hsl-1: the GATHER workgroups' slices; the last slot: what the WINDOW workgroups add to listed positions
     const size_t part = size_t(2) * (P.nsl * P.hsl + 1) * D.B * D.Hkv * P.gl_total * D.d * 4;
     P.off_wpart = P.off_part + align256(part);
@@ -138,6 +141,14 @@ static BwdPlan make_plan(const Dims& D) {
 }
 
 size_t attn_bwd_mfma_ws_bytes(const Dims& D) { return make_plan(D).bytes; }
+
+// the grids of the forward, dQ and dK/dV launches (the reduction's threads are fewer than the bytes of its partials)
+bool mfma_grids_fit(const Dims& D) {
+    const QTileMap M = make_qtile_map(D, heads_per_wg(D), DQ_WAVES);
+    const BwdPlan P = make_plan(D);
+    return grid_fits(int64_t(D.B) * D.Hkv * (M.tix_hi - M.tix_lo) * M.gsubs, DQ_THREADS) &&
+           grid_fits(gather_workgroups(D, P) + window_workgroups(D, P), KV_THREADS);
+}
 
 // ------------------------------------------------------------------------------------ dQ
 // One 64-key tile for one wave: per 32 keys S^T and dA^T, then dS^T, then dQ^T += K^T dS^T.

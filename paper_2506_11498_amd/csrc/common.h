@@ -84,6 +84,7 @@ hipError_t launch_attn_bwd_f32(const Dims&, const void* Q, const void* K, const 
                                const int32_t* idx, void* dQ, void* dK, void* dV, void* ws, hipStream_t st);
 
 bool mfma_supported(const Dims&);
+bool mfma_grids_fit(const Dims&);
 size_t attn_fwd_mfma_ws_bytes(const Dims&);
 hipError_t launch_attn_fwd_mfma(const Dims&, const void* Q, const void* K, const void* V, const int32_t* idx,
                                 void* O, float* lse, void* ws, hipStream_t st);
@@ -92,6 +93,10 @@ hipError_t launch_attn_bwd_mfma(const Dims&, const void* Q, const void* K, const
                                 const void* dO, const float* lse, const int32_t* idx, void* dQ, void* dK,
                                 void* dV, float* accK, float* accV, void* ws, hipStream_t st);
 hipError_t launch_bwd_acc_finish(const Dims&, const float* accK, const float* accV, void* dK, void* dV, hipStream_t st);
+
+// A launch has fewer than 2^32 work-items per grid dimension (and fewer than 2^31 workgroups).  The runtime does not refuse a larger
+// one: the count wraps and most workgroups never run.
+inline bool grid_fits(int64_t workgroups, int threads) { return workgroups < (int64_t(1) << 32) / threads && workgroups < (int64_t(1) << 31); }
 
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 

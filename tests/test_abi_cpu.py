@@ -135,6 +135,42 @@ def test_scoring_route_of_the_workloads_and_of_edge_shapes():
                                                                                    # workgroups between writer and reader
 
 
+def test_attention_route_at_the_limits_of_a_launch():
+    """Host arithmetic: the tiled kernels serve a shape as long as their grids stay below 2^32 work-items; beyond it the
+    plain kernels do, whose grids spread over three dimensions."""
+    f32, bf = torch.float32, torch.bfloat16
+    for kw, want in [
+        (dict(dtype=f32), 1), (dict(dtype=f32, d=64), 1), (dict(dtype=bf), 2), (dict(dtype=bf, d=64), 2),
+        (dict(dtype=f32, impl=binding.IMPL_GENERIC), 0), (dict(dtype=bf, impl=binding.IMPL_GENERIC), 0),
+        (dict(dtype=bf, impl=binding.IMPL_COMPACT), 2), (dict(dtype=f32, impl=binding.IMPL_COMPACT), 1),
+        # fp32, head_dim 64: 1024 threads for 16 rows at most; a chunk of two rows is a tile of its own
+        (dict(dtype=f32, d=64, Hq=64, Hkv=8, n=131072, sink=0, lag=2, topk=1), 0),          # 2^22 workgroups
+        (dict(dtype=f32, d=64, Hq=64, Hkv=8, n=131070, sink=0, lag=2, topk=1), 1),          # 64 fewer
+        (dict(dtype=f32, d=64, B=8, Hq=64, Hkv=64, n=131072, sink=0, lag=1024, topk=16), 0),
+        (dict(dtype=f32, d=64, B=7, Hq=64, Hkv=64, n=131072, sink=0, lag=1024, topk=16), 1),
+        # head_dim 128: 512 threads; 2^23 of them
+        (dict(dtype=f32, Hq=64, Hkv=8, n=131072, sink=0, lag=2, topk=1), 1),
+        (dict(dtype=f32, Hq=128, Hkv=8, n=131072, sink=0, lag=2, topk=1), 0),
+        (dict(dtype=f32, Hq=128, Hkv=8, n=131070, sink=0, lag=2, topk=1), 1),
+        # bf16: 512 threads for 256 rows of one to four heads
+        (dict(dtype=bf, d=64, Hq=128, Hkv=128, n=131072, sink=0, lag=2, topk=1), 0),
+        (dict(dtype=bf, d=64, Hq=128, Hkv=128, n=131068, sink=0, lag=1024, topk=16), 2),
+        (dict(dtype=bf, B=16, Hq=64, Hkv=8, n=1 << 19, sink=64, lag=2048, topk=512), 2),    # large, and in its range
+    ]:
+        p = _params(**kw)
+        assert lrsa.attn_route(p) == want, kw
+        assert lrsa.workspace_bytes(p, binding.WS_ATTN_BWD) > 0
+    with pytest.raises(lrsa.LrsaError):
+        lrsa.attn_route(_params(topk=0))
+    # filling steps: the window's own grid counts
+    p = _params(dtype=bf, B=2, Hq=128, Hkv=128, n=131072, sink=0, lag=2, topk=1)
+    assert lrsa.fill_workspace_bytes(p, 0, p.seq, binding.WS_ATTN_BWD) == 0
+    fake = ctypes.c_void_p(4096)
+    rc = lrsa.lib().lrsa_attn_fwd_fill(ctypes.byref(p), 0, p.seq, *([fake] * 7), 0, None)
+    assert rc == -2 and b"work-items" in lrsa.lib().lrsa_last_error()
+    assert lrsa.fill_workspace_bytes(p, 0, 1024, binding.WS_ATTN_BWD) > 0
+
+
 def test_product_package_does_not_import_the_oracle():
     pkg = os.path.join(ROOT, "paper_2506_11498_amd")
     for dirpath, _, files in os.walk(pkg):

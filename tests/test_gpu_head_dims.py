@@ -134,3 +134,32 @@ def test_f32(cfg, d, local_prev, layout):
     for k in want:
         bar = 1.25 * err(plain[k], want[k]) + 2.0 ** -23
         assert err(got[k], want[k]) <= bar, f"{k}: {err(got[k], want[k]):.3e} (bar {bar:.3e})"
+
+
+@pytest.mark.parametrize("dtype,B", [("f32", 64), ("bf16", 65)])
+def test_more_heads_than_a_launch_of_the_tiled_kernels_holds(dtype, B):
+    """B x 65535 query heads of three rows: two query tiles per head are past 2^32 work-items (fp32: 1024 threads a tile, bf16: 512), so
+    the plain kernels serve the call.  All keys are visible causally (two chunks); some heads against 64 bits, dK and dV over
+    all heads."""
+    dt = {"f32": torch.float32, "bf16": torch.bfloat16}[dtype]
+    Hq, n, d = 65535, 3, 64
+    g = torch.Generator(device=DEV).manual_seed(11)
+    Q, dO = (torch.randn((B, Hq, n, d), generator=g, device=DEV, dtype=dt) for _ in range(2))
+    K, V = (torch.randn((B, 1, n, d), generator=g, device=DEV, dtype=dt) for _ in range(2))
+    p = lrsa.params_for(Q, K, sink=0, lag=2, topk=1)
+    assert lrsa.attn_route(p) == 0 and lrsa.num_scored_chunks(p) == 0
+    O, lse = lrsa.lrsa_attn_fwd(p, Q, K, V, None)
+    dQ, dK, dV = lrsa.lrsa_attn_bwd(p, Q, K, V, O, dO, lse, None)
+    mask = torch.ones(n, n, dtype=torch.bool, device=DEV).tril()
+    # roundings of the results, and of some hundred (dK, dV: 200 K) fp32 additions
+    tol, tol_kv = {"f32": (2e-6, 2e-5), "bf16": (1e-2, 1e-2)}[dtype]
+    for b in (0, B - 1):
+        Kb, Vb = K[b, 0].double(), V[b, 0].double()
+        q, o, go = (t[b].double() for t in (Q, dO, O))
+        s = (q @ Kb.T * d ** -0.5).masked_fill(~mask, float("-inf"))
+        P = torch.softmax(s, -1)
+        want_O = P @ Vb
+        dS = P * (o @ Vb.T - (o * want_O).sum(-1, keepdim=True)) * d ** -0.5
+        for got, want, t in ((go, want_O, tol), (lse[b].double(), torch.logsumexp(s, -1), tol), (dQ[b].double(), dS @ Kb, 2 * tol),
+                             (dK[b, 0].double(), (dS.transpose(1, 2) @ q).sum(0), tol_kv), (dV[b, 0].double(), (P.transpose(1, 2) @ o).sum(0), tol_kv)):
+            assert (got - want).norm() <= t * want.norm()
