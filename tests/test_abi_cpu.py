@@ -232,3 +232,20 @@ def test_binding_refuses_tensors_whose_layout_differs_from_the_params():
         lrsa.lrsa_attn_fwd(p, Q, K, K, idx, lse=torch.zeros(B, Hq, 2 * n)[:, :, ::2])
     with pytest.raises(ValueError, match="dtype"):
         lrsa.lrsa_select(p, torch.zeros(B, Hkv, idx.shape[2], 32, dtype=torch.float64))
+
+
+def test_the_benchmark_counts_every_kernel():
+    """bench.py sums kernel times by name: every kernel that the library records belongs to one of its stages, and to one only."""
+    import glob
+    import bench
+    names = set()
+    for path in glob.glob(os.path.join(ROOT, "paper_2506_11498_amd", "csrc", "*.hip")):
+        names.update(re.findall(r'LRSA_TIMED_LAUNCH\("(\w+)"', open(path).read()))
+    assert len(names) > 20
+    for name in names:
+        assert bench.stage_of(name) in bench.STAGES
+        assert sum(name in kernels for kernels in bench.STAGES.values()) == 1
+    assert set().union(*bench.STAGES.values()) == names         # and no name of a kernel that is gone
+    with pytest.raises(KeyError):
+        bench.stage_of("k_unknown")
+    assert bench.frac_of_hbm_peak(4000.0, "x") == 0.5 and bench.frac_of_hbm_peak(50258.0, "x") is None
