@@ -105,6 +105,23 @@ __device__ __forceinline__ float col_all(float v, Op op) {
     return op(__uint_as_float(a.x), __uint_as_float(a.y));
 }
 
+// A tile in which some (query, key) pairs are masked: a weight of zero times an infinity would be NaN in the sums of a query (key)
+// that does not see the row.  The operand's non-finite values become zeros there; the return value says whether the row that this
+// lane's register i stands for has any, and the weights of the pairs that do see it become NaN.
+template <int DH>
+__device__ __forceinline__ bool clean_row(ColFrag<DH>& f, int q4) {
+    bool bad = false;
+#pragma unroll
+    for (int g = 0; g < DH / 64; ++g)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const bool x = !__builtin_isfinite(f.v[g][e]);
+            f.v[g][e] = x ? 0.0f : f.v[g][e];
+            bad |= x;
+        }
+    return (__builtin_amdgcn_ballot_w64(bad) >> (16 * q4) & 0xffff) != 0;   // over the 16 lanes that hold the row
+}
+
 // Query tiles of 16 rows inside the sink and inside every chunk; the latest (most keys) first.
 struct QTiles { int sink, tpc, count; };
 static QTiles make_qtiles(const Dims& D) {
@@ -158,6 +175,7 @@ __global__ __launch_bounds__(64 * F32_WAVES<DH>) void k_fwd_f32(Dims D, const fl
     const int tr = min(R.t0 + c, R.t_last);
     const RowFrag<DH> q = row_frag<DH>(Q + qoff + int64_t(tr) * D.qs[2], q4);
     const int lim = R.ng + tr - R.cs;                    // last stream entry the lane's query sees
+    const int lim_min = R.ng + R.t0 - R.cs;              // ... the first query sees
     float m = -INFINITY, l = 0.0f;
     Acc<DH> o;
     zero(o);
@@ -168,6 +186,10 @@ __global__ __launch_bounds__(64 * F32_WAVES<DH>) void k_fwd_f32(Dims D, const fl
 #pragma unroll
         for (int i = 0; i < 4; ++i) v[i] = col_frag<DH>(Vh + int64_t(__shfl(pos, 4 * q4 + i, 64)) * D.ks[2], c);
         fx4 s = dot_tile<DH>(k, q);
+        if (j0 + 15 > lim_min) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s[i] = clean_row<DH>(v[i], q4) ? NAN : s[i];
+        }
         float mx = m;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -233,7 +255,7 @@ __global__ __launch_bounds__(64 * F32_WAVES<DH>) void k_bwd_dq_f32(Dims D, const
     const int64_t qoff = b * D.qs[0] + hq * D.qs[1];
 
     const int t = R.t0 + c, tr = min(t, R.t_last);
-    const int lim = R.ng + tr - R.cs;
+    const int lim = R.ng + tr - R.cs, lim_min = R.ng + R.t0 - R.cs;
     const RowFrag<DH> q = row_frag<DH>(Q + qoff + int64_t(tr) * D.qs[2], q4), g = row_frag<DH>(dO + qoff + int64_t(tr) * D.qs[2], q4);
     const float ls = lse[int64_t(bh) * D.n + tr];
     float Dt = 0.0f;
@@ -254,13 +276,18 @@ __global__ __launch_bounds__(64 * F32_WAVES<DH>) void k_bwd_dq_f32(Dims D, const
         ColFrag<DH> kc[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) kc[i] = col_frag<DH>(Kh + int64_t(__shfl(pos, 4 * q4 + i, 64)) * D.ks[2], c);
-        const fx4 s = dot_tile<DH>(k, q), dp = dot_tile<DH>(v, g);
+        fx4 s = dot_tile<DH>(k, q);
+        const fx4 dp = dot_tile<DH>(v, g);
+        if (j0 + 15 > lim_min) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s[i] = clean_row<DH>(kc[i], q4) ? NAN : s[i];
+        }
         Acc<DH> t16;
         zero(t16);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const float p = j0 + 4 * q4 + i <= lim ? expf(D.scale * s[i] - ls) : 0.0f;
-            add_outer<DH>(t16, kc[i], p * (dp[i] - Dt));
+            const float ds = expf(D.scale * s[i] - ls) * (dp[i] - Dt);
+            add_outer<DH>(t16, kc[i], j0 + 4 * q4 + i <= lim ? ds : 0.0f);
         }
         add_acc<DH>(dq, 1.0f, t16);
     }
@@ -345,7 +372,8 @@ __global__ __launch_bounds__(64 * F32_KV_WAVES) void k_bwd_dkv_f32(Dims D, const
         }
         key += base;
     }
-    const int first_row = __builtin_amdgcn_readfirstlane(key);     // lane 0 holds the tile's lowest position
+    const int first_row = __builtin_amdgcn_readfirstlane(key);     // lane 0 holds the tile's lowest position, lane 15 its highest
+    const int last_key = __builtin_amdgcn_readlane(key, 15);
     if (threadIdx.x < 16) sPos[threadIdx.x] = key;
     const int64_t koff = b * D.ks[0] + h * D.ks[1];
     const RowFrag<DH> k = row_frag<DH>(K + koff + int64_t(key) * D.ks[2], q4), v = row_frag<DH>(V + koff + int64_t(key) * D.ks[2], q4);
@@ -369,19 +397,31 @@ __global__ __launch_bounds__(64 * F32_KV_WAVES) void k_bwd_dkv_f32(Dims D, const
             ls[i] = lse[rid + t];
             Dt[i] = Dsum[rid + t];
         }
-        const fx4 s = dot_tile<DH>(q, k), dp = dot_tile<DH>(g, v);
-        Acc<DH> tk, tv;
-        zero(tk);
-        zero(tv);
+        fx4 s = dot_tile<DH>(q, k), dp = dot_tile<DH>(g, v);
+        const bool masked = r0 < last_key || r0 + 16 > rend;
+        bool seen[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) seen[i] = r0 + 4 * q4 + i >= key && r0 + 4 * q4 + i < rend;
+        if (masked) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) s[i] = clean_row<DH>(gc[i], q4) ? NAN : s[i];
+        }
+        Acc<DH> t16;
+        zero(t16);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int t = r0 + 4 * q4 + i;
-            const float p = t >= key && t < rend ? expf(D.scale * s[i] - ls[i]) : 0.0f;
-            add_outer<DH>(tv, gc[i], p);
-            add_outer<DH>(tk, qc[i], p * (dp[i] - Dt[i]));
+            s[i] = expf(D.scale * s[i] - ls[i]);
+            add_outer<DH>(t16, gc[i], seen[i] ? s[i] : 0.0f);
         }
-        add_acc<DH>(dk, 1.0f, tk);
-        add_acc<DH>(dv, 1.0f, tv);
+        add_acc<DH>(dv, 1.0f, t16);
+        if (masked) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) dp[i] = clean_row<DH>(qc[i], q4) ? NAN : dp[i];
+        }
+        zero(t16);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) add_outer<DH>(t16, qc[i], seen[i] ? s[i] * (dp[i] - Dt[i]) : 0.0f);
+        add_acc<DH>(dk, 1.0f, t16);
     }
     put_acc<DH>(sK[wave], dk, c, q4);
     put_acc<DH>(sV[wave], dv, c, q4);

@@ -157,6 +157,7 @@ template <int DH, bool MASK>
 __device__ __forceinline__ void dq_tile(const unsigned char* sK, const unsigned char* sV, const bf16x8 (&qf)[KK<DH>],
                                         const bf16x8 (&gf)[KK<DH>], const LaneOffs& lo, f32x16 (&dq)[DB<DH>], int j0, int lim,
                                         int wave_lim_max, float c2, float lse2, float Dq, int lane) {
+    constexpr bool CLEAN = MASK && DH == 64;   // keys that a query does not see must not reach it, whatever they hold
     const int g = lane >> 5;
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
@@ -177,6 +178,8 @@ __device__ __forceinline__ void dq_tile(const unsigned char* sK, const unsigned 
             Weights<TERMS<DH>> dsf0, dsf1;
 #pragma unroll
             for (int n = 0; n < N4; ++n) {
+                if (CLEAN && n < N1) s = poison_rows(a[n % DQ_PF], s);
+                if (CLEAN && n >= N2) a[n % DQ_PF] = finite_operand(a[n % DQ_PF]);
                 if (n < N1) s = mfma32(a[n % DQ_PF], qf[n], s);
                 else if (n < N2) dp = mfma32(a[n % DQ_PF], gf[n - N1], dp);
                 else if (n < N3) dq[n - N2] = mfma32_w(a[n % DQ_PF], dsf0, dq[n - N2]);
@@ -196,7 +199,10 @@ __device__ __forceinline__ void dq_tile(const unsigned char* sK, const unsigned 
                 }
                 if (n == N2 - 1) {
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) s[i] *= dp[i] - Dq;
+                    for (int i = 0; i < 16; ++i) {
+                        s[i] *= dp[i] - Dq;
+                        if (CLEAN) s[i] = j0 + kb * 32 + 8 * (i >> 2) + 4 * g + (i & 3) <= lim ? s[i] : 0.0f;
+                    }
                     dsf0 = pack_weights<TERMS<DH>>(s, 0);
                     dsf1 = pack_weights<TERMS<DH>>(s, 8);
                 }
@@ -347,7 +353,18 @@ __global__ __launch_bounds__(DQ_THREADS, 2) void k_bwd_dq(Dims D, const bf16_t* 
         for (int i = 0; i < 8; ++i) Dq = __builtin_fmaf(float(o8[i]), float(gf[kk][i]), Dq);
     }
     Dq += __shfl_xor(Dq, 32, 64);
-    if (tq <= t_last && g == 0) { Dsum[rowid] = -Dq; lse2_out[rowid] = lse2; }   // -D: the key-outer kernel starts its dA sums from it
+    // head_dim 64: a row that holds an infinity or NaN anywhere is marked for the key-outer kernel by an lse of NaN
+    bool odd = false;
+    if constexpr (DH == 64) {
+        float z = (lse2 + Dq) * 0.0f;
+#pragma unroll
+        for (int kk = 0; kk < KK<DH>; ++kk)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) z = __builtin_fmaf(float(qf[kk][i]), 0.0f, __builtin_fmaf(float(gf[kk][i]), 0.0f, z));
+        z += __shfl_xor(z, 32, 64);
+        odd = z != 0.0f;
+    }
+    if (tq <= t_last && g == 0) { Dsum[rowid] = odd ? 0.0f : -Dq; lse2_out[rowid] = odd ? NAN : lse2; }   // -D: the key-outer kernel starts its dA sums from it
     const int lim = ng + tq - cs;
     const int wave_lim_max = ng + min(t0 + wq * 32 + 31, t_last) - cs;
 
@@ -558,6 +575,25 @@ __device__ __forceinline__ void dkv_step(const Dims& D, const unsigned char* sQ,
 #undef LRSA_OPND
 }
 
+// Query rows that hold infinities or NaN (the query-outer kernel has made their lse NaN) must make NaN of the sums of the keys that
+// see them, and leave the others of the step alone, although a sub-step multiplies its masked pairs by zero: the rows become zeros in
+// the stage's tiles.  A = exp(S - lse) is NaN where it is seen and 0 where it is masked.  Every wave clears all of them before
+// it reads the tiles: its own reads come after its own writes, and all waves write the same.
+template <int DH>
+__device__ __forceinline__ void clear_odd_rows(unsigned char* sQ, unsigned char* sG, const float* sLD, int lane) {
+    static_assert(KV_ROWS == 64, "a lane looks at a row");
+    const float l = sLD[lane];
+    unsigned long long rows = __builtin_amdgcn_ballot_w64(l != l);
+    while (rows) {
+        const int r = __builtin_ctzll(rows);
+        rows &= rows - 1;
+        if (lane * 16 < ROW_BYTES<DH>) {
+            *reinterpret_cast<uint4*>(sQ + r * ROW_BYTES<DH> + lane * 16) = uint4{0u, 0u, 0u, 0u};
+            *reinterpret_cast<uint4*>(sG + r * ROW_BYTES<DH> + lane * 16) = uint4{0u, 0u, 0u, 0u};
+        }
+    }
+}
+
 // Two stages of 64 rows: one barrier per 64 MFMAs of a wave; the copies of the next stage run during
 // the two sub-steps of the current one.
 
@@ -765,6 +801,7 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
     {                                                                                                    \
         wait_vmcnt<0>();     /* this wave's copies for `step` have landed */                             \
         __syncthreads();     /* ... everybody's have, and everybody is done with the other stage */      \
+        if constexpr (DH == 64) clear_odd_rows<DH>(sQ, sG, sL + wave * 2 * KV_ROWS, lane);              \
         if ((step) + 1 < nsteps) issue((step) + 1, sQn, sGn, sLn);                                       \
         int r0s_, rend_, lim_u_;                                                                         \
         step_rows(step, r0s_, rend_, lim_u_);                                                            \

@@ -85,6 +85,13 @@ __device__ __forceinline__ void fwd_tile(const unsigned char* sK, const unsigned
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
         for (int i = 0; i < 16; ++i) s[kb][i] = 0.0f;
+    constexpr bool CLEAN = MASK && DH == 64;   // rows that a query does not see must not reach it, whatever they hold
+    if constexpr (CLEAN) {
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+            for (int kk = 0; kk < KK<DH>; ++kk) s[kb] = poison_rows(read_rows_o<DH>(sV, lo, 32 * kb, kk), s[kb]);
+    }
     // S^T = K Q^T: operands are read a block ahead of the MFMAs that consume them
     {
         bf16x8 a[KK<DH>];
@@ -177,6 +184,9 @@ __device__ __forceinline__ void fwd_tile(const unsigned char* sK, const unsigned
             if (kg < 2 || two) {
                 // a term at a time, what is left of the weights in their own registers
                 f32x16& w = s[kg >> 1];
+                if constexpr (CLEAN)
+#pragma unroll
+                    for (int db = 0; db < DB<DH>; ++db) va[db] = finite_operand(va[db]);
 #pragma unroll
                 for (int t = 0; t < TERMS<DH>; ++t) {
                     const bf16x8 pf = pack8(w, 8 * (kg & 1));

@@ -143,6 +143,21 @@ __device__ __forceinline__ f32x16 mfma32_w(bf16x8 a, const Weights<TERMS>& w, f3
 }
 template <int DH> constexpr int TERMS = DH == 64 ? 3 : 1;
 
+// Tiles in which some (query, key) pairs are masked, head_dim 64: a weight of zero times an infinity would be NaN in the sums of a
+// query (key) that does not see the row.  finite_operand() makes zeros of an operand's non-finite values; poison_rows() turns
+// the logits of a tile's rows that have any into NaN (a product with zeros: 0 otherwise), for the pairs that do see them.
+__device__ __forceinline__ bf16x8 finite_operand(bf16x8 a) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    u32x4 w = __builtin_bit_cast(u32x4, a);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t lo = (w[i] & 0x7f80u) == 0x7f80u ? 0xffff0000u : ~0u, hi = (w[i] & 0x7f800000u) == 0x7f800000u ? 0xffffu : ~0u;
+        w[i] &= lo & hi;
+    }
+    return __builtin_bit_cast(bf16x8, w);
+}
+__device__ __forceinline__ f32x16 poison_rows(bf16x8 rows, f32x16 s) { return mfma32(rows, bf16x8{}, s); }
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // Units of the logits inside the kernels: log2 units, so that a weight is one fma and one exponential; head_dim 64: natural

@@ -163,3 +163,47 @@ def test_more_heads_than_a_launch_of_the_tiled_kernels_holds(dtype, B):
         for got, want, t in ((go, want_O, tol), (lse[b].double(), torch.logsumexp(s, -1), tol), (dQ[b].double(), dS @ Kb, 2 * tol),
                              (dK[b, 0].double(), (dS.transpose(1, 2) @ q).sum(0), tol_kv), (dV[b, 0].double(), (P.transpose(1, 2) @ o).sum(0), tol_kv)):
             assert (got - want).norm() <= t * want.norm()
+
+
+@pytest.mark.parametrize("which", ["K", "V", "Q", "dO"])
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 64), ("f32", 128)])
+def test_non_finite_rows_stay_with_those_that_see_them(dtype, d, which):
+    """Infinities and NaN in a row (padding behind the end, say) reach only the queries that see the key and the keys that the query
+    sees, although a tile multiplies its masked pairs by zero.  Everything else is as with finite values there: the same bits in
+    fp32; in bf16 up to the last bit (a wave refreshes its running maxima for all of its queries at once)."""
+    def same(a, b):
+        return torch.equal(a, b) if dtype == "f32" else bool(a.isfinite().all()) and bool((a - b).float().norm() <= 2.0 ** -9 * b.float().norm())
+
+    w = inputs.small_workload(d=d, dtype=dtype, n=5 + 6 * 72 + 41, L=72, S=5, K=20, Hq=4, Hkv=2)
+    x = inputs.make_inputs(w)
+    idx, _ = reference(w, x, 1)
+    idx_dev = torch.from_numpy(idx).to(DEV)
+    clean, _ = run(w, {k: v.to(DEV) for k, v in x.items()}, idx_dev, lrsa.IMPL_AUTO)
+    # rows inside and at the edges of tiles, in a chunk that is compressed, in the last ones, the last row; values in a few channels
+    rows = [5 + 2 * 72 + 25, 5 + 4 * 72, 5 + 5 * 72 + 16, w.n - 9, w.n - 1]
+    for i, t in enumerate(rows):
+        for c, v in ((i, float("nan")), (17 + i, float("-inf")), (40 + i, float("inf")))[:1 if i % 2 else 3]:
+            x[which][:, :, t, c] = v
+    got, _ = run(w, {k: v.to(DEV) for k, v in x.items()}, idx_dev, lrsa.IMPL_AUTO)
+    bad = torch.zeros(w.n, dtype=torch.bool)
+    bad[rows] = True
+    for hq in range(w.Hq):
+        h = hq // (w.Hq // w.Hkv)
+        vis = torch.from_numpy(ref.visible_mask(w.n, w.S, w.L, idx[0, h], 1))
+        q_bad = (vis & bad).any(1) if which in "KV" else bad
+        assert 0 < q_bad.sum() < w.n
+        for k in ("O", "lse", "dQ"):
+            if which == "dO" and k != "dQ":
+                assert torch.equal(got[k], clean[k])
+                continue
+            a, b = got[k][0, hq].cpu(), clean[k][0, hq].cpu()
+            assert same(a[~q_bad], b[~q_bad]), f"{k}: {which} reaches queries that do not see it"
+            if k != "lse":
+                assert not a[q_bad].isfinite().all(-1).any(), f"{k}: a query that sees {which} does not show it"
+        k_bad = (vis & q_bad[:, None]).any(0)                # keys that an affected query sees
+        assert 0 < k_bad.sum() < w.n
+        for k in ("dK", "dV"):
+            if which in ("Q", "dO"):
+                assert not got[k][0, h].cpu()[(vis & bad[:, None]).any(0)].isfinite().all(-1).any(), f"{k}: {which} does not show"
+            a, b = got[k][0, h].cpu(), clean[k][0, h].cpu()
+            assert same(a[~k_bad], b[~k_bad]), f"{k}: {which} reaches keys that no affected query sees"
