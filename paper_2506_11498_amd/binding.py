@@ -249,15 +249,30 @@ def lrsa_score_select(p: LrsaParams, K: torch.Tensor, V: torch.Tensor, score: Op
     return score, idx
 
 
+def cache_compress_ws_bytes(p: LrsaParams, length: int, done: int) -> int:
+    """Workspace of lrsa_cache_compress for these counts; 0 where it has nothing to move."""
+    return int(lib().lrsa_cache_compress_ws_bytes(ctypes.byref(p), int(length), int(done)))
+
+
 def lrsa_cache_compress(p: LrsaParams, Kc: torch.Tensor, Vc: torch.Tensor, pos: Optional[torch.Tensor],
-                        length: int, done: int):
+                        length: int, done: int, ws: Optional[torch.Tensor] = None):
     """Inference-time cache: compress (in place) while the uncompressed tail holds 2*lag rows.
-    Kc, Vc: [B, Hkv, cap, d] with cap = p.seq; pos: int32 [B, Hkv, cap] or None.  Returns (length, done)."""
+    Kc, Vc: [B, Hkv, cap, d] with cap = p.seq; pos: int32 [B, Hkv, cap] or None.  Returns (length, done).
+    ws: cache_compress_ws_bytes() bytes.  Without one, a workspace is allocated for the call; under graph capture (where nothing
+    would hold it until the replays) and where there is no memory for it, the same steps run one by one without."""
     new_len, new_done = ctypes.c_int32(0), ctypes.c_int32(0)
-    need = lib().lrsa_cache_compress_ws_bytes(ctypes.byref(p), int(length), int(done))
-    ws = torch.empty(need, dtype=torch.uint8, device=Kc.device) if need else None
-    _check(lib().lrsa_cache_compress_ws(ctypes.byref(p), _ptr(Kc), _ptr(Vc), _ptr(pos), int(length), int(done),
-                                        ctypes.byref(new_len), ctypes.byref(new_done), _ptr(ws), need, _stream()))
+    counts = (int(length), int(done), ctypes.byref(new_len), ctypes.byref(new_done))
+    need = cache_compress_ws_bytes(p, length, done) if Kc is not None else 0
+    if need and ws is None and not torch.cuda.is_current_stream_capturing():
+        try:
+            ws = torch.empty(need, dtype=torch.uint8, device=Kc.device)
+        except torch.OutOfMemoryError:
+            pass
+    if need and ws is None:
+        _check(lib().lrsa_cache_compress(ctypes.byref(p), _ptr(Kc), _ptr(Vc), _ptr(pos), *counts, _stream()))
+    else:
+        nb = 0 if ws is None else ws.numel() * ws.element_size()
+        _check(lib().lrsa_cache_compress_ws(ctypes.byref(p), _ptr(Kc), _ptr(Vc), _ptr(pos), *counts, _ptr(ws), nb, _stream()))
     return new_len.value, new_done.value
 
 

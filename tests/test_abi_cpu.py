@@ -202,6 +202,13 @@ def test_inference_cache_calls_validate_on_the_host():
     assert L.lrsa_cache_compress(ctypes.byref(p), None, None, None, 100, 0, None, None, None) == -1
     p2 = _params(n=4096, sink=16, lag=256, topk=64, local_prev=2)
     assert L.lrsa_cache_compress(ctypes.byref(p2), None, None, None, 16 + 512, 0, *out, None) == -2
+    # with a workspace: its size and alignment
+    need = lrsa.cache_compress_ws_bytes(p, 16 + 512, 0)
+    assert need > 0 and lrsa.cache_compress_ws_bytes(p, 16 + 511, 0) == 0
+    fake = ctypes.c_void_p(4096)
+    for ws, nb in ((None, need), (ctypes.c_void_p(8192), need - 1), (ctypes.c_void_p(8192 + 16), need)):
+        assert L.lrsa_cache_compress_ws(ctypes.byref(p), fake, fake, None, 16 + 512, 0, *out, ws, nb, None) == -1
+        assert b"workspace" in L.lrsa_last_error()
     # decode attention: length and pointers
     assert L.lrsa_decode_attn(ctypes.byref(p), None, None, None, 0, None, None, None, 0, None) == -1
     assert L.lrsa_decode_attn(ctypes.byref(p), None, None, None, 10, None, None, None, 0, None) == -1

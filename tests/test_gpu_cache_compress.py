@@ -79,3 +79,62 @@ def test_a_whole_prompt_equals_the_token_by_token_procedure():
         assert np.array_equal(pos[0, h, :length].cpu().numpy(), po)
         assert np.array_equal(Kc[0, h, :length].float().cpu().numpy(), Ko)
         assert np.array_equal(Vc[0, h, :length].float().cpu().numpy(), Vo)
+
+
+def _prompt():
+    B, Hkv, d, L, K, S, n = 1, 2, 128, 64, 16, 8, 8 + 5 * 64 + 7
+    g = torch.Generator().manual_seed(4)
+    Kc, Vc = (torch.randn((B, Hkv, n, d), generator=g).to(torch.bfloat16).to(DEV) for _ in range(2))
+    pos = torch.arange(n, dtype=torch.int32, device=DEV).expand(B, Hkv, n).contiguous()
+    p = lrsa.make_params((B, Hkv, n, d), (B, Hkv, n, d), Kc.stride(), Kc.stride(), dtype=torch.bfloat16, sink=S, lag=L, topk=K)
+    return p, (Kc, Vc, pos), n
+
+
+def test_under_graph_capture_nothing_is_allocated():
+    """A workspace from torch's allocator would not be held until the replays: without one of the caller's, the steps are
+    recorded that need none.  Every replay, with eager work in between, equals the eager call."""
+    p, start, n = _prompt()
+    want = [t.clone() for t in start]
+    counts = lrsa.lrsa_cache_compress(p, *want, n, 0)
+    for own_ws in (False, True):
+        ws = torch.empty(lrsa.cache_compress_ws_bytes(p, n, 0), dtype=torch.uint8, device=DEV) if own_ws else None
+        bufs = [t.clone() for t in start]
+        lrsa.lrsa_cache_compress(p, *bufs, n, 0, ws)                  # everything is loaded before the capture
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            before = torch.cuda.memory_stats()["allocation.all.allocated"]
+            assert lrsa.lrsa_cache_compress(p, *bufs, n, 0, ws) == counts
+            assert torch.cuda.memory_stats()["allocation.all.allocated"] == before
+        for _ in range(3):
+            for b, t in zip(bufs, start):
+                b.copy_(t)
+            torch.empty(1 << 20, device=DEV).normal_()
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            for b, r in zip(bufs, want):
+                assert torch.equal(b[:, :, :counts[0]], r[:, :, :counts[0]])
+
+
+def test_without_memory_for_a_workspace_the_call_still_runs(monkeypatch):
+    p, start, n = _prompt()
+    want = [t.clone() for t in start]
+    counts = lrsa.lrsa_cache_compress(p, *want, n, 0)
+
+    def no_memory(*a, **k):
+        raise torch.OutOfMemoryError("out of memory")
+    monkeypatch.setattr(torch, "empty", no_memory)
+    assert lrsa.lrsa_cache_compress(p, *start, n, 0) == counts
+    monkeypatch.undo()
+    for b, r in zip(start, want):
+        assert torch.equal(b[:, :, :counts[0]], r[:, :, :counts[0]])
+
+
+def test_missing_buffers_and_short_workspaces_are_reported_by_the_library():
+    p, (Kc, Vc, pos), n = _prompt()
+    for K, V in ((None, Vc), (Kc, None), (None, None)):
+        with pytest.raises(lrsa.LrsaError, match="NULL"):
+            lrsa.lrsa_cache_compress(p, K, V, pos, n, 0)
+    with pytest.raises(lrsa.LrsaError, match="workspace"):
+        lrsa.lrsa_cache_compress(p, Kc, Vc, pos, n, 0, torch.empty(256, dtype=torch.uint8, device=DEV))
