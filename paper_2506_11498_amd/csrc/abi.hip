@@ -363,6 +363,7 @@ int lrsa_attn_fwd_fill(const lrsa_params* p, int32_t row_begin, int32_t row_end,
     if (D.fq1 - 1 - D.lp > 0 && !idx) return fail(LRSA_ERR_INVALID_ARG, "lrsa_attn_fwd_fill: idx is NULL but the rows see compressed chunks");
     if (misaligned16(Q) || misaligned16(K) || misaligned16(V) || misaligned16(O))
         return fail(LRSA_ERR_INVALID_ARG, "lrsa_attn_fwd_fill: tensors must be 16-byte aligned");
+    if (!idx) D.Ns = 0;     // none of the rows sees a compressed chunk; the forward kernel reads its list ahead where there is one
     const size_t need = lrsa::attn_fwd_mfma_ws_bytes(D);
     if (need > 0 && (!ws || ws_bytes < need)) return fail(LRSA_ERR_INVALID_ARG, "lrsa_attn_fwd_fill: workspace of %zu bytes needed", need);
     return hip_result(lrsa::launch_attn_fwd_mfma(D, shift_rows(Q, D, D.qs[2]), K, V, idx,

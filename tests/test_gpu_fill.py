@@ -152,3 +152,27 @@ def test_fill_rejects_windows_off_the_chunk_grid():
     p = lrsa.params_for(xd["Q"], xd["K"], sink=w.S, lag=w.L, topk=w.K)
     for a, b in ((0, 50), (17, 16 + 64), (16 + 64, 16 + 64), (16, w.n + 1)):
         assert lrsa.fill_workspace_bytes(p, a, b, 3) == 0
+
+
+@pytest.mark.parametrize("Hkv,G", [(1, 4), (3, 2)])
+def test_steps_that_see_no_compressed_chunk_need_no_idx(Hkv, G):
+    """idx may be missing as long as the step's queries see no compressed chunk (the first two chunks): same bits as with one."""
+    w = inputs.small_workload(n=16 + 6 * 64 + 40, L=64, S=16, K=16, d=128, Hq=Hkv * G, Hkv=Hkv, B=2, dtype="bf16")
+    xd = {k: v.to(DEV) for k, v in inputs.make_inputs(w).items()}
+    kw = dict(sink=w.S, lag=w.L, topk=w.K)
+    _, idx = lrsa.lrsa_score_select(lrsa.params_for(xd["Q"], xd["K"], **kw), xd["K"], xd["V"])
+    for a, b in ((0, 16 + 64), (16 + 64, 16 + 128), (0, 16 + 128)):
+        Qs, dOs = xd["Q"][:, :, a:b].contiguous(), xd["dO"][:, :, a:b].contiguous()
+        p = lrsa.params_for(Qs, xd["K"], **kw)
+        p.seq = w.n
+        res = []
+        for list_ in (idx, None):
+            O, lse = lrsa.lrsa_attn_fwd_fill(p, a, b, Qs, xd["K"], xd["V"], list_)
+            acc = [torch.zeros(xd["K"].shape, dtype=torch.float32, device=DEV) for _ in range(2)]
+            dQ = lrsa.lrsa_attn_bwd_fill(p, a, b, Qs, xd["K"], xd["V"], O, dOs, lse, list_, *acc)
+            res.append((O, lse, dQ, *acc))
+        for x, y in zip(*res):
+            assert torch.equal(x, y)
+    p = lrsa.params_for(xd["Q"], xd["K"], **kw)
+    with pytest.raises(lrsa.LrsaError, match="idx"):
+        lrsa.lrsa_attn_fwd_fill(p, 0, w.n, xd["Q"], xd["K"], xd["V"], None)
