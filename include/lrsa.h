@@ -194,7 +194,9 @@ int lrsa_attn_bwd(const lrsa_params *p, const void *Q, const void *K, const void
  *                  them before the first step; steps in any order, one after the other on one stream);
  *                  lrsa_attn_bwd_finish converts the sums to dK, dV (by kv_stride, dtype `dtype`)
  * Workspace: lrsa_fill_workspace_bytes(p, row_begin, row_end, LRSA_WS_ATTN_FWD / LRSA_WS_ATTN_BWD) -- it grows
- * with the rows of the step and the cache they see, not with n * n_q.  Built for bf16 with head_dim 128
+ * with the rows of the step and the cache they see, not with n * n_q.  That is the size for the fastest plan of dK and
+ * dV, which for short steps splits the work further and sums in another order; a backward call (lrsa_attn_bwd too) with less
+ * takes the plan without splits, so that a workspace sized for the longest step serves the others.  Built for bf16 with head_dim 128
  * (LRSA_ERR_UNSUPPORTED otherwise); impl LRSA_IMPL_COMPACT is treated as LRSA_IMPL_AUTO. */
 size_t lrsa_fill_workspace_bytes(const lrsa_params *p, int32_t row_begin, int32_t row_end, int which);
 int lrsa_attn_fwd_fill(const lrsa_params *p, int32_t row_begin, int32_t row_end, const void *Q, const void *K,

@@ -90,7 +90,7 @@ size_t ws_need(const lrsa_params* p, const lrsa::Dims& D, int which) {
 }
 
 int check_ws(const lrsa_params* p, const lrsa::Dims& D, int which, const void* ws, size_t ws_bytes) {
-    const size_t need = ws_need(p, D, which);
+    const size_t need = which == LRSA_WS_ATTN_BWD && use_mfma(p, D) ? lrsa::attn_bwd_mfma_ws_min_bytes(D) : ws_need(p, D, which);
     if (need == 0) return LRSA_OK;
     if (!ws) return fail(LRSA_ERR_INVALID_ARG, "workspace is NULL but %zu bytes are needed", need);
     if (ws_bytes < need) return fail(LRSA_ERR_INVALID_ARG, "workspace has %zu bytes, %zu are needed", ws_bytes, need);
@@ -302,7 +302,7 @@ int lrsa_attn_bwd(const lrsa_params* p, const void* Q, const void* K, const void
         return fail(LRSA_ERR_INVALID_ARG, "lrsa_attn_bwd: tensors must be 16-byte aligned");
     if ((rc = check_ws(p, D, LRSA_WS_ATTN_BWD, ws, ws_bytes)) != LRSA_OK) return rc;
     const hipError_t e =
-        use_mfma(p, D) ? lrsa::launch_attn_bwd_mfma(D, Q, K, V, O, dO, lse, idx, dQ, dK, dV, nullptr, nullptr, ws, (hipStream_t)stream)
+        use_mfma(p, D) ? lrsa::launch_attn_bwd_mfma(D, Q, K, V, O, dO, lse, idx, dQ, dK, dV, nullptr, nullptr, ws, ws_bytes, (hipStream_t)stream)
                        : use_f32_tiles(p, D) ? lrsa::launch_attn_bwd_f32(D, Q, K, V, O, dO, lse, idx, dQ, dK, dV, ws, (hipStream_t)stream)
                        : lrsa::launch_attn_bwd_generic(D, Q, K, V, O, dO, lse, idx, dQ, dK, dV, ws, (hipStream_t)stream);
     return hip_result(e, "lrsa_attn_bwd");
@@ -386,14 +386,14 @@ int lrsa_attn_bwd_fill(const lrsa_params* p, int32_t row_begin, int32_t row_end,
     if (misaligned16(Q) || misaligned16(K) || misaligned16(V) || misaligned16(O) || misaligned16(dO) || misaligned16(dQ) ||
         misaligned16(dK_acc) || misaligned16(dV_acc))
         return fail(LRSA_ERR_INVALID_ARG, "lrsa_attn_bwd_fill: tensors must be 16-byte aligned");
-    const size_t need = lrsa::attn_bwd_mfma_ws_bytes(D);
+    const size_t need = lrsa::attn_bwd_mfma_ws_min_bytes(D);
     if (!ws || ws_bytes < need) return fail(LRSA_ERR_INVALID_ARG, "lrsa_attn_bwd_fill: workspace of %zu bytes needed", need);
     if (reinterpret_cast<uintptr_t>(ws) % 256 != 0) return fail(LRSA_ERR_INVALID_ARG, "workspace is not 256-byte aligned");
     D.acc = 1;
     return hip_result(lrsa::launch_attn_bwd_mfma(D, shift_rows(Q, D, D.qs[2]), K, V, shift_rows(O, D, D.qs[2]),
                                                  shift_rows(dO, D, D.qs[2]), lse - D.row_begin, idx,
                                                  const_cast<void*>(shift_rows(dQ, D, D.qs[2])), nullptr, nullptr, dK_acc,
-                                                 dV_acc, ws, (hipStream_t)stream),
+                                                 dV_acc, ws, ws_bytes, (hipStream_t)stream),
                       "lrsa_attn_bwd_fill");
 }
 

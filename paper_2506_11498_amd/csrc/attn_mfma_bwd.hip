@@ -78,7 +78,8 @@ static int head_parts(const Dims& D, double rows, double bytes, double bytes_one
 static int64_t gather_workgroups(const Dims& D, const BwdPlan& P) { return (int64_t(D.B) * D.Hkv * P.nsl * P.hsl + 7) / 8 * 8 * P.gtiles; }
 static int64_t window_workgroups(const Dims& D, const BwdPlan& P) { return (int64_t(D.B) * D.Hkv * P.ktiles * P.wsl + 7) / 8 * 8; }
 
-static BwdPlan make_plan(const Dims& D) {
+// split: with parts of the heads and the finest slices, where their rules ask for them; both take more workspace
+static BwdPlan make_plan(const Dims& D, bool split) {
     BwdPlan P;
     const int sink_rows = D.S < D.n ? D.S : D.n;
     P.fq0 = D.fq0;
@@ -104,7 +105,7 @@ static BwdPlan make_plan(const Dims& D) {
     // fewer than a quarter as many as CUs: down to 256 rows.  (2.6K tokens, 4 heads on 2, 2 requests, 24 workgroups: 164 ->
     // 157 us; 2.2K tokens in filling steps, 4 heads on 1: 710 -> 633 us.  From 84 workgroups on it costs more than it gives:
     // 5.5K tokens, 4 heads on 2, 4 requests 264 -> 272 us, 4K tokens, 8 heads on 8, 2 requests, 128 of them, 271 -> 295 us.)
-    while (qch > min_qch && qch > 1 && (qch / 2) * int64_t(D.L) * D.G >= 256 &&
+    while (split && qch > min_qch && qch > 1 && (qch / 2) * int64_t(D.L) * D.G >= 256 &&
            int64_t(D.B) * D.Hkv * P.gtiles * ((nqf + qch - 1) / qch) / 2 < 64)
         qch /= 2;
     P.qch = int(qch);
@@ -116,7 +117,7 @@ static BwdPlan make_plan(const Dims& D) {
     P.hsl = P.wsl = 1;
     const int units = D.B * D.Hkv;
     const double w_rows = double(D.lp + 1) * D.L * D.G, g_rows = P.nsl > 0 ? double(P.qch) * D.L * D.G : 0.0;   // of a workgroup
-    if (D.G > 1) {
+    if (split && D.G > 1) {
         double visible = 0.0;   // query chunks that see a list tile, over all tiles
         for (int t = 0; t < P.gtiles; ++t) {
             const int qf = first_chunk_seeing(D, t * KV_BK);
@@ -140,12 +141,23 @@ static BwdPlan make_plan(const Dims& D) {
     return P;
 }
 
-size_t attn_bwd_mfma_ws_bytes(const Dims& D) { return make_plan(D).bytes; }
+// What a plan needs does not grow steadily from one filling step to the next: a split step may need more than a later, longer
+// one that is not split (up to three times, in every sixth of 2400 shapes).  A call whose workspace holds the plan without splits, as
+// one that was sized for the last step does, takes that plan.
+static BwdPlan plan_for(const Dims& D, size_t ws_bytes) {
+    const BwdPlan P = make_plan(D, true);
+    return P.bytes <= ws_bytes ? P : make_plan(D, false);
+}
+size_t attn_bwd_mfma_ws_bytes(const Dims& D) { return make_plan(D, true).bytes; }
+size_t attn_bwd_mfma_ws_min_bytes(const Dims& D) {
+    const size_t whole = make_plan(D, false).bytes, split = attn_bwd_mfma_ws_bytes(D);
+    return whole < split ? whole : split;
+}
 
 // the grids of the forward, dQ and dK/dV launches (the reduction's threads are fewer than the bytes of its partials)
 bool mfma_grids_fit(const Dims& D) {
     const QTileMap M = make_qtile_map(D, heads_per_wg(D), DQ_WAVES);
-    const BwdPlan P = make_plan(D);
+    const BwdPlan P = make_plan(D, true);
     return grid_fits(int64_t(D.B) * D.Hkv * (M.tix_hi - M.tix_lo) * M.gsubs, DQ_THREADS) &&
            grid_fits(gather_workgroups(D, P) + window_workgroups(D, P), KV_THREADS);
 }
@@ -1028,8 +1040,8 @@ hipError_t launch_bwd_acc_finish(const Dims& D, const float* accK, const float* 
 // ------------------------------------------------------------------------------------ launcher
 hipError_t launch_attn_bwd_mfma(const Dims& D, const void* Q, const void* K, const void* V, const void* O,
                                 const void* dO, const float* lse, const int32_t* idx, void* dQ, void* dK,
-                                void* dV, float* accK, float* accV, void* ws, hipStream_t st) {
-    const BwdPlan P = make_plan(D);
+                                void* dV, float* accK, float* accV, void* ws, size_t ws_bytes, hipStream_t st) {
+    const BwdPlan P = plan_for(D, ws_bytes);
     // D and lse in the logits' units hold the rows of the window only; like the caller's tensors they are addressed by
     // absolute row, hence the shifted bases
     float* Dsum = reinterpret_cast<float*>(ws) - D.row_begin;

@@ -88,10 +88,11 @@ bool mfma_grids_fit(const Dims&);
 size_t attn_fwd_mfma_ws_bytes(const Dims&);
 hipError_t launch_attn_fwd_mfma(const Dims&, const void* Q, const void* K, const void* V, const int32_t* idx,
                                 void* O, float* lse, void* ws, hipStream_t st);
-size_t attn_bwd_mfma_ws_bytes(const Dims&);
+size_t attn_bwd_mfma_ws_bytes(const Dims&);       // for the fastest plan
+size_t attn_bwd_mfma_ws_min_bytes(const Dims&);   // for one without splits: what a call must have
 hipError_t launch_attn_bwd_mfma(const Dims&, const void* Q, const void* K, const void* V, const void* O,
                                 const void* dO, const float* lse, const int32_t* idx, void* dQ, void* dK,
-                                void* dV, float* accK, float* accV, void* ws, hipStream_t st);
+                                void* dV, float* accK, float* accV, void* ws, size_t ws_bytes, hipStream_t st);
 hipError_t launch_bwd_acc_finish(const Dims&, const float* accK, const float* accV, void* dK, void* dV, hipStream_t st);
 
 // A launch has fewer than 2^32 work-items per grid dimension (and fewer than 2^31 workgroups).  The runtime does not refuse a larger

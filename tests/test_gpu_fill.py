@@ -176,3 +176,34 @@ def test_steps_that_see_no_compressed_chunk_need_no_idx(Hkv, G):
     p = lrsa.params_for(xd["Q"], xd["K"], **kw)
     with pytest.raises(lrsa.LrsaError, match="idx"):
         lrsa.lrsa_attn_fwd_fill(p, 0, w.n, xd["Q"], xd["K"], xd["V"], None)
+
+
+def test_a_workspace_for_the_last_whole_step_serves_every_step():
+    """The split plan of an early step may need more than the last step; with that one's workspace it takes the plan without
+    splits: dQ the same bits, dK and dV up to the order of the additions."""
+    w = inputs.small_workload(n=4087, L=170, S=0, K=42, d=128, Hq=6, Hkv=1, B=4, dtype="bf16")
+    xd = {k: v.to(DEV) for k, v in inputs.make_inputs(w).items()}
+    kw = dict(sink=w.S, lag=w.L, topk=w.K)
+    p = lrsa.params_for(xd["Q"], xd["K"], **kw)
+    _, idx = lrsa.lrsa_score_select(p, xd["K"], xd["V"])
+    steps = windows(w, 1)
+    last = max(s for s in steps if s[1] - s[0] == w.L)
+    pq = lrsa.params_for(xd["Q"][:, :, :w.L], xd["K"], **kw)                   # Q, O, dO, dQ rows as views
+    pq.seq = w.n
+    small = lrsa.fill_workspace_bytes(pq, *last, 3)
+    assert max(lrsa.fill_workspace_bytes(pq, a, b, 3) for a, b in steps) > 1.2 * small
+    O, lse = lrsa.lrsa_attn_fwd(p, xd["Q"], xd["K"], xd["V"], idx)
+    out = []
+    for ws in (None, torch.empty(small, dtype=torch.uint8, device=DEV)):
+        acc = [torch.zeros(xd["K"].shape, dtype=torch.float32, device=DEV) for _ in range(2)]
+        dQ = torch.empty_like(xd["Q"])
+        for a, b in steps:
+            lrsa.lrsa_attn_bwd_fill(pq, a, b, xd["Q"][:, :, a:b], xd["K"], xd["V"], O[:, :, a:b], xd["dO"][:, :, a:b], lse[:, :, a:b].contiguous(), idx,
+                                    *acc, dQ[:, :, a:b], ws)
+        out.append((dQ, *acc))
+    assert torch.equal(out[0][0], out[1][0])
+    for a, b in zip(out[0][1:], out[1][1:]):
+        assert (a - b).norm() <= 1e-6 * a.norm()                              # fp32 sums of some hundred to thousand bf16 products
+    with pytest.raises(lrsa.LrsaError, match="workspace"):
+        lrsa.lrsa_attn_bwd_fill(pq, *last, xd["Q"][:, :, :w.L], xd["K"], xd["V"], O[:, :, :w.L], xd["dO"][:, :, :w.L], lse[:, :, :w.L].contiguous(),
+                                idx, *acc, None, torch.empty(1 << 16, dtype=torch.uint8, device=DEV))
