@@ -37,16 +37,21 @@ static int decode_static_splits(const Dims& D, int len) {
     return s < 1 ? 1 : s > DEC_MAX_SPLITS ? DEC_MAX_SPLITS : s;
 }
 static size_t part_bytes(const Dims& D, int splits) { return size_t(D.B) * D.Hq * splits * (D.d + 2) * 4; }
-// Two workgroups of k_decode_mfma share a CU (registers), so 512 run at once: at most that many, so that none runs alone
-// behind them, or many more where 512 / units would leave CUs with half the work of others.  At least 128 rows each, a tile
-// per wave (the 2.3K-row call above: 18 slices instead of 9).  A call that the scratch of lrsa_decode_attn_static
-// held with decode_static_splits still fits: beyond it the slices stay at that number.
+// Two workgroups share a CU (registers), so 512 run at once: at most that many, so that none runs alone behind them, or many more
+// where 512 / units would leave CUs with half the work of others.  At least 128 rows each, a tile per wave of k_decode_mfma
+// (12 heads on 2, 2.3K rows: 18 slices instead of 9, with the rest of k_decode_mfma 24.3 -> 11.3 us; fp32 33.9 -> 21.1 us).
+// fp32 with three and more heads per group is bound by the vector pipe, which wants waves: beyond some units it keeps the count of
+// decode_static_splits (104 units of 4 heads, 4K rows: 95 us, 108 with 512 / units; 88 units of 3 heads, 3.6K rows: 70 us, 67).
+// A call that the scratch of lrsa_decode_attn_static held with decode_static_splits still fits: beyond it the slices stay at that
+// number, in both calls, so that they give the same bits (more of them are no gain there: bf16, 512 units of 16 heads, 8K rows
+// 356 us, 378 with four slices; 2K rows 124 and 114 us).
 static int decode_splits(const Dims& D, int len) {
     const int units = D.B * D.Hkv, most = (len + 127) / 128;
     int s = units <= 128 ? 512 / units : 2048 / units;
     s = s < most ? s : most;
     s = s < 1 ? 1 : s > DEC_MAX_SPLITS ? DEC_MAX_SPLITS : s;
     const int base = decode_static_splits(D, len);
+    if (D.dtype == 0 && D.G > 2 && units > (D.G == 3 ? 128 : 84)) return base;
     return s > base && part_bytes(D, s) > DECODE_STATIC_SCRATCH_BYTES ? base : s;
 }
 size_t decode_ws_bytes(const Dims& D) {

@@ -127,3 +127,36 @@ def test_decode_attention_at_tile_edges(d, G, length):
             bound = 2.0 ** -8 * np.abs(O_ref) + 2.0 ** -20 * max(np.abs(lse_ref).max(), 8.0) * np.abs(Vc[b, h, :length].float().numpy()).max()
             assert np.all(np.abs(O[b, sl] - O_ref) <= bound)
             assert np.all(np.abs(lse[b, sl] - lse_ref) <= 2.0 ** -20 * np.maximum(np.abs(lse_ref), 8.0))
+
+
+# Slices per (batch, KV head): up to 256, four per lane of the merge; few heads and long caches take them all.  fp32: both rules for
+# the number of slices (84 units of four heads and more keep fewer).
+@pytest.mark.parametrize("dtype,B,Hkv,G,d,length,slices", [
+    ("bf16", 1, 1, 1, 128, 128 * 256 + 5, 256), ("bf16", 1, 1, 4, 64, 128 * 200 + 77, 201), ("bf16", 1, 4, 3, 128, 128 * 128 + 1, 128),
+    ("bf16", 1, 2, 2, 64, 128 * 65, 65), ("bf16", 1, 1, 2, 128, 40000, 256), ("f32", 1, 1, 1, 64, 128 * 256 + 5, 256),
+    ("f32", 1, 1, 9, 128, 128 * 190 + 3, 191), ("f32", 1, 2, 2, 128, 128 * 66 + 100, 67), ("f32", 2, 2, 4, 64, 3000, 24),
+    ("f32", 11, 8, 4, 64, 1500, 6), ("f32", 10, 8, 4, 64, 1500, 6), ("f32", 33, 4, 3, 64, 1100, 4), ("f32", 3, 4, 8, 128, 129, 2),
+])
+def test_decode_attention_over_many_slices(dtype, B, Hkv, G, d, length, slices):
+    cap = length + 3
+    g = torch.Generator(device=DEV).manual_seed(length + G)
+    T = {"bf16": torch.bfloat16, "f32": torch.float32}[dtype]
+    # K grows along the cache: the slices' maxima differ, and the last ones do not hold all of the weight
+    Kc = (torch.randn((B, Hkv, cap, d), generator=g, device=DEV) * torch.linspace(0.5, 1.5, cap, device=DEV)[:, None]).to(T)
+    Vc = torch.randn((B, Hkv, cap, d), generator=g, device=DEV).to(T)
+    q = torch.randn((B, Hkv * G, d), generator=g, device=DEV).to(T)
+    p = lrsa.make_params((B, Hkv * G, cap, d), tuple(Kc.shape), (Hkv * G * cap * d, cap * d, d, 1), Kc.stride(), dtype=T, sink=4, lag=16, topk=4)
+    ws = torch.full((lrsa.workspace_bytes(p, lrsa.binding.WS_DECODE_ATTN) // 4,), float("nan"), device=DEV)
+    O, lse = lrsa.lrsa_decode_attn(p, q, Kc, Vc, length, ws=ws)
+    torch.cuda.synchronize()
+    # the records of the slices, as many as the case is meant for, fill the front of the workspace
+    assert int((~ws.isnan()).sum()) == B * Hkv * G * slices * (d + 2)
+    K64, V64 = (t[:, :, :length].double().cpu().numpy() for t in (Kc, Vc))
+    for b in sorted({0, B - 1}):
+        for h in sorted({0, Hkv - 1}):
+            sl = slice(h * G, (h + 1) * G)
+            O_ref, lse_ref = dec.decode_attn(q[b, sl].double().cpu().numpy(), K64[b, h], V64[b, h])
+            # fp32 logits of magnitude up to |lse| (weights off by 2^-20 of that each), and the rounding of a bf16 output
+            bound = 2.0 ** -20 * max(np.abs(lse_ref).max(), 8.0) * np.abs(V64[b, h]).max() + (2.0 ** -8 * np.abs(O_ref) if dtype == "bf16" else 0.0)
+            assert np.all(np.abs(O[b, sl].double().cpu().numpy() - O_ref) <= bound)
+            assert np.all(np.abs(lse[b, sl].cpu().numpy() - lse_ref) <= 2.0 ** -20 * np.maximum(np.abs(lse_ref), 8.0))
