@@ -49,7 +49,8 @@ typedef enum { LRSA_F32 = 0, LRSA_BF16 = 1 } lrsa_dtype;
 /* Which kernels serve the attention calls. */
 typedef enum {
     LRSA_IMPL_AUTO = 0,    /* bf16: MFMA kernels (head_dim 64: with the weights as three bf16 terms, which hold all
-                              24 bits of fp32 weights); fp32: fp32 matrix kernels */
+                              24 bits of fp32 weights); fp32: fp32 matrix kernels; the plain ones beyond their
+                              limits and for some lags below 4 (lrsa_attn_route) */
     LRSA_IMPL_GENERIC = 1, /* force the plain fp32-arithmetic kernels (any supported dtype/head_dim)  */
     LRSA_IMPL_COMPACT = 2  /* MFMA kernels over a physically condensed KV cache: lrsa_attn_fwd and
                               lrsa_attn_bwd first copy the rows of the gather list (sink, survivors) into

@@ -72,9 +72,24 @@ int make_dims(const lrsa_params* p, lrsa::Dims* D) {
     return LRSA_OK;
 }
 
-bool use_mfma(const lrsa_params* p, const lrsa::Dims& D) { return p->impl != LRSA_IMPL_GENERIC && lrsa::mfma_supported(D) && lrsa::mfma_grids_fit(D); }
+// Lags of two and three rows at head_dim 64: a tile of query rows ends with its chunk and is nearly empty, and the plain kernels (a
+// wave per row) are the faster ones as long as there are few visible pairs or few keys per row.  Forward + backward, plain and
+// tiled: bf16, lag 2, one head of 512 rows 52 and 90 us, of 1024 rows 83 and 160 us, 16 heads of 768 rows 400 and 355 us; 512 heads of 128
+// rows 758 and 963 us, of 512 rows 5.3 and 4.6 ms; lag 3, 16 heads of 256 rows 100 and 88 us.  fp32, lag 2, 512 heads of 512 rows 7.1 and
+// 9.7 ms, 16 of 1024 rows 0.89 ms both; lag 3, 512 heads of 384 rows 3.4 and 4.0 ms, 64 of 512 rows 0.74 ms both.
+bool plain_for_short_lag(const lrsa::Dims& D) {
+    if (D.d != 64 || D.L > 3) return false;
+    const double n = D.n, rows = n * D.B * D.Hq;
+    const double keys = (D.K * n / D.L + D.S) / 2 + D.S / 2.0 + D.L * (D.lp + 0.5);      // of a row, about
+    if (D.dtype == LRSA_BF16) return rows * keys <= (D.L == 2 ? 1.2e6 : 2.0e5) || (D.L == 2 && keys < 80);
+    return D.L == 2 ? rows >= 4096 && keys < 200 : rows >= 16384 && keys < 90;
+}
 
-bool use_f32_tiles(const lrsa_params* p, const lrsa::Dims& D) { return p->impl != LRSA_IMPL_GENERIC && lrsa::f32_tiles_supported(D); }
+bool use_mfma(const lrsa_params* p, const lrsa::Dims& D) {
+    return p->impl != LRSA_IMPL_GENERIC && lrsa::mfma_supported(D) && lrsa::mfma_grids_fit(D) && !plain_for_short_lag(D);
+}
+
+bool use_f32_tiles(const lrsa_params* p, const lrsa::Dims& D) { return p->impl != LRSA_IMPL_GENERIC && lrsa::f32_tiles_supported(D) && !plain_for_short_lag(D); }
 // the filling-step calls are built for head_dim 128; their grids are those of a window of rows
 bool fill_supported(const lrsa_params* p, const lrsa::Dims& D) { return p->impl != LRSA_IMPL_GENERIC && lrsa::mfma_supported(D) && D.d == 128; }
 

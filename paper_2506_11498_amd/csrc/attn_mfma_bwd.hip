@@ -91,21 +91,23 @@ static BwdPlan make_plan(const Dims& D, bool split) {
     P.ktiles = P.sink_tiles_k + (D.fq1 - P.kc_lo) * P.tpc_k;
     P.gl_total = D.fq1 > 0 ? gather_count(D, D.fq1 - 1) : 0;
     P.gtiles = (P.gl_total + KV_BK - 1) / KV_BK;
-    // aim at ~8192 query rows (x G heads) per workgroup, but never more than KV_MAX_SLICES slices
-    int64_t qch = (256 * 32) / (int64_t(D.L) * D.G);
+    // aim at ~8192 query rows (x G heads) per workgroup, but never more than KV_MAX_SLICES slices.  head_dim 64: rows as the steps of
+    // KV_ROWS take them, which end with a chunk (512 rows, lag 2, one head: 351 -> 62 us in the backward; all in one slice before)
+    const int64_t rows = D.d == 64 ? (int64_t(D.L) + KV_ROWS - 1) / KV_ROWS * KV_ROWS * D.G : int64_t(D.L) * D.G;   // of a chunk
+    int64_t qch = (256 * 32) / rows;
     if (qch < 1) qch = 1;
     const int min_qch = (nqf + KV_MAX_SLICES - 1) / KV_MAX_SLICES;
     if (qch < min_qch) qch = min_qch;
     if (qch < 1) qch = 1;
     // small problems: shorter slices (down to ~1024 query rows x G heads) until the gather workgroups -- about
     // half of the (tile, slice) grid sees any query -- fill the chip twice
-    while (qch > min_qch && qch > 1 && (qch / 2) * int64_t(D.L) * D.G >= 1024 &&
+    while (qch > min_qch && qch > 1 && (qch / 2) * rows >= 1024 &&
            int64_t(D.B) * D.Hkv * P.gtiles * ((nqf + qch - 1) / qch) / 2 < 512)
         qch /= 2;
     // fewer than a quarter as many as CUs: down to 256 rows.  (2.6K tokens, 4 heads on 2, 2 requests, 24 workgroups: 164 ->
     // 157 us; 2.2K tokens in filling steps, 4 heads on 1: 710 -> 633 us.  From 84 workgroups on it costs more than it gives:
     // 5.5K tokens, 4 heads on 2, 4 requests 264 -> 272 us, 4K tokens, 8 heads on 8, 2 requests, 128 of them, 271 -> 295 us.)
-    while (split && qch > min_qch && qch > 1 && (qch / 2) * int64_t(D.L) * D.G >= 256 &&
+    while (split && qch > min_qch && qch > 1 && (qch / 2) * rows >= 256 &&
            int64_t(D.B) * D.Hkv * P.gtiles * ((nqf + qch - 1) / qch) / 2 < 64)
         qch /= 2;
     P.qch = int(qch);

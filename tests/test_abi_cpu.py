@@ -155,6 +155,11 @@ def test_attention_route_at_the_limits_of_a_launch():
         # bf16: 512 threads for 256 rows of one to four heads
         (dict(dtype=bf, d=64, Hq=128, Hkv=128, n=131072, sink=0, lag=2, topk=1), 0),
         (dict(dtype=bf, d=64, Hq=128, Hkv=128, n=131068, sink=0, lag=1024, topk=16), 2),
+        # lags of two and three rows at head_dim 64: few pairs, or few keys per row
+        (dict(dtype=bf, d=64, Hq=1, Hkv=1, n=1024, sink=4, lag=2, topk=1), 0), (dict(dtype=bf, d=64, Hq=1, Hkv=1, n=1024, sink=4, lag=4, topk=1), 2),
+        (dict(dtype=bf, d=64, Hq=16, Hkv=4, n=4000, sink=4, lag=2, topk=1), 2), (dict(dtype=bf, Hq=1, Hkv=1, n=1024, sink=4, lag=2, topk=1), 2),
+        (dict(dtype=f32, d=64, B=32, Hq=16, Hkv=4, n=512, sink=4, lag=2, topk=1), 0), (dict(dtype=f32, d=64, Hq=1, Hkv=1, n=512, sink=4, lag=2, topk=1), 1),
+        (dict(dtype=f32, d=64, B=32, Hq=16, Hkv=4, n=256, sink=4, lag=3, topk=1), 0), (dict(dtype=f32, d=64, B=32, Hq=16, Hkv=4, n=256, sink=4, lag=4, topk=1), 1),
         (dict(dtype=bf, B=16, Hq=64, Hkv=8, n=1 << 19, sink=64, lag=2048, topk=512), 2),    # large, and in its range
     ]:
         p = _params(**kw)
