@@ -200,6 +200,11 @@ int lrsa_attn_bwd(const lrsa_params *p, const void *Q, const void *K, const void
  * takes the plan without splits, so that a workspace sized for the longest step serves the others.  Built for bf16 with head_dim 128
  * (LRSA_ERR_UNSUPPORTED otherwise); impl LRSA_IMPL_COMPACT is treated as LRSA_IMPL_AUTO. */
 size_t lrsa_fill_workspace_bytes(const lrsa_params *p, int32_t row_begin, int32_t row_end, int which);
+
+/* Parts that a backward call over these rows (0 and n: lrsa_attn_bwd) splits the heads of a group into, given the workspace
+ * asked for above: the work on listed keys (`gather`), on the local window (`window`).  Host arithmetic, for tests and for
+ * reading profiles. */
+int lrsa_attn_bwd_parts(const lrsa_params *p, int32_t row_begin, int32_t row_end, int32_t *gather, int32_t *window);
 int lrsa_attn_fwd_fill(const lrsa_params *p, int32_t row_begin, int32_t row_end, const void *Q, const void *K,
                        const void *V, const int32_t *idx, void *O, float *lse, void *ws, size_t ws_bytes, void *stream);
 int lrsa_attn_bwd_fill(const lrsa_params *p, int32_t row_begin, int32_t row_end, const void *Q, const void *K,

@@ -22,7 +22,7 @@ WS_SCORE, WS_SELECT, WS_ATTN_FWD, WS_ATTN_BWD, WS_DECODE_ATTN = 0, 1, 2, 3, 4
 EXPORTS = ("lrsa_abi_version", "lrsa_last_error", "lrsa_num_scored_chunks", "lrsa_score_route", "lrsa_attn_route", "lrsa_score_poll_limit", "lrsa_workspace_bytes",
            "lrsa_score", "lrsa_select", "lrsa_score_select", "lrsa_check_idx", "lrsa_attn_fwd", "lrsa_attn_bwd",
            "lrsa_cache_compress", "lrsa_cache_compress_ws", "lrsa_cache_compress_ws_bytes", "lrsa_decode_attn", "lrsa_decode_attn_static",
-           "lrsa_fill_workspace_bytes", "lrsa_attn_fwd_fill", "lrsa_attn_bwd_fill", "lrsa_attn_bwd_finish",
+           "lrsa_fill_workspace_bytes", "lrsa_attn_bwd_parts", "lrsa_attn_fwd_fill", "lrsa_attn_bwd_fill", "lrsa_attn_bwd_finish",
            "lrsa_timing_enable", "lrsa_timing_count", "lrsa_timing_read")
 
 
@@ -77,6 +77,7 @@ def lib() -> ctypes.CDLL:
         i32 = ctypes.c_int32
         L.lrsa_fill_workspace_bytes.restype = ctypes.c_size_t
         L.lrsa_fill_workspace_bytes.argtypes = [vp, i32, i32, ctypes.c_int]
+        L.lrsa_attn_bwd_parts.argtypes = [vp, i32, i32, vp, vp]
         L.lrsa_attn_fwd_fill.argtypes = [vp, i32, i32, vp, vp, vp, vp, vp, vp, vp, sz, vp]
         L.lrsa_attn_bwd_fill.argtypes = [vp, i32, i32, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
         L.lrsa_attn_bwd_finish.argtypes = [vp, vp, vp, vp, vp, vp]
@@ -335,6 +336,13 @@ def lrsa_attn_bwd(p: LrsaParams, Q, K, V, O, dO, lse, idx, dQ=None, dK=None, dV=
 
 def fill_workspace_bytes(p: LrsaParams, row_begin: int, row_end: int, which: int) -> int:
     return int(lib().lrsa_fill_workspace_bytes(ctypes.byref(p), int(row_begin), int(row_end), which))
+
+
+def attn_bwd_parts(p: LrsaParams, row_begin: int, row_end: int) -> Tuple[int, int]:
+    """Parts that a backward call over these rows splits the heads of a group into: (listed keys, local window)."""
+    a, b = ctypes.c_int32(0), ctypes.c_int32(0)
+    _check(lib().lrsa_attn_bwd_parts(ctypes.byref(p), int(row_begin), int(row_end), ctypes.byref(a), ctypes.byref(b)))
+    return a.value, b.value
 
 
 def _fill_ws(p, row_begin, row_end, which, device, ws):

@@ -199,16 +199,14 @@ int lrsa_score_select(const lrsa_params* p, const void* K, const void* V, float*
     return hip_result(lrsa::launch_score_select(D, K, V, score, idx, ws, (hipStream_t)stream), "lrsa_score_select");
 }
 
-// Arguments of a compression call: derived dimensions, steps to take and the new counts (host arithmetic)
-static int compress_plan(const lrsa_params* p, int32_t len, int32_t done, lrsa::Dims* D, int* steps) {
-    const int rc = make_dims(p, D);
-    if (rc != LRSA_OK) return rc;
-    if (!lrsa::cache_compress_supported(*D))
+// Checks the counts of a compression call; the steps to take (host arithmetic)
+static int compress_plan(const lrsa::Dims& D, int32_t len, int32_t done, int* steps) {
+    if (!lrsa::cache_compress_supported(D))
         return fail(LRSA_ERR_UNSUPPORTED, "lrsa_cache_compress needs local_prev == 1 and lag <= 4096");
-    if (len < 0 || len > D->n || done < 0) return fail(LRSA_ERR_INVALID_ARG, "lrsa_cache_compress: len %d outside [0, cap=%d] or done < 0", len, D->n);
-    const int64_t tail = (int64_t)len - D->S - (int64_t)D->K * done;
-    if (done > 0 && tail < D->L) return fail(LRSA_ERR_INVALID_ARG, "lrsa_cache_compress: len %d is too short for %d compressed chunks", len, done);
-    *steps = tail >= 2 * (int64_t)D->L ? (int)(tail / D->L) - 1 : 0;
+    if (len < 0 || len > D.n || done < 0) return fail(LRSA_ERR_INVALID_ARG, "lrsa_cache_compress: len %d outside [0, cap=%d] or done < 0", len, D.n);
+    const int64_t tail = (int64_t)len - D.S - (int64_t)D.K * done;
+    if (done > 0 && tail < D.L) return fail(LRSA_ERR_INVALID_ARG, "lrsa_cache_compress: len %d is too short for %d compressed chunks", len, done);
+    *steps = tail >= 2 * (int64_t)D.L ? (int)(tail / D.L) - 1 : 0;
     return LRSA_OK;
 }
 
@@ -224,7 +222,7 @@ static int cache_compress(const lrsa_params* p, void* Kc, void* Vc, int32_t* pos
     int rc = make_dims(p, &D), steps = 0;
     if (rc != LRSA_OK) return rc;
     if (!len_out || !done_out) return fail(LRSA_ERR_INVALID_ARG, "lrsa_cache_compress: len_out and done_out must not be NULL");
-    if ((rc = compress_plan(p, len, done, &D, &steps)) != LRSA_OK) return rc;
+    if ((rc = compress_plan(D, len, done, &steps)) != LRSA_OK) return rc;
     *len_out = len - steps * (D.L - D.K);
     *done_out = done + steps;
     if (steps == 0) return LRSA_OK;
@@ -248,7 +246,7 @@ int lrsa_cache_compress(const lrsa_params* p, void* Kc, void* Vc, int32_t* pos, 
 size_t lrsa_cache_compress_ws_bytes(const lrsa_params* p, int32_t len, int32_t done) {
     lrsa::Dims D;
     int steps = 0;
-    return compress_plan(p, len, done, &D, &steps) == LRSA_OK ? compress_ws_need(D, len, done, steps) : 0;
+    return make_dims(p, &D) == LRSA_OK && compress_plan(D, len, done, &steps) == LRSA_OK ? compress_ws_need(D, len, done, steps) : 0;
 }
 
 int lrsa_cache_compress_ws(const lrsa_params* p, void* Kc, void* Vc, int32_t* pos, int32_t len, int32_t done, int32_t* len_out,
@@ -365,6 +363,18 @@ size_t lrsa_fill_workspace_bytes(const lrsa_params* p, int32_t row_begin, int32_
     if (which == LRSA_WS_ATTN_FWD) return lrsa::attn_fwd_mfma_ws_bytes(D);
     if (which == LRSA_WS_ATTN_BWD) return lrsa::attn_bwd_mfma_ws_bytes(D);
     return 0;
+}
+
+int lrsa_attn_bwd_parts(const lrsa_params* p, int32_t row_begin, int32_t row_end, int32_t* gather, int32_t* window) {
+    lrsa::Dims D;
+    int rc = make_dims(p, &D);
+    if (rc != LRSA_OK) return rc;
+    if (!gather || !window) return fail(LRSA_ERR_INVALID_ARG, "lrsa_attn_bwd_parts: gather and window must not be NULL");
+    if (!(row_begin == 0 && row_end == D.n ? use_mfma(p, D) : fill_supported(p, D)))
+        return fail(LRSA_ERR_UNSUPPORTED, "lrsa_attn_bwd_parts: these params have no bf16 MFMA backward");
+    if ((row_begin != 0 || row_end != D.n) && (rc = set_row_window(&D, row_begin, row_end, "lrsa_attn_bwd_parts")) != LRSA_OK) return rc;
+    lrsa::attn_bwd_mfma_parts(D, gather, window);
+    return LRSA_OK;
 }
 
 int lrsa_attn_fwd_fill(const lrsa_params* p, int32_t row_begin, int32_t row_end, const void* Q, const void* K,

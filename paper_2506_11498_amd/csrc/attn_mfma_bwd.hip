@@ -151,6 +151,11 @@ static BwdPlan plan_for(const Dims& D, size_t ws_bytes) {
     return P.bytes <= ws_bytes ? P : make_plan(D, false);
 }
 size_t attn_bwd_mfma_ws_bytes(const Dims& D) { return make_plan(D, true).bytes; }
+void attn_bwd_mfma_parts(const Dims& D, int32_t* gather, int32_t* window) {
+    const BwdPlan P = make_plan(D, true);
+    *gather = P.hsl;
+    *window = P.wsl;
+}
 size_t attn_bwd_mfma_ws_min_bytes(const Dims& D) {
     const size_t whole = make_plan(D, false).bytes, split = attn_bwd_mfma_ws_bytes(D);
     return whole < split ? whole : split;

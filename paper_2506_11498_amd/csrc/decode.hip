@@ -293,7 +293,6 @@ static hipError_t run_compress_ws(const Dims& D, T* Kc, T* Vc, int32_t* pos, int
 
 hipError_t launch_cache_compress_ws(const Dims& D, void* Kc, void* Vc, int32_t* pos, int len, int done, int steps, void* ws,
                                     hipStream_t st) {
-    if (D.K == D.L) return hipSuccess;     // everything survives where it is
     return D.dtype == 1 ? run_compress_ws(D, (bf16_t*)Kc, (bf16_t*)Vc, pos, len, done, steps, ws, st)
                         : run_compress_ws(D, (float*)Kc, (float*)Vc, pos, len, done, steps, ws, st);
 }

@@ -176,6 +176,20 @@ def test_attention_route_at_the_limits_of_a_launch():
     assert lrsa.fill_workspace_bytes(p, 0, 1024, binding.WS_ATTN_BWD) > 0
 
 
+def test_parts_of_a_backward_call_are_reported():
+    p = _params(n=16 + 40 * 64)
+    assert all(x >= 1 for x in lrsa.attn_bwd_parts(p, 0, p.seq)) and lrsa.attn_bwd_parts(p, 0, 16 + 128)[1] == 2
+    assert lrsa.attn_bwd_parts(_params(Hq=2, Hkv=2), 0, 1000) == (1, 1)        # one head per group
+    for bad, code in (((0, 50), -1), ((5, p.seq), -1), ((64, 64), -1)):
+        with pytest.raises(lrsa.LrsaError) as e:
+            lrsa.attn_bwd_parts(p, *bad)
+        assert e.value.code == code
+    for kw in (dict(dtype=torch.float32), dict(impl=binding.IMPL_GENERIC)):
+        with pytest.raises(lrsa.LrsaError) as e:
+            lrsa.attn_bwd_parts(_params(**kw), 0, 1000)
+        assert e.value.code == -2
+
+
 def test_product_package_does_not_import_the_oracle():
     pkg = os.path.join(ROOT, "paper_2506_11498_amd")
     for dirpath, _, files in os.walk(pkg):

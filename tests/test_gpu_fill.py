@@ -207,3 +207,45 @@ def test_a_workspace_for_the_last_whole_step_serves_every_step():
     with pytest.raises(lrsa.LrsaError, match="workspace"):
         lrsa.lrsa_attn_bwd_fill(pq, *last, xd["Q"][:, :, :w.L], xd["K"], xd["V"], O[:, :, :w.L], xd["dO"][:, :, :w.L], lse[:, :, :w.L].contiguous(),
                                 idx, *acc, None, torch.empty(1 << 16, dtype=torch.uint8, device=DEV))
+
+
+def _steps_and_parts(w, m, **kw):
+    p = lrsa.make_params((w.B, w.Hq, w.n, w.d), (w.B, w.Hkv, w.n, w.d), (w.Hq * w.n * w.d, w.n * w.d, w.d, 1), (w.Hkv * w.n * w.d, w.n * w.d, w.d, 1),
+                         dtype=torch.bfloat16, sink=w.S, lag=w.L, topk=w.K, **kw)
+    return [lrsa.attn_bwd_parts(p, a, b) for a, b in (windows(w, m) if m else [(0, w.n)])]
+
+
+def test_the_shapes_above_split_the_heads():
+    """The filling steps and the one-shot calls that are compared above take the split paths of dK/dV: parts of both kinds of work, even
+    and uneven ones and different numbers in the steps of one call."""
+    seen = {}
+    for cfg in SHAPES:
+        w = inputs.small_workload(dtype="bf16", **{k: v for k, v in cfg.items() if k != "name"})
+        seen[cfg["name"]] = {m: _steps_and_parts(w, m) for m in (0, 1, 2, 3)}
+    assert all(min(g, x) > 1 for by_m in seen.values() for parts in by_m.values() for g, x in parts)
+    assert seen["heads_in_uneven_parts"][0] == [(2, 5)] and seen["group_of_six"][0] == [(2, 3)]     # 5 heads in 2 parts
+    assert {g for g, _ in seen["many_chunks"][2]} == {4, 8} and len(set(seen["gqa"][3])) == 2
+    w = inputs.WORKLOADS["C4"]
+    assert _steps_and_parts(w, 0) == [(1, 1)]                                  # a long call stays whole
+
+
+@pytest.mark.parametrize("cfg", [c for c in SHAPES if c["name"] in ("heads_in_uneven_parts", "group_of_six", "odd_sizes_no_tail_chunk")],
+                         ids=lambda c: c["name"])
+def test_condensed_cache_with_split_heads_equals_gathering(cfg):
+    w = inputs.small_workload(dtype="bf16", **{k: v for k, v in cfg.items() if k != "name"})
+    xd = {k: v.to(DEV) for k, v in inputs.make_inputs(w).items()}
+    res = []
+    for impl in (lrsa.IMPL_AUTO, lrsa.IMPL_COMPACT):
+        assert min(_steps_and_parts(w, 0, impl=impl)[0]) > 1
+        p = lrsa.params_for(xd["Q"], xd["K"], sink=w.S, lag=w.L, topk=w.K, impl=impl)
+        _, idx = lrsa.lrsa_score_select(p, xd["K"], xd["V"])
+        O, lse = lrsa.lrsa_attn_fwd(p, xd["Q"], xd["K"], xd["V"], idx)
+        lrsa.timing_enable(True)
+        grads = lrsa.lrsa_attn_bwd(p, xd["Q"], xd["K"], xd["V"], O, xd["dO"], lse, idx)
+        torch.cuda.synchronize()
+        names = {n for n, _ in lrsa.timing_records()}
+        lrsa.timing_enable(False)
+        assert ("k_bwd_scatter_dkv" in names) == (impl == lrsa.IMPL_COMPACT)
+        res.append((O, lse, *grads))
+    for a, b in zip(*res):
+        assert torch.equal(a, b)
