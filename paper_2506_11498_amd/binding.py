@@ -261,19 +261,19 @@ def lrsa_cache_compress(p: LrsaParams, Kc: torch.Tensor, Vc: torch.Tensor, pos: 
     Kc, Vc: [B, Hkv, cap, d] with cap = p.seq; pos: int32 [B, Hkv, cap] or None.  Returns (length, done).
     ws: cache_compress_ws_bytes() bytes.  Without one, a workspace is allocated for the call; under graph capture (where nothing
     would hold it until the replays) and where there is no memory for it, the same steps run one by one without."""
-    new_len, new_done = ctypes.c_int32(0), ctypes.c_int32(0)
-    counts = (int(length), int(done), ctypes.byref(new_len), ctypes.byref(new_done))
-    need = cache_compress_ws_bytes(p, length, done) if Kc is not None else 0
+    L, pp, new_len, new_done = lib(), ctypes.byref(p), ctypes.c_int32(0), ctypes.c_int32(0)
+    length, done = int(length), int(done)
+    need = L.lrsa_cache_compress_ws_bytes(pp, length, done) if Kc is not None else 0
     if need and ws is None and not torch.cuda.is_current_stream_capturing():
         try:
             ws = torch.empty(need, dtype=torch.uint8, device=Kc.device)
         except torch.OutOfMemoryError:
             pass
+    args = (pp, _ptr(Kc), _ptr(Vc), _ptr(pos), length, done, ctypes.byref(new_len), ctypes.byref(new_done))
     if need and ws is None:
-        _check(lib().lrsa_cache_compress(ctypes.byref(p), _ptr(Kc), _ptr(Vc), _ptr(pos), *counts, _stream()))
+        _check(L.lrsa_cache_compress(*args, _stream()))
     else:
-        nb = 0 if ws is None else ws.numel() * ws.element_size()
-        _check(lib().lrsa_cache_compress_ws(ctypes.byref(p), _ptr(Kc), _ptr(Vc), _ptr(pos), *counts, _ptr(ws), nb, _stream()))
+        _check(L.lrsa_cache_compress_ws(*args, _ptr(ws), 0 if ws is None else ws.numel() * ws.element_size(), _stream()))
     return new_len.value, new_done.value
 
 

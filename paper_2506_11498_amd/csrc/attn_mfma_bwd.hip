@@ -603,14 +603,15 @@ __device__ __forceinline__ void clear_odd_rows(unsigned char* sQ, unsigned char*
     static_assert(KV_ROWS == 64, "a lane looks at a row");
     const float l = sLD[lane];
     unsigned long long rows = __builtin_amdgcn_ballot_w64(l != l);
-    while (rows) {
+    if (rows == 0) return;
+    for (; rows; rows &= rows - 1) {
         const int r = __builtin_ctzll(rows);
-        rows &= rows - 1;
         if (lane * 16 < ROW_BYTES<DH>) {
             *reinterpret_cast<uint4*>(sQ + r * ROW_BYTES<DH> + lane * 16) = uint4{0u, 0u, 0u, 0u};
             *reinterpret_cast<uint4*>(sG + r * ROW_BYTES<DH> + lane * 16) = uint4{0u, 0u, 0u, 0u};
         }
     }
+    asm volatile("" ::: "memory");   // the tiles are read through integer addresses
 }
 
 // Two stages of 64 rows: one barrier per 64 MFMAs of a wave; the copies of the next stage run during
