@@ -213,6 +213,7 @@ static int compress_plan(const lrsa::Dims& D, int32_t len, int32_t done, int* st
 static size_t compress_ws_need(const lrsa::Dims& D, int32_t len, int32_t done, int steps) {
     // nothing moves; beyond the launch grid or 32-bit row pieces: step by step
     if (steps == 0 || D.K == D.L || steps > 65535 || int64_t(len) * 32 > INT32_MAX) return 0;
+    if (steps == 1 && !lrsa::cache_step_is_long(D)) return 0;
     return lrsa::cache_compress_ws_bytes(D, len, done, steps);
 }
 

@@ -54,6 +54,7 @@ bool cache_compress_supported(const Dims&);
 hipError_t launch_cache_compress(const Dims&, void* Kc, void* Vc, int32_t* pos, int len, int done, int steps, hipStream_t st);
 // the same with a workspace: all steps at once over many workgroups
 size_t cache_compress_ws_bytes(const Dims&, int len, int done, int steps);
+bool cache_step_is_long(const Dims&);   // a single step is the faster one with a workspace
 hipError_t launch_cache_compress_ws(const Dims&, void* Kc, void* Vc, int32_t* pos, int len, int done, int steps, void* ws,
                                     hipStream_t st);
 size_t cache_sigma_ws_floats(const Dims&);

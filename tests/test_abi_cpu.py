@@ -176,6 +176,19 @@ def test_attention_route_at_the_limits_of_a_launch():
     assert lrsa.fill_workspace_bytes(p, 0, 1024, binding.WS_ATTN_BWD) > 0
 
 
+def test_one_compression_step_takes_a_workspace_only_where_it_gains():
+    """Short chunks and many heads go through the kernel of one workgroup per head, which needs none; several steps never do."""
+    def need(B, Hkv, L, steps=1, **kw):
+        n = 16 + (steps + 1) * L
+        return lrsa.cache_compress_ws_bytes(_params(B=B, Hq=Hkv, Hkv=Hkv, n=n, sink=16, lag=L, topk=8, **kw), n, 0)
+    f32 = dict(dtype=torch.float32)
+    assert need(4, 8, 72) == 0 and need(4, 8, 255) == 0 and need(4, 8, 256) > 0
+    assert need(4, 9, 1023) == 0 and need(4, 9, 1024) > 0 and need(13, 5, 4096) == 0
+    assert need(2, 8, 255, **f32) == 0 and need(2, 8, 256, **f32) > 0 and need(1, 17, 511, **f32) == 0 and need(1, 17, 512, **f32) > 0
+    assert need(4, 8, 511, d=64) == 0 and need(4, 8, 512, d=64) > 0
+    assert min(need(4, 8, 72, steps=2), need(13, 5, 16, steps=2), need(1, 1, 16, steps=2, **f32)) > 0
+
+
 def test_parts_of_a_backward_call_are_reported():
     p = _params(n=16 + 40 * 64)
     assert all(x >= 1 for x in lrsa.attn_bwd_parts(p, 0, p.seq)) and lrsa.attn_bwd_parts(p, 0, 16 + 128)[1] == 2

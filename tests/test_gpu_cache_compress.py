@@ -64,6 +64,40 @@ def test_all_steps_at_once_equal_the_steps_one_by_one(B, Hkv, d, L, K, S, done, 
             assert torch.equal(got[:, :, length:], ref[:, :, length:])
 
 
+# one step on both sides of the line that its route is chosen by: chunks of 64 KB (32 heads of K, bf16), 256 KB (64 heads), 128
+# KB per 256 workgroups (fp32), never more than 64 heads; ragged lags, a rest longer and shorter than the shift
+@pytest.mark.parametrize("B,Hkv,d,L,K,S,done,rest,dtype,long", [
+    (2, 16, 128, 256, 100, 5, 1, 255, "bf16", True),
+    (2, 16, 128, 255, 100, 5, 1, 3, "bf16", False),
+    (3, 1, 64, 513, 512, 0, 2, 511, "bf16", True),
+    (11, 3, 128, 1023, 17, 3, 0, 0, "bf16", False),
+    (11, 3, 128, 1024, 17, 3, 0, 9, "bf16", True),
+    (5, 13, 64, 2048, 1000, 1, 0, 1, "bf16", False),
+    (1, 1, 128, 4096, 4095, 64, 1, 4000, "bf16", True),
+    (2, 8, 128, 257, 1, 7, 3, 250, "f32", True),
+    (2, 8, 128, 255, 1, 7, 3, 250, "f32", False),
+    (1, 17, 128, 511, 200, 0, 0, 33, "f32", False),
+    (1, 17, 128, 515, 200, 0, 0, 33, "f32", True),
+    (1, 3, 64, 600, 599, 2, 1, 0, "f32", True),
+])
+def test_one_step_by_either_route(B, Hkv, d, L, K, S, done, rest, dtype, long):
+    dt = {"bf16": torch.bfloat16, "f32": torch.float32}[dtype]
+    length = S + K * done + 2 * L + rest
+    cap = length + 3
+    g = torch.Generator(device=DEV).manual_seed(L * 5 + K)
+    Kc, Vc = (torch.randn((B, cap, Hkv, d), generator=g, device=DEV).to(dt).permute(0, 2, 1, 3) for _ in range(2))
+    P = torch.arange(B * Hkv * cap, dtype=torch.int32, device=DEV).reshape(B, Hkv, cap)
+    p = lrsa.make_params((B, Hkv, cap, d), (B, Hkv, cap, d), Kc.stride(), Kc.stride(), dtype=dt, sink=S, lag=L, topk=K)
+    assert (lrsa.cache_compress_ws_bytes(p, length, done) > 0) == long
+    want = [t.clone(memory_format=torch.preserve_format) for t in (Kc, Vc, P)]
+    counts = _without_ws(p, *want, length, done)
+    assert lrsa.lrsa_cache_compress(p, Kc, Vc, P, length, done) == counts == (length - (L - K), done + 1)
+    torch.cuda.synchronize()
+    for got, ref in zip((Kc, Vc, P), want):
+        assert torch.equal(got[:, :, :counts[0]], ref[:, :, :counts[0]])
+        assert torch.equal(got[:, :, length:], ref[:, :, length:])
+
+
 def test_a_whole_prompt_equals_the_token_by_token_procedure():
     B, Hkv, d, L, K, S, n = 1, 2, 128, 64, 16, 8, 8 + 9 * 64 + 30
     g = torch.Generator().manual_seed(3)
