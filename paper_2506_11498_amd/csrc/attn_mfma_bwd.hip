@@ -53,10 +53,14 @@ __host__ __device__ __forceinline__ int first_chunk_seeing(const Dims& D, int j0
     return j0 < D.S ? 0 : (j0 - D.S) / D.K + D.lp + 1;
 }
 
+// (head, query) rows that a CU's workgroup walks per us, as measured
+static double rows_per_us(const Dims& D) { return D.d == 64 ? 24.0 : 16.0; }
+
 // Parts that the heads of a group are split into, for launches in which a workgroup is long beside what every CU has to do:
 // half of the longest workgroup is idle time at the end of the launch, and every part writes fp32 partials that the
 // reduction reads again.  The number of parts with the smallest sum of the two, if it saves a fifth.  `rows`: (head, query)
-// rows of a workgroup with one part, `bytes`: partials of one part, `bytes_one`: partials where there is only one part.
+// rows of a workgroup with one part, `bytes`: partials of one part, `bytes_one`: partials where there is only one part; the us
+// that it expects to save are added to `saved`.
 // Rates as measured: 16 (head_dim 64: 24) rows per us and CU; 1 TB/s for partials (each CU stores 32 bytes of a row at a time).
 // The filling steps live from it: their windows of a few chunks leave about as many workgroups as CUs, of which the WINDOW
 // ones (whole chunks, all heads) were twice as long as the others and came last.  32K tokens, 12 heads on 2, lag 1024, four
@@ -64,14 +68,16 @@ __host__ __device__ __forceinline__ int first_chunk_seeing(const Dims& D, int j0
 // 1.94 -> 1.16 ms.  Training steps of 2.6K tokens in one call 206 -> 155 us (with the finer slices
 // of make_plan); long sequences keep one part.  With partials at 4.4 TB/s and a tenth instead of a fifth it splits too often:
 // 3.5K tokens, 16 heads on 4, 4 requests 505 -> 535 us, now as before.
-static int head_parts(const Dims& D, double rows, double bytes, double bytes_one) {
-    const double rate = D.d == 64 ? 24.0 : 16.0;   // query rows per us and CU
+static int head_parts(const Dims& D, double rows, double bytes, double bytes_one, double* saved) {
+    const double rate = rows_per_us(D);
     int best = 1;
-    double t_best = 0.5 * rows / rate + bytes_one / 1.0e6;
+    const double t_one = 0.5 * rows / rate + bytes_one / 1.0e6;
+    double t_best = t_one;
     for (int k = 2; k <= D.G; ++k) {
         const double t = 0.5 * rows * ((D.G + k - 1) / k) / D.G / rate + k * bytes / 1.0e6;
         if (t < 0.8 * t_best) { best = k; t_best = t; }
     }
+    *saved += t_one - t_best;
     return best;
 }
 
@@ -128,8 +134,17 @@ static BwdPlan make_plan(const Dims& D, bool split) {
         const double per_cu = units * (visible * D.L * D.G + 0.75 * w_rows * P.ktiles) / 256.0;
         const double row = 2.0 * units * D.d * 4;   // bytes of a row of dK and dV partials of all heads
         // a workgroup shorter than a quarter of a CU's work is no tail worth partials
-        if (per_cu < 4.0 * w_rows) P.wsl = head_parts(D, w_rows, row * (P.whi - P.wlo), 0.0);
-        if (per_cu < 4.0 * g_rows) P.hsl = head_parts(D, g_rows, 0.5 * row * P.nsl * P.gl_total, 0.5 * row * P.nsl * P.gl_total);
+        double saved = 0.0;
+        if (per_cu < 4.0 * w_rows) P.wsl = head_parts(D, w_rows, row * (P.whi - P.wlo), 0.0, &saved);
+        if (per_cu < 4.0 * g_rows) P.hsl = head_parts(D, g_rows, 0.5 * row * P.nsl * P.gl_total, 0.5 * row * P.nsl * P.gl_total, &saved);
+        // Parts of one kind are worth nothing while the other kind's workgroups are as long, and parts of one kind alone are
+        // more workgroups and partials for what the shorter ones of the other kind partly hide: they have to save a quarter
+        // of a CU's work.  Of 250 training shapes of 1K to 10K tokens 24 were slower split than whole, 24 heads on 8, 2
+        // requests of 2.5K tokens 228 -> 260 us; with this rule 6, by 6 percent at most.  A gain of less than a tenth goes with
+        // them (a threshold of a fifth keeps more of it and the 260 us).
+        const double one = w_rows > g_rows ? w_rows : g_rows, wp = w_rows * ((D.G + P.wsl - 1) / P.wsl) / D.G,
+                     gp = g_rows * ((D.G + P.hsl - 1) / P.hsl) / D.G;
+        if ((wp > gp ? wp : gp) > 0.95 * one || ((P.wsl == 1 || P.hsl == 1) && saved < 0.25 * per_cu / rows_per_us(D))) P.wsl = P.hsl = 1;
     }
     P.window_first = w_rows * ((D.G + P.wsl - 1) / P.wsl) > g_rows * ((D.G + P.hsl - 1) / P.hsl);
     P.gather_wgs = int(gather_workgroups(D, P));

@@ -176,6 +176,19 @@ def test_attention_route_at_the_limits_of_a_launch():
     assert lrsa.fill_workspace_bytes(p, 0, 1024, binding.WS_ATTN_BWD) > 0
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,n,L,K,S,whole", [
+    (2, 24, 8, 2489, 207, 25, 33, True),       # WINDOW workgroups stay as long as before beside split GATHER ones: 228 -> 260 us split
+    (2, 16, 2, 2291, 97, 16, 64, True),        # GATHER alone, for less than a quarter of a CU's work: 235 -> 251 us split
+    (1, 12, 2, 2560, 128, 32, 16, False),      # both kinds
+    (1, 10, 2, 16 + 9 * 128 + 50, 128, 32, 16, False),
+    (1, 12, 2, 32768, 1024, 256, 64, True),    # enough workgroups
+])
+def test_heads_are_split_only_where_the_longest_workgroup_gets_shorter(B, Hq, Hkv, n, L, K, S, whole):
+    p = _params(B=B, Hq=Hq, Hkv=Hkv, n=n, sink=S, lag=L, topk=K)
+    parts = lrsa.attn_bwd_parts(p, 0, n)
+    assert (parts == (1, 1)) == whole, parts
+
+
 def test_one_compression_step_takes_a_workspace_only_where_it_gains():
     """Short chunks and many heads go through the kernel of one workgroup per head, which needs none; several steps never do."""
     def need(B, Hkv, L, steps=1, **kw):
