@@ -236,7 +236,8 @@ int lrsa_cache_compress(const lrsa_params *p, void *Kc, void *Vc, int32_t *pos, 
 
 /* lrsa_cache_compress with a device workspace: the same rows end up in the same places, but all steps of the call
  * run at once and over many workgroups (without a workspace: one workgroup per (batch, KV head), step after step).
- *   ws : lrsa_cache_compress_ws_bytes(p, len, done) bytes, 256-byte aligned; may be NULL when that is 0 */
+ *   ws : lrsa_cache_compress_ws_bytes(p, len, done) bytes, 256-byte aligned; may be NULL when that is 0 (nothing moves, or a
+ *        single step of short chunks or many heads, which one workgroup per head does faster: it runs as without one) */
 size_t lrsa_cache_compress_ws_bytes(const lrsa_params *p, int32_t len, int32_t done);
 int lrsa_cache_compress_ws(const lrsa_params *p, void *Kc, void *Vc, int32_t *pos, int32_t len, int32_t done,
                            int32_t *len_out, int32_t *done_out, void *ws, size_t ws_bytes, void *stream);

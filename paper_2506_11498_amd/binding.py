@@ -251,7 +251,7 @@ def lrsa_score_select(p: LrsaParams, K: torch.Tensor, V: torch.Tensor, score: Op
 
 
 def cache_compress_ws_bytes(p: LrsaParams, length: int, done: int) -> int:
-    """Workspace of lrsa_cache_compress for these counts; 0 where it has nothing to move."""
+    """Workspace of lrsa_cache_compress for these counts; 0 where nothing moves or a single step is the faster one without."""
     return int(lib().lrsa_cache_compress_ws_bytes(ctypes.byref(p), int(length), int(done)))
 
 

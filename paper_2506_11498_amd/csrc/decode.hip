@@ -264,7 +264,7 @@ static CompressWs compress_ws(const Dims& D, int len, int done, int steps) {
     W.bytes = W.words + align256(heads * bounced * 4);
     return W;
 }
-// A single step gains from the CUs that k_cache_compress leaves idle, and loses three launches against one and a softmax and
+// A single step with a workspace gains from the CUs that k_cache_compress leaves idle, and loses three launches against one and a softmax and
 // selection in every workgroup of k_cache_select_move: with the bytes of a chunk it gains, with the heads it loses.  Measured
 // with the allocation, call by call to its end, k_cache_compress -> three launches, us: bf16, d 128, 32 heads of K: lag 128
 // 28.4 -> 29.8, lag 256 (64 KB) 32.5 -> 31.3; 64 heads: lag 512 45 -> 49, lag 1024 (256 KB) 70 -> 64; 128 heads (device
