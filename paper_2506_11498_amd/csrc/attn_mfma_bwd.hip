@@ -113,6 +113,7 @@ static BwdPlan make_plan(const Dims& D, bool split) {
     // fewer than a quarter as many as CUs: down to 256 rows.  (2.6K tokens, 4 heads on 2, 2 requests, 24 workgroups: 164 ->
     // 157 us; 2.2K tokens in filling steps, 4 heads on 1: 710 -> 633 us.  From 84 workgroups on it costs more than it gives:
     // 5.5K tokens, 4 heads on 2, 4 requests 264 -> 272 us, 4K tokens, 8 heads on 8, 2 requests, 128 of them, 271 -> 295 us.)
+    const int64_t coarse = qch;
     while (split && qch > min_qch && qch > 1 && (qch / 2) * rows >= 256 &&
            int64_t(D.B) * D.Hkv * P.gtiles * ((nqf + qch - 1) / qch) / 2 < 64)
         qch /= 2;
@@ -137,14 +138,15 @@ static BwdPlan make_plan(const Dims& D, bool split) {
         double saved = 0.0;
         if (per_cu < 4.0 * w_rows) P.wsl = head_parts(D, w_rows, row * (P.whi - P.wlo), 0.0, &saved);
         if (per_cu < 4.0 * g_rows) P.hsl = head_parts(D, g_rows, 0.5 * row * P.nsl * P.gl_total, 0.5 * row * P.nsl * P.gl_total, &saved);
-        // Parts of one kind are worth nothing while the other kind's workgroups are as long, and parts of one kind alone are
-        // more workgroups and partials for what the shorter ones of the other kind partly hide: they have to save a quarter
-        // of a CU's work.  Of 250 training shapes of 1K to 10K tokens 24 were slower split than whole, 24 heads on 8, 2
-        // requests of 2.5K tokens 228 -> 260 us; with this rule 6, by 6 percent at most.  A gain of less than a tenth goes with
-        // them (a threshold of a fifth keeps more of it and the 260 us).
+        // In short launches (under 150 us of work for a CU) parts of one kind are worth nothing while the other kind's workgroups
+        // are as long, and parts of one kind alone have to save a quarter of a CU's work.  Of 250 training shapes of 2K to 12K
+        // tokens 19 were more than 1.2 percent slower split than whole, by up to 14 (24 heads on 8, 2 requests of 2.5K tokens: 228 ->
+        // 260 us); with this rule 12, by up to 6.  Gains of up to 9 percent go with them.  In longer launches it would take as much
+        // as it gives (8 heads on 2, 37K tokens, lag 1547: training step 3.28 -> 3.50 ms; 4 on 1, 18K tokens: backward 575 -> 524), and where
+        // the slices are the finer ones idle CUs take the parts (8 on 2, 2.1K tokens: 82 -> 94 us without).
         const double one = w_rows > g_rows ? w_rows : g_rows, wp = w_rows * ((D.G + P.wsl - 1) / P.wsl) / D.G,
-                     gp = g_rows * ((D.G + P.hsl - 1) / P.hsl) / D.G;
-        if ((wp > gp ? wp : gp) > 0.95 * one || ((P.wsl == 1 || P.hsl == 1) && saved < 0.25 * per_cu / rows_per_us(D))) P.wsl = P.hsl = 1;
+                     gp = g_rows * ((D.G + P.hsl - 1) / P.hsl) / D.G, work = per_cu / rows_per_us(D);
+        if (qch == coarse && work < 150.0 && ((wp > gp ? wp : gp) > 0.95 * one || ((P.wsl == 1 || P.hsl == 1) && saved < 0.25 * work))) P.wsl = P.hsl = 1;
     }
     P.window_first = w_rows * ((D.G + P.wsl - 1) / P.wsl) > g_rows * ((D.G + P.hsl - 1) / P.hsl);
     P.gather_wgs = int(gather_workgroups(D, P));
