@@ -54,7 +54,7 @@ def _check_scalar_loads(src: str) -> None:
         raise RuntimeError(f"hipcc -S failed on {src}")
     ins = [(i, t.strip()) for i, t in enumerate(open(asm).read().split("\n")) if t.strip() and not t.strip().startswith(";")]
     for k, (i, t) in enumerate(ins):
-        m = re.match(r"s_load_dword (s\d+),", t)
+        m = re.match(r"s_load_dword (s\d+), s\[\d+:\d+\], s\d+", t)
         if not m:
             continue
         dest = m.group(1)

@@ -3,7 +3,7 @@
 // D = rowsum(dO * O), dS = A * (dA - D), dQ = scale dS K, dK = scale dS^T Q.
 //
 // Deterministic, no atomics.  Three launches on one stream:
-//   k_bwd_dq          query-outer: a workgroup owns 256 (head, query) rows of one KV group and walks their
+//   k_bwd_dq          query-outer: a workgroup owns eight (or four) pieces of 32 query rows of one KV group and walks their
 //                     key stream exactly like the forward (gather list, then the local window), recomputing A;
 //                     it also leaves D[b,hq,t] = dO[t] . O[t] and lse in the units of the logits (mfma_tiles.h) in the workspace
 //   k_bwd_dkv         key-outer, two kinds of workgroups in one launch.  GATHER: 256 consecutive entries of one
@@ -24,8 +24,6 @@ constexpr int KV_WAVES = 8;              // waves per workgroup of the key-outer
 constexpr int KV_THREADS = 64 * KV_WAVES;
 constexpr int DQ_BN = 64;
 constexpr int DQ_PF = 4;                 // LDS operands of the query-outer kernel are read this many MFMAs ahead
-constexpr int DQ_WAVES = 8;              // waves per workgroup of the query-outer kernel (two per SIMD)
-constexpr int DQ_THREADS = 64 * DQ_WAVES;
 constexpr int KV_NB = 1;                        // 32-key blocks per wave (2 needs one wave per SIMD: measured slower)
 constexpr int KV_BK = 32 * KV_NB * KV_WAVES;   // keys per workgroup
 constexpr int KV_BQ = 32;   // query rows per MFMA sub-step
@@ -180,9 +178,10 @@ size_t attn_bwd_mfma_ws_min_bytes(const Dims& D) {
 
 // the grids of the forward, dQ and dK/dV launches (the reduction's threads are fewer than the bytes of its partials)
 bool mfma_grids_fit(const Dims& D) {
-    const QTileMap M = make_qtile_map(D, heads_per_wg(D), DQ_WAVES);
+    const int waves = qtile_waves(D);
+    const QTileMap M = make_qtile_map(D, waves);
     const BwdPlan P = make_plan(D, true);
-    return grid_fits(int64_t(D.B) * D.Hkv * (M.tix_hi - M.tix_lo) * M.gsubs, DQ_THREADS) &&
+    return grid_fits(int64_t(D.B) * D.Hkv * M.per_unit, 64 * waves) &&
            grid_fits(gather_workgroups(D, P) + window_workgroups(D, P), KV_THREADS);
 }
 
@@ -320,10 +319,13 @@ __device__ __forceinline__ void dq_tile_full(const unsigned char* sK, const unsi
 #undef LRSA_DQ_OPND
 }
 
-// GH query heads of one KV group share the workgroup (8 waves = GH heads x 256/GH queries), as in the forward.
+// A wave per piece of 32 query rows of one head, eight or four neighbouring pieces per workgroup, as in the forward (mfma_tiles.h, QTileMap).
+// The first tile is asked for before the wave's own rows, and its copies take 32-bit offsets from a scalar base (in 64 bits the
+// addresses took 15 registers more, and the variant of four waves spilled; whole backward of 32K tokens, 32 heads on 8,
+// 9.55 -> 9.40 ms).
 // COMPACT: the rows of the gather list come from the condensed cache Kc, Vc (contiguous), no index is read.
-template <int DH, int GH, bool COMPACT>
-__global__ __launch_bounds__(DQ_THREADS, 2) void k_bwd_dq(Dims D, const bf16_t* __restrict__ Q,
+template <int DH, int WAVES, bool COMPACT>
+__global__ __launch_bounds__(64 * WAVES, 2) void k_bwd_dq(Dims D, const bf16_t* __restrict__ Q,
                                                            const bf16_t* __restrict__ K,
                                                            const bf16_t* __restrict__ V,
                                                            const bf16_t* __restrict__ O,
@@ -334,8 +336,6 @@ __global__ __launch_bounds__(DQ_THREADS, 2) void k_bwd_dq(Dims D, const bf16_t* 
                                                            const bf16_t* __restrict__ Kc,
                                                            const bf16_t* __restrict__ Vc,
                                                            bf16_t* __restrict__ dQ, QTileMap M) {
-    constexpr int WPH = DQ_WAVES / GH;   // waves per head
-    constexpr int QT = 32 * WPH;         // queries per head and workgroup
     __shared__ __attribute__((aligned(16))) unsigned char sK0[DQ_BN * ROW_BYTES<DH>];
     __shared__ __attribute__((aligned(16))) unsigned char sV0[DQ_BN * ROW_BYTES<DH>];
     __shared__ __attribute__((aligned(16))) unsigned char sK1[DQ_BN * ROW_BYTES<DH>];
@@ -343,23 +343,10 @@ __global__ __launch_bounds__(DQ_THREADS, 2) void k_bwd_dq(Dims D, const bf16_t* 
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, g = lane >> 5;
-    int b, h, gsub, tix;
-    decode_qtile(M, D, blockIdx.x, b, h, gsub, tix);
-    const int hq = h * D.G + gsub * GH + wave / WPH;
-    const int wq = wave % WPH;
-
-    int qc, t0, seg_end;
-    if (tix < M.sink_tiles) {
-        qc = -1; t0 = tix * QT; seg_end = D.S < D.n ? D.S : D.n;
-    } else {
-        const int tt = tix - M.sink_tiles;
-        qc = tt / M.tpc;
-        t0 = D.S + qc * D.L + (tt % M.tpc) * QT;
-        const int64_t e = int64_t(D.S) + int64_t(qc + 1) * D.L;
-        seg_end = e < D.n ? int(e) : D.n;
-    }
-    if (t0 >= seg_end) return;
-    const int t_last = min(t0 + QT, seg_end) - 1;
+    int b, h, tix, qc, seg_end, tw, head, t_last;
+    if (!decode_qtile(M, D, blockIdx.x, b, h, tix) || !qtile_rows(M, D, tix, WAVES, wave, qc, seg_end, tw, head, t_last)) return;   // uniform for the workgroup
+    if constexpr (DH == 128) asm volatile("" : "+v"(tw));   // else the walk's branches become scalar, and zeros are kept in registers for them
+    const int hq = h * D.G + head;
     const int ng = gather_count(D, qc), cs = window_start(D, qc);
     const int m_max = ng + t_last - cs + 1;
     const int ntiles = (m_max + DQ_BN - 1) / DQ_BN;
@@ -368,8 +355,44 @@ __global__ __launch_bounds__(DQ_THREADS, 2) void k_bwd_dq(Dims D, const bf16_t* 
     const bf16_t* Vh = V + b * D.ks[0] + h * D.ks[1];
     const int32_t* idx_h = idx + (int64_t(b) * D.Hkv + h) * D.Ns * D.K;
 
-    const int tq = t0 + wq * 32 + l32;
-    const int tq_ld = tq < t_last ? tq : t_last;
+    const int64_t coff = COMPACT ? (int64_t(b) * D.Hkv + h) * (int64_t(D.S) + int64_t(D.K) * D.Ns) * 128 : 0;
+    const bf16_t* Kc_h = Kc + coff;
+    const bf16_t* Vc_h = Vc + coff;
+    constexpr int RPW = DQ_BN / WAVES, COPIES = RPW / COPY_ROWS<DH>;   // of K (and V) per wave and tile
+    int pos[COPIES];   // COMPACT: stream entries; else positions (fetched through idx one tile ahead)
+    auto fetch_pos = [&](int tile) {
+#pragma unroll
+        for (int i = 0; i < COPIES; ++i) {
+            int j = tile * DQ_BN + async_row<DH>(RPW * wave + COPY_ROWS<DH> * i, lane);
+            j = j < m_max ? j : m_max - 1;
+            pos[i] = COMPACT ? j : stream_pos(D, idx_h, j, ng, cs);
+        }
+    };
+    const int wv = __builtin_amdgcn_readfirstlane(wave);   // wave-uniform: LDS destinations are scalars
+    auto issue = [&](unsigned char* sK, unsigned char* sV) {
+#pragma unroll
+        for (int i = 0; i < COPIES; ++i) {
+            const int r0 = RPW * wv + COPY_ROWS<DH> * i;
+            const int ch = async_chunk<DH>(async_row<DH>(r0, lane), lane) * 8;
+            if (COMPACT) {
+                async_rows<DH>(stream_row(Kc_h, Kh, D.ks[2], pos[i], ng, cs) + ch, sK, r0);
+                async_rows<DH>(stream_row(Vc_h, Vh, D.ks[2], pos[i], ng, cs) + ch, sV, r0);
+            } else {
+                // byte offset inside the head: below 2^31 (a condition of this kernel, checked on the host)
+                const unsigned off = (unsigned(pos[i]) * unsigned(D.ks[2]) + unsigned(ch)) * 2u;
+                async_copy16_so(Kh, off, lds_addr(sK) + r0 * ROW_BYTES<DH>);
+                async_copy16_so(Vh, off, lds_addr(sV) + r0 * ROW_BYTES<DH>);
+            }
+        }
+    };
+
+    // the first tile is on its way while the wave's own rows are read
+    fetch_pos(0);
+    issue(sK0, sV0);
+    if (ntiles > 1) fetch_pos(1);
+
+    const int tq = tw + l32;
+    const int tq_ld = tq < seg_end ? tq : seg_end - 1;
     const int64_t qoff = b * D.qs[0] + hq * D.qs[1] + int64_t(tq_ld) * D.qs[2];
     bf16x8 qf[KK<DH>], gf[KK<DH>];
 #pragma unroll
@@ -400,42 +423,13 @@ __global__ __launch_bounds__(DQ_THREADS, 2) void k_bwd_dq(Dims D, const bf16_t* 
         z += __shfl_xor(z, 32, 64);
         odd = z != 0.0f;
     }
-    if (tq <= t_last && g == 0) { Dsum[rowid] = odd ? 0.0f : -Dq; lse2_out[rowid] = odd ? NAN : lse2; }   // -D: the key-outer kernel starts its dA sums from it
+    if (tq < seg_end && g == 0) { Dsum[rowid] = odd ? 0.0f : -Dq; lse2_out[rowid] = odd ? NAN : lse2; }   // -D: the key-outer kernel starts its dA sums from it
     const int lim = ng + tq - cs;
-    const int wave_lim_max = ng + min(t0 + wq * 32 + 31, t_last) - cs;
-
-    const int64_t coff = COMPACT ? (int64_t(b) * D.Hkv + h) * (int64_t(D.S) + int64_t(D.K) * D.Ns) * 128 : 0;
-    const bf16_t* Kc_h = Kc + coff;
-    const bf16_t* Vc_h = Vc + coff;
-    constexpr int COPIES = 8 / COPY_ROWS<DH>;   // of K (and V) per wave and tile
-    int pos[COPIES];   // COMPACT: stream entries; else positions (fetched through idx one tile ahead)
-    auto fetch_pos = [&](int tile) {
-#pragma unroll
-        for (int i = 0; i < COPIES; ++i) {
-            int j = tile * DQ_BN + async_row<DH>(8 * wave + COPY_ROWS<DH> * i, lane);
-            j = j < m_max ? j : m_max - 1;
-            pos[i] = COMPACT ? j : stream_pos(D, idx_h, j, ng, cs);
-        }
-    };
-    auto issue = [&](unsigned char* sK, unsigned char* sV) {
-#pragma unroll
-        for (int i = 0; i < COPIES; ++i) {
-            const int r0 = 8 * wave + COPY_ROWS<DH> * i;
-            const int ch = async_chunk<DH>(async_row<DH>(r0, lane), lane) * 8;
-            if (COMPACT) {
-                async_rows<DH>(stream_row(Kc_h, Kh, D.ks[2], pos[i], ng, cs) + ch, sK, r0);
-                async_rows<DH>(stream_row(Vc_h, Vh, D.ks[2], pos[i], ng, cs) + ch, sV, r0);
-            } else {
-                const int64_t off = int64_t(pos[i]) * D.ks[2] + ch;
-                async_rows<DH>(Kh + off, sK, r0);
-                async_rows<DH>(Vh + off, sV, r0);
-            }
-        }
-    };
+    const int wave_lim_max = tw < seg_end ? ng + min(tw + 31, seg_end - 1) - cs : -1;   // a wave without a row only copies
 
     const float c2 = D.scale * LOGIT_UNIT<DH>;
     const LaneOffs lo = make_lane_offs<DH>(lane);
-    const int wave_lim_min = ng + t0 + wq * 32 - cs;   // last stream entry the wave's first query sees
+    const int wave_lim_min = wave_lim_max < 0 ? -1 : ng + tw - cs;   // last stream entry the wave's first query sees
 #define LRSA_DQ_TILE(sK, sV, j0_)                                                                              \
     {                                                                                                           \
         const int j0 = (j0_);                                                                                   \
@@ -450,9 +444,6 @@ __global__ __launch_bounds__(DQ_THREADS, 2) void k_bwd_dq(Dims D, const bf16_t* 
 #pragma unroll
         for (int i = 0; i < 16; ++i) dq[db][i] = 0.0f;
 
-    fetch_pos(0);
-    issue(sK0, sV0);
-    if (ntiles > 1) fetch_pos(1);
     for (int tile = 0; tile < ntiles; tile += 2) {
         wait_vmcnt<0>();
         __syncthreads();
@@ -473,7 +464,7 @@ __global__ __launch_bounds__(DQ_THREADS, 2) void k_bwd_dq(Dims D, const bf16_t* 
 
 #undef LRSA_DQ_TILE
 
-    if (tq <= t_last) {
+    if (tq < seg_end) {
         bf16_t* orow = dQ + b * D.qs[0] + hq * D.qs[1] + int64_t(tq) * D.qs[2];
 #pragma unroll
         for (int db = 0; db < DB<DH>; ++db)
@@ -768,6 +759,31 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
         }
     };
 
+    // ---- loader: wave w fills rows 8w .. 8w+7 of the Q and dO tiles (two copies of 4 rows each) and
+    // its own lse|D block (one copy each).
+    auto issue = [&](int step, unsigned char* sQ, unsigned char* sG, float* sL) {
+        const int gi = step / sph;
+        int r0, rend, lim_unused;
+        step_rows(step, r0, rend, lim_unused);
+        const int hq = h * D.G + h0 + gi;
+        const int64_t base = b * D.qs[0] + hq * D.qs[1];
+#pragma unroll
+        for (int i = 0; i < KV_ROWS / (COPY_ROWS<DH> * KV_WAVES); ++i) {
+            const int rc = (KV_ROWS / KV_WAVES) * wave + COPY_ROWS<DH> * i;
+            const int row = async_row<DH>(rc, lane);
+            const int t = min(r0 + row, rend - 1);
+            const int64_t off = base + int64_t(t) * D.qs[2] + async_chunk<DH>(row, lane) * 8;
+            async_rows<DH>(Q + off, sQ, rc);
+            async_rows<DH>(dO + off, sG, rc);
+        }
+        const int64_t rid = (int64_t(b) * D.Hq + hq) * D.lse_stride + min(r0 + lane, rend - 1);
+        async_copy4(lse + rid, sL + wave * 2 * KV_ROWS);
+        async_copy4(Dsum + rid, sL + wave * 2 * KV_ROWS + KV_ROWS);
+    };
+
+    // the first step's rows are on their way while the keys are read (through idx: two trips to memory)
+    issue(0, sQ0, sG0, sL0);
+
     // ---- this lane's key columns (one per 32-key block): K fragments stay in registers, the V rows
     // go to LDS in the swizzled tile layout (row = key within the workgroup)
     const int wave_key0 = key0 + wave * (32 * KV_NB);
@@ -803,28 +819,6 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
     const unsigned char* sVw = sVk + wave * (32 * KV_NB) * ROW_BYTES<DH>;
     const LaneOffs lo = make_lane_offs<DH>(lane);
 
-    // ---- loader: wave w fills rows 8w .. 8w+7 of the Q and dO tiles (two copies of 4 rows each) and
-    // its own lse|D block (one copy each).
-    auto issue = [&](int step, unsigned char* sQ, unsigned char* sG, float* sL) {
-        const int gi = step / sph;
-        int r0, rend, lim_unused;
-        step_rows(step, r0, rend, lim_unused);
-        const int hq = h * D.G + h0 + gi;
-        const int64_t base = b * D.qs[0] + hq * D.qs[1];
-#pragma unroll
-        for (int i = 0; i < KV_ROWS / (COPY_ROWS<DH> * KV_WAVES); ++i) {
-            const int rc = (KV_ROWS / KV_WAVES) * wave + COPY_ROWS<DH> * i;
-            const int row = async_row<DH>(rc, lane);
-            const int t = min(r0 + row, rend - 1);
-            const int64_t off = base + int64_t(t) * D.qs[2] + async_chunk<DH>(row, lane) * 8;
-            async_rows<DH>(Q + off, sQ, rc);
-            async_rows<DH>(dO + off, sG, rc);
-        }
-        const int64_t rid = (int64_t(b) * D.Hq + hq) * D.lse_stride + min(r0 + lane, rend - 1);
-        async_copy4(lse + rid, sL + wave * 2 * KV_ROWS);
-        async_copy4(Dsum + rid, sL + wave * 2 * KV_ROWS + KV_ROWS);
-    };
-
     const float c2 = D.scale * LOGIT_UNIT<DH>;
     f32x16 dk[KV_NB][DB<DH>], dv[KV_NB][DB<DH>];
 #pragma unroll
@@ -859,14 +853,13 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
         }                                                                                                \
     }
 
-    // the K fragments have arrived before the first asynchronous copy is issued: the compiler then places
+    // the K fragments have arrived before the walk: the compiler then places
     // no vector-memory waits of its own in the loop (they would also wait for the copies in flight)
     wait_all_vmem_known();
 #pragma unroll
     for (int nb = 0; nb < KV_NB; ++nb)
 #pragma unroll
         for (int kk = 0; kk < KK<DH>; ++kk) pin_loaded(kf[nb][kk]);
-    issue(0, sQ0, sG0, sL0);
     for (int step = 0; step < nsteps; step += 2) {
         LRSA_KV_STEP(step, sQ0, sG0, sL0, sQ1, sG1, sL1);
         if (step + 1 >= nsteps) break;
@@ -1078,23 +1071,23 @@ hipError_t launch_attn_bwd_mfma(const Dims& D, const void* Q, const void* K, con
     const bool compact = D.compact && P.gl_total > 0;
     const bf16_t *kc = nullptr, *vc = nullptr;
     {
-        const int gh = heads_per_wg(D);
-        const QTileMap M = make_qtile_map(D, gh, DQ_WAVES);
-        const int64_t wgs = int64_t(D.B) * D.Hkv * M.per_unit;
+        const int waves = qtile_waves(D);
+        const QTileMap M = make_qtile_map(D, waves);
+        const int64_t wgs = M.wgs;
         if (compact && wgs > 0) {
             kc = reinterpret_cast<const bf16_t*>(reinterpret_cast<const char*>(ws) + P.off_compact);
             vc = reinterpret_cast<const bf16_t*>(reinterpret_cast<const char*>(ws) + P.off_compact + compact_kv_bytes(D) / 2);
             const hipError_t e = launch_compact_kv(D, K, V, idx, (void*)kc, (void*)vc, st);
             if (e != hipSuccess) return e;
         }
-#define LRSA_DQ_LAUNCH(DH_, GH_, C_)                                                                                  \
-    LRSA_TIMED_LAUNCH("k_bwd_dq", st, (k_bwd_dq<DH_, GH_, C_>), dim3((unsigned)wgs), dim3(DQ_THREADS), 0, st, D, q, k, v, o, g, lse, \
+#define LRSA_DQ_LAUNCH(DH_, W_, C_)                                                                              \
+    LRSA_TIMED_LAUNCH("k_bwd_dq", st, (k_bwd_dq<DH_, W_, C_>), dim3((unsigned)wgs), dim3(64 * W_), 0, st, D, q, k, v, o, g, lse, \
                       Dsum, lse2, idx, kc, vc, (bf16_t*)dQ, M)
         if (wgs > 0) {
-            if (D.d == 64) { if (gh == 4) LRSA_DQ_LAUNCH(64, 4, false); else if (gh == 2) LRSA_DQ_LAUNCH(64, 2, false); else LRSA_DQ_LAUNCH(64, 1, false); }
-            else if (gh == 4) { if (compact) LRSA_DQ_LAUNCH(128, 4, true); else LRSA_DQ_LAUNCH(128, 4, false); }
-            else if (gh == 2) { if (compact) LRSA_DQ_LAUNCH(128, 2, true); else LRSA_DQ_LAUNCH(128, 2, false); }
-            else { if (compact) LRSA_DQ_LAUNCH(128, 1, true); else LRSA_DQ_LAUNCH(128, 1, false); }
+            if (D.d == 64) LRSA_DQ_LAUNCH(64, 4, false);
+            else if (compact) LRSA_DQ_LAUNCH(128, 8, true);
+            else if (waves == 4) LRSA_DQ_LAUNCH(128, 4, false);
+            else LRSA_DQ_LAUNCH(128, 8, false);
         }
 #undef LRSA_DQ_LAUNCH
     }

@@ -1,13 +1,14 @@
 // LRSA attention forward on bf16 MFMA (gfx950), head_dim 128 or 64: Eq. 2-3 of the paper under the
 // chunked mask, flash style (online softmax, only the log-sum-exp is kept for the backward).
 //
-// One workgroup (8 waves) owns 256 (head, query) rows: GH query heads of one KV group x 256/GH
-// consecutive queries of one segment (the sink, or one chunk); a wave owns 32 queries of one head.  The keys those queries see form one
+// A wave owns a piece of 32 consecutive queries of one head; eight (or four) neighbouring pieces of one KV group and segment (the sink, or
+// one chunk) make a workgroup (mfma_tiles.h, QTileMap, qtile_waves).  The keys those queries see form one
 // stream: the gather list (sink, then the survivors of the compressed chunks) followed by the
 // contiguous local window up to the query itself.  Stream entry j is visible to query t iff
 // j <= ng + t - cs, so only the last tiles need a mask.  The stream is walked in tiles of 64
 // keys; K and V rows of a tile are copied (gathered by position) asynchronously from global
-// memory straight into a four-stage LDS ring, three tiles ahead, row-major and swizzled.
+// memory straight into an LDS ring, row-major and swizzled: of four stages, three tiles ahead, where the workgroup has the CU to itself; of
+// two stages, one tile ahead, with four waves, where two workgroups share it and cover for each other.
 //
 // Per tile and wave:  S^T = K Q^T  (keys x queries, so a lane owns one query column and the
 // softmax statistics are per lane), P^T = exp2(S^T - m), O^T += V^T P^T with the accumulator
@@ -16,7 +17,7 @@
 //
 // head_dim 64: P^T enters as three bf16 terms (mfma_tiles.h, Weights), which is all of an fp32 weight, twice as many MFMAs
 // in all; bound by the vector pipe (exponentials and the split).  8192 tokens, 16 query heads on 4 KV heads, lag 256, 64
-// kept: 4.7 ms with the plain fp32-arithmetic kernel (a wave per query row) -> 0.16 ms; backward 14.2 ms -> 0.50 ms.  With two
+// kept: 4.7 ms with the plain fp32-arithmetic kernel (a wave per query row) -> 0.14 ms; backward 14.2 ms -> 0.44 ms.  With two
 // terms and logits in log2 units 0.125 and 0.40 ms, but 1.6 per mille of the elements of O are then off the correct rounding
 // of the exact value, of dV 2.2 (1K to 4K rows, five kinds of values); now 0.22 and 0.41, the plain kernels 0.21 and 0.40.
 #include "mfma_tiles.h"
@@ -24,8 +25,6 @@
 namespace lrsa {
 
 constexpr int FWD_BN = 64;     // keys per tile
-constexpr int FWD_WAVES = 8;   // waves per workgroup (two per SIMD), 32 queries each
-constexpr int FWD_THREADS = 64 * FWD_WAVES;
 
 // bf16 and a head's K/V rows within 2 GiB of its first row (the copies use 32-bit byte offsets)
 bool mfma_supported(const Dims& D) {
@@ -143,12 +142,8 @@ __device__ __forceinline__ void fwd_tile(const unsigned char* sK, const unsigned
             }
             mx = fmaxf(mx, s[kb][i]);
         }
-    if constexpr (DH == 64) {   // a swap needs no address registers
-        const lanes_u32x2 x = pair32(__float_as_uint(mx));
-        mx = fmaxf(__uint_as_float(x.x), __uint_as_float(x.y)) * c2;
-    } else {
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * c2;
-    }
+    const lanes_u32x2 x = pair32(__float_as_uint(mx));   // not through LDS, whose queue is full of operand reads
+    mx = fmaxf(__uint_as_float(x.x), __uint_as_float(x.y)) * c2;
     if (__builtin_amdgcn_ballot_w64(mx > st.m_run + (DH == 64 ? 5.0f : 8.0f)) != 0) {   // wave-uniform; always taken on the first tile
         const float m_new = fmaxf(st.m_run, mx);   // finite: the first tile holds a visible key for every query
         const float corr = exp_units<DH>(st.m_run - m_new);
@@ -211,12 +206,10 @@ __device__ __forceinline__ void fwd_tile(const unsigned char* sK, const unsigned
 #undef LRSA_PV
 }
 
-// GH query heads of one KV group share the workgroup: its 8 waves cover GH heads x QT = 256/GH queries,
-// so every K/V tile staged in LDS serves 256 (head, query) rows.
 // COMPACT: the rows of the gather list come from the condensed cache Kc, Vc (contiguous), no index is read.
-// DH = 64 needs half the registers, so that two workgroups share a CU.
-template <int DH, int GH, bool COMPACT>
-__global__ __launch_bounds__(FWD_THREADS, DH == 64 ? 4 : 2) void k_fwd_mfma(Dims D, const bf16_t* __restrict__ Q,
+// DH = 64: three waves per SIMD; the 128 registers of a fourth would spill.
+template <int DH, int WAVES, bool COMPACT>
+__global__ __launch_bounds__(64 * WAVES, DH == 64 ? 3 : 2) void k_fwd_mfma(Dims D, const bf16_t* __restrict__ Q,
                                                               const bf16_t* __restrict__ K,
                                                               const bf16_t* __restrict__ V,
                                                               const int32_t* __restrict__ idx,
@@ -224,34 +217,20 @@ __global__ __launch_bounds__(FWD_THREADS, DH == 64 ? 4 : 2) void k_fwd_mfma(Dims
                                                               const bf16_t* __restrict__ Vc,
                                                               bf16_t* __restrict__ O, float* __restrict__ lse,
                                                               QTileMap M) {
-    constexpr int WPH = FWD_WAVES / GH;   // waves per head
-    constexpr int QT = 32 * WPH;          // queries per head and workgroup
-    // four stages, each one array holding the K tile then the V tile; separate arrays per stage so that
+    // the stages, each one array holding the K tile then the V tile; separate arrays per stage so that
     // reads of one stage need not wait for the asynchronous fill of another (the compiler tracks only a
     // handful of such arrays, hence K and V share one)
     constexpr int TILE_BYTES = FWD_BN * ROW_BYTES<DH>;
-    __shared__ __attribute__((aligned(16))) unsigned char sT0[2 * TILE_BYTES], sT1[2 * TILE_BYTES], sT2[2 * TILE_BYTES],
-        sT3[2 * TILE_BYTES];
+    constexpr int STAGES = WAVES == 8 ? 4 : 2, RPW = FWD_BN / WAVES;   // ring stages; tile rows a wave copies
+    __shared__ __attribute__((aligned(16))) unsigned char sT0[2 * TILE_BYTES], sT1[2 * TILE_BYTES];
+    __shared__ __attribute__((aligned(16))) unsigned char sT2[STAGES == 4 ? 2 * TILE_BYTES : 16], sT3[STAGES == 4 ? 2 * TILE_BYTES : 16];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, g = lane >> 5;
-    int b, h, gsub, tix;
-    decode_qtile(M, D, blockIdx.x, b, h, gsub, tix);
-    const int hq = h * D.G + gsub * GH + wave / WPH;
-    const int wq = wave % WPH;
-
-    int qc, t0, seg_end;
-    if (tix < M.sink_tiles) {
-        qc = -1; t0 = tix * QT; seg_end = D.S < D.n ? D.S : D.n;
-    } else {
-        const int tt = tix - M.sink_tiles;
-        qc = tt / M.tpc;
-        t0 = D.S + qc * D.L + (tt % M.tpc) * QT;
-        const int64_t e = int64_t(D.S) + int64_t(qc + 1) * D.L;
-        seg_end = e < D.n ? int(e) : D.n;
-    }
-    if (t0 >= seg_end) return;  // uniform for the workgroup
-    const int t_last = min(t0 + QT, seg_end) - 1;
+    int b, h, tix, qc, seg_end, tw, head, t_last;
+    if (!decode_qtile(M, D, blockIdx.x, b, h, tix) || !qtile_rows(M, D, tix, WAVES, wave, qc, seg_end, tw, head, t_last)) return;   // uniform for the workgroup
+    if constexpr (DH == 128) asm volatile("" : "+v"(tw));   // else the walk's branches become scalar, and zeros are kept in registers for them
+    const int hq = h * D.G + head;
     const int ng = gather_count(D, qc), cs = window_start(D, qc);
     const int m_max = ng + t_last - cs + 1;           // stream entries the last row sees
     const int ntiles = (m_max + FWD_BN - 1) / FWD_BN;
@@ -264,8 +243,8 @@ __global__ __launch_bounds__(FWD_THREADS, DH == 64 ? 4 : 2) void k_fwd_mfma(Dims
     const bf16_t* Vc_h = Vc + coff;
 
     // this lane's query column
-    const int tq = t0 + wq * 32 + l32;
-    const int tq_ld = tq < t_last ? tq : t_last;
+    const int tq = tw + l32;
+    const int tq_ld = tq < seg_end ? tq : seg_end - 1;
     bf16x8 qf[KK<DH>];
     {
         const bf16_t* qrow = Q + b * D.qs[0] + hq * D.qs[1] + int64_t(tq_ld) * D.qs[2];
@@ -273,11 +252,12 @@ __global__ __launch_bounds__(FWD_THREADS, DH == 64 ? 4 : 2) void k_fwd_mfma(Dims
         for (int kk = 0; kk < KK<DH>; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(qrow + kk * 16 + g * 8);
     }
     const int lim = ng + tq - cs;                                     // last stream entry this query sees
-    const int wave_lim_max = ng + min(t0 + wq * 32 + 31, t_last) - cs;  // ... the wave's last valid query sees
-    const int wave_lim_min = ng + t0 + wq * 32 - cs;                    // ... the wave's first query sees
+    // ... the wave's last valid query sees; a wave without one only copies
+    const int wave_lim_max = tw < seg_end ? ng + min(tw + 31, seg_end - 1) - cs : -1;
+    const int wave_lim_min = wave_lim_max < 0 ? -1 : ng + tw - cs;   // ... the wave's first query sees
 
-    // loader: wave w fills tile rows 8w .. 8w+7 with two asynchronous copies of 4 rows each (DH = 64: one of 8 rows),
-    // K and V alike; rows past the stream end re-read its last key and are masked.  The 8 stream
+    // loader: wave w fills tile rows RPW * w .. with asynchronous copies of 4 rows each (DH = 64: of 8 rows),
+    // K and V alike; rows past the stream end re-read its last key and are masked.  The stream
     // positions a wave needs per tile are wave-uniform addresses, so they are fetched through the scalar
     // cache (one iteration ahead); the only vector memory operations in the loop are the asynchronous
     // copies, always OPS_PER_TILE per wave and tile, which lets s_waitcnt vmcnt(n) address a tile.
@@ -285,25 +265,35 @@ __global__ __launch_bounds__(FWD_THREADS, DH == 64 ? 4 : 2) void k_fwd_mfma(Dims
     const int idx_last = D.Ns > 0 ? D.Ns * D.K - 1 : 0;
     const int wv = __builtin_amdgcn_readfirstlane(wave);
     auto pos_entry = [&](int tc, int r) {   // clamped index into idx of row r of the wave's 8 tile rows
-        const int e = min(tc * FWD_BN + 8 * wv + r, m_max - 1) - D.S;
+        const int e = min(tc * FWD_BN + RPW * wv + r, m_max - 1) - D.S;
         return e < 0 ? 0 : (e > idx_last ? idx_last : e);
     };
-    auto fetch_pos = [&](int tile, Scalar8& raw) {
+    struct Pos { Scalar8 e[RPW / 8]; };
+    auto fetch_pos = [&](int tile, Pos& raw) {
         if (COMPACT) return;
         const int tc = tile < ntiles ? tile : ntiles - 1;   // past the end: repeat the last tile (never consumed)
-        raw.a0 = smem_load(idx_ld, pos_entry(tc, 0)); raw.a1 = smem_load(idx_ld, pos_entry(tc, 1));
-        raw.a2 = smem_load(idx_ld, pos_entry(tc, 2)); raw.a3 = smem_load(idx_ld, pos_entry(tc, 3));
-        raw.a4 = smem_load(idx_ld, pos_entry(tc, 4)); raw.a5 = smem_load(idx_ld, pos_entry(tc, 5));
-        raw.a6 = smem_load(idx_ld, pos_entry(tc, 6)); raw.a7 = smem_load(idx_ld, pos_entry(tc, 7));
+#pragma unroll
+        for (int i = 0; i < RPW / 8; ++i) {
+            Scalar8& w = raw.e[i];
+            w.a0 = smem_load(idx_ld, pos_entry(tc, 8 * i + 0)); w.a1 = smem_load(idx_ld, pos_entry(tc, 8 * i + 1));
+            w.a2 = smem_load(idx_ld, pos_entry(tc, 8 * i + 2)); w.a3 = smem_load(idx_ld, pos_entry(tc, 8 * i + 3));
+            w.a4 = smem_load(idx_ld, pos_entry(tc, 8 * i + 4)); w.a5 = smem_load(idx_ld, pos_entry(tc, 8 * i + 5));
+            w.a6 = smem_load(idx_ld, pos_entry(tc, 8 * i + 6)); w.a7 = smem_load(idx_ld, pos_entry(tc, 8 * i + 7));
+        }
+    };
+    auto wait_pos = [&](Pos& raw) {
+        if (!COMPACT)
+#pragma unroll
+            for (int i = 0; i < RPW / 8; ++i) smem_wait(raw.e[i]);
     };
     // laK, laV: LDS byte addresses of the stage's K tile and V tile (compile-time constants at the call sites)
-    auto issue = [&](int tile, Scalar8& raw, unsigned laK, unsigned laV) {
+    auto issue = [&](int tile, Pos& raw, unsigned laK, unsigned laV) {
         const int tc = tile < ntiles ? tile : ntiles - 1;
         const int sub = async_row<DH>(0, lane);                         // this lane's row of a copy
-        if (!COMPACT) smem_wait(raw);
+        wait_pos(raw);
 #pragma unroll
-        for (int i = 0; i < 8 / COPY_ROWS<DH>; ++i) {
-            const int r0 = 8 * wv + COPY_ROWS<DH> * i;
+        for (int i = 0; i < RPW / COPY_ROWS<DH>; ++i) {
+            const int r0 = RPW * wv + COPY_ROWS<DH> * i;
             int j = tc * FWD_BN + r0 + sub;
             j = j < m_max ? j : m_max - 1;
             const int ch = async_chunk<DH>(r0 + sub, lane) * 8;
@@ -312,8 +302,9 @@ __global__ __launch_bounds__(FWD_THREADS, DH == 64 ? 4 : 2) void k_fwd_mfma(Dims
                 async_copy16_la(stream_row(Kc_h, Kh, D.ks[2], j, ng, cs) + ch, laK + row_la);
                 async_copy16_la(stream_row(Vc_h, Vh, D.ks[2], j, ng, cs) + ch, laV + row_la);
             } else {
-                const int lo4 = pick4(sub & 3, raw.a0, raw.a1, raw.a2, raw.a3), hi4 = pick4(sub & 3, raw.a4, raw.a5, raw.a6, raw.a7);
-                const int sel = DH == 128 ? (i == 0 ? lo4 : hi4) : (sub < 4 ? lo4 : hi4);
+                const Scalar8& w = raw.e[i * COPY_ROWS<DH> / 8];
+                const int lo4 = pick4(sub & 3, w.a0, w.a1, w.a2, w.a3), hi4 = pick4(sub & 3, w.a4, w.a5, w.a6, w.a7);
+                const int sel = DH == 128 ? (i % 2 == 0 ? lo4 : hi4) : (sub < 4 ? lo4 : hi4);
                 const int pos = j < ng ? (j < D.S ? j : sel) : cs + (j - ng);
                 // byte offset inside the head: below 2^31 (a condition of this kernel, checked on the host)
                 const unsigned off = (unsigned(pos) * unsigned(D.ks[2]) + unsigned(ch)) * 2u;
@@ -322,7 +313,7 @@ __global__ __launch_bounds__(FWD_THREADS, DH == 64 ? 4 : 2) void k_fwd_mfma(Dims
             }
         }
     };
-    constexpr int OPS_PER_TILE = 2 * 8 / COPY_ROWS<DH>;   // asynchronous copies per wave and tile
+    constexpr int OPS_PER_TILE = 2 * RPW / COPY_ROWS<DH>;   // asynchronous copies per wave and tile
 
     const float c2 = D.scale * LOGIT_UNIT<DH>;
     const LaneOffs lo = make_lane_offs<DH>(lane);
@@ -343,38 +334,67 @@ __global__ __launch_bounds__(FWD_THREADS, DH == 64 ? 4 : 2) void k_fwd_mfma(Dims
 
     // A wave's vector memory operations in order:  A(0) A(1) A(2) | iteration t: A(t+3)   (A = the copies
     // of a tile).  At the top of iteration t the operations issued after A(t) are A(t+1) A(t+2).
-    Scalar8 posA, posB;
-    const unsigned la0 = lds_addr(sT0), la1 = lds_addr(sT1), la2 = lds_addr(sT2), la3 = lds_addr(sT3);
-    fetch_pos(0, posA); issue(0, posA, la0, la0 + TILE_BYTES);
-    fetch_pos(1, posB); issue(1, posB, la1, la1 + TILE_BYTES);
-    fetch_pos(2, posA); issue(2, posA, la2, la2 + TILE_BYTES);
-    fetch_pos(3, posB);
-    wait_all_vmem_known();   // the Q fragments (and the first tiles) are here
-#define LRSA_FWD_STEP(t_, sT, laN, pos_use, pos_fetch)                                               \
+    Pos pos;   // of the tile that is copied next
+    if constexpr (STAGES == 4) {
+        const unsigned la0 = lds_addr(sT0), la1 = lds_addr(sT1), la2 = lds_addr(sT2), la3 = lds_addr(sT3);
+        Pos pos1, pos2;      // one trip to memory for all three
+        fetch_pos(0, pos); fetch_pos(1, pos1); fetch_pos(2, pos2);
+        issue(0, pos, la0, la0 + TILE_BYTES);
+        issue(1, pos1, la1, la1 + TILE_BYTES);
+        issue(2, pos2, la2, la2 + TILE_BYTES);
+        fetch_pos(3, pos);
+        wait_all_vmem_known();   // the Q fragments (and the first tiles) are here
+#define LRSA_FWD_STEP(t_, sT, laN)                                                                   \
     {                                                                                                \
         wait_vmcnt<2 * OPS_PER_TILE>();   /* this wave's copies for tile t_ have landed */            \
         ring_barrier();                   /* everybody's have; everybody is done with tile t_-1 */   \
-        issue((t_) + 3, pos_use, laN, laN + TILE_BYTES); /* tile t_+3 into the stage tile t_-1 used */ \
-        fetch_pos((t_) + 4, pos_fetch);   /* after the copies: their wait for positions is for ALL scalar loads */ \
+        issue((t_) + 3, pos, laN, laN + TILE_BYTES); /* tile t_+3 into the stage tile t_-1 used */    \
+        fetch_pos((t_) + 4, pos);         /* after the copies: their wait for positions is for ALL scalar loads */ \
         LRSA_FWD_TILE(sT, sT + TILE_BYTES, (t_) * FWD_BN);                                           \
     }
-    for (int tile = 0; tile < ntiles; tile += 4) {
-        LRSA_FWD_STEP(tile, sT0, la3, posB, posA);
-        if (tile + 1 >= ntiles) break;
-        LRSA_FWD_STEP(tile + 1, sT1, la0, posA, posB);
-        if (tile + 2 >= ntiles) break;
-        LRSA_FWD_STEP(tile + 2, sT2, la1, posB, posA);
-        if (tile + 3 >= ntiles) break;
-        LRSA_FWD_STEP(tile + 3, sT3, la2, posA, posB);
-    }
+        for (int tile = 0; tile < ntiles; tile += 4) {
+            LRSA_FWD_STEP(tile, sT0, la3);
+            if (tile + 1 >= ntiles) break;
+            LRSA_FWD_STEP(tile + 1, sT1, la0);
+            if (tile + 2 >= ntiles) break;
+            LRSA_FWD_STEP(tile + 2, sT2, la1);
+            if (tile + 3 >= ntiles) break;
+            LRSA_FWD_STEP(tile + 3, sT3, la2);
+        }
 #undef LRSA_FWD_STEP
+    } else {
+        const unsigned la0 = lds_addr(sT0), la1 = lds_addr(sT1);
+        Pos pos0;
+        fetch_pos(0, pos0); fetch_pos(1, pos);
+        issue(0, pos0, la0, la0 + TILE_BYTES);
+        wait_all_vmem_known();
+#define LRSA_FWD_STEP2(t_, sT, laN)                                                                   \
+    {                                                                                                \
+        wait_vmcnt<0>();                                                                              \
+        ring_barrier();                                                                              \
+        if ((t_) + 1 < ntiles) {                                                                      \
+            issue((t_) + 1, pos, laN, laN + TILE_BYTES);                                              \
+            fetch_pos((t_) + 2, pos);                                                                 \
+        }                                                                                            \
+        LRSA_FWD_TILE(sT, sT + TILE_BYTES, (t_) * FWD_BN);                                           \
+    }
+        for (int tile = 0; tile < ntiles; tile += 2) {
+            LRSA_FWD_STEP2(tile, sT0, la1);
+            if (tile + 1 >= ntiles) break;
+            LRSA_FWD_STEP2(tile + 1, sT1, la0);
+        }
+#undef LRSA_FWD_STEP2
+    }
+    wait_pos(pos);     // the last positions, which nobody uses, must not land in registers that the epilogue has taken
     wait_vmcnt<0>();   // copies issued past the end must land before the workgroup's LDS is released
 #undef LRSA_FWD_TILE
 
     const float l_tot = st.l_run + __shfl_xor(st.l_run, 32, 64);
     // row and head once more, from scalars: kept across the walk they would cost vector registers
-    const int hq_o = h * D.G + gsub * GH + wv / WPH, tq_o = t0 + (wv % WPH) * 32 + l32;
-    if (tq_o <= t_last) {
+    int tw_o, head_o;
+    qtile_rows(M, D, tix, WAVES, wv, qc, seg_end, tw_o, head_o, t_last);
+    const int hq_o = h * D.G + head_o, tq_o = tw_o + l32;
+    if (tq_o < seg_end) {
         const float inv = 1.0f / l_tot;
         bf16_t* orow = O + b * D.qs[0] + hq_o * D.qs[1] + int64_t(tq_o) * D.qs[2];
 #pragma unroll
@@ -396,9 +416,9 @@ __global__ __launch_bounds__(FWD_THREADS, DH == 64 ? 4 : 2) void k_fwd_mfma(Dims
 
 hipError_t launch_attn_fwd_mfma(const Dims& D, const void* Q, const void* K, const void* V, const int32_t* idx,
                                 void* O, float* lse, void* ws, hipStream_t st) {
-    const int gh = heads_per_wg(D);
-    const QTileMap M = make_qtile_map(D, gh, FWD_WAVES);
-    const int64_t wgs = int64_t(D.B) * D.Hkv * M.per_unit;
+    const int waves = qtile_waves(D);
+    const QTileMap M = make_qtile_map(D, waves);
+    const int64_t wgs = M.wgs;
     if (wgs == 0) return hipSuccess;
     const bf16_t *q = (const bf16_t*)Q, *k = (const bf16_t*)K, *v = (const bf16_t*)V;
     const bool compact = D.compact && gather_list_len(D) > 0;
@@ -409,13 +429,13 @@ hipError_t launch_attn_fwd_mfma(const Dims& D, const void* Q, const void* K, con
         const hipError_t e = launch_compact_kv(D, K, V, idx, (void*)kc, (void*)vc, st);
         if (e != hipSuccess) return e;
     }
-#define LRSA_FWD_LAUNCH(DH_, GH_, C_)                                                                                   \
-    LRSA_TIMED_LAUNCH("k_fwd_mfma", st, (k_fwd_mfma<DH_, GH_, C_>), dim3((unsigned)wgs), dim3(FWD_THREADS), 0, st, D, q, k, v, \
+#define LRSA_FWD_LAUNCH(DH_, W_, C_)                                                                                   \
+    LRSA_TIMED_LAUNCH("k_fwd_mfma", st, (k_fwd_mfma<DH_, W_, C_>), dim3((unsigned)wgs), dim3(64 * W_), 0, st, D, q, k, v, \
                       idx, kc, vc, (bf16_t*)O, lse, M)
-    if (D.d == 64) { if (gh == 4) LRSA_FWD_LAUNCH(64, 4, false); else if (gh == 2) LRSA_FWD_LAUNCH(64, 2, false); else LRSA_FWD_LAUNCH(64, 1, false); }
-    else if (gh == 4) { if (compact) LRSA_FWD_LAUNCH(128, 4, true); else LRSA_FWD_LAUNCH(128, 4, false); }
-    else if (gh == 2) { if (compact) LRSA_FWD_LAUNCH(128, 2, true); else LRSA_FWD_LAUNCH(128, 2, false); }
-    else { if (compact) LRSA_FWD_LAUNCH(128, 1, true); else LRSA_FWD_LAUNCH(128, 1, false); }
+    if (D.d == 64) LRSA_FWD_LAUNCH(64, 4, false);
+    else if (compact) LRSA_FWD_LAUNCH(128, 8, true);
+    else if (waves == 4) LRSA_FWD_LAUNCH(128, 4, false);
+    else LRSA_FWD_LAUNCH(128, 8, false);
 #undef LRSA_FWD_LAUNCH
     return hipGetLastError();
 }

@@ -296,30 +296,89 @@ __device__ __forceinline__ int stream_pos(const Dims& D, const int32_t* idx_h, i
     return cs + (j - ng);
 }
 
-// Which (batch, KV head, head subset, query tile) a workgroup of a query-outer kernel takes.
-// per_unit = workgroups per (batch, KV head).  With xcd_map, consecutive workgroup ids -- which the
-// hardware deals round-robin to the 8 XCDs -- belong to 8 different KV heads, so that one XCD's L2
-// keeps serving the K/V rows of the same head.
-struct QTileMap {
-    int sink_tiles, tpc, tiles;   // query tiles of QT rows: in the sink, per chunk, per head
-    int tix_lo, tix_hi;           // the tiles that are launched (all of them unless a row window is set)
-    int gsubs, per_unit, xcd_map;
+// x / d for x up to the largest one given on the host, by a multiplication (a division is some thirty dependent instructions, and a
+// workgroup needs several before it can ask for its first row): m = ceil(2^32 / d) is exact as long as x * d < 2^32; 0: divide.
+struct FastDiv {
+    unsigned d, m;
 };
-__device__ __forceinline__ void decode_qtile(const QTileMap& M, const Dims& D, int i, int& b, int& h, int& gsub,
-                                             int& tix) {
+inline FastDiv make_fast_div(int64_t d, int64_t x_max) {
+    const bool exact = d > 1 && x_max < (int64_t(1) << 32) / d;
+    return FastDiv{unsigned(d), exact ? unsigned(((int64_t(1) << 32) + d - 1) / d) : 0u};
+}
+__device__ __forceinline__ int fast_div(int x, FastDiv f) {
+    return f.m ? int(__umulhi(unsigned(x), f.m)) : f.d == 1 ? x : int(unsigned(x) / f.d);
+}
+
+// Which (batch, KV head, query tile) a workgroup of a query-outer kernel takes.
+//
+// A segment (the sink, or one query chunk) is a list of pieces, 32 rows of one query head each: block of heads by block of heads, rows
+// in order, the heads of a block side by side.  A block is the group, or four of its heads where that divides it (with all eight of a
+// group side by side 4 requests of 3.5K tokens, 16 heads on 2, lag 109, take 118 us instead of 113: no wave ends early).  All pieces
+// of a segment walk the same gather list, so a workgroup takes any `waves` neighbours, one per wave, and the last workgroup of a segment is the only one with idle waves.  (Whole heads x a fixed number of rows per workgroup
+// wasted up to half of them: 24 heads on 8, 2 requests of 6.2K tokens, lag 258 -- two tiles of 256 rows per chunk, the second
+// with 2 -- forward 538 -> 335 us.)
+//
+// Orders of the tiles, the heaviest (latest) first in each.  With a multiple of eight heads, consecutive workgroup ids -- which the
+// hardware deals round-robin to the 8 XCDs -- belong to 8 different KV heads, so that one XCD's L2 keeps serving the K / V rows of the same
+// head until it is done.  Otherwise, and where all workgroups are resident at once, so that nothing is dealt later to a CU that is done
+// early, all heads side by side; with two workgroups per CU the second 256 come backwards, so that a long one shares its CU with a
+// short one.  2 requests of 4K tokens, 8 heads on 8: forward 51.4 us with the first order, 42.2 with the second; one head after
+// another instead of side by side: 9.4K tokens, 12 heads on 4, 144 and 117 us; 16K tokens, 24 on 4, 751 and 701.
+struct QTileMap {
+    int sink_tiles, tpc, tiles;   // query tiles (of `waves` pieces): in the sink, per chunk, in all
+    int tix_lo, tix_hi;           // the tiles that are launched (all of them unless a row window is set)
+    int per_unit;                 // workgroups per (batch, KV head)
+    int wgs;                      // workgroups of the launch
+    int side_by_side, backwards;
+    int heads;                    // of a block
+    FastDiv by_unit, by_units, by_hkv, by_tpc, by_heads;
+};
+__device__ __forceinline__ bool decode_qtile(const QTileMap& M, const Dims& D, int i, int& b, int& h, int& tix) {
     int unit, w;
-    if (M.xcd_map) {
-        const int j = i >> 3;
-        unit = (i & 7) + 8 * (j / M.per_unit);
-        w = j % M.per_unit;
+    if (M.side_by_side) {
+        int j = i >> 3;
+        if (M.backwards && (j >> 5) == 1) j = 95 - j;
+        i = j * 8 + (i & 7);
+        w = fast_div(i, M.by_units);
+        if (w >= M.per_unit) return false;
+        unit = i - w * D.B * D.Hkv;
     } else {
-        unit = i / M.per_unit;
-        w = i % M.per_unit;
+        const int j = i >> 3, e = fast_div(j, M.by_unit);
+        unit = (i & 7) + 8 * e;
+        w = j - e * M.per_unit;
     }
-    b = unit / D.Hkv;
-    h = unit % D.Hkv;
-    gsub = w % M.gsubs;
-    tix = M.tix_hi - 1 - w / M.gsubs;   // heaviest (latest) query tile first
+    b = fast_div(unit, M.by_hkv);
+    h = unit - b * D.Hkv;
+    tix = M.tix_hi - 1 - w;
+    return true;
+}
+// The rows of tile `tix`: query chunk (-1: sink), end of the segment, first row and head (of the group) of this wave's piece, last row
+// of the workgroup; false: it has none.  A wave whose first row is not below seg_end has no piece.
+__device__ __forceinline__ bool qtile_rows(const QTileMap& M, const Dims& D, int tix, int waves, int wave, int& qc, int& seg_end, int& tw,
+                                           int& head, int& t_last) {
+    int ts, u0, rows;
+    if (tix < M.sink_tiles) {
+        qc = -1; ts = 0; u0 = tix * waves; rows = seg_end = D.S < D.n ? D.S : D.n;
+    } else {
+        const int tt = tix - M.sink_tiles;
+        qc = fast_div(tt, M.by_tpc);
+        ts = D.S + qc * D.L;
+        u0 = (tt - qc * M.tpc) * waves;
+        const int64_t e = int64_t(D.S) + int64_t(qc + 1) * D.L;
+        seg_end = e < D.n ? int(e) : D.n;
+        rows = D.L;
+    }
+    const int block = (rows + 31) / 32 * M.heads;   // pieces of a block of heads
+    int u1 = u0 + waves - 1, hb = 0;                // hb: first head of the block that piece u0 is in
+    while (u0 >= block && hb + M.heads < D.G) { u0 -= block; u1 -= block; hb += M.heads; }
+    const bool next = u1 >= block && hb + M.heads < D.G;   // the tile reaches into the next block, whose first rows are there
+    int u = u0 + wave;
+    while (u >= block && hb + M.heads < D.G) { u -= block; hb += M.heads; }
+    const int rb = fast_div(u, M.by_heads);
+    tw = ts + rb * 32;                              // past the segment: no piece
+    head = hb + u - rb * M.heads;
+    t_last = next ? seg_end - 1 : min(ts + (fast_div(u1, M.by_heads) + 1) * 32, seg_end) - 1;
+    return next || ts + fast_div(u0, M.by_heads) * 32 < seg_end;
 }
 
 // ---- condensed KV cache --------------------------------------------------------------------------
@@ -337,22 +396,49 @@ __device__ __forceinline__ const bf16_t* stream_row(const bf16_t* Zc, const bf16
     return j < ng ? Zc + int64_t(j) * 128 : Z + int64_t(cs + (j - ng)) * stride;
 }
 
-// heads of a group that share a workgroup: the largest of 4, 2, 1 that divides the group size
-inline int heads_per_wg(const Dims& D) { return D.G % 4 == 0 ? 4 : D.G % 2 == 0 ? 2 : 1; }
+// all of a launch's workgroups on the chip at once, or nearly: two per CU of four waves, one of eight
+inline bool resident_tiles(int64_t wgs, int waves) { return wgs * waves <= 2048 + 512; }
 
-inline QTileMap make_qtile_map(const Dims& D, int gh, int waves) {
+inline QTileMap make_qtile_map(const Dims& D, int waves) {
     QTileMap M;
-    const int qt = 32 * (waves / gh);
     const int sink_rows = D.S < D.n ? D.S : D.n;
-    M.sink_tiles = (sink_rows + qt - 1) / qt;
-    M.tpc = (D.L + qt - 1) / qt;
+    M.heads = D.G % 4 == 0 ? 4 : D.G;
+    auto tiles = [&](int64_t rows) { return int(((rows + 31) / 32 * D.G + waves - 1) / waves); };
+    M.sink_tiles = tiles(sink_rows);
+    M.tpc = tiles(D.L);
     M.tiles = M.sink_tiles + D.nq * M.tpc;
     M.tix_lo = D.row_begin == 0 ? 0 : M.sink_tiles + D.fq0 * M.tpc;
     M.tix_hi = M.sink_tiles + D.fq1 * M.tpc;
-    M.gsubs = D.G / gh;
-    M.per_unit = (M.tix_hi - M.tix_lo) * M.gsubs;
-    M.xcd_map = (D.B * D.Hkv) % 8 == 0 ? 1 : 0;
+    M.per_unit = M.tix_hi - M.tix_lo;
+    const int64_t units = int64_t(D.B) * D.Hkv, wgs = units * M.per_unit;
+    M.side_by_side = units % 8 != 0 || resident_tiles(wgs, waves);
+    M.backwards = waves == 4;
+    M.wgs = int(M.side_by_side && wgs < 512 ? (wgs + 255) / 256 * 256 : wgs);   // the second 256 are whole
+    M.by_unit = make_fast_div(M.per_unit, wgs);
+    M.by_units = make_fast_div(units, M.wgs);
+    M.by_hkv = make_fast_div(D.Hkv, units);
+    M.by_tpc = make_fast_div(M.tpc, M.tiles);
+    M.by_heads = make_fast_div(M.heads, int64_t(M.tpc > M.sink_tiles ? M.tpc : M.sink_tiles) * waves + waves);
     return M;
+}
+
+// Waves per workgroup of the forward and dQ kernels.  Eight share one staged K / V tile; four, two workgroups of which fit a CU, copy it
+// twice and take 2 to 5 percent longer where the chip is full and the walks are long (32K tokens, 32 heads on 8: forward 2718 us with
+// eight, 2819 with four).  Four
+//  - where the launch is resident at once or nearly: its longest workgroup is what counts, and it is half as long, runs alone on its
+//    SIMDs or is paired with a short one (QTileMap).  2.4K tokens, 8 heads on 2: 23 -> 19 us; 2 requests of 4K tokens, 8 heads on 8: 48 ->
+//    42 us; 14.3K tokens, 4 heads on 4: 212 -> 185 us (with eight 23.8, 47.8 and 207);
+//  - where eight would leave more than one wave in ten idle at the ends of the chunks: 4 requests of 2.9K tokens, 12 heads on 4,
+//    lag 91: 128 us with eight, 99 with four;
+//  - for walks of up to a thousand keys, whose beginning and end the other workgroup of the CU covers: 2.5K tokens, 64 heads on 8, lag 128:
+//    58 and 50 us; from 1.3K keys on eight are faster again (7.4K tokens, 48 heads on 8: 268 and 275 us);
+//  - head_dim 64, whose tiles are half as large: never slower than eight but for launches that eight just fill (7.1K tokens, 8 heads on 4:
+//    80 and 87 us); 8K tokens, 16 heads on 4: 154 and 138 us.
+inline int qtile_waves(const Dims& D) {
+    if (D.compact) return 8;
+    const int64_t units = int64_t(D.B) * D.Hkv, n4 = units * make_qtile_map(D, 4).per_unit, n8 = units * make_qtile_map(D, 8).per_unit;
+    const int keys = gather_count(D, (D.fq0 + D.fq1) / 2) + D.L + D.L / 2;   // of a walk, about
+    return D.d == 64 || resident_tiles(n4, 4) || 20 * n8 > 11 * n4 || keys <= 1000 ? 4 : 8;
 }
 
 }  // namespace lrsa
