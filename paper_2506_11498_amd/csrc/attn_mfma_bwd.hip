@@ -6,29 +6,29 @@
 //   k_bwd_dq          query-outer: a workgroup owns eight (or four) pieces of 32 query rows of one KV group and walks their
 //                     key stream exactly like the forward (gather list, then the local window), recomputing A;
 //                     it also leaves D[b,hq,t] = dO[t] . O[t] and lse in the units of the logits (mfma_tiles.h) in the workspace
-//   k_bwd_dkv         key-outer, two kinds of workgroups in one launch.  GATHER: 256 consecutive entries of one
+//   k_bwd_dkv         key-outer, two kinds of workgroups in one launch.  GATHER: 256 (four waves: 128) consecutive entries of one
 //                     KV head's gather list (sink ++ survivors) x one slice of query chunks -> fp32 partial
-//                     dK, dV rows in the workspace.  WINDOW: 256 consecutive positions x the queries that see
+//                     dK, dV rows in the workspace.  WINDOW: as many consecutive positions x the queries that see
 //                     them through the local window (own chunk causally, the next local_prev chunks in full);
 //                     positions outside the gather list are written as final dK, dV, listed ones as one more
 //                     fp32 partial.
 //   k_bwd_dkv_reduce  listed positions: window partial + the slices, in a fixed order -> dK, dV
 // In the key-outer kernel a lane owns one key column of S = Q K^T: K fragments stay in registers for the
-// whole walk, the workgroup's V rows in LDS; Q and dO rows stream through LDS 64 rows at a time and are read
+// whole walk, the workgroup's V rows in LDS; Q and dO rows stream through LDS 64 (four waves: 32) rows at a time and are read
 // both row-wise (for S and dA) and transposed (for dV^T += dO^T A and dK^T += Q^T dS).
 #include "mfma_tiles.h"
 
 namespace lrsa {
 
-constexpr int KV_WAVES = 8;              // waves per workgroup of the key-outer kernel (two per SIMD)
-constexpr int KV_THREADS = 64 * KV_WAVES;
 constexpr int DQ_BN = 64;
 constexpr int DQ_PF = 4;                 // LDS operands of the query-outer kernel are read this many MFMAs ahead
-constexpr int KV_NB = 1;                        // 32-key blocks per wave (2 needs one wave per SIMD: measured slower)
-constexpr int KV_BK = 32 * KV_NB * KV_WAVES;   // keys per workgroup
-constexpr int KV_BQ = 32;   // query rows per MFMA sub-step
-constexpr int KV_SUB = 2;   // sub-steps per pipeline step (one LDS stage, one barrier)
-constexpr int KV_ROWS = KV_BQ * KV_SUB;   // query rows per step
+// The key-outer kernel, with W = 8 or 4 waves per workgroup (two workgroups of four fit a CU), 32 keys each
+constexpr int KV_NB = 1;                                   // 32-key blocks per wave (2 needs one wave per SIMD: measured slower)
+template <int W> constexpr int KV_BK = 32 * KV_NB * W;     // keys per workgroup
+constexpr int KV_BQ = 32;                                  // query rows per MFMA sub-step
+template <int W> constexpr int KV_SUB = W == 8 ? 2 : 1;    // sub-steps per pipeline step (one LDS stage, one barrier)
+template <int W> constexpr int KV_ROWS = KV_BQ * KV_SUB<W>;   // query rows per step
+constexpr int KV_LD = 64;                                  // floats of lse (and of -D) that a wave copies per step
 constexpr int KV_MAX_SLICES = 16;
 
 // ------------------------------------------------------------------------------------ host-side plan
@@ -36,6 +36,7 @@ struct BwdPlan {
     int sink_tiles_k, tpc_k;    // dK/dV window mode: key tiles of KV_BK positions in the sink / per chunk
     int kc_lo, ktiles;          // first key chunk and number of key tiles of the window part
     int fq0, fq1;               // query chunks whose rows take part (all of them unless a row window is set)
+    int waves, bk;              // of a workgroup of the dK/dV kernel, its keys
     int gl_total, gtiles;       // gather list length per KV head as the last query chunk sees it, its tiles
     int qch, nsl;               // query chunks per slice, slices per gather tile (<= KV_MAX_SLICES)
     int hsl, wsl;               // parts that the group's heads are split into: GATHER slices, WINDOW tiles
@@ -82,22 +83,37 @@ static int head_parts(const Dims& D, double rows, double bytes, double bytes_one
 static int64_t gather_workgroups(const Dims& D, const BwdPlan& P) { return (int64_t(D.B) * D.Hkv * P.nsl * P.hsl + 7) / 8 * 8 * P.gtiles; }
 static int64_t window_workgroups(const Dims& D, const BwdPlan& P) { return (int64_t(D.B) * D.Hkv * P.ktiles * P.wsl + 7) / 8 * 8; }
 
+// (head, query) rows that all workgroups of `bk` keys walk
+static double kv_rows(const Dims& D, int bk) {
+    const int gl = D.fq1 > 0 ? gather_count(D, D.fq1 - 1) : 0, kc_lo = D.fq0 - D.lp > 0 ? D.fq0 - D.lp : 0;
+    double chunks = 0.0;   // query chunks that see a list tile, over all tiles
+    for (int t = 0; t < (gl + bk - 1) / bk; ++t) {
+        const int qf = first_chunk_seeing(D, t * bk);
+        chunks += qf < D.fq1 ? D.fq1 - (qf > D.fq0 ? qf : D.fq0) : 0;
+    }
+    const int64_t ktiles = int64_t(D.fq1 - kc_lo) * ((D.L + bk - 1) / bk) + (D.row_begin == 0 ? (D.S + bk - 1) / bk : 0);
+    return double(D.B) * D.Hkv * D.L * D.G * (chunks + 0.75 * (D.lp + 1) * ktiles);
+}
+
 // split: with parts of the heads and the finest slices, where their rules ask for them; both take more workspace
-static BwdPlan make_plan(const Dims& D, bool split) {
+static BwdPlan plan_of(const Dims& D, bool split, int waves) {
     BwdPlan P;
+    P.waves = waves;
+    P.bk = 32 * P.waves;
+    const int step = P.waves == 8 ? KV_ROWS<8> : KV_ROWS<4>;
     const int sink_rows = D.S < D.n ? D.S : D.n;
     P.fq0 = D.fq0;
     P.fq1 = D.fq1;
     const int nqf = D.fq1 - D.fq0;                 // query chunks in the window
-    P.sink_tiles_k = D.row_begin == 0 ? (sink_rows + KV_BK - 1) / KV_BK : 0;   // sink keys see only sink queries here
-    P.tpc_k = (D.L + KV_BK - 1) / KV_BK;
+    P.sink_tiles_k = D.row_begin == 0 ? (sink_rows + P.bk - 1) / P.bk : 0;   // sink keys see only sink queries here
+    P.tpc_k = (D.L + P.bk - 1) / P.bk;
     P.kc_lo = D.fq0 - D.lp > 0 ? D.fq0 - D.lp : 0;  // the local window reaches lp chunks back
     P.ktiles = P.sink_tiles_k + (D.fq1 - P.kc_lo) * P.tpc_k;
     P.gl_total = D.fq1 > 0 ? gather_count(D, D.fq1 - 1) : 0;
-    P.gtiles = (P.gl_total + KV_BK - 1) / KV_BK;
+    P.gtiles = (P.gl_total + P.bk - 1) / P.bk;
     // aim at ~8192 query rows (x G heads) per workgroup, but never more than KV_MAX_SLICES slices.  head_dim 64: rows as the steps of
     // KV_ROWS take them, which end with a chunk (512 rows, lag 2, one head: 351 -> 62 us in the backward; all in one slice before)
-    const int64_t rows = D.d == 64 ? (int64_t(D.L) + KV_ROWS - 1) / KV_ROWS * KV_ROWS * D.G : int64_t(D.L) * D.G;   // of a chunk
+    const int64_t rows = D.d == 64 ? (int64_t(D.L) + step - 1) / step * step * D.G : int64_t(D.L) * D.G;   // of a chunk
     int64_t qch = (256 * 32) / rows;
     if (qch < 1) qch = 1;
     const int min_qch = (nqf + KV_MAX_SLICES - 1) / KV_MAX_SLICES;
@@ -106,14 +122,14 @@ static BwdPlan make_plan(const Dims& D, bool split) {
     // small problems: shorter slices (down to ~1024 query rows x G heads) until the gather workgroups -- about
     // half of the (tile, slice) grid sees any query -- fill the chip twice
     while (qch > min_qch && qch > 1 && (qch / 2) * rows >= 1024 &&
-           int64_t(D.B) * D.Hkv * P.gtiles * ((nqf + qch - 1) / qch) / 2 < 512)
+           int64_t(D.B) * D.Hkv * P.gtiles * ((nqf + qch - 1) / qch) * P.waves / 16 < 512)
         qch /= 2;
     // fewer than a quarter as many as CUs: down to 256 rows.  (2.6K tokens, 4 heads on 2, 2 requests, 24 workgroups: 164 ->
     // 157 us; 2.2K tokens in filling steps, 4 heads on 1: 710 -> 633 us.  From 84 workgroups on it costs more than it gives:
     // 5.5K tokens, 4 heads on 2, 4 requests 264 -> 272 us, 4K tokens, 8 heads on 8, 2 requests, 128 of them, 271 -> 295 us.)
     const int64_t coarse = qch;
     while (split && qch > min_qch && qch > 1 && (qch / 2) * rows >= 256 &&
-           int64_t(D.B) * D.Hkv * P.gtiles * ((nqf + qch - 1) / qch) / 2 < 64)
+           int64_t(D.B) * D.Hkv * P.gtiles * ((nqf + qch - 1) / qch) * P.waves / 16 < 64)
         qch /= 2;
     P.qch = int(qch);
     P.nsl = nqf > 0 ? (nqf + P.qch - 1) / P.qch : 0;
@@ -125,12 +141,7 @@ static BwdPlan make_plan(const Dims& D, bool split) {
     const int units = D.B * D.Hkv;
     const double w_rows = double(D.lp + 1) * D.L * D.G, g_rows = P.nsl > 0 ? double(P.qch) * D.L * D.G : 0.0;   // of a workgroup
     if (split && D.G > 1) {
-        double visible = 0.0;   // query chunks that see a list tile, over all tiles
-        for (int t = 0; t < P.gtiles; ++t) {
-            const int qf = first_chunk_seeing(D, t * KV_BK);
-            visible += qf < P.fq1 ? P.fq1 - (qf > P.fq0 ? qf : P.fq0) : 0;
-        }
-        const double per_cu = units * (visible * D.L * D.G + 0.75 * w_rows * P.ktiles) / 256.0;
+        const double per_cu = kv_rows(D, P.bk) * P.waves / 2048.0;   // per workgroup that runs at once
         const double row = 2.0 * units * D.d * 4;   // bytes of a row of dK and dV partials of all heads
         // a workgroup shorter than a quarter of a CU's work is no tail worth partials
         double saved = 0.0;
@@ -158,6 +169,29 @@ static BwdPlan make_plan(const Dims& D, bool split) {
     return P;
 }
 
+// Waves per workgroup of the dK/dV kernel.  Two workgroups of four (128 keys each) fit a CU, but read every query row twice, and 32 rows
+// per step instead of 64 leave half the time for a step's copies: 1 to 8 percent slower in long launches (backward of 32K tokens, 16
+// heads on 8: 5.30 and 5.71 ms; 32 on 8: 8.99 and 9.45).  In short ones their finer grain and the second workgroup's work beside the first
+// one's beginning and end count for more: 2 requests of 4K tokens, 8 heads on 8: 186 -> 161 us; 2 requests of 2.5K tokens, 16 on 4: 189 -> 134;
+// 4 requests of 4K tokens, 32 on 8: 1016 -> 885.  Short: less than 600 us of work for a CU, and no workgroup that is long beside that (which
+// would share its CU: 8.1K tokens, 16 on 4, lag 727, 364 us in a workgroup, 291 for a CU: 520 -> 565 us) unless it is short in itself.  Of 80
+// random shapes on this side of the line the backward takes 0.93 of the time (geometric mean), two 1.08.  head_dim 64: always (0.86 to 1.01).
+static BwdPlan make_plan(const Dims& D, bool split) {
+    int waves = 4;
+    if (D.d != 64) {
+        const double rate = rows_per_us(D), work = kv_rows(D, 256) / 256.0 / rate;   // us for a CU
+        if (work >= 600.0) {
+            waves = 8;
+        } else {
+            const BwdPlan P = plan_of(D, true, 8);
+            const double w = double(D.lp + 1) * D.L * ((D.G + P.wsl - 1) / P.wsl), g = P.nsl > 0 ? double(P.qch) * D.L * ((D.G + P.hsl - 1) / P.hsl) : 0.0;
+            const double longest = (w > g ? w : g) / rate;
+            waves = longest <= 0.8 * work || longest <= 100.0 ? 4 : 8;
+        }
+    }
+    return plan_of(D, split, waves);
+}
+
 // What a plan needs does not grow steadily from one filling step to the next: a split step may need more than a later, longer
 // one that is not split (up to three times, in every sixth of 2400 shapes).  A call whose workspace holds the plan without splits, as
 // one that was sized for the last step does, takes that plan.
@@ -178,11 +212,11 @@ size_t attn_bwd_mfma_ws_min_bytes(const Dims& D) {
 
 // the grids of the forward, dQ and dK/dV launches (the reduction's threads are fewer than the bytes of its partials)
 bool mfma_grids_fit(const Dims& D) {
-    const int waves = qtile_waves(D);
-    const QTileMap M = make_qtile_map(D, waves);
-    const BwdPlan P = make_plan(D, true);
-    return grid_fits(int64_t(D.B) * D.Hkv * M.per_unit, 64 * waves) &&
-           grid_fits(gather_workgroups(D, P) + window_workgroups(D, P), KV_THREADS);
+    const int64_t units = int64_t(D.B) * D.Hkv;
+    const BwdPlan P = make_plan(D, true), P8 = plan_of(D, true, 8);   // also where workgroups have four waves: which shapes are served does not change with it
+    return grid_fits(units * make_qtile_map(D, 8).per_unit, 512) && grid_fits(units * make_qtile_map(D, 4).per_unit, 256) &&
+           grid_fits(gather_workgroups(D, P8) + window_workgroups(D, P8), 512) &&
+           grid_fits(gather_workgroups(D, P) + window_workgroups(D, P), 64 * P.waves);
 }
 
 // ------------------------------------------------------------------------------------ dQ
@@ -480,8 +514,8 @@ __global__ __launch_bounds__(64 * WAVES, 2) void k_bwd_dq(Dims D, const bf16_t* 
 
 // ------------------------------------------------------------------------------------ dK, dV
 // One sub-step (32 query rows: rows rowbase .. rowbase+31 of the stage tiles) of the key-outer walk for
-// one wave.  sLD holds this wave's copy of the stage rows' lse in the logits' units (floats 0..KV_ROWS-1) and -D
-// (the next KV_ROWS floats; D = rowsum(dO * O), negated by the query-outer kernel that wrote it).  r0 = first row of the sub-step; rows >= tb are padding.
+// one wave.  sLD holds this wave's copy of the stage rows' lse in the logits' units (floats 0 ..) and -D
+// (KV_LD floats on; D = rowsum(dO * O), negated by the query-outer kernel that wrote it).  r0 = first row of the sub-step; rows >= tb are padding.
 // lim_u: GATHER (steps never straddle a chunk): the largest gather-list entry the step's chunk sees.
 // The wave's K fragments are in registers, its V rows in LDS (sVw): K fragments and the accumulators
 // fill the register file.
@@ -510,7 +544,7 @@ __device__ __forceinline__ void dkv_step(const Dims& D, const unsigned char* sQ,
     // dA - D comes out of the MFMAs themselves: the accumulators start from -D of their rows (sLD holds -D)
 #pragma unroll
     for (int a4 = 0; a4 < 4; ++a4) {
-        const f32x4 d4 = *reinterpret_cast<const f32x4*>(sLD + KV_ROWS + rowbase + 8 * a4 + 4 * g);
+        const f32x4 d4 = *reinterpret_cast<const f32x4*>(sLD + KV_LD + rowbase + 8 * a4 + 4 * g);
 #pragma unroll
         for (int nb = 0; nb < KV_NB; ++nb)
 #pragma unroll
@@ -606,11 +640,11 @@ __device__ __forceinline__ void dkv_step(const Dims& D, const unsigned char* sQ,
 // see them, and leave the others of the step alone, although a sub-step multiplies its masked pairs by zero: the rows become zeros in
 // the stage's tiles.  A = exp(S - lse) is NaN where it is seen and 0 where it is masked.  Every wave clears all of them before
 // it reads the tiles: its own reads come after its own writes, and all waves write the same.
-template <int DH>
+template <int DH, int W>
 __device__ __forceinline__ void clear_odd_rows(unsigned char* sQ, unsigned char* sG, const float* sLD, int lane) {
-    static_assert(KV_ROWS == 64, "a lane looks at a row");
+    static_assert(KV_ROWS<W> <= 64, "a lane looks at a row");
     const float l = sLD[lane];
-    unsigned long long rows = __builtin_amdgcn_ballot_w64(l != l);
+    unsigned long long rows = __builtin_amdgcn_ballot_w64(l != l && lane < KV_ROWS<W>);
     if (rows == 0) return;
     for (; rows; rows &= rows - 1) {
         const int r = __builtin_ctzll(rows);
@@ -622,8 +656,7 @@ __device__ __forceinline__ void clear_odd_rows(unsigned char* sQ, unsigned char*
     asm volatile("" ::: "memory");   // the tiles are read through integer addresses
 }
 
-// Two stages of 64 rows: one barrier per 64 MFMAs of a wave; the copies of the next stage run during
-// the two sub-steps of the current one.
+// Two stages of KV_ROWS rows, one barrier per step; the copies of the next stage run during the sub-steps of the current one.
 
 // LDS of the dK/dV kernel: two stages of (Q rows, dO rows, per-wave lse|D) -- separate arrays so that reads
 // of one stage need not wait for the asynchronous fill of the other -- and the workgroup's V rows
@@ -633,12 +666,12 @@ struct KvLds {
     unsigned char* sVk;
 };
 // one set of arrays for both kinds of workgroup (inside the body's template each would get a set of its own)
-template <int DH>
+template <int DH, int W>
 __device__ __forceinline__ KvLds kv_lds() {
-    __shared__ __attribute__((aligned(256))) unsigned char sQ0[KV_ROWS * ROW_BYTES<DH>], sQ1[KV_ROWS * ROW_BYTES<DH>];
-    __shared__ __attribute__((aligned(256))) unsigned char sG0[KV_ROWS * ROW_BYTES<DH>], sG1[KV_ROWS * ROW_BYTES<DH>];
-    __shared__ __attribute__((aligned(16))) float sL0[KV_WAVES * 2 * KV_ROWS], sL1[KV_WAVES * 2 * KV_ROWS];
-    __shared__ __attribute__((aligned(256))) unsigned char sVk[KV_BK * ROW_BYTES<DH>];
+    __shared__ __attribute__((aligned(256))) unsigned char sQ0[KV_ROWS<W> * ROW_BYTES<DH>], sQ1[KV_ROWS<W> * ROW_BYTES<DH>];
+    __shared__ __attribute__((aligned(256))) unsigned char sG0[KV_ROWS<W> * ROW_BYTES<DH>], sG1[KV_ROWS<W> * ROW_BYTES<DH>];
+    __shared__ __attribute__((aligned(16))) float sL0[W * 2 * KV_LD], sL1[W * 2 * KV_LD];
+    __shared__ __attribute__((aligned(256))) unsigned char sVk[KV_BK<W> * ROW_BYTES<DH>];
     return KvLds{sQ0, sQ1, sG0, sG1, sL0, sL1, sVk};
 }
 
@@ -686,7 +719,7 @@ __device__ __forceinline__ int listed_entry(const Dims& D, const BwdPlan& P, con
     return -1;
 }
 
-template <int DH, bool GATHER>
+template <int DH, int W, bool GATHER>
 __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K,
                                          const bf16_t* __restrict__ V, const bf16_t* __restrict__ Kc,
                                          const bf16_t* __restrict__ Vc, const bf16_t* __restrict__ dO,
@@ -695,7 +728,7 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
                                          bf16_t* __restrict__ dV, float* __restrict__ accK, float* __restrict__ accV,
                                          float* __restrict__ part, float* __restrict__ wpart, const BwdPlan& P,
                                          const int block) {
-    const KvLds sh = kv_lds<DH>();
+    const KvLds sh = kv_lds<DH, W>();
     unsigned char *const sQ0 = sh.sQ0, *const sQ1 = sh.sQ1, *const sG0 = sh.sG0, *const sG1 = sh.sG1;
     float *const sL0 = sh.sL0, *const sL1 = sh.sL1;
     unsigned char* const sVk = sh.sVk;
@@ -721,7 +754,7 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
             if (grp >= units * P.nsl * P.hsl) return;
             unit = grp % units;
             slot = P.nsl * P.hsl - 1 - grp / units;   // latest slices (most list tiles) first
-            key0 = (seq % P.gtiles) * KV_BK;
+            key0 = (seq % P.gtiles) * KV_BK<W>;
             h0 = slot % P.hsl * D.G / P.hsl;
             h1 = (slot % P.hsl + 1) * D.G / P.hsl;
         } else {
@@ -750,13 +783,13 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
     } else {
         const int tix = key0;
         if (tix < P.sink_tiles_k) {
-            key0 = tix * KV_BK;
+            key0 = tix * KV_BK<W>;
             key_end = D.S < D.n ? D.S : D.n;
             tb = key_end < D.row_end ? key_end : D.row_end;   // only sink queries see sink keys through the window
         } else {
             const int tt = tix - P.sink_tiles_k;
             const int kc = P.kc_lo + tt / P.tpc_k;
-            key0 = D.S + kc * D.L + (tt % P.tpc_k) * KV_BK;
+            key0 = D.S + kc * D.L + (tt % P.tpc_k) * KV_BK<W>;
             const int64_t e = int64_t(D.S) + int64_t(kc + 1) * D.L;
             key_end = e < D.n ? int(e) : D.n;
             const int64_t e2 = int64_t(D.S) + (int64_t(kc) + 1 + D.lp) * D.L;
@@ -768,20 +801,20 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
     }
     // Steps of KV_ROWS rows.  WINDOW: consecutive rows of [ta, tb).  GATHER: chunk by chunk (the last step
     // of a chunk may be partial), so that one step never sees two different gather-list prefixes.
-    const int spc = (D.L + KV_ROWS - 1) / KV_ROWS;                               // GATHER: steps per chunk
-    const int sph = GATHER ? ((tb - ta + D.L - 1) / D.L) * spc : (tb - ta + KV_ROWS - 1) / KV_ROWS;   // steps per head
+    const int spc = (D.L + KV_ROWS<W> - 1) / KV_ROWS<W>;                               // GATHER: steps per chunk
+    const int sph = GATHER ? ((tb - ta + D.L - 1) / D.L) * spc : (tb - ta + KV_ROWS<W> - 1) / KV_ROWS<W>;   // steps per head
     const int nsteps = sph * (h1 - h0);
     // first row, row end and chunk-visible limit of a step
     auto step_rows = [&](int sidx, int& r0, int& rend, int& lim_u) {
         const int w = sidx % sph;
         if (GATHER) {
             const int c = qa + w / spc;
-            r0 = D.S + c * D.L + (w % spc) * KV_ROWS;
+            r0 = D.S + c * D.L + (w % spc) * KV_ROWS<W>;
             const int64_t e = int64_t(D.S) + int64_t(c + 1) * D.L;
             rend = e < tb ? int(e) : tb;
             lim_u = gather_count(D, c) - 1;
         } else {
-            r0 = ta + w * KV_ROWS;
+            r0 = ta + w * KV_ROWS<W>;
             rend = tb;
             lim_u = 0;
         }
@@ -796,8 +829,8 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
         const int hq = h * D.G + h0 + gi;
         const int64_t base = b * D.qs[0] + hq * D.qs[1];
 #pragma unroll
-        for (int i = 0; i < KV_ROWS / (COPY_ROWS<DH> * KV_WAVES); ++i) {
-            const int rc = (KV_ROWS / KV_WAVES) * wave + COPY_ROWS<DH> * i;
+        for (int i = 0; i < KV_ROWS<W> / (COPY_ROWS<DH> * W); ++i) {
+            const int rc = (KV_ROWS<W> / W) * wave + COPY_ROWS<DH> * i;
             const int row = async_row<DH>(rc, lane);
             const int t = min(r0 + row, rend - 1);
             const int64_t off = base + int64_t(t) * D.qs[2] + async_chunk<DH>(row, lane) * 8;
@@ -805,8 +838,8 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
             async_rows<DH>(dO + off, sG, rc);
         }
         const int64_t rid = (int64_t(b) * D.Hq + hq) * D.lse_stride + min(r0 + lane, rend - 1);
-        async_copy4(lse + rid, sL + wave * 2 * KV_ROWS);
-        async_copy4(Dsum + rid, sL + wave * 2 * KV_ROWS + KV_ROWS);
+        async_copy4(lse + rid, sL + wave * 2 * KV_LD);
+        async_copy4(Dsum + rid, sL + wave * 2 * KV_LD + KV_LD);
     };
 
     // the first step's rows are on their way while the keys are read (through idx: two trips to memory)
@@ -860,11 +893,11 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
     {                                                                                                    \
         wait_vmcnt<0>();     /* this wave's copies for `step` have landed */                             \
         __syncthreads();     /* ... everybody's have, and everybody is done with the other stage */      \
-        if constexpr (DH == 64) clear_odd_rows<DH>(sQ, sG, sL + wave * 2 * KV_ROWS, lane);              \
+        if constexpr (DH == 64) clear_odd_rows<DH, W>(sQ, sG, sL + wave * 2 * KV_LD, lane);              \
         if ((step) + 1 < nsteps) issue((step) + 1, sQn, sGn, sLn);                                       \
         int r0s_, rend_, lim_u_;                                                                         \
         step_rows(step, r0s_, rend_, lim_u_);                                                            \
-        _Pragma("unroll 1") for (int sub_ = 0; sub_ < KV_SUB; ++sub_) {                                    \
+        _Pragma("unroll 1") for (int sub_ = 0; sub_ < KV_SUB<W>; ++sub_) {                                    \
             const int r0_ = r0s_ + sub_ * KV_BQ;                                                         \
             /* nothing to do: padding rows or keys only, rows that see none of the wave's keys.  The flag */ \
             /* is made opaque so that each sub-step body stays a basic block of its own: merged into one */ \
@@ -876,7 +909,7 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
             const bool full_ = wave_keys_valid && r0_ + KV_BQ <= rend_ &&                                \
                                (GATHER ? lim_u_ >= wave_key0 + 32 * KV_NB - 1 : r0_ >= wave_key0 + 32 * KV_NB - 1); \
             if (run_)                                                                                    \
-                dkv_step<DH, GATHER>(D, sQ, sG, sL + wave * 2 * KV_ROWS, kf, sVw, lo, dk, dv, r0_, rend_, kcmp, lim_u_, \
+                dkv_step<DH, GATHER>(D, sQ, sG, sL + wave * 2 * KV_LD, kf, sVw, lo, dk, dv, r0_, rend_, kcmp, lim_u_, \
                                  !full_, c2, lane, sub_ * KV_BQ);                                        \
         }                                                                                                \
     }
@@ -951,8 +984,8 @@ __device__ __forceinline__ void dkv_body(const Dims& D, const bf16_t* __restrict
 }
 
 // One launch for all of dK/dV, so that the chip has one tail, not two: the part with the longer workgroups first.
-template <int DH>
-__global__ __launch_bounds__(KV_THREADS, KV_WAVES == 8 ? 2 : 1) void k_bwd_dkv(Dims D, const bf16_t* __restrict__ Q,
+template <int DH, int W>
+__global__ __launch_bounds__(64 * W, 2) void k_bwd_dkv(Dims D, const bf16_t* __restrict__ Q,
                                                                                 const bf16_t* __restrict__ K,
                                                                                 const bf16_t* __restrict__ V,
                                                                                 const bf16_t* __restrict__ Kc,
@@ -970,8 +1003,8 @@ __global__ __launch_bounds__(KV_THREADS, KV_WAVES == 8 ? 2 : 1) void k_bwd_dkv(D
     const int first = P.window_first ? P.window_wgs : P.gather_wgs;
     const bool in_first = int(blockIdx.x) < first;
     const int block = in_first ? blockIdx.x : blockIdx.x - first;
-    if (in_first != bool(P.window_first)) dkv_body<DH, true>(D, Q, K, V, Kc, Vc, dO, lse, Dsum, idx, dK, dV, accK, accV, part, wpart, P, block);
-    else dkv_body<DH, false>(D, Q, K, V, Kc, Vc, dO, lse, Dsum, idx, dK, dV, accK, accV, part, wpart, P, block);
+    if (in_first != bool(P.window_first)) dkv_body<DH, W, true>(D, Q, K, V, Kc, Vc, dO, lse, Dsum, idx, dK, dV, accK, accV, part, wpart, P, block);
+    else dkv_body<DH, W, false>(D, Q, K, V, Kc, Vc, dO, lse, Dsum, idx, dK, dV, accK, accV, part, wpart, P, block);
 }
 
 // dK, dV of the listed positions (sink tokens and survivors): the WINDOW contribution plus the GATHER slices
@@ -1024,7 +1057,7 @@ __global__ __launch_bounds__(256) void k_bwd_dkv_reduce(Dims D, const int32_t* _
             x = *reinterpret_cast<const f32x4*>(p0 + size_t(slots) * part_stride);
             y = *reinterpret_cast<const f32x4*>(p0 + size_t(slots) * part_stride + part_v);
         }
-        const int qf0 = first_chunk_seeing(D, (j / KV_BK) * KV_BK);
+        const int qf0 = first_chunk_seeing(D, j / P.bk * P.bk);
         if (qf0 < P.fq1)
             for (int sl = qf0 > P.fq0 ? (qf0 - P.fq0) / P.qch * P.hsl : 0; sl < slots; ++sl) {
                 x += *reinterpret_cast<const f32x4*>(p0 + size_t(sl) * part_stride);
@@ -1125,7 +1158,7 @@ hipError_t launch_attn_bwd_mfma(const Dims& D, const void* Q, const void* K, con
     float* wpart = reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + P.off_wpart);
     const int64_t wgs = int64_t(P.gather_wgs) + P.window_wgs;
     if (wgs > 0)
-        LRSA_TIMED_LAUNCH("k_bwd_dkv", st, (D.d == 64 ? k_bwd_dkv<64> : k_bwd_dkv<128>), dim3((unsigned)wgs), dim3(KV_THREADS), 0, st, D, q, k, v, kc, vc, g,
+        LRSA_TIMED_LAUNCH("k_bwd_dkv", st, (D.d == 64 ? k_bwd_dkv<64, 4> : P.waves == 4 ? k_bwd_dkv<128, 4> : k_bwd_dkv<128, 8>), dim3((unsigned)wgs), dim3(64 * P.waves), 0, st, D, q, k, v, kc, vc, g,
                           lse2, Dsum, idx, (bf16_t*)dK, (bf16_t*)dV, accK, accV, part, wpart, P);
     const int64_t entries = int64_t(D.B) * D.Hkv * P.gl_total;
     float *dkc = nullptr, *dvc = nullptr;
