@@ -10,7 +10,7 @@
 // bytes of row 4*q4 + i, channels 64*grp + 4c .. +3: one channel for each of four output blocks, whose row m is channel
 // 64*grp + 4m + block ("column fragment").
 //
-// Query-outer (forward, dQ): a workgroup owns 16 query rows of one head; its F32_WAVES waves take the 16-key tiles of
+// Query-outer (forward, dQ): a workgroup owns 16 query rows of one head; its W waves take the 16-key tiles of
 // the visible stream (gather list, then the local window) in turn, each with a softmax state of its own, and are merged in
 // LDS in a fixed order.  Key-outer (dK, dV): a workgroup owns 16 keys that are seen by about the same rows -- sink tokens,
 // survivors of one chunk (all later rows), or the rest of a chunk (up to the end of the local window) -- and its waves take
@@ -27,6 +27,18 @@ namespace lrsa {
 typedef float fx4 __attribute__((ext_vector_type(4)));
 
 template <int DH> constexpr int F32_WAVES = DH == 64 ? 16 : 8;   // 128 (256) registers per lane
+
+// Waves of a query-outer workgroup: F32_WAVES, so that few query tiles still fill the chip, or half of that, or four, where there are
+// more of them: a wave then takes more than the two or three key tiles that it has of 16 waves, and fewer states are merged.  As long as
+// the chip holds the waves (head_dim 128: twice as many; with only as many 1.2K tokens, 4 heads on 4, take 31 us instead of 23).
+// 2 requests of 2.2K tokens, 8 heads of 64 on 2: forward 98 -> 72 us, dQ 151 -> 107; 2 requests of 2.4K tokens, 16 heads of 128 on 4:
+// forward 457 -> 350 us.  Errors against 64 bits 0.95 to 1.00 of those with all waves; two waves at head_dim 128 are as fast, with 1.003.
+static int f32_query_waves(const Dims& D, int64_t tiles) {
+    const int most = D.d == 64 ? F32_WAVES<64> : F32_WAVES<128>, rounds = D.d == 64 ? 1 : 2;
+    int w = most;
+    while (w > 4 && tiles * w > rounds * 256 * int64_t(most)) w /= 2;
+    return w;
+}
 
 __device__ __forceinline__ fx4 mfma_f32(float a, float b, fx4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
@@ -154,11 +166,10 @@ __device__ __forceinline__ int stream_row(const Dims& D, const int32_t* idx_h, i
 }
 
 // ------------------------------------------------------------------------------------ forward
-template <int DH>
-__global__ __launch_bounds__(64 * F32_WAVES<DH>) void k_fwd_f32(Dims D, const float* __restrict__ Q, const float* __restrict__ K,
+template <int DH, int W>
+__global__ __launch_bounds__(64 * W, DH == 64 ? 4 : 2) void k_fwd_f32(Dims D, const float* __restrict__ Q, const float* __restrict__ K,
                                                                 const float* __restrict__ V, const int32_t* __restrict__ idx,
                                                                 float* __restrict__ O, float* __restrict__ lse, QTiles T) {
-    constexpr int W = F32_WAVES<DH>;
     __shared__ __attribute__((aligned(16))) float sO[W][16 * LROW<DH>];
     __shared__ float sM[W][16], sL[W][16];
     const int heads = D.B * D.Hq;
@@ -235,13 +246,12 @@ __global__ __launch_bounds__(64 * F32_WAVES<DH>) void k_fwd_f32(Dims D, const fl
 }
 
 // ------------------------------------------------------------------------------------ backward: dQ (and D)
-template <int DH>
-__global__ __launch_bounds__(64 * F32_WAVES<DH>) void k_bwd_dq_f32(Dims D, const float* __restrict__ Q, const float* __restrict__ K,
+template <int DH, int W>
+__global__ __launch_bounds__(64 * W, DH == 64 ? 4 : 2) void k_bwd_dq_f32(Dims D, const float* __restrict__ Q, const float* __restrict__ K,
                                                                    const float* __restrict__ V, const float* __restrict__ O,
                                                                    const float* __restrict__ dO, const float* __restrict__ lse,
                                                                    const int32_t* __restrict__ idx, float* __restrict__ dQ,
                                                                    float* __restrict__ Dsum, QTiles T) {
-    constexpr int W = F32_WAVES<DH>;
     __shared__ __attribute__((aligned(16))) float sQ[W][16 * LROW<DH>];
     const int heads = D.B * D.Hq;
     const int bh = blockIdx.x % heads, b = bh / D.Hq, hq = bh % D.Hq, h = hq / D.G;
@@ -470,7 +480,10 @@ bool f32_tiles_supported(const Dims& D) {
 template <int DH>
 static hipError_t run_fwd(const Dims& D, const float* Q, const float* K, const float* V, const int32_t* idx, float* O, float* lse, hipStream_t st) {
     const QTiles T = make_qtiles(D);
-    LRSA_TIMED_LAUNCH("k_fwd_f32", st, k_fwd_f32<DH>, dim3(T.count * D.B * D.Hq), dim3(64 * F32_WAVES<DH>), 0, st, D, Q, K, V, idx, O, lse, T);
+    constexpr int W = F32_WAVES<DH>;
+    const int w = f32_query_waves(D, int64_t(T.count) * D.B * D.Hq);
+    LRSA_TIMED_LAUNCH("k_fwd_f32", st, (w == W ? k_fwd_f32<DH, W> : w == 8 ? k_fwd_f32<DH, 8> : k_fwd_f32<DH, 4>), dim3(T.count * D.B * D.Hq),
+                      dim3(64 * w), 0, st, D, Q, K, V, idx, O, lse, T);
     return hipGetLastError();
 }
 hipError_t launch_attn_fwd_f32(const Dims& D, const void* Q, const void* K, const void* V, const int32_t* idx, void* O, float* lse, hipStream_t st) {
@@ -493,8 +506,10 @@ static hipError_t run_bwd(const Dims& D, const float* Q, const float* K, const f
     float* part = slices > 1 ? reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + f32_part_off(D)) : nullptr;
     const QTiles QT = make_qtiles(D);
     const KTiles KT = make_ktiles(D);
-    LRSA_TIMED_LAUNCH("k_bwd_dq_f32", st, k_bwd_dq_f32<DH>, dim3(QT.count * D.B * D.Hq), dim3(64 * F32_WAVES<DH>), 0, st, D, Q, K, V, O, dO, lse,
-                      idx, dQ, Dsum, QT);
+    constexpr int W = F32_WAVES<DH>;
+    const int w = f32_query_waves(D, int64_t(QT.count) * D.B * D.Hq);
+    LRSA_TIMED_LAUNCH("k_bwd_dq_f32", st, (w == W ? k_bwd_dq_f32<DH, W> : w == 8 ? k_bwd_dq_f32<DH, 8> : k_bwd_dq_f32<DH, 4>),
+                      dim3(QT.count * D.B * D.Hq), dim3(64 * w), 0, st, D, Q, K, V, O, dO, lse, idx, dQ, Dsum, QT);
     LRSA_TIMED_LAUNCH("k_bwd_dkv_f32", st, k_bwd_dkv_f32<DH>, dim3(KT.count * D.B * D.Hkv * slices), dim3(64 * F32_KV_WAVES), 0, st, D, Q, K, V, dO,
                       lse, Dsum, idx, dK, dV, part, slices, KT);
     if (part)

@@ -55,3 +55,26 @@ def test_every_row_once(cfg, d):
     if d == 128:
         for k in ("O", "lse", "dQ"):
             assert torch.equal(got[lrsa.IMPL_AUTO][k], got[lrsa.IMPL_COMPACT][k]), k
+
+
+@pytest.mark.parametrize("d,B,Hq,Hkv", [(64, 1, 16, 4), (64, 3, 32, 8), (128, 1, 16, 4), (128, 3, 32, 8)])   # 8, 4, 8 and 4 waves per workgroup
+def test_fp32_with_fewer_waves(d, B, Hq, Hkv):
+    """Many query tiles: fewer waves share a tile's keys.  The bar of the fp32 kernels: a quarter above the plain kernels' error, plus an ulp."""
+    w = inputs.small_workload(d=d, dtype="f32", n=5 + 5 * 50 + 33, L=50, S=5, K=17, Hq=Hq, Hkv=Hkv, B=B)
+    x = inputs.make_inputs(w)
+    xf = {k: v.numpy() for k, v in x.items()}
+    idx = ref.select(ref.score(xf["K"], xf["V"], w.S, w.L), w.S, w.L, w.K)
+    O, lse = ref.attn_fwd_dense(xf["Q"], xf["K"], xf["V"], idx, w.S, w.L)
+    g = ref.attn_bwd_dense(xf["Q"], xf["K"], xf["V"], xf["dO"], idx, w.S, w.L)
+    want = dict(O=O, lse=lse, dQ=g[0], dK=g[1], dV=g[2])
+    xd = {k: v.to(DEV) for k, v in x.items()}
+    idx = torch.from_numpy(idx).to(DEV)
+    errs = []
+    for impl in (lrsa.IMPL_AUTO, lrsa.IMPL_GENERIC):
+        p = lrsa.params_for(xd["Q"], xd["K"], sink=w.S, lag=w.L, topk=w.K, impl=impl)
+        O, lse = lrsa.lrsa_attn_fwd(p, xd["Q"], xd["K"], xd["V"], idx)
+        dQ, dK, dV = lrsa.lrsa_attn_bwd(p, xd["Q"], xd["K"], xd["V"], O, xd["dO"], lse, idx)
+        got = dict(O=O, lse=lse, dQ=dQ, dK=dK, dV=dV)
+        errs.append({k: np.linalg.norm(got[k].double().cpu().numpy() - r) / np.linalg.norm(r) for k, r in want.items()})
+    for k in want:
+        assert errs[0][k] <= 1.25 * errs[1][k] + 2.0 ** -23, f"{k}: {errs[0][k]:.3e}, the plain kernels {errs[1][k]:.3e}"
