@@ -31,8 +31,9 @@ template <int DH> constexpr int F32_WAVES = DH == 64 ? 16 : 8;   // 128 (256) re
 // Waves of a query-outer workgroup: F32_WAVES, so that few query tiles still fill the chip, or half of that, or four, where there are
 // more of them: a wave then takes more than the two or three key tiles that it has of 16 waves, and fewer states are merged.  As long as
 // the chip holds the waves (head_dim 128: twice as many; with only as many 1.2K tokens, 4 heads on 4, take 31 us instead of 23).
-// 2 requests of 2.2K tokens, 8 heads of 64 on 2: forward 98 -> 72 us, dQ 151 -> 107; 2 requests of 2.4K tokens, 16 heads of 128 on 4:
-// forward 457 -> 350 us.  Errors against 64 bits 0.95 to 1.00 of those with all waves; two waves at head_dim 128 are as fast, with 1.003.
+// 2 requests of 2.0K tokens, 8 heads of 64 on 2: forward 97 -> 72 us, backward 345 -> 300; 2 requests of 2.4K tokens, 16 heads of 128 on 4:
+// forward 457 -> 349 us, backward 1370 -> 1289.  Errors of O, lse and dQ against 64 bits 0.94 to 1.001 of those with all waves; of dK and dV,
+// whose kernel is the same and reads those, 0.94 to 1.008, 0.99 on average.  Two waves at head_dim 128 are as fast, with 1.003.
 static int f32_query_waves(const Dims& D, int64_t tiles) {
     const int most = D.d == 64 ? F32_WAVES<64> : F32_WAVES<128>, rounds = D.d == 64 ? 1 : 2;
     int w = most;
