@@ -193,6 +193,47 @@ __device__ __forceinline__ float wave_sum(float v) { return wave_all(v, [](float
 __device__ __forceinline__ float wave_max(float v) { return wave_all(v, [](float a, float b) { return fmaxf(a, b); }); }
 // sum over the 16 lanes of a row, every lane gets the total
 __device__ __forceinline__ float row16_sum(float v) { return row16_all(v, [](float a, float b) { return a + b; }); }
+// sums over aligned groups of 8, 16 or 32 lanes of N values together, so that their chains overlap; every lane gets its group's; the pairs
+// are those of a butterfly 16, 8, 4, 2, 1
+template <int LANES, int N>
+__device__ __forceinline__ void group_sums(float (&v)[N]) {
+    static_assert(LANES == 8 || LANES == 16 || LANES == 32, "group size");
+    if constexpr (LANES == 8) {
+        // of the two row shifts by 4 each writes the half of the lanes whose source lies in their own group of 8
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const int x = __float_as_int(v[j]);
+            const int up = __builtin_amdgcn_update_dpp(0, x, 0x104, 0xf, 0x5, false);            // row_shl:4 into lanes 0-3 and 8-11
+            v[j] += __int_as_float(__builtin_amdgcn_update_dpp(up, x, 0x114, 0xf, 0xa, false));  // row_shr:4 into lanes 4-7 and 12-15
+            v[j] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v[j]), 0x4e, 0xf, 0xf, false));   // quad_perm 2 3 0 1
+            v[j] += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v[j]), 0xb1, 0xf, 0xf, false));   // quad_perm 1 0 3 2
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            if constexpr (LANES == 32) {
+                const lanes_u32x2 a = pair16(__float_as_uint(v[j]));
+                v[j] = __uint_as_float(a.x) + __uint_as_float(a.y);
+            }
+            v[j] = row16_sum(v[j]);
+        }
+    }
+}
+// op (min or max) of N values over the lanes l, l + LANES, l + 2 * LANES ... of a wave
+template <int LANES, int N, class Op>
+__device__ __forceinline__ void across_groups(float (&v)[N], Op op) {
+    static_assert(LANES == 8 || LANES == 16 || LANES == 32, "group size");
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        if constexpr (LANES == 8) v[j] = op(v[j], __uint_as_float(row_ror<8>(__float_as_uint(v[j]))));
+        if constexpr (LANES <= 16) {
+            const lanes_u32x2 c = pair16(__float_as_uint(v[j]));
+            v[j] = op(__uint_as_float(c.x), __uint_as_float(c.y));
+        }
+        const lanes_u32x2 a = pair32(__float_as_uint(v[j]));
+        v[j] = op(__uint_as_float(a.x), __uint_as_float(a.y));
+    }
+}
 __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
     lanes_u32x2 a = pair32(v);
     v = a.x < a.y ? a.x : a.y;

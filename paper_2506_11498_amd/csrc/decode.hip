@@ -90,7 +90,7 @@ __device__ __forceinline__ void move_words(int32_t* A, int dst0, int count, SrcF
     }
 }
 
-template <typename T>
+template <typename T, int DH>
 __global__ __launch_bounds__(FUSED_THREADS) void k_cache_compress(Dims D, T* __restrict__ Kc, T* __restrict__ Vc,
                                                                   int32_t* __restrict__ pos, int len, int done) {
     const int bh = blockIdx.x, b = bh / D.Hkv, h = bh % D.Hkv;
@@ -100,7 +100,7 @@ __global__ __launch_bounds__(FUSED_THREADS) void k_cache_compress(Dims D, T* __r
     __shared__ ScoreLds sh;
     __shared__ SelectLds sel;
     __shared__ int32_t keep[FUSED_MAX_L];  // the K surviving rows, relative to base, ascending
-    score_chunk_block<T>(D.L, D.d, D.ddof, Kh + int64_t(base) * D.ks[2], Kh + int64_t(base + D.L) * D.ks[2],
+    score_chunk_block<T, DH>(D.L, D.ddof, Kh + int64_t(base) * D.ks[2], Kh + int64_t(base + D.L) * D.ks[2],
                          Vh + int64_t(base) * D.ks[2], Vh + int64_t(base + D.L) * D.ks[2], D.ks[2], sh, nullptr);
     __syncthreads();
     select_topk_block<FUSED_THREADS>(reinterpret_cast<const uint32_t*>(sh.sig[0]), D.L, D.K, 0, keep, sel);
@@ -125,10 +125,12 @@ hipError_t launch_cache_compress(const Dims& D, void* Kc, void* Vc, int32_t* pos
                                  hipStream_t st) {
     for (int s = 0; s < steps; ++s) {
         if (D.dtype == 1)
-            LRSA_TIMED_LAUNCH("k_cache_compress", st, k_cache_compress<bf16_t>, dim3(D.B * D.Hkv), dim3(FUSED_THREADS), 0, st, D,
+            LRSA_TIMED_LAUNCH("k_cache_compress", st, (D.d == 64 ? k_cache_compress<bf16_t, 64> : k_cache_compress<bf16_t, 128>),
+                              dim3(D.B * D.Hkv), dim3(FUSED_THREADS), 0, st, D,
                               (bf16_t*)Kc, (bf16_t*)Vc, pos, len, done);
         else
-            LRSA_TIMED_LAUNCH("k_cache_compress", st, k_cache_compress<float>, dim3(D.B * D.Hkv), dim3(FUSED_THREADS), 0, st, D,
+            LRSA_TIMED_LAUNCH("k_cache_compress", st, (D.d == 64 ? k_cache_compress<float, 64> : k_cache_compress<float, 128>),
+                              dim3(D.B * D.Hkv), dim3(FUSED_THREADS), 0, st, D,
                               (float*)Kc, (float*)Vc, pos, len, done);
         len -= D.L - D.K;
         done += 1;

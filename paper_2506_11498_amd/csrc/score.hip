@@ -86,13 +86,13 @@ __global__ __launch_bounds__(SCORE_THREADS) void k_minmax(Dims D, const T* __res
     }
 }
 
-template <typename T>
+template <typename T, int DH>
 __global__ __launch_bounds__(SCORE_THREADS) void k_sigma(Dims D, const T* __restrict__ Kp, const T* __restrict__ Vp,
                                                           const float* __restrict__ mm, float* __restrict__ sigma,
                                                           int rows_wg) {
     constexpr int VEC = Elem<T>::VEC;
-    const int lpr = D.d / VEC;
-    const int rpp = SCORE_THREADS / lpr;
+    constexpr int lpr = DH / VEC;
+    constexpr int rpp = SCORE_THREADS / lpr;
     const int split = blockIdx.x, p = blockIdx.y;
     const int z = blockIdx.z & 1, bh = blockIdx.z >> 1;
     const int b = bh / D.Hkv, h = bh % D.Hkv;
@@ -119,13 +119,13 @@ __global__ __launch_bounds__(SCORE_THREADS) void k_sigma(Dims D, const T* __rest
     // partial (coalesced, the loads of different partials independent of each other), then every thread picks
     // up its own channels from LDS
     __shared__ float s_mm[2 * 128];
-    if (threadIdx.x < 2 * D.d) {
-        const float* src = mm + unit * nsplit * 2 * D.d + threadIdx.x;
-        const bool is_min = threadIdx.x < D.d;
+    if (threadIdx.x < 2 * DH) {
+        const float* src = mm + unit * nsplit * 2 * DH + threadIdx.x;
+        const bool is_min = threadIdx.x < DH;
         float a = is_min ? INFINITY : -INFINITY;
 #pragma unroll 4
         for (int s = 0; s < nsplit; ++s) {
-            const float x = src[int64_t(s) * 2 * D.d];
+            const float x = src[int64_t(s) * 2 * DH];
             a = is_min ? fminf(a, x) : fmaxf(a, x);
         }
         s_mm[threadIdx.x] = a;
@@ -136,23 +136,13 @@ __global__ __launch_bounds__(SCORE_THREADS) void k_sigma(Dims D, const T* __rest
     for (int i = 0; i < VEC; ++i) {
         const int c = lane * VEC + i;
         mn[i] = s_mm[c];
-        const float dd = s_mm[D.d + c] - mn[i];
+        const float dd = s_mm[DH + c] - mn[i];
         den[i] = dd == 0.0f ? 1.0f : dd;
         inv[i] = 1.0f / den[i];
     }
-    const float inv_d = 1.0f / float(D.d), inv_dof = 1.0f / float(D.d - D.ddof);
+    const float inv_d = 1.0f / float(DH), inv_dof = 1.0f / float(DH - D.ddof);
     // The lanes of one row run the same iterations, so the exchanges stay among active lanes.  The quotient of Eq. 6 is
     // the reciprocal product with one fused residual correction, which reproduces the IEEE quotient.
-    auto row_sums = [&](float (&x)[4]) {
-        if (lpr == 16) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) x[j] = row16_sum(x[j]);
-            return;
-        }
-        for (int o = lpr >> 1; o > 0; o >>= 1)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) x[j] += __shfl_xor(x[j], o, 64);
-    };
     for (int r = r0 + rg; r < r1; r += 4 * rpp) {
         float v[4][VEC], s[4], q[4];
 #pragma unroll
@@ -171,7 +161,7 @@ __global__ __launch_bounds__(SCORE_THREADS) void k_sigma(Dims D, const T* __rest
             }
             s[j] = acc;
         }
-        row_sums(s);
+        group_sums<lpr>(s);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const float mean = s[j] * inv_d;
@@ -180,7 +170,7 @@ __global__ __launch_bounds__(SCORE_THREADS) void k_sigma(Dims D, const T* __rest
             for (int i = 0; i < VEC; ++i) { const float dv = v[j][i] - mean; acc += dv * dv; }
             q[j] = acc;
         }
-        row_sums(q);
+        group_sums<lpr>(q);
         if (lane == 0) {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
@@ -227,26 +217,31 @@ __global__ __launch_bounds__(SCORE_THREADS) void k_softmax(Dims D, const float* 
 
 // ---------------------------------------------------------------------------------------------
 // Fused variant: one workgroup of 1024 threads per (batch, KV head, chunk p) does all of Eq. 4-8:
-//   phase 1  per-channel min / max of K and of V over chunk p+1 (registers -> wave shuffles -> LDS)
+//   phase 1  per-channel min / max of K and of V over chunk p+1 (registers -> lanes of a wave -> LDS)
 //   phase 2  rows of chunk p normalised (Eq. 6), Std over channels -> sigma_K, sigma_V in LDS
 //   phase 3  softmax over the chunk's tokens for K and V, summed, written out
 // Chunk p+1 is read here as the reference and, at about the same time, by workgroup p+1 as its scored
 // chunk, so the second read is served by L2 / the memory-side cache.  The division of Eq. 6 is done as
 // a multiplication by the correctly rounded reciprocal plus one fused residual correction
 // (q + (a - b*q) * rcp), which reproduces the IEEE quotient.
+// Bound by the chain of its phases where every CU has at most one workgroup: all exchanges between lanes are in the vector pipe, the
+// lanes of a row a constant (f32, head_dim 128, 128 chunks of 128 rows: 14.8 -> 13.0 us against shuffles through LDS and a number of lanes
+// known at run time; bf16, head_dim 64, the same: 15.3 -> 13.4; f32, head_dim 64 had no shuffles for the row sums: 12.2 either way).  With
+// fp32's 64 registers per lane a CU holds two workgroups (66 before): 768 chunks of 64 rows 35.9 -> 24.4 us, 384 of 128 rows 32.0 -> 24.1.
+// (The rows of phase 2 and the next ones of each phase asked for ahead: 1.01 of the time, and 81 registers.)
 // One workgroup per (batch, KV head, chunk p).  SELECT: the workgroup also takes the top K of the chunk it has
 // just scored (the scores are still in LDS).
-template <typename T, bool SELECT>
-__global__ __launch_bounds__(FUSED_THREADS) void k_score_fused(Dims D, const T* __restrict__ Kp,
-                                                               const T* __restrict__ Vp,
-                                                               float* __restrict__ score, int32_t* __restrict__ idx) {
+template <typename T, int DH, bool SELECT>
+__global__ __launch_bounds__(FUSED_THREADS, sizeof(T) == 4 ? 8 : 4) void k_score_fused(Dims D, const T* __restrict__ Kp,
+                                                                                                   const T* __restrict__ Vp,
+                                                                                                   float* __restrict__ score, int32_t* __restrict__ idx) {
     const int p = blockIdx.x, bh = blockIdx.y;
     const int b = bh / D.Hkv, h = bh % D.Hkv;
     const int64_t hoff = b * D.ks[0] + h * D.ks[1];
     const int64_t cur0 = int64_t(D.S) + int64_t(p) * D.L;       // first row of the scored chunk
     const int64_t ref0 = cur0 + D.L;                             // first row of the reference chunk p+1
     __shared__ ScoreLds sh;
-    score_chunk_block<T>(D.L, D.d, D.ddof, Kp + hoff + cur0 * D.ks[2], Kp + hoff + ref0 * D.ks[2],
+    score_chunk_block<T, DH>(D.L, D.ddof, Kp + hoff + cur0 * D.ks[2], Kp + hoff + ref0 * D.ks[2],
                          Vp + hoff + cur0 * D.ks[2], Vp + hoff + ref0 * D.ks[2], D.ks[2], sh,
                          score + (int64_t(bh) * D.Ns + p) * D.L);
     if (SELECT) {
@@ -277,7 +272,7 @@ template <typename T>
 static void run_sigma(const Dims& D, const void* K, const void* V, float* mm, float* sigma, int rows_wg, hipStream_t st) {
     const dim3 grid((D.L + rows_wg - 1) / rows_wg, D.Ns, D.B * D.Hkv * 2);
     LRSA_TIMED_LAUNCH("k_minmaxT", st, k_minmax<T>, grid, dim3(SCORE_THREADS), 0, st, D, (const T*)K, (const T*)V, mm, rows_wg);
-    LRSA_TIMED_LAUNCH("k_sigmaT", st, k_sigma<T>, grid, dim3(SCORE_THREADS), 0, st, D, (const T*)K, (const T*)V, mm, sigma, rows_wg);
+    LRSA_TIMED_LAUNCH("k_sigmaT", st, (D.d == 64 ? k_sigma<T, 64> : k_sigma<T, 128>), grid, dim3(SCORE_THREADS), 0, st, D, (const T*)K, (const T*)V, mm, sigma, rows_wg);
 }
 
 // The same for the chunks of an inference-time cache (D.S = first row of the oldest chunk, D.Ns chunks): slices of 64
@@ -304,10 +299,10 @@ static hipError_t run_score(const Dims& D, const void* K, const void* V, float* 
     if (route == 3) return launch_score_resident(D, K, V, score, idx, reinterpret_cast<float*>(ws), st);
     if (route == 1) {
         if (idx)
-            LRSA_TIMED_LAUNCH("k_score_select_fused", st, (k_score_fused<T, true>), dim3(D.Ns, D.B * D.Hkv), dim3(FUSED_THREADS),
+            LRSA_TIMED_LAUNCH("k_score_select_fused", st, (D.d == 64 ? k_score_fused<T, 64, true> : k_score_fused<T, 128, true>), dim3(D.Ns, D.B * D.Hkv), dim3(FUSED_THREADS),
                               0, st, D, (const T*)K, (const T*)V, score, idx);
         else
-            LRSA_TIMED_LAUNCH("k_score_fused", st, (k_score_fused<T, false>), dim3(D.Ns, D.B * D.Hkv), dim3(FUSED_THREADS), 0,
+            LRSA_TIMED_LAUNCH("k_score_fused", st, (D.d == 64 ? k_score_fused<T, 64, false> : k_score_fused<T, 128, false>), dim3(D.Ns, D.B * D.Hkv), dim3(FUSED_THREADS), 0,
                               st, D, (const T*)K, (const T*)V, score, idx);
         return hipGetLastError();
     }

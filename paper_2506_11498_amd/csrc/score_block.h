@@ -117,18 +117,18 @@ __device__ __forceinline__ void softmax_sum_regs(const float* __restrict__ sk, c
     }
 }
 
-template <typename T>
-__device__ __forceinline__ void score_chunk_block(int L, int d, int ddof, const T* __restrict__ Kcur,
+template <typename T, int DH>
+__device__ __forceinline__ void score_chunk_block(int L, int ddof, const T* __restrict__ Kcur,
                                                   const T* __restrict__ Kref, const T* __restrict__ Vcur,
                                                   const T* __restrict__ Vref, int64_t stride, ScoreLds& sh,
                                                   float* __restrict__ out) {
     constexpr int VEC = Elem<T>::VEC;
     constexpr int NW = FUSED_THREADS / 64;
-    const int lpr = d / VEC;                  // lanes per row
-    const int rpp = FUSED_THREADS / lpr;      // rows per pass
+    constexpr int d = DH;
+    constexpr int lpr = d / VEC;              // lanes per row
+    constexpr int rpp = FUSED_THREADS / lpr;  // rows per pass
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int sub = tid % lpr, rg = tid / lpr;
-    const bool rows16 = lpr == 16;                  // 256-byte rows: the channel sums stay inside a row of 16 lanes
     const float inv_d = 1.0f / float(d);            // exact: head_dim is a power of two
     const float inv_dof = 1.0f / float(d - ddof);
     // ---- phase 1
@@ -152,15 +152,12 @@ __device__ __forceinline__ void score_chunk_block(int L, int d, int ddof, const 
                 mn[1][i] = fminf(mn[1][i], fminf(v0[i], v1[i])); mx[1][i] = fmaxf(mx[1][i], fmaxf(v0[i], v1[i]));
             }
         }
-        // lanes of one wave that hold the same channels (different rows): shuffle over the row groups
-        for (int o = lpr; o < 64; o <<= 1)
+        // lanes of one wave that hold the same channels (different rows)
 #pragma unroll
-            for (int z = 0; z < 2; ++z)
-#pragma unroll
-                for (int i = 0; i < VEC; ++i) {
-                    mn[z][i] = fminf(mn[z][i], __shfl_xor(mn[z][i], o, 64));
-                    mx[z][i] = fmaxf(mx[z][i], __shfl_xor(mx[z][i], o, 64));
-                }
+        for (int z = 0; z < 2; ++z) {
+            across_groups<lpr>(mn[z], [](float x, float y) { return fminf(x, y); });
+            across_groups<lpr>(mx[z], [](float x, float y) { return fmaxf(x, y); });
+        }
         if (lane < lpr) {
 #pragma unroll
             for (int i = 0; i < VEC; ++i) {
@@ -213,14 +210,7 @@ __device__ __forceinline__ void score_chunk_block(int L, int d, int ddof, const 
                 }
                 sm4[j] = acc;
             }
-            if (rows16) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) sm4[j] = row16_sum(sm4[j]);
-            } else {
-                for (int o = lpr >> 1; o > 0; o >>= 1)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) sm4[j] += __shfl_xor(sm4[j], o, 64);
-            }
+            group_sums<lpr>(sm4);
             float var4[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -230,14 +220,7 @@ __device__ __forceinline__ void score_chunk_block(int L, int d, int ddof, const 
                 for (int i = 0; i < VEC; ++i) { const float dd = x[j][i] - m; acc += dd * dd; }
                 var4[j] = acc;
             }
-            if (rows16) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) var4[j] = row16_sum(var4[j]);
-            } else {
-                for (int o = lpr >> 1; o > 0; o >>= 1)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) var4[j] += __shfl_xor(var4[j], o, 64);
-            }
+            group_sums<lpr>(var4);
             if (sub == 0) {
                 sh.sig[0][r] = sqrtf(var4[0] * inv_dof);
                 sh.sig[1][r] = sqrtf(var4[2] * inv_dof);
