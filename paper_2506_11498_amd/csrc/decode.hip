@@ -269,9 +269,9 @@ static CompressWs compress_ws(const Dims& D, int len, int done, int steps) {
 // A single step with a workspace gains from the CUs that k_cache_compress leaves idle, and loses three launches against one and a softmax and
 // selection in every workgroup of k_cache_select_move: with the bytes of a chunk it gains, with the heads it loses.  Measured
 // with the allocation, call by call to its end, k_cache_compress -> three launches, us: bf16, d 128, 32 heads of K: lag 128
-// 28.4 -> 29.8, lag 256 (64 KB) 32.5 -> 31.3; 64 heads: lag 512 45 -> 49, lag 1024 (256 KB) 70 -> 64; 128 heads (device
-// time) lag 72 17.5 -> 38, lag 2048 146 -> 159.  fp32, d 128, 16 heads: lag 128 30 -> 32, lag 256 (128 KB) 39 -> 34; 32
-// heads, of which k_cache_select_move has two workgroups per CU: lag 256 39 -> 43, lag 512 61 -> 51; 64: lag 1024 113 -> 98.
+// 27.7 -> 29.3, lag 256 (64 KB) 31.7 -> 31.4; 64 heads: lag 512 45 -> 47, lag 1024 (256 KB) 70 -> 63; 128 heads (device
+// time) lag 72 17.5 -> 38, lag 2048 146 -> 159.  fp32, d 128, 16 heads: lag 128 27 -> 29, lag 256 (128 KB) 36 -> 33; 32
+// heads, of which k_cache_select_move has two workgroups per CU: lag 256 36 -> 37, lag 512 56 -> 49; 64: lag 1024 106 -> 96.
 // Several steps always gain: k_cache_compress takes them one after another.
 bool cache_step_is_long(const Dims& D) {
     const int64_t heads = int64_t(D.B) * D.Hkv, row = D.d * (D.dtype == 1 ? 2 : 4), chunk = D.L * row;
