@@ -95,12 +95,13 @@ static double kv_rows(const Dims& D, int bk) {
     return double(D.B) * D.Hkv * D.L * D.G * (chunks + 0.75 * (D.lp + 1) * ktiles);
 }
 
-// split: with parts of the heads and the finest slices, where their rules ask for them; both take more workspace
-static BwdPlan plan_of(const Dims& D, bool split, int waves) {
+// split: with parts of the heads and the finest slices, where their rules ask for them; both take more workspace; slices_of: the waves
+// whose slices the plan has, 8 or 4
+static BwdPlan plan_of(const Dims& D, bool split, int waves, int slices_of) {
     BwdPlan P;
     P.waves = waves;
     P.bk = 32 * P.waves;
-    const int step = P.waves == 8 ? KV_ROWS<8> : KV_ROWS<4>;
+    const int step = slices_of == 8 ? KV_ROWS<8> : KV_ROWS<4>;
     const int sink_rows = D.S < D.n ? D.S : D.n;
     P.fq0 = D.fq0;
     P.fq1 = D.fq1;
@@ -111,6 +112,7 @@ static BwdPlan plan_of(const Dims& D, bool split, int waves) {
     P.ktiles = P.sink_tiles_k + (D.fq1 - P.kc_lo) * P.tpc_k;
     P.gl_total = D.fq1 > 0 ? gather_count(D, D.fq1 - 1) : 0;
     P.gtiles = (P.gl_total + P.bk - 1) / P.bk;
+    const int stiles = (P.gl_total + 32 * slices_of - 1) / (32 * slices_of);
     // aim at ~8192 query rows (x G heads) per workgroup, but never more than KV_MAX_SLICES slices.  head_dim 64: rows as the steps of
     // KV_ROWS take them, which end with a chunk (512 rows, lag 2, one head: 351 -> 62 us in the backward; all in one slice before)
     const int64_t rows = D.d == 64 ? (int64_t(D.L) + step - 1) / step * step * D.G : int64_t(D.L) * D.G;   // of a chunk
@@ -122,14 +124,14 @@ static BwdPlan plan_of(const Dims& D, bool split, int waves) {
     // small problems: shorter slices (down to ~1024 query rows x G heads) until the gather workgroups -- about
     // half of the (tile, slice) grid sees any query -- fill the chip twice
     while (qch > min_qch && qch > 1 && (qch / 2) * rows >= 1024 &&
-           int64_t(D.B) * D.Hkv * P.gtiles * ((nqf + qch - 1) / qch) * P.waves / 16 < 512)
+           int64_t(D.B) * D.Hkv * stiles * ((nqf + qch - 1) / qch) * slices_of / 16 < 512)
         qch /= 2;
     // fewer than a quarter as many as CUs: down to 256 rows.  (2.6K tokens, 4 heads on 2, 2 requests, 24 workgroups: 164 ->
     // 157 us; 2.2K tokens in filling steps, 4 heads on 1: 710 -> 633 us.  From 84 workgroups on it costs more than it gives:
     // 5.5K tokens, 4 heads on 2, 4 requests 264 -> 272 us, 4K tokens, 8 heads on 8, 2 requests, 128 of them, 271 -> 295 us.)
     const int64_t coarse = qch;
     while (split && qch > min_qch && qch > 1 && (qch / 2) * rows >= 256 &&
-           int64_t(D.B) * D.Hkv * P.gtiles * ((nqf + qch - 1) / qch) * P.waves / 16 < 64)
+           int64_t(D.B) * D.Hkv * stiles * ((nqf + qch - 1) / qch) * slices_of / 16 < 64)
         qch /= 2;
     P.qch = int(qch);
     P.nsl = nqf > 0 ? (nqf + P.qch - 1) / P.qch : 0;
@@ -176,28 +178,31 @@ static BwdPlan plan_of(const Dims& D, bool split, int waves) {
 // 4 requests of 4K tokens, 32 on 8: 1016 -> 885.  Short: less than 600 us of work for a CU, and no workgroup that is long beside that (which
 // would share its CU: 8.1K tokens, 16 on 4, lag 727, 364 us in a workgroup, 291 for a CU: 520 -> 565 us) unless it is short in itself.  Of 80
 // random shapes on this side of the line the backward takes 0.93 of the time (geometric mean), two 1.08.  head_dim 64: always (0.86 to 1.01).
-static BwdPlan make_plan(const Dims& D, bool split) {
+static BwdPlan make_plan(const Dims& D, bool split, bool slices_of_8 = false) {
     int waves = 4;
     if (D.d != 64) {
         const double rate = rows_per_us(D), work = kv_rows(D, 256) / 256.0 / rate;   // us for a CU
         if (work >= 600.0) {
             waves = 8;
         } else {
-            const BwdPlan P = plan_of(D, true, 8);
+            const BwdPlan P = plan_of(D, true, 8, 8);
             const double w = double(D.lp + 1) * D.L * ((D.G + P.wsl - 1) / P.wsl), g = P.nsl > 0 ? double(P.qch) * D.L * ((D.G + P.hsl - 1) / P.hsl) : 0.0;
             const double longest = (w > g ? w : g) / rate;
             waves = longest <= 0.8 * work || longest <= 100.0 ? 4 : 8;
         }
     }
-    return plan_of(D, split, waves);
+    return plan_of(D, split, waves, slices_of_8 ? 8 : waves);
 }
 
 // What a plan needs does not grow steadily from one filling step to the next: a split step may need more than a later, longer
 // one that is not split (up to three times, in every sixth of 2400 shapes).  A call whose workspace holds the plan without splits, as
-// one that was sized for the last step does, takes that plan.
+// one that was sized for the last step does, takes that plan.  With four waves the slices may come out finer than with eight (five
+// of 1500 shapes, up to 1.9 times the partials): a workspace that holds the slices of eight, without parts, is enough as well.
 static BwdPlan plan_for(const Dims& D, size_t ws_bytes) {
     const BwdPlan P = make_plan(D, true);
-    return P.bytes <= ws_bytes ? P : make_plan(D, false);
+    if (P.bytes <= ws_bytes) return P;
+    const BwdPlan whole = make_plan(D, false);
+    return whole.bytes <= ws_bytes ? whole : make_plan(D, false, true);
 }
 size_t attn_bwd_mfma_ws_bytes(const Dims& D) { return make_plan(D, true).bytes; }
 void attn_bwd_mfma_parts(const Dims& D, int32_t* gather, int32_t* window) {
@@ -206,14 +211,15 @@ void attn_bwd_mfma_parts(const Dims& D, int32_t* gather, int32_t* window) {
     *window = P.wsl;
 }
 size_t attn_bwd_mfma_ws_min_bytes(const Dims& D) {
-    const size_t whole = make_plan(D, false).bytes, split = attn_bwd_mfma_ws_bytes(D);
-    return whole < split ? whole : split;
+    const size_t whole = make_plan(D, false).bytes, split = attn_bwd_mfma_ws_bytes(D), of_8 = make_plan(D, false, true).bytes;
+    const size_t least = whole < split ? whole : split;
+    return of_8 < least ? of_8 : least;
 }
 
 // the grids of the forward, dQ and dK/dV launches (the reduction's threads are fewer than the bytes of its partials)
 bool mfma_grids_fit(const Dims& D) {
     const int64_t units = int64_t(D.B) * D.Hkv;
-    const BwdPlan P = make_plan(D, true), P8 = plan_of(D, true, 8);   // also where workgroups have four waves: which shapes are served does not change with it
+    const BwdPlan P = make_plan(D, true), P8 = plan_of(D, true, 8, 8);   // also where workgroups have four waves: which shapes are served does not change with it
     return grid_fits(units * make_qtile_map(D, 8).per_unit, 512) && grid_fits(units * make_qtile_map(D, 4).per_unit, 256) &&
            grid_fits(gather_workgroups(D, P8) + window_workgroups(D, P8), 512) &&
            grid_fits(gather_workgroups(D, P) + window_workgroups(D, P), 64 * P.waves);
