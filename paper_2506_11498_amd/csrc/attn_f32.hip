@@ -28,16 +28,30 @@ typedef float fx4 __attribute__((ext_vector_type(4)));
 
 template <int DH> constexpr int F32_WAVES = DH == 64 ? 16 : 8;   // 128 (256) registers per lane
 
+// Keys of the longest walk: the last query chunk, which may be a short one, the chunk before it, or the sink's last row.
+static int64_t longest_walk(const Dims& D) {
+    int64_t keys = D.S < D.n ? D.S : D.n;
+    for (int q = D.nq - 1; q >= 0 && q >= D.nq - 2; --q) {
+        const int64_t end = int64_t(D.S) + (int64_t(q) + 1) * D.L, k = gather_count(D, q) + (end < D.n ? end : D.n) - window_start(D, q);
+        keys = k > keys ? k : keys;
+    }
+    return keys;
+}
+
 // Waves of a query-outer workgroup: F32_WAVES, so that few query tiles still fill the chip, or half of that, or four, where there are
 // more of them: a wave then takes more than the two or three key tiles that it has of 16 waves, and fewer states are merged.  As long as
-// the chip holds the waves (head_dim 128: twice as many; with only as many 1.2K tokens, 4 heads on 4, take 31 us instead of 23).
-// 2 requests of 2.0K tokens, 8 heads of 64 on 2: forward 97 -> 72 us, backward 345 -> 300; 2 requests of 2.4K tokens, 16 heads of 128 on 4:
-// forward 457 -> 349 us, backward 1370 -> 1289.  Errors of O, lse and dQ against 64 bits 0.94 to 1.001 of those with all waves; of dK and dV,
-// whose kernel is the same and reads those, 0.94 to 1.008, 0.99 on average.  Two waves at head_dim 128 are as fast, with 1.003.
+//  - the chip holds the waves (head_dim 128: twice as many; with only as many 1.2K tokens, 4 heads on 4, take 31 us instead of 23);
+//  - a wave has at most 16 key tiles (head_dim 128: 8) of the longest walk.  It adds its tiles one after another, and their rounding
+//    grows with their number: 2-norm error of O against 64 bits, over that with all waves, of the last rows of uncompressed sequences,
+//    five kinds of values: head_dim 64, four waves 0.93 to 1.01 up to 1024 keys, 1.00 to 1.04 at 2048, 1.02 to 1.08 at 4096, 1.05 to 1.26
+//    at 12288; eight waves 0.94 to 1.005 up to 2048, 1.08 at 12288; head_dim 128, four waves 0.96 to 1.005 up to 512, 1.015 at 768,
+//    1.07 at 4096, 1.13 at 12288.  Of dQ, whose error jumps more from one set of rows to the next, 0.77 to 1.05 up to these lines, 1.28 beyond.
+// 2 requests of 2.0K tokens, 8 heads of 64 on 2: forward 97 -> 72 us, backward 345 -> 300.
 static int f32_query_waves(const Dims& D, int64_t tiles) {
-    const int most = D.d == 64 ? F32_WAVES<64> : F32_WAVES<128>, rounds = D.d == 64 ? 1 : 2;
+    const int most = D.d == 64 ? F32_WAVES<64> : F32_WAVES<128>, rounds = D.d == 64 ? 1 : 2, wave_keys = D.d == 64 ? 256 : 128;
+    const int64_t keys = longest_walk(D);
     int w = most;
-    while (w > 4 && tiles * w > rounds * 256 * int64_t(most)) w /= 2;
+    while (w > 4 && tiles * w > rounds * 256 * int64_t(most) && keys <= w / 2 * wave_keys) w /= 2;
     return w;
 }
 
