@@ -45,13 +45,16 @@ static int64_t longest_walk(const Dims& D) {
 //    grows with their number: 2-norm error of O against 64 bits, over that with all waves, of the last rows of uncompressed sequences,
 //    five kinds of values: head_dim 64, four waves 0.93 to 1.01 up to 1024 keys, 1.00 to 1.04 at 2048, 1.02 to 1.08 at 4096, 1.05 to 1.26
 //    at 12288; eight waves 0.94 to 1.005 up to 2048, 1.08 at 12288; head_dim 128, four waves 0.96 to 1.005 up to 512, 1.015 at 768,
-//    1.07 at 4096, 1.13 at 12288.  Of dQ, whose error jumps more from one set of rows to the next, 0.77 to 1.05 up to these lines, 1.28 beyond.
+//    1.07 at 4096, 1.13 at 12288.  Of dQ, whose error jumps more from one set of rows to the next, 0.77 to 1.05 up to these lines, 1.28 beyond;
+//  - sixteen waves of walks beyond 512 keys are more than 1.6 times what the chip holds: with 1.0 to 1.6 times as many eight waves are
+//    twice as long and leave the second round's gain behind (2.1K tokens, 2 heads on 1, 33 survivors of 65: forward 20.3 us with sixteen, 24.2
+//    with eight; 14 shapes between 1.02 and 1.19 in the forward, up to 1.09 in the backward); up to 512 keys 0.82 to 0.95.
 // 2 requests of 2.0K tokens, 8 heads of 64 on 2: forward 97 -> 72 us, backward 345 -> 300.
 static int f32_query_waves(const Dims& D, int64_t tiles) {
     const int most = D.d == 64 ? F32_WAVES<64> : F32_WAVES<128>, rounds = D.d == 64 ? 1 : 2, wave_keys = D.d == 64 ? 256 : 128;
     const int64_t keys = longest_walk(D);
     int w = most;
-    while (w > 4 && tiles * w > rounds * 256 * int64_t(most) && keys <= w / 2 * wave_keys) w /= 2;
+    while (w > 4 && tiles * w > rounds * 256 * int64_t(most) * (w == 16 && keys > 512 ? 1.6 : 1.0) && keys <= w / 2 * wave_keys) w /= 2;
     return w;
 }
 

@@ -119,7 +119,7 @@ def test_fp32_error_of_long_walks(d, bar):
     assert e["O"] <= bar and e["lse"] <= 2.0 ** -23 and e["dQ"] <= 3 * bar, e
 
 
-@pytest.mark.parametrize("d,n,heads", [(64, 1024, 16), (64, 2048, 3), (128, 512, 20)])   # 4, 8 and 4 waves per tile; a single head has all
+@pytest.mark.parametrize("d,n,heads", [(64, 1024, 16), (64, 2048, 5), (128, 512, 20)])   # 4, 8 and 4 waves per tile; a single head has all
 def test_fp32_error_of_the_longest_walks_with_fewer_waves(d, n, heads):
     """As long as walks with fewer waves get.  Measured 0.97, 0.99 and 0.99 of the error of O with all waves, 0.98 to 1.0 of dQ's; a tenth is the
     spread of dQ from one set of rows to the next."""
