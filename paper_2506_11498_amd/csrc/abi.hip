@@ -90,22 +90,27 @@ bool use_mfma(const lrsa_params* p, const lrsa::Dims& D) {
 }
 
 bool use_f32_tiles(const lrsa_params* p, const lrsa::Dims& D) { return p->impl != LRSA_IMPL_GENERIC && lrsa::f32_tiles_supported(D) && !plain_for_short_lag(D); }
+// which kernels serve an attention call: 2 bf16 MFMA, 1 fp32 matrix, 0 plain
+int attn_route(const lrsa_params* p, const lrsa::Dims& D) { return use_mfma(p, D) ? 2 : use_f32_tiles(p, D) ? 1 : 0; }
 // the filling-step calls are built for head_dim 128; their grids are those of a window of rows
 bool fill_supported(const lrsa_params* p, const lrsa::Dims& D) { return p->impl != LRSA_IMPL_GENERIC && lrsa::mfma_supported(D) && D.d == 128; }
 
-size_t ws_need(const lrsa_params* p, const lrsa::Dims& D, int which) {
+size_t ws_need(const lrsa::Dims& D, int which, int route) {
     switch (which) {
         case LRSA_WS_SCORE: return lrsa::score_ws_bytes(D);
         case LRSA_WS_SELECT: return lrsa::select_ws_bytes(D);
-        case LRSA_WS_ATTN_FWD: return use_mfma(p, D) ? lrsa::attn_fwd_mfma_ws_bytes(D) : lrsa::attn_fwd_generic_ws_bytes(D);
-        case LRSA_WS_ATTN_BWD: return use_mfma(p, D) ? lrsa::attn_bwd_mfma_ws_bytes(D) : use_f32_tiles(p, D) ? lrsa::attn_bwd_f32_ws_bytes(D) : lrsa::attn_bwd_generic_ws_bytes(D);
+        case LRSA_WS_ATTN_FWD: return route == 2 ? lrsa::attn_fwd_mfma_ws_bytes(D) : lrsa::attn_fwd_generic_ws_bytes(D);
+        case LRSA_WS_ATTN_BWD: return route == 2 ? lrsa::attn_bwd_mfma_ws_bytes(D) : route == 1 ? lrsa::attn_bwd_f32_ws_bytes(D) : lrsa::attn_bwd_generic_ws_bytes(D);
         case LRSA_WS_DECODE_ATTN: return lrsa::decode_ws_bytes(D);
         default: return 0;
     }
 }
 
-int check_ws(const lrsa_params* p, const lrsa::Dims& D, int which, const void* ws, size_t ws_bytes) {
-    const size_t need = which == LRSA_WS_ATTN_BWD && use_mfma(p, D) ? lrsa::attn_bwd_mfma_ws_min_bytes(D) : ws_need(p, D, which);
+// route: of an attention call
+int check_ws(const lrsa::Dims& D, int which, const void* ws, size_t ws_bytes, int route = 0) {
+    size_t need = ws_need(D, which, route);
+    // planning takes a good part of a microsecond: the least workspace is only looked for where the preferred one is not there
+    if (which == LRSA_WS_ATTN_BWD && route == 2 && (!ws || ws_bytes < need)) need = lrsa::attn_bwd_mfma_ws_min_bytes(D);
     if (need == 0) return LRSA_OK;
     if (!ws) return fail(LRSA_ERR_INVALID_ARG, "workspace is NULL but %zu bytes are needed", need);
     if (ws_bytes < need) return fail(LRSA_ERR_INVALID_ARG, "workspace has %zu bytes, %zu are needed", ws_bytes, need);
@@ -143,7 +148,7 @@ int lrsa_score_route(const lrsa_params* p) {
 int lrsa_attn_route(const lrsa_params* p) {
     lrsa::Dims D;
     const int rc = make_dims(p, &D);
-    return rc != LRSA_OK ? rc : use_mfma(p, D) ? 2 : use_f32_tiles(p, D) ? 1 : 0;
+    return rc != LRSA_OK ? rc : attn_route(p, D);
 }
 
 int lrsa_score_poll_limit(int polls) { return lrsa::score_poll_limit(polls); }
@@ -151,7 +156,7 @@ int lrsa_score_poll_limit(int polls) { return lrsa::score_poll_limit(polls); }
 size_t lrsa_workspace_bytes(const lrsa_params* p, int which) {
     lrsa::Dims D;
     if (make_dims(p, &D) != LRSA_OK) return 0;
-    return ws_need(p, D, which);
+    return ws_need(D, which, which == LRSA_WS_ATTN_FWD || which == LRSA_WS_ATTN_BWD ? attn_route(p, D) : 0);
 }
 
 int lrsa_score(const lrsa_params* p, const void* K, const void* V, float* score, void* ws, size_t ws_bytes,
@@ -162,7 +167,7 @@ int lrsa_score(const lrsa_params* p, const void* K, const void* V, float* score,
     if (D.Ns == 0) return LRSA_OK;
     if (!K || !V || !score) return fail(LRSA_ERR_INVALID_ARG, "lrsa_score: K, V and score must not be NULL");
     if (misaligned16(K) || misaligned16(V)) return fail(LRSA_ERR_INVALID_ARG, "lrsa_score: K and V must be 16-byte aligned");
-    if ((rc = check_ws(p, D, LRSA_WS_SCORE, ws, ws_bytes)) != LRSA_OK) return rc;
+    if ((rc = check_ws(D, LRSA_WS_SCORE, ws, ws_bytes)) != LRSA_OK) return rc;
     return hip_result(lrsa::launch_score(D, K, V, score, ws, (hipStream_t)stream), "lrsa_score");
 }
 
@@ -172,7 +177,7 @@ int lrsa_select(const lrsa_params* p, const float* score, int32_t* idx, void* ws
     if (rc != LRSA_OK) return rc;
     if (D.Ns == 0) return LRSA_OK;
     if (!score || !idx) return fail(LRSA_ERR_INVALID_ARG, "lrsa_select: score and idx must not be NULL");
-    if ((rc = check_ws(p, D, LRSA_WS_SELECT, ws, ws_bytes)) != LRSA_OK) return rc;
+    if ((rc = check_ws(D, LRSA_WS_SELECT, ws, ws_bytes)) != LRSA_OK) return rc;
     return hip_result(lrsa::launch_select(D, score, idx, ws, (hipStream_t)stream), "lrsa_select");
 }
 
@@ -195,7 +200,7 @@ int lrsa_score_select(const lrsa_params* p, const void* K, const void* V, float*
         return fail(LRSA_ERR_INVALID_ARG, "lrsa_score_select: K, V, score and idx must not be NULL");
     if (misaligned16(K) || misaligned16(V))
         return fail(LRSA_ERR_INVALID_ARG, "lrsa_score_select: K and V must be 16-byte aligned");
-    if ((rc = check_ws(p, D, LRSA_WS_SCORE, ws, ws_bytes)) != LRSA_OK) return rc;
+    if ((rc = check_ws(D, LRSA_WS_SCORE, ws, ws_bytes)) != LRSA_OK) return rc;
     return hip_result(lrsa::launch_score_select(D, K, V, score, idx, ws, (hipStream_t)stream), "lrsa_score_select");
 }
 
@@ -264,7 +269,7 @@ int lrsa_decode_attn(const lrsa_params* p, const void* q, const void* Kc, const 
     if (!q || !Kc || !Vc || !O) return fail(LRSA_ERR_INVALID_ARG, "lrsa_decode_attn: q, Kc, Vc and O must not be NULL");
     if (misaligned16(q) || misaligned16(Kc) || misaligned16(Vc))
         return fail(LRSA_ERR_INVALID_ARG, "lrsa_decode_attn: q, Kc and Vc must be 16-byte aligned");
-    if ((rc = check_ws(p, D, LRSA_WS_DECODE_ATTN, ws, ws_bytes)) != LRSA_OK) return rc;
+    if ((rc = check_ws(D, LRSA_WS_DECODE_ATTN, ws, ws_bytes)) != LRSA_OK) return rc;
     return hip_result(lrsa::launch_decode_attn(D, q, Kc, Vc, len, O, lse, ws, (hipStream_t)stream), "lrsa_decode_attn");
 }
 
@@ -295,9 +300,10 @@ int lrsa_attn_fwd(const lrsa_params* p, const void* Q, const void* K, const void
     if (D.Ns > 0 && !idx) return fail(LRSA_ERR_INVALID_ARG, "lrsa_attn_fwd: idx is NULL but %d chunks are compressed", D.Ns);
     if (misaligned16(Q) || misaligned16(K) || misaligned16(V) || misaligned16(O))
         return fail(LRSA_ERR_INVALID_ARG, "lrsa_attn_fwd: tensors must be 16-byte aligned");
-    if ((rc = check_ws(p, D, LRSA_WS_ATTN_FWD, ws, ws_bytes)) != LRSA_OK) return rc;
-    const hipError_t e = use_mfma(p, D) ? lrsa::launch_attn_fwd_mfma(D, Q, K, V, idx, O, lse, ws, (hipStream_t)stream)
-                                        : use_f32_tiles(p, D) ? lrsa::launch_attn_fwd_f32(D, Q, K, V, idx, O, lse, (hipStream_t)stream)
+    const int route = attn_route(p, D);
+    if ((rc = check_ws(D, LRSA_WS_ATTN_FWD, ws, ws_bytes, route)) != LRSA_OK) return rc;
+    const hipError_t e = route == 2 ? lrsa::launch_attn_fwd_mfma(D, Q, K, V, idx, O, lse, ws, (hipStream_t)stream)
+                                        : route == 1 ? lrsa::launch_attn_fwd_f32(D, Q, K, V, idx, O, lse, (hipStream_t)stream)
                                         : lrsa::launch_attn_fwd_generic(D, Q, K, V, idx, O, lse, ws, (hipStream_t)stream);
     return hip_result(e, "lrsa_attn_fwd");
 }
@@ -314,10 +320,11 @@ int lrsa_attn_bwd(const lrsa_params* p, const void* Q, const void* K, const void
     if (misaligned16(Q) || misaligned16(K) || misaligned16(V) || misaligned16(O) || misaligned16(dO) ||
         misaligned16(dQ) || misaligned16(dK) || misaligned16(dV))
         return fail(LRSA_ERR_INVALID_ARG, "lrsa_attn_bwd: tensors must be 16-byte aligned");
-    if ((rc = check_ws(p, D, LRSA_WS_ATTN_BWD, ws, ws_bytes)) != LRSA_OK) return rc;
+    const int route = attn_route(p, D);
+    if ((rc = check_ws(D, LRSA_WS_ATTN_BWD, ws, ws_bytes, route)) != LRSA_OK) return rc;
     const hipError_t e =
-        use_mfma(p, D) ? lrsa::launch_attn_bwd_mfma(D, Q, K, V, O, dO, lse, idx, dQ, dK, dV, nullptr, nullptr, ws, ws_bytes, (hipStream_t)stream)
-                       : use_f32_tiles(p, D) ? lrsa::launch_attn_bwd_f32(D, Q, K, V, O, dO, lse, idx, dQ, dK, dV, ws, (hipStream_t)stream)
+        route == 2 ? lrsa::launch_attn_bwd_mfma(D, Q, K, V, O, dO, lse, idx, dQ, dK, dV, nullptr, nullptr, ws, ws_bytes, (hipStream_t)stream)
+                       : route == 1 ? lrsa::launch_attn_bwd_f32(D, Q, K, V, O, dO, lse, idx, dQ, dK, dV, ws, (hipStream_t)stream)
                        : lrsa::launch_attn_bwd_generic(D, Q, K, V, O, dO, lse, idx, dQ, dK, dV, ws, (hipStream_t)stream);
     return hip_result(e, "lrsa_attn_bwd");
 }
@@ -412,8 +419,10 @@ int lrsa_attn_bwd_fill(const lrsa_params* p, int32_t row_begin, int32_t row_end,
     if (misaligned16(Q) || misaligned16(K) || misaligned16(V) || misaligned16(O) || misaligned16(dO) || misaligned16(dQ) ||
         misaligned16(dK_acc) || misaligned16(dV_acc))
         return fail(LRSA_ERR_INVALID_ARG, "lrsa_attn_bwd_fill: tensors must be 16-byte aligned");
-    const size_t need = lrsa::attn_bwd_mfma_ws_min_bytes(D);
-    if (!ws || ws_bytes < need) return fail(LRSA_ERR_INVALID_ARG, "lrsa_attn_bwd_fill: workspace of %zu bytes needed", need);
+    if (!ws || ws_bytes < lrsa::attn_bwd_mfma_ws_bytes(D)) {
+        const size_t need = lrsa::attn_bwd_mfma_ws_min_bytes(D);
+        if (!ws || ws_bytes < need) return fail(LRSA_ERR_INVALID_ARG, "lrsa_attn_bwd_fill: workspace of %zu bytes needed", need);
+    }
     if (reinterpret_cast<uintptr_t>(ws) % 256 != 0) return fail(LRSA_ERR_INVALID_ARG, "workspace is not 256-byte aligned");
     D.acc = 1;
     return hip_result(lrsa::launch_attn_bwd_mfma(D, shift_rows(Q, D, D.qs[2]), K, V, shift_rows(O, D, D.qs[2]),

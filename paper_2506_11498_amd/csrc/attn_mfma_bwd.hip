@@ -87,17 +87,23 @@ static int64_t window_workgroups(const Dims& D, const BwdPlan& P) { return (int6
 static double kv_rows(const Dims& D, int bk) {
     const int gl = D.fq1 > 0 ? gather_count(D, D.fq1 - 1) : 0, kc_lo = D.fq0 - D.lp > 0 ? D.fq0 - D.lp : 0;
     double chunks = 0.0;   // query chunks that see a list tile, over all tiles
-    for (int t = 0; t < (gl + bk - 1) / bk; ++t) {
-        const int qf = first_chunk_seeing(D, t * bk);
-        chunks += qf < D.fq1 ? D.fq1 - (qf > D.fq0 ? qf : D.fq0) : 0;
+    int64_t j0 = 0;
+    for (; j0 < gl && j0 < D.S; j0 += bk) chunks += D.fq1 - D.fq0;   // tiles that begin with a sink token
+    // first_chunk_seeing of the others, without a division per tile
+    int64_t qf = D.lp + 1 + (j0 - D.S) / D.K, rem = (j0 - D.S) % D.K;
+    for (; j0 < gl && qf < D.fq1; j0 += bk) {
+        chunks += double(D.fq1 - (qf > D.fq0 ? qf : D.fq0));
+        qf += bk / D.K;
+        rem += bk % D.K;
+        if (rem >= D.K) { rem -= D.K; ++qf; }
     }
     const int64_t ktiles = int64_t(D.fq1 - kc_lo) * ((D.L + bk - 1) / bk) + (D.row_begin == 0 ? (D.S + bk - 1) / bk : 0);
     return double(D.B) * D.Hkv * D.L * D.G * (chunks + 0.75 * (D.lp + 1) * ktiles);
 }
 
 // split: with parts of the heads and the finest slices, where their rules ask for them; both take more workspace; slices_of: the waves
-// whose slices the plan has, 8 or 4
-static BwdPlan plan_of(const Dims& D, bool split, int waves, int slices_of) {
+// whose slices the plan has, 8 or 4; all_rows: kv_rows of such workgroups where that is known
+static BwdPlan plan_of(const Dims& D, bool split, int waves, int slices_of, double all_rows = -1.0) {
     BwdPlan P;
     P.waves = waves;
     P.bk = 32 * P.waves;
@@ -143,7 +149,7 @@ static BwdPlan plan_of(const Dims& D, bool split, int waves, int slices_of) {
     const int units = D.B * D.Hkv;
     const double w_rows = double(D.lp + 1) * D.L * D.G, g_rows = P.nsl > 0 ? double(P.qch) * D.L * D.G : 0.0;   // of a workgroup
     if (split && D.G > 1) {
-        const double per_cu = kv_rows(D, P.bk) * P.waves / 2048.0;   // per workgroup that runs at once
+        const double per_cu = (all_rows < 0.0 ? kv_rows(D, P.bk) : all_rows) * P.waves / 2048.0;   // per workgroup that runs at once
         const double row = 2.0 * units * D.d * 4;   // bytes of a row of dK and dV partials of all heads
         // a workgroup shorter than a quarter of a CU's work is no tail worth partials
         double saved = 0.0;
@@ -181,14 +187,15 @@ static BwdPlan plan_of(const Dims& D, bool split, int waves, int slices_of) {
 static BwdPlan make_plan(const Dims& D, bool split, bool slices_of_8 = false) {
     int waves = 4;
     if (D.d != 64) {
-        const double rate = rows_per_us(D), work = kv_rows(D, 256) / 256.0 / rate;   // us for a CU
+        const double rate = rows_per_us(D), rows = kv_rows(D, 256), work = rows / 256.0 / rate;   // us for a CU
         if (work >= 600.0) {
             waves = 8;
         } else {
-            const BwdPlan P = plan_of(D, true, 8, 8);
+            const BwdPlan P = plan_of(D, true, 8, 8, rows);
             const double w = double(D.lp + 1) * D.L * ((D.G + P.wsl - 1) / P.wsl), g = P.nsl > 0 ? double(P.qch) * D.L * ((D.G + P.hsl - 1) / P.hsl) : 0.0;
             const double longest = (w > g ? w : g) / rate;
             waves = longest <= 0.8 * work || longest <= 100.0 ? 4 : 8;
+            if (waves == 8 && split) return P;
         }
     }
     return plan_of(D, split, waves, slices_of_8 ? 8 : waves);
@@ -218,9 +225,14 @@ size_t attn_bwd_mfma_ws_min_bytes(const Dims& D) {
 
 // the grids of the forward, dQ and dK/dV launches (the reduction's threads are fewer than the bytes of its partials)
 bool mfma_grids_fit(const Dims& D) {
+    // An upper bound on the work-items of each, for nearly all calls: a workgroup's threads are at most 64 per piece of 32 rows x head and 2 per
+    // key, and 512 for the remainder of a segment or list; there are at most KV_MAX_SLICES slices and as many parts as heads.
+    const double heads = double(D.B) * D.Hq, gl = D.fq1 > 0 ? gather_count(D, D.fq1 - 1) : 0;
+    const double q = heads * (2.0 * D.S + 576.0 + D.fq1 * (2.0 * D.L + 576.0)), g = (heads * KV_MAX_SLICES + 7.0) * (2.0 * gl + 512.0);
+    if (q + g + 4096.0 < 2147483648.0) return true;
     const int64_t units = int64_t(D.B) * D.Hkv;
     const BwdPlan P = make_plan(D, true), P8 = plan_of(D, true, 8, 8);   // also where workgroups have four waves: which shapes are served does not change with it
-    return grid_fits(units * make_qtile_map(D, 8).per_unit, 512) && grid_fits(units * make_qtile_map(D, 4).per_unit, 256) &&
+    return grid_fits(units * tiles_per_unit(D, 8), 512) && grid_fits(units * tiles_per_unit(D, 4), 256) &&
            grid_fits(gather_workgroups(D, P8) + window_workgroups(D, P8), 512) &&
            grid_fits(gather_workgroups(D, P) + window_workgroups(D, P), 64 * P.waves);
 }

@@ -399,13 +399,17 @@ __device__ __forceinline__ const bf16_t* stream_row(const bf16_t* Zc, const bf16
 // all of a launch's workgroups on the chip at once, or nearly: two per CU of four waves, one of eight
 inline bool resident_tiles(int64_t wgs, int waves) { return wgs * waves <= 2048 + 512; }
 
+// tiles of `waves` pieces in a segment of `rows` rows, and in all that is launched for a (batch, KV head)
+inline int segment_tiles(const Dims& D, int64_t rows, int waves) { return int(((rows + 31) / 32 * D.G + waves - 1) / waves); }
+inline int64_t tiles_per_unit(const Dims& D, int waves) {
+    return (D.row_begin == 0 ? segment_tiles(D, D.S < D.n ? D.S : D.n, waves) : 0) + int64_t(D.fq1 - (D.row_begin == 0 ? 0 : D.fq0)) * segment_tiles(D, D.L, waves);
+}
+
 inline QTileMap make_qtile_map(const Dims& D, int waves) {
     QTileMap M;
-    const int sink_rows = D.S < D.n ? D.S : D.n;
     M.heads = D.G % 4 == 0 ? 4 : D.G;
-    auto tiles = [&](int64_t rows) { return int(((rows + 31) / 32 * D.G + waves - 1) / waves); };
-    M.sink_tiles = tiles(sink_rows);
-    M.tpc = tiles(D.L);
+    M.sink_tiles = segment_tiles(D, D.S < D.n ? D.S : D.n, waves);
+    M.tpc = segment_tiles(D, D.L, waves);
     M.tiles = M.sink_tiles + D.nq * M.tpc;
     M.tix_lo = D.row_begin == 0 ? 0 : M.sink_tiles + D.fq0 * M.tpc;
     M.tix_hi = M.sink_tiles + D.fq1 * M.tpc;
@@ -436,9 +440,10 @@ inline QTileMap make_qtile_map(const Dims& D, int waves) {
 //    80 and 87 us); 8K tokens, 16 heads on 4: 154 and 138 us.
 inline int qtile_waves(const Dims& D) {
     if (D.compact) return 8;
-    const int64_t units = int64_t(D.B) * D.Hkv, n4 = units * make_qtile_map(D, 4).per_unit, n8 = units * make_qtile_map(D, 8).per_unit;
+    if (D.d == 64) return 4;
+    const int64_t units = int64_t(D.B) * D.Hkv, n4 = units * tiles_per_unit(D, 4), n8 = units * tiles_per_unit(D, 8);
     const int keys = gather_count(D, (D.fq0 + D.fq1) / 2) + D.L + D.L / 2;   // of a walk, about
-    return D.d == 64 || resident_tiles(n4, 4) || 20 * n8 > 11 * n4 || keys <= 1000 ? 4 : 8;
+    return resident_tiles(n4, 4) || 20 * n8 > 11 * n4 || keys <= 1000 ? 4 : 8;
 }
 
 }  // namespace lrsa
