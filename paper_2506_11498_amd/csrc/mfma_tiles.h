@@ -305,8 +305,13 @@ inline FastDiv make_fast_div(int64_t d, int64_t x_max) {
     const bool exact = d > 1 && x_max < (int64_t(1) << 32) / d;
     return FastDiv{unsigned(d), exact ? unsigned(((int64_t(1) << 32) + d - 1) / d) : 0u};
 }
-__device__ __forceinline__ int fast_div(int x, FastDiv f) {
-    return f.m ? int(__umulhi(unsigned(x), f.m)) : f.d == 1 ? x : int(unsigned(x) / f.d);
+__host__ __device__ __forceinline__ int fast_div(int x, FastDiv f) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const unsigned q = __umulhi(unsigned(x), f.m);   // (a shifted product of 64 bits goes to the vector pipe)
+#else
+    const unsigned q = unsigned(uint64_t(unsigned(x)) * f.m >> 32);
+#endif
+    return f.m ? int(q) : f.d == 1 ? x : int(unsigned(x) / f.d);
 }
 
 // Which (batch, KV head, query tile) a workgroup of a query-outer kernel takes.
@@ -333,7 +338,7 @@ struct QTileMap {
     int heads;                    // of a block
     FastDiv by_unit, by_units, by_hkv, by_tpc, by_heads;
 };
-__device__ __forceinline__ bool decode_qtile(const QTileMap& M, const Dims& D, int i, int& b, int& h, int& tix) {
+__host__ __device__ __forceinline__ bool decode_qtile(const QTileMap& M, const Dims& D, int i, int& b, int& h, int& tix) {
     int unit, w;
     if (M.side_by_side) {
         int j = i >> 3;
@@ -354,7 +359,7 @@ __device__ __forceinline__ bool decode_qtile(const QTileMap& M, const Dims& D, i
 }
 // The rows of tile `tix`: query chunk (-1: sink), end of the segment, first row and head (of the group) of this wave's piece, last row
 // of the workgroup; false: it has none.  A wave whose first row is not below seg_end has no piece.
-__device__ __forceinline__ bool qtile_rows(const QTileMap& M, const Dims& D, int tix, int waves, int wave, int& qc, int& seg_end, int& tw,
+__host__ __device__ __forceinline__ bool qtile_rows(const QTileMap& M, const Dims& D, int tix, int waves, int wave, int& qc, int& seg_end, int& tw,
                                            int& head, int& t_last) {
     int ts, u0, rows;
     if (tix < M.sink_tiles) {
