@@ -46,19 +46,26 @@ def _check_scratch(remarks: str, src: str) -> None:
 # sees their result as unused it reuses the destination register at once, and if it copies the result before the
 # kernel's own wait the copy is stale; either way a kernel could compute an address from garbage.  So the
 # generated assembly of every source that uses them is scanned: between such a load and the next
-# `s_waitcnt lgkmcnt(0)` (text order) no other instruction may touch the load's destination register.
-def _check_scalar_loads(src: str) -> None:
-    asm = os.path.join(OBJ, os.path.basename(src) + ".s")
-    r = subprocess.run([HIPCC, *FLAGS, "-S", "--cuda-device-only", src, "-o", asm], capture_output=True, text=True)
-    if r.returncode != 0:
-        raise RuntimeError(f"hipcc -S failed on {src}")
-    ins = [(i, t.strip()) for i, t in enumerate(open(asm).read().split("\n")) if t.strip() and not t.strip().startswith(";")]
-    for k, (i, t) in enumerate(ins):
-        m = re.match(r"s_load_dword (s\d+), s\[\d+:\d+\], s\d+", t)
+# `s_waitcnt lgkmcnt(0)` (text order) no other instruction may touch the load's destination register.  Any scalar load
+# inside the compiler's marks of inline assembly is one of them, whatever registers its address is in.
+def _scan_scalar_loads(text: str, src: str) -> int:
+    """Raises if a load's destination is touched before it is waited for; the number of loads."""
+    ins, inline, in_asm = [], [], False
+    for i, t in enumerate(text.split("\n")):
+        t = t.strip()
+        if "#ASMSTART" in t or "#ASMEND" in t:
+            in_asm = "#ASMSTART" in t
+        elif t and not t.startswith(";"):
+            if in_asm and t.startswith("s_load_dword"):
+                inline.append(len(ins))
+            ins.append((i, t))
+    for k in inline:
+        i, t = ins[k]
+        m = re.match(r"s_load_dword (s\d+), ", t)
         if not m:
-            continue
+            raise RuntimeError(f"{src}: line {i + 1}: `{t}` -- not a load of one word into a numbered register, which is all that is checked here")
         dest = m.group(1)
-        for j, u in ins[k + 1:k + 600]:
+        for j, u in ins[k + 1:]:
             if "lgkmcnt(0)" in u:
                 break
             if u.startswith("."):
@@ -70,8 +77,19 @@ def _check_scalar_loads(src: str) -> None:
             for a, b, c in re.findall(r"\bs\[(\d+):(\d+)\]|\b(s\d+)\b", ops[1]):
                 used.update([c] if c else [f"s{n}" for n in range(int(a), int(b) + 1)])
             if dest in used:
-                raise RuntimeError(f"{src}: line {i + 1} of {asm}: `{t}` -- {dest} is touched by `{u}` (line {j + 1}) "
-                                   f"before the load is waited for")
+                raise RuntimeError(f"{src}: line {i + 1}: `{t}` -- {dest} is touched by `{u}` (line {j + 1}) before the load is waited for")
+        else:
+            raise RuntimeError(f"{src}: line {i + 1}: `{t}` -- never waited for")
+    return len(inline)
+
+
+def _check_scalar_loads(src: str) -> None:
+    asm = os.path.join(OBJ, os.path.basename(src) + ".s")
+    r = subprocess.run([HIPCC, *FLAGS, "-S", "--cuda-device-only", src, "-o", asm], capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"hipcc -S failed on {src}")
+    if _scan_scalar_loads(open(asm).read(), asm) == 0:
+        raise RuntimeError(f"{src} issues scalar loads, but none was found in {asm}")
 
 
 def _compile(src: str) -> str:
