@@ -22,7 +22,7 @@ WS_SCORE, WS_SELECT, WS_ATTN_FWD, WS_ATTN_BWD, WS_DECODE_ATTN = 0, 1, 2, 3, 4
 EXPORTS = ("lrsa_abi_version", "lrsa_last_error", "lrsa_num_scored_chunks", "lrsa_score_route", "lrsa_attn_route", "lrsa_score_poll_limit", "lrsa_workspace_bytes",
            "lrsa_score", "lrsa_select", "lrsa_score_select", "lrsa_check_idx", "lrsa_attn_fwd", "lrsa_attn_bwd",
            "lrsa_cache_compress", "lrsa_cache_compress_ws", "lrsa_cache_compress_ws_bytes", "lrsa_decode_attn", "lrsa_decode_attn_static",
-           "lrsa_fill_workspace_bytes", "lrsa_attn_bwd_parts", "lrsa_attn_fwd_fill", "lrsa_attn_bwd_fill", "lrsa_attn_bwd_finish",
+           "lrsa_fill_workspace_bytes", "lrsa_attn_bwd_parts", "lrsa_attn_plan", "lrsa_attn_fwd_fill", "lrsa_attn_bwd_fill", "lrsa_attn_bwd_finish",
            "lrsa_timing_enable", "lrsa_timing_count", "lrsa_timing_read")
 
 
@@ -78,6 +78,7 @@ def lib() -> ctypes.CDLL:
         L.lrsa_fill_workspace_bytes.restype = ctypes.c_size_t
         L.lrsa_fill_workspace_bytes.argtypes = [vp, i32, i32, ctypes.c_int]
         L.lrsa_attn_bwd_parts.argtypes = [vp, i32, i32, vp, vp]
+        L.lrsa_attn_plan.argtypes = [vp, i32, i32, sz, vp]
         L.lrsa_attn_fwd_fill.argtypes = [vp, i32, i32, vp, vp, vp, vp, vp, vp, vp, sz, vp]
         L.lrsa_attn_bwd_fill.argtypes = [vp, i32, i32, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
         L.lrsa_attn_bwd_finish.argtypes = [vp, vp, vp, vp, vp, vp]
@@ -350,6 +351,22 @@ def attn_bwd_parts(p: LrsaParams, row_begin: int, row_end: int) -> Tuple[int, in
     a, b = ctypes.c_int32(0), ctypes.c_int32(0)
     _check(lib().lrsa_attn_bwd_parts(ctypes.byref(p), int(row_begin), int(row_end), ctypes.byref(a), ctypes.byref(b)))
     return a.value, b.value
+
+
+class AttnPlan(ctypes.Structure):
+    """Mirror of lrsa_attn_plan_info in include/lrsa.h."""
+    _fields_ = [(k, ctypes.c_int32) for k in ("query_waves", "key_waves", "slices", "gather_parts", "window_parts")]
+
+
+def attn_plan(p: LrsaParams, row_begin: int = 0, row_end: Optional[int] = None, bwd_ws_bytes: Optional[int] = None) -> AttnPlan:
+    """The kernels' variants that a forward and a backward call over these rows run, with a backward workspace of that size (the one
+    that the size query gives)."""
+    row_end = p.seq if row_end is None else row_end
+    if bwd_ws_bytes is None:
+        bwd_ws_bytes = workspace_bytes(p, WS_ATTN_BWD) if (row_begin, row_end) == (0, p.seq) else fill_workspace_bytes(p, row_begin, row_end, WS_ATTN_BWD)
+    plan = AttnPlan()
+    _check(lib().lrsa_attn_plan(ctypes.byref(p), int(row_begin), int(row_end), int(bwd_ws_bytes), ctypes.byref(plan)))
+    return plan
 
 
 def _fill_ws(p, row_begin, row_end, which, device, ws):

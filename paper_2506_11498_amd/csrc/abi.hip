@@ -385,6 +385,26 @@ int lrsa_attn_bwd_parts(const lrsa_params* p, int32_t row_begin, int32_t row_end
     return LRSA_OK;
 }
 
+int lrsa_attn_plan(const lrsa_params* p, int32_t row_begin, int32_t row_end, size_t bwd_ws_bytes, lrsa_attn_plan_info* plan) {
+    lrsa::Dims D;
+    int rc = make_dims(p, &D);
+    if (rc != LRSA_OK) return rc;
+    if (!plan) return fail(LRSA_ERR_INVALID_ARG, "lrsa_attn_plan: plan must not be NULL");
+    const bool whole = row_begin == 0 && row_end == D.n;
+    const int route = whole ? attn_route(p, D) : fill_supported(p, D) ? 2 : 0;
+    if (route == 0) return fail(LRSA_ERR_UNSUPPORTED, "lrsa_attn_plan: the plain kernels serve these calls");
+    if (!whole && (rc = set_row_window(&D, row_begin, row_end, "lrsa_attn_plan")) != LRSA_OK) return rc;
+    const size_t need = route == 2 ? lrsa::attn_bwd_mfma_ws_min_bytes(D) : lrsa::attn_bwd_f32_ws_bytes(D);
+    if (bwd_ws_bytes < need) return fail(LRSA_ERR_INVALID_ARG, "lrsa_attn_plan: workspace has %zu bytes, %zu are needed", bwd_ws_bytes, need);
+    if (route == 2) {
+        plan->query_waves = lrsa::attn_mfma_query_waves(D);
+        lrsa::attn_bwd_mfma_plan(D, bwd_ws_bytes, &plan->key_waves, &plan->slices, &plan->gather_parts, &plan->window_parts);
+    } else {
+        *plan = lrsa_attn_plan_info{lrsa::attn_f32_query_waves(D), lrsa::attn_f32_key_waves(), lrsa::attn_f32_slices(D), 1, 1};
+    }
+    return LRSA_OK;
+}
+
 int lrsa_attn_fwd_fill(const lrsa_params* p, int32_t row_begin, int32_t row_end, const void* Q, const void* K,
                        const void* V, const int32_t* idx, void* O, float* lse, void* ws, size_t ws_bytes, void* stream) {
     lrsa::Dims D;

@@ -495,6 +495,10 @@ bool f32_tiles_supported(const Dims& D) {
            grid_fits(int64_t(make_ktiles(D).count) * D.B * D.Hkv * f32_slices(D), 64 * F32_KV_WAVES);
 }
 
+int attn_f32_query_waves(const Dims& D) { return f32_query_waves(D, int64_t(make_qtiles(D).count) * D.B * D.Hq); }
+int attn_f32_key_waves() { return F32_KV_WAVES; }
+int attn_f32_slices(const Dims& D) { return f32_slices(D); }
+
 template <int DH>
 static hipError_t run_fwd(const Dims& D, const float* Q, const float* K, const float* V, const int32_t* idx, float* O, float* lse, hipStream_t st) {
     const QTiles T = make_qtiles(D);

@@ -38,7 +38,7 @@ struct BwdPlan {
     int fq0, fq1;               // query chunks whose rows take part (all of them unless a row window is set)
     int waves, bk;              // of a workgroup of the dK/dV kernel, its keys
     int gl_total, gtiles;       // gather list length per KV head as the last query chunk sees it, its tiles
-    int qch, nsl;               // query chunks per slice, slices per gather tile (<= KV_MAX_SLICES)
+    int qch, nsl;               // query chunks per slice, slices per gather tile (KV_MAX_SLICES, before they are halved where that fills the chip)
     int hsl, wsl;               // parts that the group's heads are split into: GATHER slices, WINDOW tiles
     int wlo, whi;               // positions [wlo, whi) of the WINDOW tiles
     int gather_wgs, window_wgs; // workgroups of the two parts of the dK/dV launch (multiples of 8)
@@ -217,6 +217,14 @@ void attn_bwd_mfma_parts(const Dims& D, int32_t* gather, int32_t* window) {
     *gather = P.hsl;
     *window = P.wsl;
 }
+int attn_mfma_query_waves(const Dims& D) { return qtile_waves(D); }
+void attn_bwd_mfma_plan(const Dims& D, size_t ws_bytes, int32_t* waves, int32_t* slices, int32_t* gather, int32_t* window) {
+    const BwdPlan P = plan_for(D, ws_bytes);
+    *waves = P.waves;
+    *slices = P.nsl;
+    *gather = P.hsl;
+    *window = P.wsl;
+}
 size_t attn_bwd_mfma_ws_min_bytes(const Dims& D) {
     const size_t whole = make_plan(D, false).bytes, split = attn_bwd_mfma_ws_bytes(D), of_8 = make_plan(D, false, true).bytes;
     const size_t least = whole < split ? whole : split;
@@ -226,9 +234,9 @@ size_t attn_bwd_mfma_ws_min_bytes(const Dims& D) {
 // the grids of the forward, dQ and dK/dV launches (the reduction's threads are fewer than the bytes of its partials)
 bool mfma_grids_fit(const Dims& D) {
     // An upper bound on the work-items of each, for nearly all calls: a workgroup's threads are at most 64 per piece of 32 rows x head and 2 per
-    // key, and 512 for the remainder of a segment or list; there are at most KV_MAX_SLICES slices and as many parts as heads.
+    // key, and 512 for the remainder of a segment or list; there are at most 2 * KV_MAX_SLICES slices and as many parts as heads.
     const double heads = double(D.B) * D.Hq, gl = D.fq1 > 0 ? gather_count(D, D.fq1 - 1) : 0;
-    const double q = heads * (2.0 * D.S + 576.0 + D.fq1 * (2.0 * D.L + 576.0)), g = (heads * KV_MAX_SLICES + 7.0) * (2.0 * gl + 512.0);
+    const double q = heads * (2.0 * D.S + 576.0 + D.fq1 * (2.0 * D.L + 576.0)), g = (heads * 2.0 * KV_MAX_SLICES + 7.0) * (2.0 * gl + 512.0);
     if (q + g + 4096.0 < 2147483648.0) return true;
     const int64_t units = int64_t(D.B) * D.Hkv;
     const BwdPlan P = make_plan(D, true), P8 = plan_of(D, true, 8, 8);   // also where workgroups have four waves: which shapes are served does not change with it

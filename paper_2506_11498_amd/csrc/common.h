@@ -80,6 +80,9 @@ hipError_t launch_attn_bwd_generic(const Dims&, const void* Q, const void* K, co
 // fp32 data on the fp32 matrix instruction
 bool f32_tiles_supported(const Dims&);
 size_t attn_bwd_f32_ws_bytes(const Dims&);
+int attn_f32_query_waves(const Dims&);
+int attn_f32_key_waves();
+int attn_f32_slices(const Dims&);
 hipError_t launch_attn_fwd_f32(const Dims&, const void* Q, const void* K, const void* V, const int32_t* idx, void* O, float* lse, hipStream_t st);
 hipError_t launch_attn_bwd_f32(const Dims&, const void* Q, const void* K, const void* V, const void* O, const void* dO, const float* lse,
                                const int32_t* idx, void* dQ, void* dK, void* dV, void* ws, hipStream_t st);
@@ -91,6 +94,8 @@ hipError_t launch_attn_fwd_mfma(const Dims&, const void* Q, const void* K, const
                                 void* O, float* lse, void* ws, hipStream_t st);
 size_t attn_bwd_mfma_ws_bytes(const Dims&);       // for the fastest plan
 void attn_bwd_mfma_parts(const Dims&, int32_t* gather, int32_t* window);   // of the fastest plan
+int attn_mfma_query_waves(const Dims&);
+void attn_bwd_mfma_plan(const Dims&, size_t ws_bytes, int32_t* waves, int32_t* slices, int32_t* gather, int32_t* window);
 size_t attn_bwd_mfma_ws_min_bytes(const Dims&);   // for one without splits: what a call must have
 hipError_t launch_attn_bwd_mfma(const Dims&, const void* Q, const void* K, const void* V, const void* O,
                                 const void* dO, const float* lse, const int32_t* idx, void* dQ, void* dK,

@@ -152,7 +152,9 @@ def test_attention_route_at_the_limits_of_a_launch():
         (dict(dtype=f32, Hq=64, Hkv=8, n=131072, sink=0, lag=2, topk=1), 1),
         (dict(dtype=f32, Hq=128, Hkv=8, n=131072, sink=0, lag=2, topk=1), 0),
         (dict(dtype=f32, Hq=128, Hkv=8, n=131070, sink=0, lag=2, topk=1), 1),
-        # bf16: 512 threads for 256 rows of one to four heads
+        # bf16: 64 threads for 32 rows of a head (65 * 65535 heads of 16 chunks are 2^32 * 1.016 of them)
+        (dict(dtype=bf, d=64, B=65, Hq=65535, Hkv=1, n=64, sink=0, lag=4, topk=1), 0),
+        (dict(dtype=bf, d=64, B=65, Hq=65535, Hkv=1, n=60, sink=0, lag=4, topk=1), 2),
         (dict(dtype=bf, d=64, Hq=128, Hkv=128, n=131072, sink=0, lag=2, topk=1), 0),
         (dict(dtype=bf, d=64, Hq=128, Hkv=128, n=131068, sink=0, lag=1024, topk=16), 2),
         # lags of two and three rows at head_dim 64: few pairs, or few keys per row
@@ -202,6 +204,28 @@ def test_one_compression_step_takes_a_workspace_only_where_it_gains():
     assert need(2, 8, 255, **f32) == 0 and need(2, 8, 256, **f32) > 0 and need(1, 17, 511, **f32) == 0 and need(1, 17, 512, **f32) > 0
     assert need(4, 8, 511, d=64) == 0 and need(4, 8, 512, d=64) > 0
     assert min(need(4, 8, 72, steps=2), need(13, 5, 16, steps=2), need(1, 1, 16, steps=2, **f32)) > 0
+
+
+def test_plan_of_a_call_is_reported():
+    p = _params(n=16 + 40 * 64)
+    plan = lrsa.attn_plan(p)
+    assert (plan.gather_parts, plan.window_parts) == lrsa.attn_bwd_parts(p, 0, p.seq) and plan.query_waves == plan.key_waves == 4 and plan.slices >= 1
+    assert lrsa.attn_plan(p, 16 + 64, p.seq).key_waves in (4, 8)
+    plan = lrsa.attn_plan(_params(B=1, Hq=32, Hkv=8, n=32768, sink=64, lag=1024, topk=256))
+    assert (plan.query_waves, plan.key_waves) == (8, 8)
+    f32 = dict(dtype=torch.float32, sink=0, topk=1)
+    for d, n, Hq, waves in ((64, 1024, 4, 16), (64, 1024, 8, 8), (64, 1024, 16, 4), (64, 2048, 16, 8), (64, 4096, 16, 16),
+                            (128, 512, 16, 8), (128, 512, 20, 4), (128, 1024, 20, 8)):     # two chunks: the last row sees n keys
+        plan = lrsa.attn_plan(_params(d=d, n=n, lag=n // 2, Hq=Hq, Hkv=1, **f32))
+        assert (plan.query_waves, plan.key_waves, plan.gather_parts, plan.window_parts) == (waves, 8, 1, 1), (d, n, Hq)
+    for bad, ws, code in (((0, 50), 1 << 30, -1), ((64, 64), 1 << 30, -1), ((0, p.seq), 256, -1)):
+        with pytest.raises(lrsa.LrsaError) as e:
+            lrsa.attn_plan(p, *bad, ws)
+        assert e.value.code == code
+    for kw, rows in ((dict(impl=binding.IMPL_GENERIC), (0, 1000)), (dict(dtype=torch.float32), (0, 16 + 64))):
+        with pytest.raises(lrsa.LrsaError) as e:
+            lrsa.attn_plan(_params(**kw), *rows, 1 << 30)
+        assert e.value.code == -2
 
 
 def test_parts_of_a_backward_call_are_reported():

@@ -19,15 +19,19 @@ from oracle import lrsa_ref as ref
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
-# tiles: 64 keys and 256 (head, query) rows in the query-outer kernels, 256 keys and 64 query rows in the key-outer one
+# tiles: 64 keys and four pieces of 32 rows of a head (heads of a group side by side) in the query-outer kernels, 128 keys and steps of 32
+# query rows in the key-outer one
 BF16_D64 = [
     dict(n=1, L=8, S=0, K=2, Hq=1, Hkv=1),                          # one row
     dict(n=40, L=32, S=64, K=8, Hq=2, Hkv=1),                       # sink only
-    dict(n=5 + 7 * 100 + 33, L=100, S=5, K=37, Hq=6, Hkv=2, B=2),   # group of 3: one head per workgroup
+    dict(n=5 + 7 * 100 + 33, L=100, S=5, K=37, Hq=6, Hkv=2, B=2),   # group of 3: pieces of three heads side by side
     dict(n=16 + 5 * 64 + 63, L=64, S=16, K=16, Hq=64, Hkv=8),       # group of 8, heads spread over the XCDs
     dict(n=33 + 4 * 257 + 1, L=257, S=33, K=64, Hq=2, Hkv=1),       # a chunk one row past a key tile, a tail of one row
     dict(n=7 + 6 * 130 + 129, L=130, S=7, K=130, Hq=4, Hkv=1),      # every token survives
     dict(n=4 + 9 * 64, L=64, S=4, K=1, Hq=3, Hkv=3, B=2),           # one survivor per chunk
+    dict(n=16 + 4 * 127 + 31, L=127, S=16, K=37, Hq=1, Hkv=1),      # chunks and the list of chunk 4 (127 entries) one below a tile, a tail of 31 rows
+    dict(n=16 + 4 * 128 + 32, L=128, S=16, K=56, Hq=2, Hkv=2),      # chunks, the list of chunk 3 and a tail of 32 rows that just fill theirs
+    dict(n=33 + 4 * 129 + 33, L=129, S=33, K=48, Hq=1, Hkv=1, B=2),   # chunks, the list of chunk 3 (129), sink and tail one past theirs
 ]
 
 
@@ -103,7 +107,7 @@ def test_bf16_head_dim_64_keeps_fp32_weights(structure):
         assert missed[0] <= 2 * missed[1] + 10, f"{k}: {missed[0]} elements off the correct rounding, the plain kernels {missed[1]}"
 
 
-# tiles: 16 keys, 16 query rows; 16 waves (head_dim 64) or 8 (128) take the tiles in turn; up to 8 workgroups share the rows
+# tiles: 16 keys, 16 query rows; 16, 8 or 4 waves (head_dim 64; 8 or 4: 128) take the tiles in turn; up to 8 workgroups share the rows
 # of a key tile, one where there are more than 512 key tiles
 F32 = [
     dict(n=1, L=8, S=0, K=2, Hq=1, Hkv=1),
@@ -138,8 +142,8 @@ def test_f32(cfg, d, local_prev, layout):
 
 @pytest.mark.parametrize("dtype,B", [("f32", 64), ("bf16", 65)])
 def test_more_heads_than_a_launch_of_the_tiled_kernels_holds(dtype, B):
-    """B x 65535 query heads of three rows: two query tiles per head are past 2^32 work-items (fp32: 1024 threads a tile, bf16: 512), so
-    the plain kernels serve the call.  All keys are visible causally (two chunks); some heads against 64 bits, dK and dV over
+    """B x 65535 query heads of three rows: two query tiles of fp32 per head, 1024 threads each, are past 2^32 work-items, and bf16 at lag 2
+    has few keys per row, so the plain kernels serve the call.  All keys are visible causally (two chunks); some heads against 64 bits, dK and dV over
     all heads."""
     dt = {"f32": torch.float32, "bf16": torch.bfloat16}[dtype]
     Hq, n, d = 65535, 3, 64

@@ -42,6 +42,7 @@ def test_every_row_once(cfg, d):
     got = {}
     for impl in [lrsa.IMPL_AUTO] + [lrsa.IMPL_COMPACT] * (d == 128):
         p = lrsa.params_for(xd["Q"], xd["K"], sink=w.S, lag=w.L, topk=w.K, impl=impl)
+        assert lrsa.attn_plan(p).query_waves == (8 if impl == lrsa.IMPL_COMPACT else 4)
         o = dict(O=torch.full_like(xd["Q"], float("nan")), lse=torch.full(xd["Q"].shape[:3], float("nan"), device=DEV),
                  dQ=torch.full_like(xd["Q"], float("nan")), dK=torch.full_like(xd["K"], float("nan")), dV=torch.full_like(xd["K"], float("nan")))
         ws = torch.empty(max(lrsa.workspace_bytes(p, k) for k in (2, 3)), dtype=torch.uint8, device=DEV)
@@ -72,6 +73,7 @@ def test_fp32_with_fewer_waves(d, B, Hq, Hkv):
     errs = []
     for impl in (lrsa.IMPL_AUTO, lrsa.IMPL_GENERIC):
         p = lrsa.params_for(xd["Q"], xd["K"], sink=w.S, lag=w.L, topk=w.K, impl=impl)
+        assert impl == lrsa.IMPL_GENERIC or lrsa.attn_plan(p).query_waves == (4 if Hq == 32 else 8)
         O, lse = lrsa.lrsa_attn_fwd(p, xd["Q"], xd["K"], xd["V"], idx)
         dQ, dK, dV = lrsa.lrsa_attn_bwd(p, xd["Q"], xd["K"], xd["V"], O, xd["dO"], lse, idx)
         got = dict(O=O, lse=lse, dQ=dQ, dK=dK, dV=dV)
@@ -129,3 +131,70 @@ def test_fp32_error_of_the_longest_walks_with_fewer_waves(d, n, heads):
     for k, r in want.items():
         e, e_all = (float((x[k][0, 0, -256:].double() - r).norm() / r.norm()) for x in (few, all_waves))
         assert e <= (1.1 if k == "dQ" else 1.03) * e_all, f"{k}: {e:.3e}, with all waves {e_all:.3e}"
+
+
+def dense64(x, idx, S, L, lp, dev=DEV):
+    """O, lse, dQ, dK, dV of every row in 64 bits from the mask of the definitions (ref.visible_mask), on the GPU in plain torch."""
+    out = {k: [] for k in ("O", "lse", "dQ", "dK", "dV")}
+    B, Hkv, n, d = x["K"].shape
+    G = x["Q"].shape[1] // Hkv
+    for b in range(B):
+        for h in range(Hkv):
+            vis = torch.from_numpy(ref.visible_mask(n, S, L, idx[b, h].cpu().numpy(), lp)).to(dev)
+            k, v = x["K"][b, h].double(), x["V"][b, h].double()
+            dk = dv = 0
+            for hq in range(h * G, h * G + G):
+                q, do = x["Q"][b, hq].double(), x["dO"][b, hq].double()
+                s = (q @ k.T * d ** -0.5).masked_fill(~vis, float("-inf"))
+                P = torch.softmax(s, -1)
+                O = P @ v
+                dS = P * (do @ v.T - (do * O).sum(-1, keepdim=True)) * d ** -0.5
+                dk, dv = dk + dS.T @ q, dv + P.T @ do
+                for name, t in (("O", O), ("lse", torch.logsumexp(s, -1)), ("dQ", dS @ k)):
+                    out[name].append(t)
+            out["dK"].append(dk)
+            out["dV"].append(dv)
+    return {k: torch.stack(v).view(B, -1, *v[0].shape) for k, v in out.items()}
+
+
+# lags that are no multiple of 32, so that rows and keys at chunk ends inside the sequence leave pieces, steps and waves of keys partly filled
+EIGHT = [
+    (dict(B=2, Hq=16, Hkv=8, n=2161, L=499, K=235, S=33), 1, (1, 1)),   # G, local_prev, parts of the heads (listed keys, window)
+    (dict(B=2, Hq=15, Hkv=3, n=2236, L=422, K=195, S=33), 1, (1, 3)),
+    (dict(B=1, Hq=24, Hkv=3, n=2955, L=225, K=111, S=0), 1, (1, 2)),    # two blocks of four heads
+    (dict(B=4, Hq=6, Hkv=1, n=2782, L=689, K=296, S=5), 2, (3, 3)),
+    (dict(B=4, Hq=8, Hkv=2, n=2669, L=521, K=226, S=16), 2, (1, 2)),
+]
+
+
+@pytest.mark.parametrize("cfg,lp,parts", EIGHT, ids=[f"n{c['n']}_L{c['L']}_G{c['Hq'] // c['Hkv']}" for c, _, _ in EIGHT])
+def test_eight_waves_at_odd_lags(cfg, lp, parts):
+    """The variants with eight waves of all three kernels that gather by position, in every row.  An element carries its own bf16 rounding
+    (2^-9) and that of P and dS, 2^-9 of terms that add up like random ones: a row is off by about 2^-9 to 2^-8 of its norm.  dQ and dK also
+    take D = sum(dO * O) from the rounded O: dS of a row whose dA - D nearly cancel is off by more."""
+    w = inputs.small_workload(d=128, dtype="bf16", **cfg)
+    x = {k: v.to(DEV) for k, v in inputs.make_inputs(w).items()}
+    p = lrsa.params_for(x["Q"], x["K"], sink=w.S, lag=w.L, topk=w.K, local_prev=lp)
+    plan = lrsa.attn_plan(p)
+    assert (plan.query_waves, plan.key_waves, (plan.gather_parts, plan.window_parts)) == (8, 8, parts)
+    _, idx = lrsa.lrsa_score_select(p, x["K"], x["V"])
+    got = dict(O=torch.full_like(x["Q"], float("nan")), lse=torch.full(x["Q"].shape[:3], float("nan"), device=DEV),
+               dQ=torch.full_like(x["Q"], float("nan")), dK=torch.full_like(x["K"], float("nan")), dV=torch.full_like(x["K"], float("nan")))
+    lrsa.lrsa_attn_fwd(p, x["Q"], x["K"], x["V"], idx, got["O"], got["lse"])
+    lrsa.lrsa_attn_bwd(p, x["Q"], x["K"], x["V"], got["O"], x["dO"], got["lse"], idx, got["dQ"], got["dK"], got["dV"])
+    for k, r in dense64(x, idx, w.S, w.L, lp).items():
+        g = got[k].double()
+        assert g.isfinite().all(), k
+        if k == "lse":
+            assert (g - r).abs().max() <= 1e-5          # sixteen ulps of values near 8
+            continue
+        bar = 2.0 ** -7
+        if k == "dQ":
+            late = slice(w.S + 2 * w.L, None)
+            e = ((g - r).norm(dim=-1) / r.norm(dim=-1))[:, :, late].max()
+            assert e <= bar, f"dQ behind the first two chunks: {float(e):.3e}"
+            r_norm, bar = r.norm(dim=-1) + r.norm(dim=-1).mean(), 2.0 ** -4   # the first rows see few keys: P near one, dA near D
+        else:
+            r_norm = r.norm(dim=-1)
+        e = ((g - r).norm(dim=-1) / r_norm).max()
+        assert e <= bar, f"{k}: {float(e):.3e}"
