@@ -249,3 +249,33 @@ def test_condensed_cache_with_split_heads_equals_gathering(cfg):
         res.append((O, lse, *grads))
     for a, b in zip(*res):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("m", [1, 2])
+@pytest.mark.parametrize("cfg,lp", [(dict(B=2, Hq=16, Hkv=8, n=2161, L=499, K=235, S=33), 1), (dict(B=4, Hq=6, Hkv=1, n=2782, L=689, K=296, S=5), 2)],
+                         ids=["n2161_L499", "n2782_L689"])
+def test_filling_steps_with_eight_waves_equal_the_one_shot_call(cfg, lp, m):
+    """Steps whose dK/dV kernel has eight waves, at lags that leave rows and keys of a step partly filled, with their forward and dQ in four waves where
+    the one-shot call has eight: the same bits in O, lse and dQ, and dK, dV up to one rounding to bf16 of fp32 sums in another order."""
+    w = inputs.small_workload(d=128, dtype="bf16", **cfg)
+    x = {k: v.to(DEV) for k, v in inputs.make_inputs(w).items()}
+    kw = dict(sink=w.S, lag=w.L, topk=w.K, local_prev=lp)
+    p = lrsa.params_for(x["Q"], x["K"], **kw)
+    _, idx = lrsa.lrsa_score_select(p, x["K"], x["V"])
+    O, lse = lrsa.lrsa_attn_fwd(p, x["Q"], x["K"], x["V"], idx)
+    want = lrsa.lrsa_attn_bwd(p, x["Q"], x["K"], x["V"], O, x["dO"], lse, idx)
+    acc = [torch.zeros(x["K"].shape, dtype=torch.float32, device=DEV) for _ in range(2)]
+    waves = set()
+    for a, b in windows(w, m):
+        q, do = (x[k][:, :, a:b].contiguous() for k in ("Q", "dO"))
+        pf = lrsa.params_for(q, x["K"], **kw)
+        pf.seq = w.n
+        waves.add((lrsa.attn_plan(pf, a, b).query_waves, lrsa.attn_plan(pf, a, b).key_waves))
+        o, ls = lrsa.lrsa_attn_fwd_fill(pf, a, b, q, x["K"], x["V"], idx)
+        dq = lrsa.lrsa_attn_bwd_fill(pf, a, b, q, x["K"], x["V"], o, do, ls, idx, *acc)
+        for got, whole in ((o, O), (ls, lse), (dq, want[0])):
+            assert torch.equal(got, whole[:, :, a:b])
+    assert lrsa.attn_plan(p).query_waves == 8 and (4, 8) in waves
+    for a, b in zip(acc, want[1:]):
+        b = b.double()
+        assert ((a.double() - b).abs() <= 2.0 ** -8 * b.abs() + 2.0 ** -18 * b.abs().max()).all()
