@@ -207,11 +207,11 @@ size_t lrsa_fill_workspace_bytes(const lrsa_params *p, int32_t row_begin, int32_
 int lrsa_attn_bwd_parts(const lrsa_params *p, int32_t row_begin, int32_t row_end, int32_t *gather, int32_t *window);
 
 /* Which kernels' variants a forward and a backward call over these rows (0 and n: lrsa_attn_fwd, lrsa_attn_bwd) run, the backward
- * with a workspace of `bwd_ws_bytes`: waves per workgroup of the query-outer kernels (forward, dQ) and of the key-outer one
+ * with a workspace of `bwd_ws_bytes`: waves per workgroup of the forward kernel, of the dQ kernel and of the key-outer one
  * (dK/dV), workgroups that share the query rows of a key tile, parts as above (fp32: one).  Host arithmetic, for tests and for
  * reading profiles.  LRSA_ERR_UNSUPPORTED where the plain kernels serve the calls. */
 typedef struct {
-    int32_t query_waves, key_waves, slices, gather_parts, window_parts;
+    int32_t fwd_waves, dq_waves, key_waves, slices, gather_parts, window_parts;
 } lrsa_attn_plan_info;
 int lrsa_attn_plan(const lrsa_params *p, int32_t row_begin, int32_t row_end, size_t bwd_ws_bytes, lrsa_attn_plan_info *plan);
 int lrsa_attn_fwd_fill(const lrsa_params *p, int32_t row_begin, int32_t row_end, const void *Q, const void *K,

@@ -355,7 +355,7 @@ def attn_bwd_parts(p: LrsaParams, row_begin: int, row_end: int) -> Tuple[int, in
 
 class AttnPlan(ctypes.Structure):
     """Mirror of lrsa_attn_plan_info in include/lrsa.h."""
-    _fields_ = [(k, ctypes.c_int32) for k in ("query_waves", "key_waves", "slices", "gather_parts", "window_parts")]
+    _fields_ = [(k, ctypes.c_int32) for k in ("fwd_waves", "dq_waves", "key_waves", "slices", "gather_parts", "window_parts")]
 
 
 def attn_plan(p: LrsaParams, row_begin: int = 0, row_end: Optional[int] = None, bwd_ws_bytes: Optional[int] = None) -> AttnPlan:

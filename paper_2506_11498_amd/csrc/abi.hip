@@ -397,10 +397,11 @@ int lrsa_attn_plan(const lrsa_params* p, int32_t row_begin, int32_t row_end, siz
     const size_t need = route == 2 ? lrsa::attn_bwd_mfma_ws_min_bytes(D) : lrsa::attn_bwd_f32_ws_bytes(D);
     if (bwd_ws_bytes < need) return fail(LRSA_ERR_INVALID_ARG, "lrsa_attn_plan: workspace has %zu bytes, %zu are needed", bwd_ws_bytes, need);
     if (route == 2) {
-        plan->query_waves = lrsa::attn_mfma_query_waves(D);
-        lrsa::attn_bwd_mfma_plan(D, bwd_ws_bytes, &plan->key_waves, &plan->slices, &plan->gather_parts, &plan->window_parts);
+        plan->fwd_waves = lrsa::attn_mfma_fwd_waves(D);
+        lrsa::attn_bwd_mfma_plan(D, bwd_ws_bytes, &plan->dq_waves, &plan->key_waves, &plan->slices, &plan->gather_parts, &plan->window_parts);
     } else {
-        *plan = lrsa_attn_plan_info{lrsa::attn_f32_query_waves(D), lrsa::attn_f32_key_waves(), lrsa::attn_f32_slices(D), 1, 1};
+        const int waves = lrsa::attn_f32_query_waves(D);
+        *plan = lrsa_attn_plan_info{waves, waves, lrsa::attn_f32_key_waves(), lrsa::attn_f32_slices(D), 1, 1};
     }
     return LRSA_OK;
 }

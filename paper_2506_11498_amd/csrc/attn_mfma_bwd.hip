@@ -217,9 +217,9 @@ void attn_bwd_mfma_parts(const Dims& D, int32_t* gather, int32_t* window) {
     *gather = P.hsl;
     *window = P.wsl;
 }
-int attn_mfma_query_waves(const Dims& D) { return qtile_waves(D); }
-void attn_bwd_mfma_plan(const Dims& D, size_t ws_bytes, int32_t* waves, int32_t* slices, int32_t* gather, int32_t* window) {
+void attn_bwd_mfma_plan(const Dims& D, size_t ws_bytes, int32_t* dq_waves, int32_t* waves, int32_t* slices, int32_t* gather, int32_t* window) {
     const BwdPlan P = plan_for(D, ws_bytes);
+    *dq_waves = qtile_waves(D);
     *waves = P.waves;
     *slices = P.nsl;
     *gather = P.hsl;

@@ -2,7 +2,7 @@
 // chunked mask, flash style (online softmax, only the log-sum-exp is kept for the backward).
 //
 // A wave owns a piece of 32 consecutive queries of one head; eight (or four) neighbouring pieces of one KV group and segment (the sink, or
-// one chunk) make a workgroup (mfma_tiles.h, QTileMap, qtile_waves).  The keys those queries see form one
+// one chunk) make a workgroup (mfma_tiles.h, QTileMap, fwd_waves).  The keys those queries see form one
 // stream: the gather list (sink, then the survivors of the compressed chunks) followed by the
 // contiguous local window up to the query itself.  Stream entry j is visible to query t iff
 // j <= ng + t - cs, so only the last tiles need a mask.  The stream is walked in tiles of 64
@@ -414,9 +414,11 @@ __global__ __launch_bounds__(64 * WAVES, DH == 64 ? 3 : 2) void k_fwd_mfma(Dims 
     }
 }
 
+int attn_mfma_fwd_waves(const Dims& D) { return fwd_waves(D); }
+
 hipError_t launch_attn_fwd_mfma(const Dims& D, const void* Q, const void* K, const void* V, const int32_t* idx,
                                 void* O, float* lse, void* ws, hipStream_t st) {
-    const int waves = qtile_waves(D);
+    const int waves = fwd_waves(D);
     const QTileMap M = make_qtile_map(D, waves);
     const int64_t wgs = M.wgs;
     if (wgs == 0) return hipSuccess;
@@ -432,7 +434,7 @@ hipError_t launch_attn_fwd_mfma(const Dims& D, const void* Q, const void* K, con
 #define LRSA_FWD_LAUNCH(DH_, W_, C_)                                                                                   \
     LRSA_TIMED_LAUNCH("k_fwd_mfma", st, (k_fwd_mfma<DH_, W_, C_>), dim3((unsigned)wgs), dim3(64 * W_), 0, st, D, q, k, v, \
                       idx, kc, vc, (bf16_t*)O, lse, M)
-    if (D.d == 64) LRSA_FWD_LAUNCH(64, 4, false);
+    if (D.d == 64) { if (waves == 8) LRSA_FWD_LAUNCH(64, 8, false); else LRSA_FWD_LAUNCH(64, 4, false); }
     else if (compact) LRSA_FWD_LAUNCH(128, 8, true);
     else if (waves == 4) LRSA_FWD_LAUNCH(128, 4, false);
     else LRSA_FWD_LAUNCH(128, 8, false);

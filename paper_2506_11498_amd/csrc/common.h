@@ -94,8 +94,8 @@ hipError_t launch_attn_fwd_mfma(const Dims&, const void* Q, const void* K, const
                                 void* O, float* lse, void* ws, hipStream_t st);
 size_t attn_bwd_mfma_ws_bytes(const Dims&);       // for the fastest plan
 void attn_bwd_mfma_parts(const Dims&, int32_t* gather, int32_t* window);   // of the fastest plan
-int attn_mfma_query_waves(const Dims&);
-void attn_bwd_mfma_plan(const Dims&, size_t ws_bytes, int32_t* waves, int32_t* slices, int32_t* gather, int32_t* window);
+int attn_mfma_fwd_waves(const Dims&);
+void attn_bwd_mfma_plan(const Dims&, size_t ws_bytes, int32_t* dq_waves, int32_t* waves, int32_t* slices, int32_t* gather, int32_t* window);
 size_t attn_bwd_mfma_ws_min_bytes(const Dims&);   // for one without splits: what a call must have
 hipError_t launch_attn_bwd_mfma(const Dims&, const void* Q, const void* K, const void* V, const void* O,
                                 const void* dO, const float* lse, const int32_t* idx, void* dQ, void* dK,

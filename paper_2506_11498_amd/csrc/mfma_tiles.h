@@ -441,14 +441,22 @@ inline QTileMap make_qtile_map(const Dims& D, int waves) {
 //    lag 91: 128 us with eight, 99 with four;
 //  - for walks of up to a thousand keys, whose beginning and end the other workgroup of the CU covers: 2.5K tokens, 64 heads on 8, lag 128:
 //    58 and 50 us; from 1.3K keys on eight are faster again (7.4K tokens, 48 heads on 8: 268 and 275 us);
-//  - head_dim 64, whose tiles are half as large: never slower than eight but for launches that eight just fill (7.1K tokens, 8 heads on 4:
-//    80 and 87 us); 8K tokens, 16 heads on 4: 154 and 138 us.
+//  - head_dim 64, whose tiles are half as large: three workgroups share a CU, and the backward never gains from eight by more than 3 percent (0.97
+//    to 1.24 of the time with four, 92 shapes); the forward in full launches: fwd_waves.
 inline int qtile_waves(const Dims& D) {
     if (D.compact) return 8;
     if (D.d == 64) return 4;
     const int64_t units = int64_t(D.B) * D.Hkv, n4 = units * tiles_per_unit(D, 4), n8 = units * tiles_per_unit(D, 8);
     const int keys = gather_count(D, (D.fq0 + D.fq1) / 2) + D.L + D.L / 2;   // of a walk, about
     return resident_tiles(n4, 4) || 20 * n8 > 11 * n4 || keys <= 1000 ? 4 : 8;
+}
+// The forward at head_dim 64: eight where four would be three rounds of 768 workgroups and more, and eight leave not more than one wave in
+// twenty idle.  Of 58 such shapes it takes 0.92 to 1.02 of the time with four, 0.97 on average (32K tokens, 32 heads on 8: 2950 and
+// 2846 us; 2 requests of 7.2K tokens, 16 on 4: 293 and 277); with 1300 to 2000 workgroups 0.96 to 1.09, below that up to 1.43.
+inline int fwd_waves(const Dims& D) {
+    if (D.compact || D.d != 64) return qtile_waves(D);
+    const int64_t units = int64_t(D.B) * D.Hkv, n4 = units * tiles_per_unit(D, 4), n8 = units * tiles_per_unit(D, 8);
+    return n4 >= 2048 && 40 * n8 <= 21 * n4 ? 8 : 4;
 }
 
 }  // namespace lrsa

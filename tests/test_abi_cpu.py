@@ -209,15 +209,20 @@ def test_one_compression_step_takes_a_workspace_only_where_it_gains():
 def test_plan_of_a_call_is_reported():
     p = _params(n=16 + 40 * 64)
     plan = lrsa.attn_plan(p)
-    assert (plan.gather_parts, plan.window_parts) == lrsa.attn_bwd_parts(p, 0, p.seq) and plan.query_waves == plan.key_waves == 4 and plan.slices >= 1
+    assert (plan.gather_parts, plan.window_parts) == lrsa.attn_bwd_parts(p, 0, p.seq) and plan.fwd_waves == plan.dq_waves == plan.key_waves == 4 and plan.slices >= 1
     assert lrsa.attn_plan(p, 16 + 64, p.seq).key_waves in (4, 8)
     plan = lrsa.attn_plan(_params(B=1, Hq=32, Hkv=8, n=32768, sink=64, lag=1024, topk=256))
-    assert (plan.query_waves, plan.key_waves) == (8, 8)
+    assert (plan.fwd_waves, plan.dq_waves, plan.key_waves) == (8, 8, 8)
+    # head_dim 64: the forward alone, in full launches that eight waves leave without gaps
+    for kw, waves in ((dict(B=1, Hq=32, Hkv=8, n=32768, lag=1024, topk=256), 8), (dict(B=2, Hq=16, Hkv=4, n=7243, lag=231, topk=115, sink=33), 8),
+                      (dict(B=2, Hq=16, Hkv=4, n=6000, lag=256, topk=64), 4), (dict(B=8, Hq=4, Hkv=4, n=9193, lag=383, topk=191, sink=0), 4)):
+        plan = lrsa.attn_plan(_params(**{"sink": 16, "d": 64, **kw}))
+        assert (plan.fwd_waves, plan.dq_waves, plan.key_waves) == (waves, 4, 4), kw
     f32 = dict(dtype=torch.float32, sink=0, topk=1)
     for d, n, Hq, waves in ((64, 1024, 4, 16), (64, 1024, 8, 8), (64, 1024, 16, 4), (64, 2048, 16, 8), (64, 4096, 16, 16),
                             (128, 512, 16, 8), (128, 512, 20, 4), (128, 1024, 20, 8)):     # two chunks: the last row sees n keys
         plan = lrsa.attn_plan(_params(d=d, n=n, lag=n // 2, Hq=Hq, Hkv=1, **f32))
-        assert (plan.query_waves, plan.key_waves, plan.gather_parts, plan.window_parts) == (waves, 8, 1, 1), (d, n, Hq)
+        assert (plan.fwd_waves, plan.dq_waves, plan.key_waves, plan.gather_parts, plan.window_parts) == (waves, waves, 8, 1, 1), (d, n, Hq)
     for bad, ws, code in (((0, 50), 1 << 30, -1), ((64, 64), 1 << 30, -1), ((0, p.seq), 256, -1)):
         with pytest.raises(lrsa.LrsaError) as e:
             lrsa.attn_plan(p, *bad, ws)

@@ -270,12 +270,12 @@ def test_filling_steps_with_eight_waves_equal_the_one_shot_call(cfg, lp, m):
         q, do = (x[k][:, :, a:b].contiguous() for k in ("Q", "dO"))
         pf = lrsa.params_for(q, x["K"], **kw)
         pf.seq = w.n
-        waves.add((lrsa.attn_plan(pf, a, b).query_waves, lrsa.attn_plan(pf, a, b).key_waves))
+        waves.add((lrsa.attn_plan(pf, a, b).dq_waves, lrsa.attn_plan(pf, a, b).key_waves))
         o, ls = lrsa.lrsa_attn_fwd_fill(pf, a, b, q, x["K"], x["V"], idx)
         dq = lrsa.lrsa_attn_bwd_fill(pf, a, b, q, x["K"], x["V"], o, do, ls, idx, *acc)
         for got, whole in ((o, O), (ls, lse), (dq, want[0])):
             assert torch.equal(got, whole[:, :, a:b])
-    assert lrsa.attn_plan(p).query_waves == 8 and (4, 8) in waves
+    assert lrsa.attn_plan(p).dq_waves == 8 and (4, 8) in waves
     for a, b in zip(acc, want[1:]):
         b = b.double()
         assert ((a.double() - b).abs() <= 2.0 ** -8 * b.abs() + 2.0 ** -18 * b.abs().max()).all()
