@@ -60,13 +60,17 @@ static double rows_per_us(const Dims& D) { return D.d == 64 ? 24.0 : 16.0; }
 // reduction reads again.  The number of parts with the smallest sum of the two, if it saves a fifth.  `rows`: (head, query)
 // rows of a workgroup with one part, `bytes`: partials of one part, `bytes_one`: partials where there is only one part; the us
 // that it expects to save are added to `saved`.
-// Rates as measured: 16 (head_dim 64: 24) rows per us and CU; 1 TB/s for partials (each CU stores 32 bytes of a row at a time).
+// Rates: 16 (head_dim 64: 24) rows per us and CU, as measured; 1 TB/s for partials, fitted with workgroups of eight waves that stored 32
+// bytes of a row at a time, as the figures below.  Now that partials leave in whole lines and most such launches have four waves the line
+// is on the careful side: backward with 2 TB/s over that with 1, head_dim 128 0.78 to 1.08 of the time (50 training shapes, 14 faster and 6 slower
+// by more than 1.5 percent, 0.978 on average), head_dim 64 0.82 to 1.09 (20, 0.962), filling steps 0.84 to 1.02 (12, 0.962); with 4.4 TB/s
+// 0.983, 0.955 and 0.965, up to 1.15; with 0.5 TB/s 1.02, 1.05 and 1.09.
 // The filling steps live from it: their windows of a few chunks leave about as many workgroups as CUs, of which the WINDOW
 // ones (whole chunks, all heads) were twice as long as the others and came last.  32K tokens, 12 heads on 2, lag 1024, four
 // chunks per step: dK/dV launches of 7.0 ms in all, the whole training step 12.1 -> 9.5 ms; 11.5K tokens, 8 on 2, lag 479:
 // 1.94 -> 1.16 ms.  Training steps of 2.6K tokens in one call 206 -> 155 us (with the finer slices
-// of make_plan); long sequences keep one part.  With partials at 4.4 TB/s and a tenth instead of a fifth it splits too often:
-// 3.5K tokens, 16 heads on 4, 4 requests 505 -> 535 us, now as before.
+// of make_plan); long sequences keep one part.  With partials at 4.4 TB/s and a tenth instead of a fifth it split too often:
+// 3.5K tokens, 16 heads on 4, 4 requests 505 -> 535 us.
 static int head_parts(const Dims& D, double rows, double bytes, double bytes_one, double* saved) {
     const double rate = rows_per_us(D);
     int best = 1;
@@ -132,9 +136,11 @@ static BwdPlan plan_of(const Dims& D, bool split, int waves, int slices_of, doub
     while (qch > min_qch && qch > 1 && (qch / 2) * rows >= 1024 &&
            int64_t(D.B) * D.Hkv * stiles * ((nqf + qch - 1) / qch) * slices_of / 16 < 512)
         qch /= 2;
-    // fewer than a quarter as many as CUs: down to 256 rows.  (2.6K tokens, 4 heads on 2, 2 requests, 24 workgroups: 164 ->
-    // 157 us; 2.2K tokens in filling steps, 4 heads on 1: 710 -> 633 us.  From 84 workgroups on it costs more than it gives:
-    // 5.5K tokens, 4 heads on 2, 4 requests 264 -> 272 us, 4K tokens, 8 heads on 8, 2 requests, 128 of them, 271 -> 295 us.)
+    // fewer than a quarter as many as CUs: down to 256 rows.  With eight waves and partials stored 32 bytes of a row at a time: 2.6K
+    // tokens, 4 heads on 2, 2 requests, 24 workgroups, 164 -> 157 us; 2.2K tokens in filling steps, 4 heads on 1, 710 -> 633; from 84
+    // workgroups on it cost more than it gave (4K tokens, 8 heads on 8, 2 requests, 128 of them, 271 -> 295 us).  With the present kernels, 70
+    // training shapes of grouped heads: without the finer slices 0.90 to 1.51 of the time (1.002 on average at head_dim 128, 1.048 at 64), up to 32
+    // workgroups 0.98 to 1.24 (1.001, 1.012), up to 128 0.80 to 1.06 (0.992, 0.997).
     const int64_t coarse = qch;
     while (split && qch > min_qch && qch > 1 && (qch / 2) * rows >= 256 &&
            int64_t(D.B) * D.Hkv * stiles * ((nqf + qch - 1) / qch) * slices_of / 16 < 64)
@@ -183,7 +189,7 @@ static BwdPlan plan_of(const Dims& D, bool split, int waves, int slices_of, doub
 // one's beginning and end count for more: 2 requests of 4K tokens, 8 heads on 8: 186 -> 161 us; 2 requests of 2.5K tokens, 16 on 4: 189 -> 134;
 // 4 requests of 4K tokens, 32 on 8: 1016 -> 885.  Short: less than 600 us of work for a CU, and no workgroup that is long beside that (which
 // would share its CU: 8.1K tokens, 16 on 4, lag 727, 364 us in a workgroup, 291 for a CU: 520 -> 565 us) unless it is short in itself.  Of 80
-// random shapes on this side of the line the backward takes 0.93 of the time (geometric mean), two 1.08.  head_dim 64: always (0.86 to 1.01).
+// random shapes on this side of the line the backward takes 0.93 of the time (geometric mean), two 1.08.  head_dim 64: always (0.73 to 1.05 of the time with eight over 46 shapes of 1K to 8K tokens, 0.91 on average).
 static BwdPlan make_plan(const Dims& D, bool split, bool slices_of_8 = false) {
     int waves = 4;
     if (D.d != 64) {

@@ -435,12 +435,13 @@ inline QTileMap make_qtile_map(const Dims& D, int waves) {
 // twice and take 2 to 5 percent longer where the chip is full and the walks are long (32K tokens, 32 heads on 8: forward 2718 us with
 // eight, 2819 with four).  Four
 //  - where the launch is resident at once or nearly: its longest workgroup is what counts, and it is half as long, runs alone on its
-//    SIMDs or is paired with a short one (QTileMap).  2.4K tokens, 8 heads on 2: 23 -> 19 us; 2 requests of 4K tokens, 8 heads on 8: 48 ->
-//    42 us; 14.3K tokens, 4 heads on 4: 212 -> 185 us (with eight 23.8, 47.8 and 207);
+//    SIMDs or is paired with a short one (QTileMap).  Forward with eight and with four: 2.4K tokens, 8 heads on 2, lag 96: 27.8 and 22.9 us; 2
+//    requests of 4K tokens, 8 heads on 8, lag 256: 47.1 and 42.2; 14.3K tokens, 4 heads on 4, lag 446, 111 kept: 117 and 104;
 //  - where eight would leave more than one wave in ten idle at the ends of the chunks: 4 requests of 2.9K tokens, 12 heads on 4,
-//    lag 91: 128 us with eight, 99 with four;
+//    lag 91, 22 kept: 85.9 and 64.8 us;
 //  - for walks of up to a thousand keys, whose beginning and end the other workgroup of the CU covers: 2.5K tokens, 64 heads on 8, lag 128:
-//    58 and 50 us; from 1.3K keys on eight are faster again (7.4K tokens, 48 heads on 8: 268 and 275 us);
+//    68.2 and 62.4 us, but 4 requests of 3.4K tokens, 8 on 2, lag 117: 53.2 and 55.7 (28 such shapes without gaps: with eight 0.955 to 1.13 of the
+//    time, 1.02 on average); from 1.3K keys on eight are faster again (7.4K tokens, 48 heads on 8: 269 and 274 us);
 //  - head_dim 64, whose tiles are half as large: three workgroups share a CU, and the backward never gains from eight by more than 3 percent (0.97
 //    to 1.24 of the time with four, 92 shapes); the forward in full launches: fwd_waves.
 inline int qtile_waves(const Dims& D) {
